@@ -300,7 +300,7 @@ def run_leg(wl, *, steps, warmup, all_layers, check_units, cpu_seconds, calibrat
     achieved = bytes_per_launch / (kern_us * 1e-6) / 1e9
     step_gbps = (bytes_total / steps) / (us_per_step * 1e-6) / 1e9
     stats = m.stats()
-    kernel = ("k_attend_decode_mfma" if stats.attend_impl == binding.ATTEND_MFMA else "k_attend_valu")
+    kernel = ("k_attend_decode_mfma" if stats.attend_impl == binding.ATTEND_MFMA else "k_attend_fp32")
     if one_call and stats.last_decode_fused:       # selection and attention ran as one kernel
         kernel = "k_decode_fused"
 

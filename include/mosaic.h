@@ -54,8 +54,8 @@ typedef enum {
 
 enum { MOSAIC_FP32 = 0, MOSAIC_BF16 = 1 };
 enum { MOSAIC_TIER_HBM = 0, MOSAIC_TIER_HOST = 1 };
-enum { MOSAIC_ATTEND_AUTO = 0, /* bf16 -> MFMA kernel, fp32 -> vector-ALU kernel */
-       MOSAIC_ATTEND_VALU = 1, /* vector-ALU kernel for either dtype */
+enum { MOSAIC_ATTEND_AUTO = 0, /* bf16 -> bf16 MFMA kernels, fp32 -> fp32 kernel (reported as MOSAIC_ATTEND_VALU) */
+       MOSAIC_ATTEND_VALU = 1, /* fp32 arithmetic: bf16 -> vector-ALU kernel, fp32 -> fp32 kernel (fp32 matrix instruction) */
        MOSAIC_ATTEND_MFMA = 2  /* MFMA kernel (bf16 only) */ };
 
 typedef struct {

@@ -267,7 +267,8 @@ int choose_splits(const mosaic_ctx *ctx, int n_units, int Tq, long long part_ent
     const long long NT = ((long long)Tq * dv.G + kRowTile - 1) / kRowTile;
     const bool mfma = ctx->impl == MOSAIC_ATTEND_MFMA;
     constexpr int pw = kPrefillWaves;
-    const long long row_blocks = NT == 1 ? 1 : (mfma ? (NT + pw * kPrefillTiles - 1) / (pw * kPrefillTiles) : NT);
+    const int tiles = mfma ? pw * kPrefillTiles : dv.esize == 4 ? kFp32Tiles : 1;      // row tiles per workgroup
+    const long long row_blocks = (NT + tiles - 1) / tiles;
     const long long est_pages = std::max<long long>(1, (ctx->n_frames * dv.k + dv.C - 1) / dv.C);
     const long long est_chunks = est_pages * dv.chunks_per_page;
     long long s;
@@ -1143,6 +1144,8 @@ static int attend_with(mosaic_ctx *ctx, const DeviceView &dv, int32_t layer, con
     }
     e = ctx->impl == MOSAIC_ATTEND_MFMA
             ? launch_attend_mfma(dv, u0, nu, q_dev, n_q_tokens, S, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
+        : dv.esize == 4
+            ? launch_attend_fp32(dv, u0, nu, (const float *)q_dev, n_q_tokens, S, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
             : launch_attend_valu(dv, u0, nu, q_dev, n_q_tokens, S, ctx->stream, ev0, ev1);
     if (e != hipSuccess) return fail_hip(ctx, e, "attend launch");
     e = launch_attend_combine(dv, u0, nu, n_q_tokens, S, out_dev, lse_dev, ctx->stream);

@@ -1,0 +1,144 @@
+// Attention over the retrieved KV with fp32 pages (paper Sec. V-A (2)) on the fp32 matrix
+// instruction: exact fp32 products, fp32 accumulation (operand layout in attend_fp32_device.h).
+// Against the vector-ALU kernel it replaces (a row of K and V at a time through LDS, scalar LDS reads in the inner
+// loops, nothing prefetched): a decode step's launch at D = 128, 33 k tokens in four units 61 -> 14 us, at D = 64,
+// 512 tokens 25.7 -> 8.8 us, an 84-row question at D = 64 61 -> 14 us; 1792-row question 100 TFLOP/s.  Its error
+// against 64 bits is half as large (1.1e-7 against 2.4e-7 of the output's norm).
+//
+// What bounds it.  A decode step (one row tile) reads 2 * D * 4 bytes per token and spends 4 * D / 16 matrix
+// instructions of 32 cycles on 16 tokens, about 40 % of the time the bytes take at the HBM rate: memory, and on the
+// small launches of one layer the latency of two or three dependent loads.  A question of many tokens is bound by
+// the fp32 matrix rate (153 TFLOP/s measured for a large product), so R row tiles share a wavefront's operands.
+#include "attend_fp32_device.h"
+#include "attend_reps_device.h"
+
+namespace mosaic {
+
+namespace {
+
+// grid (B [+ n_units with the global-representative augmentation], ceil(NT / R)), 4 wavefronts.
+// split_slot() shares the B workgroups of a row block out over the units by retrieved size.  A unit's
+// tokens are one flat sequence in gather order (token i = token i % T of page i / T of the selection), taken
+// 16 at a time whatever T is, so that only the very last group is padded; wavefront w of split s takes groups
+// s + S * w + 4 * S * i.  The page ids of group i + 2 and the operands of group i + 1 are in flight while group
+// i is reduced.
+template <int D, int R, bool STREAM>
+__global__ __launch_bounds__(kBlock, R == 1 ? 2 : 1) void k_attend_fp32(DeviceView dv, int u0, int n_units, const float *q,
+                                                                        int Tq, int NT, int B) {
+    if ((int)blockIdx.x >= B) {     // extra columns: the global representatives' part (augmentation)
+        for (int r = 0; r < R; ++r) {
+            const int tile = blockIdx.y * R + r;
+            if (tile < NT) attend_reps_partial<float, D>(dv, u0, (int)blockIdx.x - B, tile, q, Tq);
+            __syncthreads();
+        }
+        return;
+    }
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16;
+    const SplitSlot slot = split_slot<false>(dv.n_sel + u0, n_units, B, blockIdx.x);
+    if (slot.uc < 0) return;        // block-uniform: no barrier reached yet
+    const int uc = slot.uc, u = u0 + uc, split = slot.split, S = slot.S, T = dv.T;
+    const int lc = uc / dv.Hkv, h = u % dv.Hkv;
+    const int *sel = dv.sel_pages + (size_t)u * dv.F;
+    const float *kb = reinterpret_cast<const float *>(k_page(dv, u, 0)), *vb = reinterpret_cast<const float *>(v_page(dv, u, 0));
+    const int n_sel = __builtin_amdgcn_readfirstlane(slot.n), N = n_sel * T;      // tokens: max_frames * T fits in 32 bits
+    const int first = __builtin_amdgcn_readfirstlane(split + S * wave), stride = __builtin_amdgcn_readfirstlane(4 * S);
+    const int groups = ((N - 1) >> 4) + 1;                                         // (0 for N = 0)
+    const int n_my = __builtin_amdgcn_readfirstlane(first < groups ? (groups - first + stride - 1) / stride : 0);
+
+    // wave-uniform cursor over the groups: page (index into the selection) and token offset of a group's first token
+    const int dq = __builtin_amdgcn_readfirstlane(stride * kGroup / T), dr = __builtin_amdgcn_readfirstlane(stride * kGroup % T);
+    int cp = __builtin_amdgcn_readfirstlane(first * kGroup / T), cr = __builtin_amdgcn_readfirstlane(first * kGroup % T);
+    const int inv = 65536 / T + 1;  // floor(x / T) = (x * inv) >> 16 for x < T + 16 <= 32
+    int id = 0, at = 0;             // this lane's token (token n of the cursor's group): page id, ~offset if there is none
+    auto lookup = [&]() {           // (past the last group: the last page again)
+        int off = cr + n;
+        const int d = T >= kGroup ? (off >= T ? 1 : 0) : (off * inv) >> 16;
+        off -= d * T;
+        const bool some = cp + d < n_sel;
+        id = sel[min(cp + d, n_sel - 1)];
+        at = some ? off : ~0;
+        cp += dq;
+        cr += dr;
+        if (cr >= T) { cr -= T; ++cp; }
+        cp = min(cp, n_sel);
+    };
+    auto row = [&]() { return at < 0 ? ~(id * T) : id * T + at; };
+
+    const float sl2 = 1.4426950408889634f / sqrtf((float)D);
+    f32v4 qf[R][D / 16], acc[R][D / 16];
+    float m[R], l[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        f32_load_q<float, D>(dv, q, lc, h, Tq, ((int)blockIdx.y * R + r) * kRowTile + n, g, sl2, qf[r]);
+        m[r] = -INFINITY;
+        l[r] = 0.f;
+#pragma unroll
+        for (int b = 0; b < D / 16; ++b) acc[r][b] = f32v4{0.f, 0.f, 0.f, 0.f};
+    }
+    F32Operands<D> oa, ob;
+    if (n_my > 0) {                 // then n_sel > 0
+        lookup();
+        const int r0 = row();
+        lookup();
+        f32_issue<D, STREAM>(kb, vb, r0, g, n, oa);
+        int i = 0;
+        for (; i + 2 < n_my; i += 2) {
+            int rn = row();
+            lookup();
+            f32_issue<D, STREAM>(kb, vb, rn, g, n, ob);
+            __builtin_amdgcn_sched_barrier(0);
+            f32_step<D, R>(oa, qf, acc, m, l);
+            rn = row();
+            lookup();
+            f32_issue<D, STREAM>(kb, vb, rn, g, n, oa);
+            __builtin_amdgcn_sched_barrier(0);
+            f32_step<D, R>(ob, qf, acc, m, l);
+        }
+        if (i + 2 == n_my) {
+            f32_issue<D, STREAM>(kb, vb, row(), g, n, ob);
+            __builtin_amdgcn_sched_barrier(0);
+            f32_step<D, R>(oa, qf, acc, m, l);
+            f32_step<D, R>(ob, qf, acc, m, l);
+        } else {
+            f32_step<D, R>(oa, qf, acc, m, l);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int tile = blockIdx.y * R + r;
+        if (tile >= NT) break;      // block-uniform
+        float o[D / 16], M, L;
+        f32_merge_waves<D>(acc[r], m[r], l[r], o, M, L);
+        const int rw = tid / 16, dl = tid % 16;
+        const size_t entry = (size_t)slot.base * NT + (size_t)tile * S + split;
+        float *po = dv.part_o + (entry * kRowTile + rw) * D;
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) po[dl + 16 * i] = o[i];
+        if (dl == 0) {              // fp32 weights throughout: the two normalisers coincide
+            float *ml = dv.part_ml + entry * kMlRows * kRowTile;
+            ml[rw] = M;
+            ml[kRowTile + rw] = L;
+            ml[2 * kRowTile + rw] = L;
+        }
+    }
+}
+
+} // namespace
+
+hipError_t launch_attend_fp32(const DeviceView &dv, int u0, int n_units, const float *q, int Tq, int n_splits,
+                              bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile, R = NT == 1 ? 1 : kFp32Tiles;
+    const int B = n_units * n_splits;
+    const dim3 grid(B + (dv.aug_reps ? n_units : 0), (NT + R - 1) / R), block(kBlock);
+    auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, B); };
+    if (NT == 1) {
+        if (dv.D == 64) stream_kv ? go(k_attend_fp32<64, 1, true>) : go(k_attend_fp32<64, 1, false>);
+        else stream_kv ? go(k_attend_fp32<128, 1, true>) : go(k_attend_fp32<128, 1, false>);
+    } else {                        // several row blocks read a unit's pages: they find them in the caches
+        if (dv.D == 64) go(k_attend_fp32<64, kFp32Tiles, false>);
+        else go(k_attend_fp32<128, kFp32Tiles, false>);
+    }
+    return hipGetLastError();
+}
+
+} // namespace mosaic

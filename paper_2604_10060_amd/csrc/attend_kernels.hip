@@ -1,8 +1,8 @@
 // Attention over the retrieved KV (paper Sec. V-A (2)): vector-ALU split-KV
-// kernel (fp32 or bf16 pages, values stored [T][D]) and the combine kernel that
-// merges the per-split partials of either kernel family.
+// kernel (bf16 pages, values stored [T][D]) and the combine kernel that
+// merges the per-split partials of every kernel family.
 //
-// Work decomposition shared by both families:
+// Work decomposition:
 //   rows     the unit's G*Tq query rows, row r = t*G + g, in tiles of 16
 //   chunks   32 tokens inside one page; a unit has n_sel * ceil(T/32) chunks
 //   splits   contiguous chunk ranges; one workgroup per (split, row tile, unit)
@@ -15,20 +15,7 @@ namespace mosaic {
 
 namespace {
 
-template <typename E> __device__ __forceinline__ float to_f32(E v);
-template <> __device__ __forceinline__ float to_f32<float>(float v) { return v; }
-template <> __device__ __forceinline__ float to_f32<unsigned short>(unsigned short v) {
-    return bf16_to_f32(v);
-}
-template <typename E> __device__ __forceinline__ void load8f(const E *p, float (&v)[8]);
-template <> __device__ __forceinline__ void load8f<float>(const float *p, float (&v)[8]) {
-    const float4 a = *reinterpret_cast<const float4 *>(p);
-    const float4 b = *reinterpret_cast<const float4 *>(p + 4);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-template <> __device__ __forceinline__ void load8f<unsigned short>(const unsigned short *p,
-                                                                   float (&v)[8]) {
+__device__ __forceinline__ void load8f(const unsigned short *p, float (&v)[8]) {
     const uint4 a = *reinterpret_cast<const uint4 *>(p);
     const unsigned int w[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
@@ -56,9 +43,10 @@ __device__ __forceinline__ float group16_sumf(float x) {
 
 // grid (n_units * n_splits [+ n_units with the global-representative augmentation], NT), 256 threads:
 // thread (row = tid/16, tl = tid%16)
-template <typename E, int D>
-__global__ __launch_bounds__(kBlock) void k_attend_valu(DeviceView dv, int u0, int n_units, const E *q,
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_attend_valu(DeviceView dv, int u0, int n_units, const unsigned short *q,
                                                         int Tq, int B) {
+    typedef unsigned short E;
     constexpr int DPT = D / 16;   // output channels per thread
     constexpr int CG = D / 8;     // 8-element groups per token row
     if ((int)blockIdx.x >= B) {   // extra columns: the global representatives' part (augmentation)
@@ -82,7 +70,7 @@ __global__ __launch_bounds__(kBlock) void k_attend_valu(DeviceView dv, int u0, i
         float v = 0.f;
         if (gr < R) {
             const int t = gr / G, g = gr % G;
-            v = to_f32<E>(q[(((size_t)lc * Tq + t) * Hq + (size_t)h * G + g) * D + d]) * sl2;
+            v = bf16_to_f32(q[(((size_t)lc * Tq + t) * Hq + (size_t)h * G + g) * D + d]) * sl2;
         }
         q_sh[rr][d] = v;
     }
@@ -105,8 +93,8 @@ __global__ __launch_bounds__(kBlock) void k_attend_valu(DeviceView dv, int u0, i
             const int tok = item / CG, cg = item % CG;
             float kv[8], vv[8];
             if (tok < nt) {
-                load8f<E>(kp + (size_t)tok * D + cg * 8, kv);
-                load8f<E>(vp + (size_t)tok * D + cg * 8, vv);
+                load8f(kp + (size_t)tok * D + cg * 8, kv);
+                load8f(vp + (size_t)tok * D + cg * 8, vv);
             } else {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) { kv[i] = 0.f; vv[i] = 0.f; }
@@ -143,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void k_attend_valu(DeviceView dv, int u0, i
     const size_t entry = (size_t)slot.base * NT + (size_t)tile * n_splits + split;
 #pragma unroll
     for (int i = 0; i < DPT; ++i) dv.part_o[(entry * kRowTile + row) * D + tl + 16 * i] = acc[i];
-    if (tl == 0) {     // fp32 weights throughout: the two normalisers coincide
+    if (tl == 0) {     // fp32 weights: the two normalisers coincide
         dv.part_ml[entry * kMlRows * kRowTile + row] = m;
         dv.part_ml[entry * kMlRows * kRowTile + kRowTile + row] = l;
         dv.part_ml[entry * kMlRows * kRowTile + 2 * kRowTile + row] = l;
@@ -336,13 +324,9 @@ hipError_t launch_attend_valu(const DeviceView &dv, int u0, int n_units, const v
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
     const int B = n_units * n_splits;
     const dim3 grid(B + (dv.aug_reps ? n_units : 0), NT), block(kBlock);
-    if (dv.esize == 4) {
-        if (dv.D == 64) launch_timed((k_attend_valu<float, 64>), grid, block, 0, s, ev0, ev1, dv, u0, n_units, (const float *)q, Tq, B);
-        else launch_timed((k_attend_valu<float, 128>), grid, block, 0, s, ev0, ev1, dv, u0, n_units, (const float *)q, Tq, B);
-    } else {
-        if (dv.D == 64) launch_timed((k_attend_valu<unsigned short, 64>), grid, block, 0, s, ev0, ev1, dv, u0, n_units, (const unsigned short *)q, Tq, B);
-        else launch_timed((k_attend_valu<unsigned short, 128>), grid, block, 0, s, ev0, ev1, dv, u0, n_units, (const unsigned short *)q, Tq, B);
-    }
+    const unsigned short *qq = (const unsigned short *)q;
+    if (dv.D == 64) launch_timed((k_attend_valu<64>), grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B);
+    else launch_timed((k_attend_valu<128>), grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B);
     return hipGetLastError();
 }
 

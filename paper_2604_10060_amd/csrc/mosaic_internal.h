@@ -16,6 +16,7 @@ constexpr int kChunk = 32;        // tokens per attention step, always inside on
 constexpr int kMaxSplits = 64;    // KV splits per (unit, row tile), average over the units of a launch
 constexpr int kMaxUnitSplits = 256; // ... and the most one unit can be given when the units retrieve unequal amounts
 constexpr int kPrefillTiles = 2;  // row tiles per wavefront in the multi-tile MFMA kernel
+constexpr int kFp32Tiles = 2;     // row tiles per wavefront in the fp32 attention kernel when there is more than one
 constexpr int kPrefillWaves = 4;  // wavefronts per workgroup of that kernel (64 * kPrefillTiles * 4 = 128 query rows)
 constexpr int kMlRows = 3;        // rows of 16 floats per attention partial besides O: max, normaliser, exact-weight sum
 
@@ -188,8 +189,12 @@ hipError_t launch_expand_tok_idx(const DeviceView &dv, int u0, int n_units, hipS
 // ev0/ev1 (may be null) receive the kernel's own start/stop timestamps
 hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, const unsigned short *q, int Tq,
                                  int n_splits, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+// bf16 pages on the vector ALU (MOSAIC_ATTEND_VALU)
 hipError_t launch_attend_valu(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                               int n_splits, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+// fp32 pages (fp32 matrix instruction)
+hipError_t launch_attend_fp32(const DeviceView &dv, int u0, int n_units, const float *q, int Tq, int n_splits,
+                              bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // stream_kv: the decode-shape kernels load K/V with the non-temporal hint (stores far beyond the caches)
 hipError_t launch_attend_mfma(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                               int n_splits, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);

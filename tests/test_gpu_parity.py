@@ -75,6 +75,21 @@ def test_shapes_fp32(kw):
     _report(rep)
 
 
+# the fp32 kernel takes a unit's tokens 16 at a time across page borders and R = 2 row tiles per wavefront: pages
+# shorter than, equal to and just off a group, one token short of a whole group in all, one to five row tiles
+# (odd counts leave half a row block), every token selected and a single page
+@pytest.mark.parametrize("kw", [
+    dict(tokens_per_frame=1, n_q_heads=4, question_tokens=1, top_k=8),
+    dict(tokens_per_frame=9, n_q_heads=14, question_tokens=5, top_k=3),
+    dict(tokens_per_frame=15, n_q_heads=2, question_tokens=17, top_k=8, head_dim=64),
+    dict(tokens_per_frame=17, n_q_heads=16, question_tokens=9, top_k=1),
+    dict(tokens_per_frame=33, n_q_heads=32, question_tokens=1, top_k=2, head_dim=64),
+    dict(tokens_per_frame=49, n_q_heads=8, question_tokens=20, top_k=5, n_frames=131),
+])
+def test_fp32_kernel_at_group_and_tile_edges(kw):
+    harness.run_workload(_small(**{**dict(kv_dtype="fp32", n_layers=2, n_kv_heads=2), **kw}), decode_steps=1)
+
+
 @pytest.mark.parametrize("tq,kw", [
     (256, dict(n_frames=128, n_clusters=8, top_k=3)),          # 1792 rows: 7 full 256-row workgroups
     (41, dict(tokens_per_frame=50, n_frames=96)),              # 287 rows: 18 tiles, ragged last workgroup and tile
