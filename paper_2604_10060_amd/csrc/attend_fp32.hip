@@ -25,11 +25,11 @@ namespace {
 template <int D, int R, bool STREAM>
 __global__ __launch_bounds__(kBlock, R == 1 ? 2 : 1) void k_attend_fp32(DeviceView dv, int u0, int n_units, const float *q,
                                                                         int Tq, int NT, int B) {
+    __shared__ float lds[kF32MergeFloats<D>];
     if ((int)blockIdx.x >= B) {     // extra columns: the global representatives' part (augmentation)
         for (int r = 0; r < R; ++r) {
             const int tile = blockIdx.y * R + r;
-            if (tile < NT) attend_reps_partial<float, D>(dv, u0, (int)blockIdx.x - B, tile, q, Tq);
-            __syncthreads();
+            if (tile < NT) attend_reps_partial<float, D>(dv, u0, (int)blockIdx.x - B, tile, q, Tq, lds);
         }
         return;
     }
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kBlock, R == 1 ? 2 : 1) void k_attend_fp32(DeviceVi
         const int tile = blockIdx.y * R + r;
         if (tile >= NT) break;      // block-uniform
         float o[D / 16], M, L;
-        f32_merge_waves<D>(acc[r], m[r], l[r], o, M, L);
+        f32_merge_waves<D>(acc[r], m[r], l[r], lds, o, M, L);
         const int rw = tid / 16, dl = tid % 16;
         const size_t entry = (size_t)slot.base * NT + (size_t)tile * S + split;
         float *po = dv.part_o + (entry * kRowTile + rw) * D;

@@ -140,16 +140,19 @@ __device__ __forceinline__ void f32_step(F32Operands<D> &o, const f32v4 (&qf)[R]
                     acc[r][4 * bb + x] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.v[v][bb][x], p[r][v], acc[r][4 * bb + x], 0, 0, 0);
 }
 
+// Floats of LDS that f32_merge_waves needs.
+template <int D> constexpr int kF32MergeFloats = 4 * D * (kRowTile + 1) + 2 * 4 * kRowTile;
+
 // Merge of the four wavefronts' running (m, l, O) of one row tile.  All 256 threads call it; thread
 // (row, dl) = (tid / 16, tid % 16) gets channels dl, dl + 16, ... of its row in o, and the row's M and L.
 // Ends with the LDS free to be written again.
 template <int D>
-__device__ __forceinline__ void f32_merge_waves(const f32v4 (&acc)[D / 16], float m, float l, float (&o)[D / 16], float &M, float &L) {
+__device__ __forceinline__ void f32_merge_waves(const f32v4 (&acc)[D / 16], float m, float l, float *lds, float (&o)[D / 16], float &M, float &L) {
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16;
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
-    __shared__ float o_sh[4][D][kRowTile + 1];
-    __shared__ float m_sh[4][kRowTile], l_sh[4][kRowTile];
+    float (*o_sh)[D][kRowTile + 1] = reinterpret_cast<float (*)[D][kRowTile + 1]>(lds);
+    float (*m_sh)[kRowTile] = reinterpret_cast<float (*)[kRowTile]>(lds + 4 * D * (kRowTile + 1)), (*l_sh)[kRowTile] = m_sh + 4;
 #pragma unroll
     for (int b = 0; b < D / 16; ++b)
 #pragma unroll

@@ -50,7 +50,8 @@ __global__ __launch_bounds__(kBlock) void k_attend_valu(DeviceView dv, int u0, i
     constexpr int DPT = D / 16;   // output channels per thread
     constexpr int CG = D / 8;     // 8-element groups per token row
     if ((int)blockIdx.x >= B) {   // extra columns: the global representatives' part (augmentation)
-        attend_reps_partial<E, D>(dv, u0, (int)blockIdx.x - B, blockIdx.y, q, Tq);
+        __shared__ float lds[kF32MergeFloats<D>];
+        attend_reps_partial<E, D>(dv, u0, (int)blockIdx.x - B, blockIdx.y, q, Tq, lds);
         return;
     }
     const SplitSlot slot = split_slot<false>(dv.n_sel + u0, n_units, B, blockIdx.x);

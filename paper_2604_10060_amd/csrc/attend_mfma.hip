@@ -38,7 +38,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_attend_decode_mfma(DeviceView dv,
     constexpr int KK = D / 32, DB = D / 16;
     if constexpr (AUG) {
         if ((int)blockIdx.x >= B) {   // extra workgroups: the global representatives' part (augmentation)
-            attend_reps_partial<unsigned short, D>(dv, u0, (int)blockIdx.x - B, 0, q, Tq);
+            __shared__ float lds[kF32MergeFloats<D>];
+            attend_reps_partial<unsigned short, D>(dv, u0, (int)blockIdx.x - B, 0, q, Tq, lds);
             return;
         }
     }

@@ -86,11 +86,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     constexpr int LPW = (KW + VW) / NW;          // ... per wave: loads number wave + NW i, keys first
     static_assert(LPW >= 1 && (KW + VW) % NW == 0 && 2 * (DIST - 1) * LPW < 64, "load schedule");
     constexpr int kPending = 2 * (DIST - 1) * LPW;           // loads of a wave that may stay in flight across a barrier
+    // LDS (dynamic): NS key slots, then NS value slots, one chunk each
+    extern __shared__ __attribute__((aligned(1024))) unsigned char prefill_lds[];
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16;
     if constexpr (AUG) {
+        static_assert(kF32MergeFloats<D> * 4 <= NS * (KBYTES + VBYTES), "the representatives' merge fits the chunk slots");
         if ((int)blockIdx.x >= group_blocks) {   // extra workgroups: the global representatives' part (augmentation)
             const int idx = (int)blockIdx.x - group_blocks;
-            attend_reps_partial<unsigned short, D>(dv, u0, idx / NT, idx % NT, q, Tq);
+            attend_reps_partial<unsigned short, D>(dv, u0, idx / NT, idx % NT, q, Tq, reinterpret_cast<float *>(prefill_lds));
             return;
         }
     }
@@ -107,9 +110,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     const int T = dv.T, F = dv.F, cpp = dv.chunks_per_page;
     const int lc = uc / dv.Hkv, h = u % dv.Hkv;
     const int tile0 = (yb * NW + wave) * RTW;
-    // LDS (dynamic): NS key slots, then NS value slots, one chunk each
-    extern __shared__ __attribute__((aligned(1024))) unsigned char prefill_lds[];
-
     bf16x8 qf[RTW][KK];
 #pragma unroll
     for (int r = 0; r < RTW; ++r) load_q<D>(dv, q, lc, h, Tq, (tile0 + r) * kRowTile + n, g, qf[r]);

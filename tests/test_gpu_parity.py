@@ -675,6 +675,18 @@ def test_augmentation_bf16_mfma_decode_and_question():
     assert rep.max_out_err <= 2e-2
 
 
+# the representatives' workgroups take clusters 16 at a time, four groups side by side: tables of less than a group,
+# a group and one, five groups (one wavefront has a second turn) and more than eight (a third)
+@pytest.mark.gpu
+@pytest.mark.parametrize("C,D,dtype,tq", [(3, 128, "bf16", 1), (17, 64, "bf16", 40), (65, 64, "fp32", 1), (70, 128, "bf16", 3),
+                                          (141, 128, "fp32", 9)])
+def test_augmentation_at_the_edges_of_the_representative_groups(C, D, dtype, tq):
+    wl = inputs.CONFIGS[1].scaled(name="aug_edges", n_frames=2 * C + 30, n_scenes=9, n_clusters=C, top_k=2, head_dim=D,
+                                  kv_dtype=dtype, tokens_per_frame=10, question_tokens=tq)
+    rep = harness.run_augmented(wl, 0, True, units=[(0, 0), (0, 3)])
+    assert rep.max_out_err <= (1e-4 if dtype == "fp32" else 2e-2)
+
+
 @pytest.mark.gpu
 def test_augmentation_window_larger_than_stream_and_recluster():
     """Window >= frames ingested: nothing comes from the clusters; with re-clustering on, the
