@@ -325,14 +325,14 @@ __global__ __launch_bounds__(128) void k_value_reps(DeviceView dv, int n_frames)
 }
 
 // ---------------------------------------------------------------------------
-// Online assignment + Eq. 3, frames f0..f1-1 in order.  grid (U), 256 threads.
+// Online assignment + Eq. 3 with the self-adaptive maintainer, frames f0..f1-1 in order.
+// grid (U), 256 threads.  The insertion procedure (Sec. VI, Alg. 1 lines 1-10) follows
+// the update: running variance (Eq. 4), threshold (Eq. 5) at the size before the
+// insertion, then absorb / split / defer.
 // ---------------------------------------------------------------------------
-// With MAINT the insertion procedure of the self-adaptive maintainer (Sec. VI,
-// Alg. 1 lines 1-10) follows the update: running variance (Eq. 4), threshold
-// (Eq. 5) at the size before the insertion, then absorb / split / defer.
 enum { kActAbsorb = 1, kActSplit = 2, kActDefer = 3, kActForced = 4 };
 
-template <int D, bool MAINT>
+template <int D>
 __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0, int f1) {
     constexpr int EPL = D / 16;  // elements per lane in a 16-lane row group
     const int u = blockIdx.x, tid = threadIdx.x, C = dv.C;
@@ -341,22 +341,18 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
     __shared__ double dot_sh[1024];
     __shared__ double red_v[4];
     __shared__ int red_i[4];
-    __shared__ double snorm_sh, nsum_sh[2], dsum_sh[2], psum_sh[2];
+    __shared__ double snorm_sh, nsum_sh[2], dsum_sh[2];
     __shared__ int act_sh;
-    __shared__ SplitShared<MAINT ? D : 16> split_sh;   // (small placeholder when the maintainer is off)
+    __shared__ SplitShared<D> split_sh;
     double *r = dv.r + (size_t)u * C * D;
     double *rn = dv.rnorm + (size_t)u * C;
     int *n = dv.n + (size_t)u * C;
 
-    const bool nested = dv.P > 0;
     // the summary of the next frame travels while the current frame is processed
     double s_ahead = tid < D ? dv.summ[((size_t)u * dv.F + f0) * D + tid] : 0.0;
     for (int f = f0; f < f1; ++f) {
-        // candidates: every cluster id, or (nested hierarchy, Sec. V-B) the ids of the frame's
-        // visual partition only
-        const int part_f = nested ? dv.part[f] : 0;
-        // (maintainer: only the ids in use, [0, n_slots), can have members; the table behind them is not read)
-        const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : (MAINT ? min(C, max(dv.n_slots[u], 1)) : C);
+        // only the ids in use, [0, n_slots), can have members; the table behind them is not read
+        const int lo = 0, hi = min(C, max(dv.n_slots[u], 1));
         if (tid < D) {
             s_sh[tid] = s_ahead;
             if (f + 1 < f1) s_ahead = dv.summ[((size_t)u * dv.F + f + 1) * D + tid];
@@ -442,35 +438,14 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
         }
         if (wave < 2) {
             sq = wave_sum(sq);
-            if (MAINT) dq = wave_sum(dq);
+            dq = wave_sum(dq);
             if (lane == 0) { nsum_sh[wave] = sq; dsum_sh[wave] = dq; }
-        }
-        // nested hierarchy: the partition's representative in this unit's key space follows the
-        // same running mean (Eq. 3 one level up)
-        int pn_i = 0;
-        if (nested) {
-            double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
-            pn_i = dv.pn[(size_t)u * dv.P + part_f];
-            double psq = 0.0;
-            if (tid < D) {
-                const double pv = ((double)pn_i * prow[tid] + s_sh[tid]) / ((double)pn_i + 1.0);
-                prow[tid] = pv;
-                psq = pv * pv;
-            }
-            if (wave < 2) {
-                psq = wave_sum(psq);
-                if (lane == 0) psum_sh[wave] = psq;
-            }
         }
         __syncthreads();   // all threads have read n[a] and written r before the scalars change
         if (tid == 0) {
-            if (nested) {
-                dv.prn[(size_t)u * dv.P + part_f] = sqrt(D > 64 ? psum_sh[0] + psum_sh[1] : psum_sh[0]);
-                dv.pn[(size_t)u * dv.P + part_f] = pn_i + 1;
-            }
             rn[a] = sqrt(D > 64 ? nsum_sh[0] + nsum_sh[1] : nsum_sh[0]);
             int act = kActAbsorb;
-            if (MAINT) {
+            {
                 const double dist2 = D > 64 ? dsum_sh[0] + dsum_sh[1] : dsum_sh[0];
                 double *var = dv.var + (size_t)u * C;
                 const double var_new = (na * var[a] + dist2) / (na + 1.0);                          // Eq. 4
@@ -502,7 +477,7 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
             }
         }
         __syncthreads();
-        if constexpr (MAINT) {
+        {
             if (act_sh == kActSplit) {                  // workgroup-uniform
                 const int fresh = mt_split_cluster<D>(dv, u, a, f + 1, false, split_sh);
                 if (tid == 0) dv.mt_cnt[(size_t)u * 4 + (fresh >= 0 ? 0 : 3)] += 1;
@@ -512,32 +487,444 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
     }
 }
 
+// LDS written by one lane and read by others of the same wavefront: the wavefront runs in lockstep and LDS is in order,
+// so only the compiler has to be kept from moving the accesses across.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One channel of Eq. 3, (n r + s) / (n + 1), each operation rounded separately (no contraction).  y = RN(1 / (n + 1)).
+// The division by n + 1, the same divisor for all channels: q = RN(x y) and two residual corrections
+// q <- RN(q + RN(x - (n + 1) q) y), each residual exact in a fused multiply-add: the first leaves q within half an ulp
+// and a little of x / (n + 1), and from such a q and a correctly rounded y the second returns the correctly rounded
+// quotient (Markstein's theorem; n + 1 is a small integer, so its significand is not all ones, and nothing here is near
+// the ends of the exponent range).  The compiler's own division hands a flag from its scaling step to its last step in
+// VCC, so the divisions of several channels run one after the other.
+__device__ __forceinline__ double eq3_channel(double n, double y, double r, double s) {
+    const double nb = n + 1.0, x = __dadd_rn(__dmul_rn(n, r), s);
+    double q = __dmul_rn(x, y);
+    q = __fma_rn(__fma_rn(-nb, q, x), y, q);
+    return __fma_rn(__fma_rn(-nb, q, x), y, q);
+}
+
 // ---------------------------------------------------------------------------
-// Online assignment + Eq. 3 with the representative table held in registers
-// (maintainer off, C <= THREADS / 2).  grid (U), THREADS threads.
-// The frames of a call are strictly sequential and every step of the global-
-// memory version above is a dependent round trip to L2 (summary, table rows,
-// winner row).  Here each 16-lane group keeps its RPG rows of the unit's table
-// (row j = group + (THREADS/16) i) in registers for the whole call, sizes and
-// norms sit in LDS, the next frame's summary is fetched while the current frame
-// is processed, and the winner's row is updated in place (and written through),
-// so nothing in the per-frame chain waits on memory.  Same arithmetic per
-// element as the version above; only the norm's additions are grouped by lane.
+// Online assignment + Eq. 3 without the maintainer, frames f0..f1-1 in order.  grid (U), kChainBlock threads.
+//
+// Eq. 3 makes frame t depend on frame t - 1, but only through the one representative that t - 1 moved, and moving it
+// changes dot products by a known amount: r' = (n r + s) / (n + 1) gives r'.x = (n r.x + s.x) / (n + 1).  So the frames
+// are taken a chunk of up to 16 at a time:
+//   1. the chunk's summaries times the whole table, and times each other, on the fp64 matrix instruction (all
+//      wavefronts); every frame's nearest cluster under the table as it stands;
+//   2. those clusters -- almost always the only ones the chunk will move -- become "slots"; a frame's second best
+//      similarity of step 1 bounds what it can have with any cluster that is not a slot;
+//   3. wavefront 0 assumes that every frame joins its nearest cluster of step 1.  Then all sums are known: by the
+//      identity a slot's dot product with a frame is n r.x plus the products with the frames that joined it before
+//      (and |n r + ...|^2 likewise), so all frames are checked at once, a lane per (frame, slot).  Where a frame's best
+//      slot is another one than assumed, the first such frame is corrected and the rest checked again;
+//   4. with the winners known, Eq. 3 is applied to the rows themselves: a thread per (slot, channel) runs through the
+//      slot's frames in order, each operation rounded separately.
+// Decisions are exact: the similarities of steps 1 and 3 differ from those of the rows by rounding (sums of at most 17
+// products with r.s >= 0, so that no length cancels: below 1e-13 in the cosine), and they only decide where the best
+// is ahead by more than kChainMargin.  At a frame that is closer than that, or whose best slot does not exceed the
+// bound of step 2, the chunk ends; the frame then comes first in the next chunk, where step 1 has its similarities
+// under the rows themselves, and if even those are too close the frame is decided by the full computation in the order
+// of operations of the one-frame kernel, ties to the lowest id.  So ids and representatives are the same bits for any
+// split of the stream into calls.
+// What bounds it (16 frames, D = 128, one chunk; cycles of one workgroup): the trip to memory for table and summaries
+// 4 k (11 k while page stores saturate the memory system), the fp64 products 6-8 k, nearest clusters 3 k, decisions
+// 3.5 k, Eq. 3 on the rows 7 k (seven dependent fp64 operations per frame).  A kernel that takes the frames one after
+// the other -- table in registers, dot products, search, update, two barriers per frame -- needs 77 k.  Launch: 4 layers,
+// C = 512 in 16 partitions 48.7 -> 15.1 us, 28 layers, C = 128, beside page stores 37.1 -> 23.3 us.
 // ---------------------------------------------------------------------------
-// k_in != nullptr (one frame, THREADS = 256): the workgroup first stores frame f0's key
-// page and forms its summary itself (the table loads are already in flight by then), so a
-// single-frame call needs one launch instead of two.
-template <int D, int THREADS, typename E>
-__device__ __forceinline__ void assign_update_reg_run(const DeviceView &dv, int u, int f0, int f1, const E *k_in) {
-    constexpr int EPL = D / 16, NG = THREADS / 16, RPG = 8, NW = THREADS / 64, ROWS = NG * RPG;
-    constexpr int CHUNK = 32;                   // frames whose summaries are staged in LDS at a time
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kChainBlock = 512, kChainFrames = 16, kChainSlots = 16, kChainSims = 8192;
+constexpr double kChainMargin = 1e-11;          // in the cosine
+
+// Sum / maximum over a row of 16 lanes or a wavefront of values that may be -inf but not NaN.
+__device__ __forceinline__ double row16_max(double m) {
+    m = max_f64(m, dpp_f64<kDppXor8>(m));
+    m = max_f64(m, dpp_f64<kDppXor7>(m));
+    m = max_f64(m, dpp_f64<kDppXor3>(m));
+    return max_f64(m, dpp_f64<kDppXor1>(m));
+}
+__device__ __forceinline__ double wave_max(double m) {
+    m = row16_max(m);
+    const long long b = __double_as_longlong(m);
+    double wm = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int l = __builtin_amdgcn_readlane((int)b, 16 * r), h = __builtin_amdgcn_readlane((int)(b >> 32), 16 * r);
+        wm = fmax(wm, __longlong_as_double(((long long)h << 32) | (long long)(unsigned int)l));
+    }
+    return wm;
+}
+// 1 / sqrt(x) and 1 / x to a few ulps (for similarities that only decide with a margin); 0 for x = 0
+__device__ __forceinline__ double fast_rsqrt(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = y * (1.5 - 0.5 * x * y * y);
+    y = y * (1.5 - 0.5 * x * y * y);
+    return x > 0.0 ? y : 0.0;
+}
+__device__ __forceinline__ double fast_rcp(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double readlane_f64(double x, int l) {
+    const long long b = __double_as_longlong(x);
+    return __longlong_as_double(((long long)__builtin_amdgcn_readlane((int)(b >> 32), l) << 32) |
+                                (long long)(unsigned int)__builtin_amdgcn_readlane((int)b, l));
+}
+
+template <int D>
+__global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int f0, int f1) {
+    constexpr int EPL = D / 16, NG = kChainBlock / 16, NW = kChainBlock / 64, KS = D / 8, SPB = kChainBlock / D;
+    constexpr int FR = kChainFrames, kNone = 0x7fffffff;
+    const int u = blockIdx.x, tid = threadIdx.x, lane = tid % 64, lr = tid % 16, grp = tid / 16, C = dv.C;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64), g = lane / 16, n = lane % 16;
+    __shared__ __attribute__((aligned(16))) double s_sh[FR][D + 2];     // (row padding: 16 rows' operand reads spread over the banks)
+    __shared__ double sim_sh[kChainSims];           // [frame][candidate] dot products, -inf for an empty cluster
+    __shared__ double gram_sh[FR][FR + 1];          // s_f . s_g / |s_g|
+    __shared__ double irn_sh[1024];                 // 1 / |r_j|, 0 for a zero row
+    __shared__ int n_sh[1024], slot_sh[1024];       // sizes; slot of a cluster, -1
+    __shared__ double ss_sh[FR], sn_sh[FR], isn_sh[FR], out_v[FR], y_sh[FR], row_sh[SPB][D];
+    __shared__ int near_sh[FR], sure_sh[FR], lo_sh[FR], w_sh[FR], p_sh[FR], slot_id[kChainSlots], n_slot_sh, nc_sh;
+    double *r = dv.r + (size_t)u * C * D;
+    const bool nested = dv.P > 0;
+    const int width = nested ? dv.Cs : C;           // candidates per frame: ids lo .. lo + width - 1
+    const int NI = (width + 63) / 64;               // ... lane l takes NI consecutive ones, so that ids ascend with the lane
+    const int NF = min(FR, kChainSims / width), tiles = (C + 15) / 16;
+    for (int j = tid; j < C; j += kChainBlock) {
+        const double rn = dv.rnorm[(size_t)u * C + j];
+        n_sh[j] = dv.n[(size_t)u * C + j];
+        irn_sh[j] = rn > 0.0 ? 1.0 / rn : 0.0;
+        slot_sh[j] = -1;
+    }
+    for (int c0 = f0; c0 < f1;) {
+        int nc = min(NF, f1 - c0);
+        // ---- 1. the chunk against the whole table and against itself ----
+        // operand layout of v_mfma_f64_16x16x4_f64: A lane (row lane%16, k lane/16), B lane (column lane%16, k lane/16),
+        // result register v = (row 4v + lane/16, column lane%16); lane group k holds channels 8s + 2k, + 1 of step s
+        f64x2 b[KS];
+        auto load_rows = [&](int t) {
+            const double *rj = r + (size_t)min(16 * t + n, C - 1) * D + 2 * g;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) b[s] = *reinterpret_cast<const f64x2 *>(rj + 8 * s);
+        };
+        if (!nested && wave < tiles) load_rows(wave);               // travels with the summaries
+        {
+            const double *src = dv.summ + ((size_t)u * dv.F + c0) * D;
+            for (int i = tid; i < nc * D / 2; i += kChainBlock)
+                *reinterpret_cast<f64x2 *>(&s_sh[2 * i / D][2 * i % D]) = *reinterpret_cast<const f64x2 *>(src + 2 * i);
+            if (tid < nc) lo_sh[tid] = nested ? dv.part[c0 + tid] * dv.Cs : 0;
+        }
+        __syncthreads();
+        auto times_s = [&]() {                      // the chunk's summaries (rows) times the operand in b (columns)
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const f64x2 a = *reinterpret_cast<const f64x2 *>(&s_sh[n][8 * s + 2 * g]);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b[s].x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b[s].y, acc, 0, 0, 0);
+            }
+            return acc;
+        };
+        for (int t = wave; t < tiles; t += NW) {
+            if (nested) {                           // tiles that no frame of the chunk asks for are not read
+                const int lo = lo_sh[min(lane, nc - 1)];
+                if (__ballot(lo < 16 * t + 16 && lo + width > 16 * t) == 0) continue;
+            }
+            if (nested || t != wave) load_rows(t);
+            const f64x4 acc = times_s();
+            const int j = 16 * t + n;
+            const bool live = j < C && n_sh[min(j, C - 1)] > 0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int fc = 4 * v + g;
+                if (fc < nc && j < C) {
+                    const int cj = j - lo_sh[fc];
+                    if (cj >= 0 && cj < width) sim_sh[fc * width + cj] = live ? acc[v] : -INFINITY;
+                }
+            }
+        }
+        if (wave == NW - 1) {                       // (the wavefront with the fewest tiles)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) b[s] = *reinterpret_cast<const f64x2 *>(&s_sh[n][8 * s + 2 * g]);
+            const f64x4 acc = times_s();            // (rows and columns beyond the chunk: whatever the LDS held, never read)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (4 * v + g == n) ss_sh[n] = n < nc ? acc[v] : 0.0;
+            wave_sync();
+            const double is = fast_rsqrt(ss_sh[n]);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) gram_sh[4 * v + g][n] = acc[v] * is;
+            if (g == 0) { isn_sh[n] = is; sn_sh[n] = ss_sh[n] * is; }
+        }
+        __syncthreads();
+        for (int fc = wave; fc < nc; fc += NW) {    // the nearest cluster under the table as it stands
+            const double is = isn_sh[fc];
+            const int lo = lo_sh[fc];
+            double bv = -INFINITY, sv = -INFINITY;
+            int bi = kNone;
+            bool odd = false;
+            for (int i = 0; i < NI; ++i) {
+                const int cj = lane * NI + i;
+                if (cj < width) {
+                    const double d = sim_sh[fc * width + cj], c = d == -INFINITY ? d : d * is * irn_sh[lo + cj];
+                    odd |= !(c == c);
+                    if (c > bv) { sv = bv; bv = c; bi = lo + cj; }
+                    else if (c > sv) sv = c;
+                }
+            }
+            const double own = bv;
+            const int own_i = bi;
+            wave_best_ascending(bv, bi);
+            const double second = wave_max(own_i == bi ? sv : own);
+            const bool sure = __ballot(odd) == 0 && (bi == kNone || bv - second > kChainMargin);
+            if (lane == 0) { near_sh[fc] = bi; sure_sh[fc] = sure; out_v[fc] = second; }
+        }
+        __syncthreads();
+        if (!sure_sh[0]) {                          // the first frame by the full computation (workgroup-uniform)
+            const int lo = lo_sh[0];
+            double sl[EPL], ssq = 0.0;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) { sl[e] = s_sh[0][lr * EPL + e]; ssq += sl[e] * sl[e]; }
+            const double sn = sqrt(row16_sum(ssq));
+            for (int cj = grp; cj < width; cj += NG) {                // (uniform within a 16-lane group)
+                const double *rj = r + (size_t)(lo + cj) * D + lr * EPL;
+                double p = 0.0;
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) p += sl[e] * rj[e];
+                p = row16_sum(p);
+                const double rn = dv.rnorm[(size_t)u * C + lo + cj];
+                const double c = n_sh[lo + cj] <= 0 ? -INFINITY : (sn == 0.0 || rn == 0.0) ? 0.0 : p / (sn * rn);
+                if (lr == 0) sim_sh[cj] = c;
+            }
+            __syncthreads();
+            if (wave == 0) {
+                double bv = -INFINITY;
+                int bi = kNone;
+                for (int i = 0; i < NI; ++i) {
+                    const int cj = lane * NI + i;
+                    if (cj < width && sim_sh[cj] > bv) { bv = sim_sh[cj]; bi = lo + cj; }
+                }
+                wave_best_ascending(bv, bi);
+                if (lane == 0) near_sh[0] = bi;
+            }
+            __syncthreads();
+        }
+        // ---- 2. slots ----
+        if (wave == 0) {
+            // a first frame decided by the full computation, or without a live candidate, makes a chunk of its own
+            const int lim = !sure_sh[0] || near_sh[0] == kNone ? 1 : nc;
+            int mine = lane < lim ? near_sh[lane] : -1;
+            if (mine == kNone) mine = lo_sh[lane];  // (empty: the frame joins the first of its candidates)
+            unsigned long long left = __ballot(mine >= 0);
+            int k = 0;
+            while (left && k < kChainSlots) {
+                const int id = __builtin_amdgcn_readlane(mine, __ffsll((long long)left) - 1);
+                if (lane == 0) { slot_id[k] = id; slot_sh[id] = k; }
+                left &= ~__ballot(mine == id);
+                ++k;
+            }
+            if (lane == 0) {
+                n_slot_sh = k;
+                nc_sh = left ? __ffsll((long long)left) - 1 : lim;
+            }
+        }
+        __syncthreads();
+        nc = nc_sh;
+        const int n_slot = n_slot_sh;
+        double x0 = 0.0;                            // step 4's first rows travel meanwhile
+        if (tid / D < n_slot) x0 = r[(size_t)slot_id[tid / D] * D + tid % D];
+        // ---- 3. the decisions: lane (g, n) looks at frame n and slots g, g + 4, ... ----
+        if (wave == 0) {
+            int w = n < nc ? slot_sh[near_sh[n] == kNone ? lo_sh[n] : near_sh[n]] : -1;       // the frame's winner, as assumed
+            int done = nc;
+            if (nc > 1) {
+                const int fn = min(n, nc - 1), lo = lo_sh[fn];
+                const double is = isn_sh[fn], sn = sn_sh[fn], ss = ss_sh[fn], out = out_v[fn];
+                double gr[FR];                      // s_h . s_n / |s_n| of the earlier frames h
+#pragma unroll
+                for (int h = 0; h < FR; ++h) gr[h] = gram_sh[h][fn];
+                for (;;) {                          // (at most FR turns: the first frame that disagrees comes later in every one)
+                    double best = -INFINITY, next = -INFINITY;
+                    int bk = -1;
+                    bool odd = false, back = false;
+                    for (int kb = 0; kb < n_slot; kb += 4) {
+                        const int k = kb + g, id = slot_id[min(k, n_slot - 1)], cj = id - lo;
+                        const bool cand = k < n_slot && cj >= 0 && cj < width;
+                        const double n0 = (double)n_sh[id], ir0 = irn_sh[id];
+                        // (n r + the slot's earlier frames) . s_n / |s_n|, and the squared length of that vector
+                        double num = cand ? n0 * (sim_sh[fn * width + (cand ? cj : 0)] * is) : 0.0;
+#pragma unroll
+                        for (int h = 0; h < FR - 1; ++h)
+                            num += __builtin_amdgcn_readlane(w, h) == k && h < n ? gr[h] : 0.0;
+                        double t = w == k ? __builtin_fma(2.0 * num, sn, ss) : 0.0;
+                        back |= w == k && !(num >= 0.0);
+                        t += dpp_f64<0x111>(t);     // row_shr 1, 2, 4, 8: running sum over the frames
+                        t += dpp_f64<0x112>(t);
+                        t += dpp_f64<0x114>(t);
+                        t += dpp_f64<0x118>(t);
+                        const double len = (ir0 > 0.0 ? n0 * n0 * fast_rcp(ir0 * ir0) : 0.0) + dpp_f64<0x111>(t);
+                        const double c = cand && n0 > 0.0 ? num * fast_rsqrt(len) : -INFINITY;
+                        odd |= !(c == c);
+                        next = c > best ? best : fmax(next, c);
+                        bk = c > best ? k : bk;
+                        best = c > best ? c : best;
+                    }
+#pragma unroll
+                    for (int o = 16; o <= 32; o <<= 1) {            // over the four lanes that look at the frame
+                        const double ob = __shfl_xor(best, o, 64), on = __shfl_xor(next, o, 64);
+                        const int ok = __shfl_xor(bk, o, 64);
+                        next = fmax(fmax(next, on), fmin(best, ob));
+                        bk = ob > best ? ok : bk;
+                        best = fmax(best, ob);
+                    }
+                    const unsigned long long odds = __ballot(odd), backs = __ballot(back);
+                    const unsigned int odd16 = (unsigned int)(odds | odds >> 16 | odds >> 32 | odds >> 48) & 0xffffu;
+                    const unsigned int back16 = (unsigned int)(backs | backs >> 16 | backs >> 32 | backs >> 48) & 0xffffu;
+                    // (frame 0 joins slot 0 by construction)
+                    const bool clear = n == 0 || n >= nc || (best - fmax(next, out) > kChainMargin && !((odd16 >> n) & 1));
+                    const unsigned int vague = (unsigned int)__ballot(!clear) & 0xffffu;
+                    const unsigned int other = (unsigned int)__ballot(clear && n > 0 && n < nc && bk != w) & 0xffffu;
+                    // a winner at more than a right angle shortens the representative: the rounding errors of its dot
+                    // products grow relative to it, so the frames after it are better taken from the rows
+                    const int stop = min(vague ? __ffs((int)vague) - 1 : nc, back16 ? __ffs((int)back16) : nc);
+                    const int at = other ? __ffs((int)other) - 1 : nc;
+                    if (at >= stop) { done = min(stop, nc); break; }
+                    if (n == at) w = bk;            // ... that frame's winner, and once more
+                }
+            }
+            if (lane < done) {
+                int p = n_sh[slot_id[w]];
+#pragma unroll
+                for (int h = 0; h < FR - 1; ++h) p += h < lane && __builtin_amdgcn_readlane(w, h) == w ? 1 : 0;
+                w_sh[lane] = w;
+                p_sh[lane] = p;
+                y_sh[lane] = __ddiv_rn(1.0, (double)p + 1.0);
+                dv.assign[(size_t)u * dv.F + c0 + lane] = slot_id[w];
+                dv.pos[(size_t)u * dv.F + c0 + lane] = p;
+            }
+            if (lane == 0) nc_sh = done;
+        }
+        __syncthreads();
+        nc = nc_sh;
+        if (nested && wave == NW - 1) {
+            // nested hierarchy: the partitions' representatives in this unit's key space follow the same running mean
+            // (Eq. 3 one level up), two channels per lane, a partition's row in registers until another's turn comes
+            constexpr int CPL = D / 64;
+            const int own = lane < nc ? lo_sh[lane] / dv.Cs : -1;
+            int size = lane < nc ? dv.pn[(size_t)u * dv.P + own] : 0;
+#pragma unroll
+            for (int h = 0; h < FR - 1; ++h) size += h < lane && __builtin_amdgcn_readlane(own, h) == own ? 1 : 0;
+            const double yl = __ddiv_rn(1.0, (double)size + 1.0);
+            double pv[CPL];
+            int at = -1, pn = 0;
+            auto leave = [&]() {
+                double psq = 0.0;
+#pragma unroll
+                for (int x = 0; x < CPL; ++x) {
+                    dv.pr[((size_t)u * dv.P + at) * D + lane + 64 * x] = pv[x];
+                    const double w = wave_sum(pv[x] * pv[x]);
+                    psq = x == 0 ? w : psq + w;
+                }
+                if (lane == 0) {
+                    dv.prn[(size_t)u * dv.P + at] = sqrt(psq);
+                    dv.pn[(size_t)u * dv.P + at] = pn;
+                }
+            };
+            for (int fc = 0; fc < nc; ++fc) {
+                const int p = __builtin_amdgcn_readlane(own, fc);
+                if (p != at) {
+                    if (at >= 0) leave();
+                    at = p;
+#pragma unroll
+                    for (int x = 0; x < CPL; ++x) pv[x] = dv.pr[((size_t)u * dv.P + at) * D + lane + 64 * x];
+                }
+                pn = __builtin_amdgcn_readlane(size, fc) + 1;
+                const double nb = (double)pn, ny = readlane_f64(yl, fc);
+#pragma unroll
+                for (int x = 0; x < CPL; ++x) {     // (the quotient as in eq3_channel)
+                    const double num = __fma_rn(nb - 1.0, pv[x], s_sh[fc][lane + 64 * x]);
+                    double q = __dmul_rn(num, ny);
+                    q = __fma_rn(__fma_rn(-nb, q, num), ny, q);
+                    pv[x] = __fma_rn(__fma_rn(-nb, q, num), ny, q);
+                }
+            }
+            leave();
+        }
+        // ---- 4. Eq. 3 on the rows ----
+        for (int kb = 0; kb < n_slot; kb += SPB) {  // workgroup-uniform
+            const int k = kb + tid / D, d = tid % D;                    // wave-uniform k
+            int mine = 0;
+            if (k < n_slot) {
+                double x = kb == 0 ? x0 : r[(size_t)slot_id[k] * D + d];
+                int w1 = w_sh[0], p1 = p_sh[0];     // (the next frame's operands are read ahead of this one's arithmetic)
+                double y1 = y_sh[0], s1 = s_sh[0][d];
+                for (int fc = 0; fc < nc; ++fc) {
+                    const int w = __builtin_amdgcn_readfirstlane(w1), p = p1, fn = min(fc + 1, FR - 1);
+                    const double y = y1, sv = s1;
+                    w1 = w_sh[fn]; p1 = p_sh[fn]; y1 = y_sh[fn]; s1 = s_sh[fn][d];
+                    if (w != k) continue;
+                    x = eq3_channel((double)p, y, x, sv);
+                    ++mine;
+                }
+                if (mine > 0) r[(size_t)slot_id[k] * D + d] = x;
+                row_sh[tid / D][d] = x;
+            }
+            __syncthreads();
+            const int kn = kb + grp;                // norm of slot kn, and its new size
+            if (grp < SPB && kn < n_slot) {
+                double sq = 0.0;
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) { const double x = row_sh[grp][lr * EPL + e]; sq += x * x; }
+                sq = row16_sum(sq);
+                int cnt = 0;
+                for (int fc = 0; fc < nc; ++fc) cnt += w_sh[fc] == kn;
+                if (lr == 0) {
+                    const int j = slot_id[kn];
+                    if (cnt > 0) {
+                        const double rn = sqrt(sq);
+                        const int nj = n_sh[j] + cnt;
+                        n_sh[j] = nj;
+                        irn_sh[j] = rn > 0.0 ? 1.0 / rn : 0.0;
+                        dv.n[(size_t)u * C + j] = nj;
+                        dv.rnorm[(size_t)u * C + j] = rn;
+                    }
+                    slot_sh[j] = -1;
+                }
+            }
+            __syncthreads();
+        }
+        c0 += nc;
+        __syncthreads();                            // before the next chunk overwrites the staged summaries
+    }
+}
+
+// ---------------------------------------------------------------------------
+// One frame in one launch (maintainer off, C <= 128, HBM tier, online phase).
+// grid (U, 2), 256 threads: y = 0 key page + summary + assignment + Eq. 3, y = 1 value page.
+// The table is in flight -- eight rows per 16-lane group -- before the page store begins; what follows it runs out of
+// registers and LDS.  The same operations on the same operands as k_assign_chain, element by element.
+// ---------------------------------------------------------------------------
+template <typename E, int D>
+__global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k_in, const E *v_in, int f) {
+    constexpr int EPL = D / 16, NG = kBlock / 16, RPG = 8, NW = kBlock / 64, ROWS = NG * RPG;
+    __shared__ double red[kBlock / (D / 8)][D];
+    const int u = blockIdx.x;
+    if (blockIdx.y == 1) {
+        store_value_page<E, D>(dv, v_in, dv.v_store, u, 0, f, red);         // HBM tier only
+        return;
+    }
     const int tid = threadIdx.x, C = dv.C;
     const int lr = tid % 16, grp = tid / 16, wave = tid / 64, lane = tid % 64;
-    __shared__ __attribute__((aligned(16))) double s_sh[CHUNK][D];
-    __shared__ double dot_sh[ROWS], rn_sh[ROWS];
+    __shared__ double s_sh[D], dot_sh[ROWS], rn_sh[ROWS];
     __shared__ int n_sh[ROWS];
-    __shared__ int a_out[CHUNK], p_out[CHUNK];
-    __shared__ int chg_sh[ROWS];                // 1 = the cluster's size and norm changed in this call
     __shared__ double red_v[NW];
     __shared__ int red_i[NW];
     __shared__ double psum_sh[2];
@@ -554,214 +941,115 @@ __device__ __forceinline__ void assign_update_reg_run(const DeviceView &dv, int 
             for (int e = 0; e < EPL; ++e) rr[i][e] = 0.0;
         }
     }
-    for (int j = tid; j < ROWS; j += THREADS) {
-        n_sh[j] = j < C ? dv.n[(size_t)u * C + j] : 0;
-        rn_sh[j] = j < C ? dv.rnorm[(size_t)u * C + j] : 0.0;
-        chg_sh[j] = 0;
-    }
-    if (k_in != nullptr) {
-        if constexpr (THREADS == kBlock) {
-            __shared__ double red[kBlock / (D / 8)][D];
-            store_key_page<E, D>(dv, k_in, dv.k_store, u, 0, f0, red, s_sh[0]);      // HBM tier only
-        }
+    if (tid < ROWS) {
+        n_sh[tid] = tid < C ? dv.n[(size_t)u * C + tid] : 0;
+        rn_sh[tid] = tid < C ? dv.rnorm[(size_t)u * C + tid] : 0.0;
     }
     const bool nested = dv.P > 0;
-    // The barriers inside the frame loop order LDS traffic only, and the loop touches no global memory: the
-    // call's summaries are staged in LDS a chunk at a time, the winner's row stays in registers and is written
-    // back once after the last frame, sizes and norms live in LDS, the frames' ids and ranks collect in LDS until
-    // the chunk ends.  A full __syncthreads() waits for every outstanding global access of the wavefront, and so
-    // does any wait the compiler places for a register a load is still to fill: with the next frame's summary
-    // fetched inside the loop and the winner's row written through in every frame, each frame waited once for
-    // that load, issued a moment before, and once for the store's acknowledgement.  The nested hierarchy's
-    // partition representatives and sizes do go through global memory from one frame to the next, so there the
-    // barriers stay full ones.
-    auto frame_barrier = [&]() {
-        if (nested) __syncthreads();          // workgroup-uniform
-        else lds_barrier();
-    };
-    unsigned int dirty = 0;                   // bit i: this group's row i changed in this call
-    // a one-frame call is all latency: its results go straight to memory, with no collection and no write-back pass
-    const bool single = f1 - f0 == 1;
-    for (int c0 = f0; c0 < f1; c0 += CHUNK) {
-        const int nc = min(CHUNK, f1 - c0);
-        if (k_in == nullptr) {
-            const double *src = dv.summ + ((size_t)u * dv.F + c0) * D;
-            for (int i = tid; i < nc * D / 2; i += THREADS)
-                *reinterpret_cast<double2 *>(&s_sh[0][0] + 2 * i) = *reinterpret_cast<const double2 *>(src + 2 * i);
+    const int part_f = nested ? dv.part[f] : 0;
+    const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : C;
+    store_key_page<E, D>(dv, k_in, dv.k_store, u, 0, f, red, s_sh);
+    __syncthreads();
+    // Dot products of the summary with the rows the group holds, four rows at a time written out side by side: four
+    // independent multiply-add chains, then their 16-lane reductions step by step in lockstep, so that one chain's
+    // latency is filled by the other three.  Rows beyond the table or of empty clusters give values nobody reads.  The
+    // group also forms |s|^2 from its own share of the channels, the same bits in every group.
+    double sl[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) sl[e] = s_sh[lr * EPL + e];
+    double ssq = 0.0;
+#pragma unroll
+    for (int h = 0; h < RPG / 4; ++h) {
+        if (h > 0 && NG * 4 * h >= C) break;                  // block-uniform: passes beyond the table
+        double p[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] += sl[e] * rr[4 * h + k][e];
+            if (h == 0) ssq += sl[e] * sl[e];
         }
-        __syncthreads();
-        for (int fc = 0; fc < nc; ++fc) {
-            const int f = c0 + fc;
-            const double *sv = s_sh[fc];
-            const int part_f = nested ? dv.part[f] : 0;
-            const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : C;
-            // Dot products of the summary with the rows the group holds, four rows at a time written out side by
-            // side: four independent multiply-add chains, then their 16-lane reductions step by step in lockstep,
-            // so that one chain's latency is filled by the other three (a loop over the rows with the block-uniform
-            // test per row kept every row's chain in a basic block of its own: 2100 cycles per frame for 210
-            // instructions).  Rows beyond the table or of empty clusters give values nobody reads.  The group also
-            // forms |s|^2 from its own share of the channels, the same bits in every group.
-            double sl[EPL];
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) sl[e] = sv[lr * EPL + e];
-            double ssq = 0.0;
+        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor8>(p[k]);
+        if (h == 0) ssq += dpp_f64<kDppXor8>(ssq);
 #pragma unroll
-            for (int h = 0; h < RPG / 4; ++h) {
-                if (h > 0 && NG * 4 * h >= C) break;                  // block-uniform: passes beyond the table
-                double p[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor7>(p[k]);
+        if (h == 0) ssq += dpp_f64<kDppXor7>(ssq);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor3>(p[k]);
+        if (h == 0) ssq += dpp_f64<kDppXor3>(ssq);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor1>(p[k]);
+        if (h == 0) ssq += dpp_f64<kDppXor1>(ssq);
+        if (lr == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dot_sh[grp + NG * (4 * h + k)] = p[k];
+        }
+    }
+    const double sn = sqrt(ssq);
+    __syncthreads();
+    // argmax of the cosine over the candidates, ties to the lowest id (at most one candidate per thread)
+    double bv = -INFINITY;
+    int bi = 0x7fffffff;
+    {
+        const int j = lo + tid;
+        if (j < hi && n_sh[j] > 0) {
+            bv = (sn == 0.0 || rn_sh[j] == 0.0) ? 0.0 : dot_sh[j] / (sn * rn_sh[j]);
+            bi = j;
+        }
+    }
+    wave_best_ascending(bv, bi);        // (ids ascend with the thread: j = lo + tid)
+    if (lane == 0) { red_v[wave] = bv; red_i[wave] = bi; }
+    // nested hierarchy: the partition's representative in this unit's key space follows the same running mean
+    int pn_i = 0;
+    if (nested) {
+        double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
+        pn_i = dv.pn[(size_t)u * dv.P + part_f];
+        double psq = 0.0;
+        if (tid < D) {
+            const double pv = ((double)pn_i * prow[tid] + s_sh[tid]) / ((double)pn_i + 1.0);
+            prow[tid] = pv;
+            psq = pv * pv;
+        }
+        if (wave < 2) {
+            psq = wave_sum(psq);
+            if (lane == 0) psum_sh[wave] = psq;
+        }
+    }
+    __syncthreads();
+    // every thread merges the wavefronts' winners itself (no second barrier for one thread's merge)
+    bv = red_v[0]; bi = red_i[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w)
+        if (better(red_v[w], red_i[w], bv, bi)) { bv = red_v[w]; bi = red_i[w]; }
+    const int a = bi == 0x7fffffff ? lo : bi;
+    const int ai = __builtin_amdgcn_readfirstlane(a / NG);      // workgroup-uniform: a scalar
+    if (grp == a % NG) {                                  // the group that holds row a: Eq. 3 as in k_assign_chain
+        const int na_i = n_sh[a];
+        const double na = (double)na_i, ny = __ddiv_rn(1.0, na + 1.0);
+        double sq = 0.0;
+#pragma unroll
+        for (int i = 0; i < RPG; ++i) {
+            if (i == ai) {                                // scalar branch: one pass runs
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) p[k] += sl[e] * rr[4 * h + k][e];
-                    if (h == 0) ssq += sl[e] * sl[e];
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor8>(p[k]);
-                if (h == 0) ssq += dpp_f64<kDppXor8>(ssq);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor7>(p[k]);
-                if (h == 0) ssq += dpp_f64<kDppXor7>(ssq);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor3>(p[k]);
-                if (h == 0) ssq += dpp_f64<kDppXor3>(ssq);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor1>(p[k]);
-                if (h == 0) ssq += dpp_f64<kDppXor1>(ssq);
-                if (lr == 0) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) dot_sh[grp + NG * (4 * h + k)] = p[k];
+                    const double rv = eq3_channel(na, ny, rr[i][e], sl[e]);
+                    r[(size_t)a * D + lr * EPL + e] = rv;
+                    sq += rv * rv;
                 }
             }
-            const double sn = sqrt(ssq);
-            frame_barrier();
-            // argmax of the cosine over the candidates, ties to the lowest id (THREADS >= C: at
-            // most one candidate per thread)
-            double bv = -INFINITY;
-            int bi = 0x7fffffff;
-            {
-                const int j = lo + tid;
-                if (j < hi && n_sh[j] > 0) {
-                    bv = (sn == 0.0 || rn_sh[j] == 0.0) ? 0.0 : dot_sh[j] / (sn * rn_sh[j]);
-                    bi = j;
-                }
-            }
-            wave_best_ascending(bv, bi);        // (ids ascend with the thread: j = lo + tid)
-            if (lane == 0) { red_v[wave] = bv; red_i[wave] = bi; }
-            // nested hierarchy: the partition's representative follows the same running mean
-            int pn_i = 0;
-            if (nested) {
-                double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
-                pn_i = dv.pn[(size_t)u * dv.P + part_f];
-                double psq = 0.0;
-                if (tid < D) {
-                    const double pv = ((double)pn_i * prow[tid] + sv[tid]) / ((double)pn_i + 1.0);
-                    prow[tid] = pv;
-                    psq = pv * pv;
-                }
-                if (wave < 2) {
-                    psq = wave_sum(psq);
-                    if (lane == 0) psum_sh[wave] = psq;
-                }
-            }
-            frame_barrier();
-            // every thread merges the wavefronts' winners itself (no second barrier for one thread's merge)
-            bv = red_v[0]; bi = red_i[0];
-#pragma unroll
-            for (int w = 1; w < NW; ++w)
-                if (better(red_v[w], red_i[w], bv, bi)) { bv = red_v[w]; bi = red_i[w]; }
-            const int a = bi == 0x7fffffff ? lo : bi;
-            const int ai = __builtin_amdgcn_readfirstlane(a / NG);      // workgroup-uniform: a scalar
-            if (grp == a % NG) {                                  // the group that holds row a
-                const int na_i = n_sh[a];
-                const double na = (double)na_i;
-                // Eq. 3 with each operation rounded separately (no contraction).  The division by n + 1, the same
-                // divisor for the lane's eight channels: the compiler's division sequence hands a flag from its
-                // scaling step to its last step in VCC, so eight of them run one after the other (1400 cycles).
-                // Instead y = RN(1 / (n + 1)) once, then per channel q = RN(x y) and two residual corrections
-                // q <- RN(q + RN(x - (n + 1) q) y), each residual exact in a fused multiply-add: the first leaves q
-                // within half an ulp and a little of x / (n + 1), and from such a q and a correctly rounded y the
-                // second returns the correctly rounded quotient (Markstein's theorem; n + 1 is a small integer, so
-                // its significand is not all ones, and nothing here is near the ends of the exponent range).
-                const double nb = na + 1.0, ny = __ddiv_rn(1.0, nb);
-                double sq = 0.0;
-#pragma unroll
-                for (int i = 0; i < RPG; ++i) {
-                    if (i == ai) {                                // scalar branch: one pass runs
-#pragma unroll
-                        for (int e = 0; e < EPL; ++e) {
-                            const double x = __dadd_rn(__dmul_rn(na, rr[i][e]), sl[e]);
-                            double rv = __dmul_rn(x, ny);
-                            rv = __fma_rn(__fma_rn(-nb, rv, x), ny, rv);
-                            rv = __fma_rn(__fma_rn(-nb, rv, x), ny, rv);
-                            rr[i][e] = rv;
-                            if (single) r[(size_t)a * D + lr * EPL + e] = rv;
-                            sq += rv * rv;
-                        }
-                    }
-                }
-                if (!single) dirty |= 1u << ai;
-                sq = row16_sum(sq);
-                if (lr == 0) {
-                    const double nr = sqrt(sq);
-                    if (single) {
-                        dv.rnorm[(size_t)u * C + a] = nr;
-                        dv.n[(size_t)u * C + a] = na_i + 1;
-                        dv.assign[(size_t)u * dv.F + f] = a;
-                        dv.pos[(size_t)u * dv.F + f] = na_i;
-                    } else {
-                        rn_sh[a] = nr;
-                        n_sh[a] = na_i + 1;
-                        chg_sh[a] = 1;
-                        a_out[fc] = a;
-                        p_out[fc] = na_i;
-                    }
-                }
-            }
-            if (nested && tid == 0) {
-                dv.prn[(size_t)u * dv.P + part_f] = sqrt(D > 64 ? psum_sh[0] + psum_sh[1] : psum_sh[0]);
-                dv.pn[(size_t)u * dv.P + part_f] = pn_i + 1;
-            }
-            if (single) return;                   // workgroup-uniform: nothing follows the only frame
-            frame_barrier();
         }
-        // the chunk's ids and ranks (the barrier that ended its last frame made them visible)
-        if (tid < nc) {
-            dv.assign[(size_t)u * dv.F + c0 + tid] = a_out[tid];
-            dv.pos[(size_t)u * dv.F + c0 + tid] = p_out[tid];
-        }
-        __syncthreads();                          // before the next chunk overwrites the staged summaries
-    }
-    // write back what changed: rows, sizes and norms
-#pragma unroll
-    for (int i = 0; i < RPG; ++i) {
-        if ((dirty >> i) & 1u) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) r[(size_t)(grp + NG * i) * D + lr * EPL + e] = rr[i][e];
+        sq = row16_sum(sq);
+        if (lr == 0) {
+            dv.rnorm[(size_t)u * C + a] = sqrt(sq);
+            dv.n[(size_t)u * C + a] = na_i + 1;
+            dv.assign[(size_t)u * dv.F + f] = a;
+            dv.pos[(size_t)u * dv.F + f] = na_i;
         }
     }
-    for (int j = tid; j < C; j += THREADS) {
-        if (chg_sh[j]) {
-            dv.n[(size_t)u * C + j] = n_sh[j];
-            dv.rnorm[(size_t)u * C + j] = rn_sh[j];
-        }
+    if (nested && tid == 0) {
+        dv.prn[(size_t)u * dv.P + part_f] = sqrt(D > 64 ? psum_sh[0] + psum_sh[1] : psum_sh[0]);
+        dv.pn[(size_t)u * dv.P + part_f] = pn_i + 1;
     }
-}
-
-template <int D, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, int f0, int f1) {
-    assign_update_reg_run<D, THREADS, float>(dv, blockIdx.x, f0, f1, nullptr);
-}
-
-// One frame in one launch (maintainer off, C <= 128, HBM tier, online phase).
-// grid (U, 2), 256 threads: y = 0 key page + summary + assignment + Eq. 3, y = 1 value page.
-template <typename E, int D>
-__global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k_in, const E *v_in, int f) {
-    if (blockIdx.y == 1) {
-        __shared__ double red[kBlock / (D / 8)][D];
-        store_value_page<E, D>(dv, v_in, dv.v_store, blockIdx.x, 0, f, red);         // HBM tier only
-        return;
-    }
-    assign_update_reg_run<D, kBlock, E>(dv, blockIdx.x, f, f + 1, k_in);
 }
 
 // ---------------------------------------------------------------------------
@@ -943,8 +1231,6 @@ __global__ __launch_bounds__(kBlock) void k_exact_var(DeviceView dv, int n_frame
 // MFMAs); the order of the additions inside a dot product is therefore not the
 // channel order, which moves a similarity by rounding only.
 // ---------------------------------------------------------------------------
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // Rounds that change nothing are skipped: a round `it` that moved no frame of a unit leaves the same
 // members, hence (the sums being one fixed sequence of additions) the same representatives bit for
@@ -1476,17 +1762,11 @@ hipError_t launch_fetch(const DeviceView &dv, int u0, int n_units, int max_moves
 hipError_t launch_assign_update(const DeviceView &dv, int f0, int f1, hipStream_t s) {
     return checked([&] {
         if (dv.maint_mode) {
-            if (dv.D == 64) k_assign_update<64, true><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
-            else k_assign_update<128, true><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
-        } else if (dv.C <= 128) {          // table in registers: 8 rows per 16-lane group
-            if (dv.D == 64) k_assign_update_reg<64, 256><<<dv.U, 256, 0, s>>>(dv, f0, f1);
-            else k_assign_update_reg<128, 256><<<dv.U, 256, 0, s>>>(dv, f0, f1);
-        } else if (dv.C <= 256) {
-            if (dv.D == 64) k_assign_update_reg<64, 512><<<dv.U, 512, 0, s>>>(dv, f0, f1);
-            else k_assign_update_reg<128, 512><<<dv.U, 512, 0, s>>>(dv, f0, f1);
+            if (dv.D == 64) k_assign_update<64><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
+            else k_assign_update<128><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
         } else {
-            if (dv.D == 64) k_assign_update<64, false><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
-            else k_assign_update<128, false><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
+            if (dv.D == 64) k_assign_chain<64><<<dv.U, kChainBlock, 0, s>>>(dv, f0, f1);
+            else k_assign_chain<128><<<dv.U, kChainBlock, 0, s>>>(dv, f0, f1);
         }
     });
 }

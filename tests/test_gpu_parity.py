@@ -191,6 +191,44 @@ def test_single_frame_calls_equal_batched_ingest_variants(kw, over):
         np.testing.assert_array_equal(a, b)
 
 
+# The batched assignment decides sixteen frames at once from dot products that it carries over, and falls back to the full
+# computation where two clusters are too close: streams made of few different frames and of their multiples and
+# negatives (ties to the last bit, representatives that shrink), of new scenes every frame or two (most assumed winners
+# are wrong, more clusters move than a chunk has slots), tables of less than a tile, a tile and one, and more than a
+# wavefront's candidates, with calls on both sides of a chunk.
+@pytest.mark.parametrize("C,D,kind", [(1, 64, "repeats"), (5, 128, "repeats"), (16, 64, "negatives"), (17, 128, "negatives"),
+                                      (64, 64, "rapid"), (128, 128, "rapid"), (40, 128, "zeros")])
+def test_batched_assignment_at_ties_equals_single_frame_calls_bitwise(C, D, kind):
+    F, T, U = 2 * C + 90, 3, 2
+    rng = np.random.default_rng(C)
+    if kind == "rapid":
+        centre = rng.standard_normal((F, U, 1, D))[np.repeat(np.arange(F), 2)[:F]]
+        x = centre + 0.9 * rng.standard_normal((F, U, T, D))
+    else:
+        few = rng.integers(-3, 4, (6, U, T, D)).astype(np.float64)
+        x = few[rng.integers(0, 6, F)] * rng.choice([1.0, 2.0, 3.0], (F, 1, 1, 1))
+        if kind == "negatives":
+            x *= rng.choice([1.0, -1.0], (F, 1, 1, 1))
+        if kind == "zeros":
+            x *= rng.choice([1.0, 0.0], (F, 1, 1, 1), p=[0.8, 0.2])
+    K = torch.tensor(x[:, None].astype(np.float32)).to(DEV)
+    cfg = dict(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T, max_frames=F, n_clusters=C, top_k=1,
+               kv_dtype="fp32")
+    states = []
+    for calls in ([1] * F, [2 * C] + [7] * F, [2 * C + 1] + [33, 16, 17, 2, 1] * F, [F]):
+        m = binding.Mosaic(binding.make_config(**cfg))
+        f = 0
+        while f < F:
+            n = min(calls.pop(0), F - f)
+            m.ingest_frame(K[f:f + n], K[f:f + n])
+            f += n
+        states.append((m.assignments(), *m.centroids()))
+        m.close()
+    for other in states[1:]:
+        for a, b in zip(states[0], other):
+            np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("over", [
     dict(),
     dict(maint_mode=binding.MAINT_EAGER, init_clusters=4, tau_min=1.0, tau_max=2.0, tau_n0=8.0, recluster_every=0),
