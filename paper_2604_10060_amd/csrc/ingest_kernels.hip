@@ -12,6 +12,7 @@
 #include <algorithm>
 #include "mosaic_internal.h"
 #include "maintain_device.h"
+#include "assign_device.h"
 
 namespace mosaic {
 
@@ -53,44 +54,6 @@ __device__ __forceinline__ double wave_sum(double x) { return wave64_sum(x); }
 __device__ __forceinline__ bool better(double v, int i, double bv, int bi) {
     return v > bv || (v == bv && i < bi);
 }
-// fp64 max / min as single instructions (the builtins add an instruction per operand that quiets signalling NaNs);
-// only used on values that are never NaN
-__device__ __forceinline__ double max_f64(double a, double b) {
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ double min_f64(double a, double b) {
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-// Best (value, id) of a wavefront when the ids ascend with the lane (at most one candidate per lane, -inf and
-// 0x7fffffff in lanes without one; no NaN): the largest value by a max butterfly (three instructions per step
-// against a dozen for the (value, id) pair), then the first lane that holds it, which is the lowest id.  Left in
-// every lane.
-__device__ __forceinline__ void wave_best_ascending(double &bv, int &bi) {
-    double m = bv;
-    m = max_f64(m, dpp_f64<kDppXor8>(m));
-    m = max_f64(m, dpp_f64<kDppXor7>(m));
-    m = max_f64(m, dpp_f64<kDppXor3>(m));
-    m = max_f64(m, dpp_f64<kDppXor1>(m));
-    const long long b = __double_as_longlong(m);
-    const int lo = (int)b, hi = (int)(b >> 32);
-    double wm = -INFINITY;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int l = __builtin_amdgcn_readlane(lo, 16 * r), h = __builtin_amdgcn_readlane(hi, 16 * r);
-        wm = fmax(wm, __longlong_as_double(((long long)h << 32) | (long long)(unsigned int)l));
-    }
-    const unsigned long long at = __ballot(bv == wm);
-    const int first = __ffsll((long long)at) - 1;                       // some lane holds the maximum
-    const int id = __builtin_amdgcn_readlane(bi, first);
-    bv = wm;
-    bi = wm == -INFINITY ? 0x7fffffff : id;
-}
-
 // Best (value, id) of a wavefront, left in every lane: a butterfly inside each row of 16
 // lanes with data-parallel primitives (the order is total, so every lane of a row ends
 // with the same pair), then the four rows' pairs are read from their first lanes.
@@ -257,65 +220,24 @@ __global__ __launch_bounds__(kBlock) void k_store_summary(DeviceView dv, const E
 // Retrieval augmentation, global representatives (paper Sec. V-C): the value of a
 // cluster's pseudo token is the mean of its member frames' value summaries, its key the
 // cluster's representative.  grid (U, C), 128 threads: one workgroup per cluster lists
-// the cluster's frames in ascending order (ballot-free compaction of the assignment
-// array: every thread looks at 16 consecutive frames, a scan over the threads' match
-// counts gives each match its slot) and adds their value summaries in that order, so
+// the cluster's frames in ascending order and adds their value summaries in that order, so
 // the sum is one fixed sequence of additions: the same bits on every run, whatever the
 // order in which workgroups are scheduled.  It then writes the fp32 key / value rows of
 // the pseudo-token tables (zero rows for empty clusters).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(128) void k_value_reps(DeviceView dv, int n_frames) {
-    constexpr int NT = 128, FPT = 16, CH = NT * FPT;
+    constexpr int NT = 128, CH = NT * kListPer;
     const int u = blockIdx.x, j = blockIdx.y, tid = threadIdx.x, C = dv.C;
-    const int wave = tid / 64, lane = tid % 64;
-    __shared__ int a_sh[CH];
     __shared__ int mem[CH];
-    __shared__ int wtot[2];
+    __shared__ int wtot[NT / 64];
     const size_t row = (size_t)u * C + j;
     const int nj = dv.n[row];                       // workgroup-uniform
-    const int *assign = dv.assign + (size_t)u * dv.F;
+    const double *vb = dv.vsumm + (size_t)u * dv.F * D + tid;
     double acc = 0.0;
     for (int c0 = 0; nj > 0 && c0 < n_frames; c0 += CH) {
-        const int cend = min(n_frames, c0 + CH);
-#pragma unroll
-        for (int i = 0; i < FPT; ++i) {
-            const int f = c0 + tid + NT * i;
-            a_sh[tid + NT * i] = f < cend ? assign[f] : -1;
-        }
-        __syncthreads();
-        unsigned int mask = 0;               // bit i: frame c0 + 16 tid + i belongs to cluster j
-#pragma unroll
-        for (int i = 0; i < FPT; ++i) mask |= (a_sh[tid * FPT + i] == j ? 1u : 0u) << i;
-        const int mine = __popc(mask);
-        int incl = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += t;
-        }
-        if (lane == 63) wtot[wave] = incl;
-        __syncthreads();
-        int slot = incl - mine + (wave == 1 ? wtot[0] : 0);
-        const int filled = wtot[0] + wtot[1];
-        while (mask) {
-            const int i = __ffs((int)mask) - 1;
-            mask &= mask - 1;
-            mem[slot++] = c0 + tid * FPT + i;
-        }
-        __syncthreads();
-        if (tid < D) {
-            const double *vb = dv.vsumm + (size_t)u * dv.F * D + tid;
-            for (int m0 = 0; m0 < filled; m0 += 16) {      // sixteen loads in flight, added in order
-                double v[16];
-#pragma unroll
-                for (int x = 0; x < 16; ++x) v[x] = vb[(size_t)mem[min(m0 + x, filled - 1)] * D];
-#pragma unroll
-                for (int x = 0; x < 16; ++x)
-                    if (m0 + x < filled) acc += v[x];
-            }
-        }
-        __syncthreads();                     // mem / a_sh are rewritten by the next chunk
+        const int m = list_members<NT>(dv.assign + (size_t)u * dv.F, j, c0, n_frames, mem, wtot);
+        if (tid < D) acc = add_members<16>(acc, mem, m, [&](int f) { return vb[(size_t)f * D]; });
     }
     if (tid < D) {
         dv.rvsum[row * D + tid] = acc;
@@ -487,28 +409,6 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
     }
 }
 
-// LDS written by one lane and read by others of the same wavefront: the wavefront runs in lockstep and LDS is in order,
-// so only the compiler has to be kept from moving the accesses across.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// One channel of Eq. 3, (n r + s) / (n + 1), each operation rounded separately (no contraction).  y = RN(1 / (n + 1)).
-// The division by n + 1, the same divisor for all channels: q = RN(x y) and two residual corrections
-// q <- RN(q + RN(x - (n + 1) q) y), each residual exact in a fused multiply-add: the first leaves q within half an ulp
-// and a little of x / (n + 1), and from such a q and a correctly rounded y the second returns the correctly rounded
-// quotient (Markstein's theorem; n + 1 is a small integer, so its significand is not all ones, and nothing here is near
-// the ends of the exponent range).  The compiler's own division hands a flag from its scaling step to its last step in
-// VCC, so the divisions of several channels run one after the other.
-__device__ __forceinline__ double eq3_channel(double n, double y, double r, double s) {
-    const double nb = n + 1.0, x = __dadd_rn(__dmul_rn(n, r), s);
-    double q = __dmul_rn(x, y);
-    q = __fma_rn(__fma_rn(-nb, q, x), y, q);
-    return __fma_rn(__fma_rn(-nb, q, x), y, q);
-}
-
 // ---------------------------------------------------------------------------
 // Online assignment + Eq. 3 without the maintainer, frames f0..f1-1 in order.  grid (U), kChainBlock threads.
 //
@@ -538,47 +438,7 @@ __device__ __forceinline__ double eq3_channel(double n, double y, double r, doub
 // the other -- table in registers, dot products, search, update, two barriers per frame -- needs 77 k.  Launch: 4 layers,
 // C = 512 in 16 partitions 48.7 -> 15.1 us, 28 layers, C = 128, beside page stores 37.1 -> 23.3 us.
 // ---------------------------------------------------------------------------
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kChainBlock = 512, kChainFrames = 16, kChainSlots = 16, kChainSims = 8192;
-constexpr double kChainMargin = 1e-11;          // in the cosine
-
-// Sum / maximum over a row of 16 lanes or a wavefront of values that may be -inf but not NaN.
-__device__ __forceinline__ double row16_max(double m) {
-    m = max_f64(m, dpp_f64<kDppXor8>(m));
-    m = max_f64(m, dpp_f64<kDppXor7>(m));
-    m = max_f64(m, dpp_f64<kDppXor3>(m));
-    return max_f64(m, dpp_f64<kDppXor1>(m));
-}
-__device__ __forceinline__ double wave_max(double m) {
-    m = row16_max(m);
-    const long long b = __double_as_longlong(m);
-    double wm = -INFINITY;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int l = __builtin_amdgcn_readlane((int)b, 16 * r), h = __builtin_amdgcn_readlane((int)(b >> 32), 16 * r);
-        wm = fmax(wm, __longlong_as_double(((long long)h << 32) | (long long)(unsigned int)l));
-    }
-    return wm;
-}
-// 1 / sqrt(x) and 1 / x to a few ulps (for similarities that only decide with a margin); 0 for x = 0
-__device__ __forceinline__ double fast_rsqrt(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = y * (1.5 - 0.5 * x * y * y);
-    y = y * (1.5 - 0.5 * x * y * y);
-    return x > 0.0 ? y : 0.0;
-}
-__device__ __forceinline__ double fast_rcp(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-}
-__device__ __forceinline__ double readlane_f64(double x, int l) {
-    const long long b = __double_as_longlong(x);
-    return __longlong_as_double(((long long)__builtin_amdgcn_readlane((int)(b >> 32), l) << 32) |
-                                (long long)(unsigned int)__builtin_amdgcn_readlane((int)b, l));
-}
+constexpr int kChainBlock = 512, kChainSims = 8192;
 
 template <int D>
 __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int f0, int f1) {
@@ -745,61 +605,8 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
         if (wave == 0) {
             int w = n < nc ? slot_sh[near_sh[n] == kNone ? lo_sh[n] : near_sh[n]] : -1;       // the frame's winner, as assumed
             int done = nc;
-            if (nc > 1) {
-                const int fn = min(n, nc - 1), lo = lo_sh[fn];
-                const double is = isn_sh[fn], sn = sn_sh[fn], ss = ss_sh[fn], out = out_v[fn];
-                double gr[FR];                      // s_h . s_n / |s_n| of the earlier frames h
-#pragma unroll
-                for (int h = 0; h < FR; ++h) gr[h] = gram_sh[h][fn];
-                for (;;) {                          // (at most FR turns: the first frame that disagrees comes later in every one)
-                    double best = -INFINITY, next = -INFINITY;
-                    int bk = -1;
-                    bool odd = false, back = false;
-                    for (int kb = 0; kb < n_slot; kb += 4) {
-                        const int k = kb + g, id = slot_id[min(k, n_slot - 1)], cj = id - lo;
-                        const bool cand = k < n_slot && cj >= 0 && cj < width;
-                        const double n0 = (double)n_sh[id], ir0 = irn_sh[id];
-                        // (n r + the slot's earlier frames) . s_n / |s_n|, and the squared length of that vector
-                        double num = cand ? n0 * (sim_sh[fn * width + (cand ? cj : 0)] * is) : 0.0;
-#pragma unroll
-                        for (int h = 0; h < FR - 1; ++h)
-                            num += __builtin_amdgcn_readlane(w, h) == k && h < n ? gr[h] : 0.0;
-                        double t = w == k ? __builtin_fma(2.0 * num, sn, ss) : 0.0;
-                        back |= w == k && !(num >= 0.0);
-                        t += dpp_f64<0x111>(t);     // row_shr 1, 2, 4, 8: running sum over the frames
-                        t += dpp_f64<0x112>(t);
-                        t += dpp_f64<0x114>(t);
-                        t += dpp_f64<0x118>(t);
-                        const double len = (ir0 > 0.0 ? n0 * n0 * fast_rcp(ir0 * ir0) : 0.0) + dpp_f64<0x111>(t);
-                        const double c = cand && n0 > 0.0 ? num * fast_rsqrt(len) : -INFINITY;
-                        odd |= !(c == c);
-                        next = c > best ? best : fmax(next, c);
-                        bk = c > best ? k : bk;
-                        best = c > best ? c : best;
-                    }
-#pragma unroll
-                    for (int o = 16; o <= 32; o <<= 1) {            // over the four lanes that look at the frame
-                        const double ob = __shfl_xor(best, o, 64), on = __shfl_xor(next, o, 64);
-                        const int ok = __shfl_xor(bk, o, 64);
-                        next = fmax(fmax(next, on), fmin(best, ob));
-                        bk = ob > best ? ok : bk;
-                        best = fmax(best, ob);
-                    }
-                    const unsigned long long odds = __ballot(odd), backs = __ballot(back);
-                    const unsigned int odd16 = (unsigned int)(odds | odds >> 16 | odds >> 32 | odds >> 48) & 0xffffu;
-                    const unsigned int back16 = (unsigned int)(backs | backs >> 16 | backs >> 32 | backs >> 48) & 0xffffu;
-                    // (frame 0 joins slot 0 by construction)
-                    const bool clear = n == 0 || n >= nc || (best - fmax(next, out) > kChainMargin && !((odd16 >> n) & 1));
-                    const unsigned int vague = (unsigned int)__ballot(!clear) & 0xffffu;
-                    const unsigned int other = (unsigned int)__ballot(clear && n > 0 && n < nc && bk != w) & 0xffffu;
-                    // a winner at more than a right angle shortens the representative: the rounding errors of its dot
-                    // products grow relative to it, so the frames after it are better taken from the rows
-                    const int stop = min(vague ? __ffs((int)vague) - 1 : nc, back16 ? __ffs((int)back16) : nc);
-                    const int at = other ? __ffs((int)other) - 1 : nc;
-                    if (at >= stop) { done = min(stop, nc); break; }
-                    if (n == at) w = bk;            // ... that frame's winner, and once more
-                }
-            }
+            if (nc > 1)
+                done = chain_decide({sim_sh, width, lo_sh, sn_sh, isn_sh, ss_sh, out_v, gram_sh, slot_id, n_sh, irn_sh}, nc, n_slot, w);
             if (lane < done) {
                 int p = n_sh[slot_id[w]];
 #pragma unroll
@@ -1093,80 +900,75 @@ __global__ __launch_bounds__(kBlock) void k_lloyd_seed(DeviceView dv, int W) {
 }
 
 // ---------------------------------------------------------------------------
-// Seeds under the nested hierarchy (Sec. V-B).  grid (U), 256 threads.
+// Seeds under the nested hierarchy (Sec. V-B).  grid (U, ceil(C/64)), 256 threads: 64 cluster ids each.
 // Cluster id j = p*Cs + jj belongs to visual partition p.  With np warm-up
 // frames in p and L = min(Cs, np), id j is started (n_j = 1 as a placeholder)
 // from the summary of the partition's member floor(jj*np/L) if jj < L and is
-// left empty otherwise.
+// left empty otherwise.  A wavefront per partition walks the frame -> partition map 64 frames at a time -- once
+// to count, once to meet the members its lanes' clusters start from -- instead of a thread per partition one frame
+// at a time for all ids of a unit (W = 1024, P = 16, C = 512: 250 -> 24 us).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_lloyd_seed_nested(DeviceView dv, int W) {
     constexpr int EPL = D / 16;
-    const int u = blockIdx.x, tid = threadIdx.x, C = dv.C, Cs = dv.Cs;
-    const int lr = tid % 16, row0 = tid / 16;
-    constexpr int kPartLds = 8192;            // warm-up partitions are scanned out of LDS when they fit
-    __shared__ int np_sh[64];
-    __shared__ int part_sh[kPartLds];
-    const bool in_lds = W <= kPartLds;
-    if (in_lds)
-        for (int f = tid; f < W; f += kBlock) part_sh[f] = dv.part[f];
-    __syncthreads();
-    const int *part = in_lds ? part_sh : dv.part;
-    // member lists of the partitions, ascending, back to back in the unit's (not yet used)
-    // rank array: thread p counts, thread 0 lays out the starts, thread p fills its list
-    __shared__ int start_sh[65];
-    int *order = dv.pos + (size_t)u * dv.F;
-    if (tid < dv.P) {
-        int c = 0;
-        for (int f = 0; f < W; ++f) c += part[f] == tid;
-        np_sh[tid] = c;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int o = 0;
-        for (int p = 0; p < dv.P; ++p) { start_sh[p] = o; o += np_sh[p]; }
-    }
-    __syncthreads();
-    if (tid < dv.P) {
-        int o = start_sh[tid];
-        for (int f = 0; f < W; ++f)
-            if (part[f] == tid) order[o++] = f;
-    }
-    __syncthreads();
-    for (int j = row0; j < C; j += 16) {
-        const int p = j / Cs, jj = j - p * Cs, np = np_sh[p], L = min(Cs, np);
-        double *rj = dv.r + ((size_t)u * C + j) * D + lr * EPL;
-        if (jj >= L) {
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) rj[i] = 0.0;
-            if (lr == 0) { dv.rnorm[(size_t)u * C + j] = 0.0; dv.n[(size_t)u * C + j] = 0; }
-            continue;
+    const int u = blockIdx.x, tid = threadIdx.x, lane = tid % 64, C = dv.C, Cs = dv.Cs;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lr = tid % 16, grp = tid / 16;
+    const int j0 = blockIdx.y * 64, j1 = min(C, j0 + 64);
+    __shared__ int src_sh[64];                // frame that starts cluster j0 + i, -1: stays empty
+    for (int p = j0 / Cs + wave; p <= (j1 - 1) / Cs; p += kBlock / 64) {
+        int np = 0;
+        for (int f0 = 0; f0 < W; f0 += 64)
+            np += __popcll(__ballot(f0 + lane < W && dv.part[min(f0 + lane, W - 1)] == p));
+        const int jj = j0 + lane - p * Cs, L = min(Cs, np);
+        const bool mine = j0 + lane < j1 && jj >= 0 && jj < Cs;
+        const int want = mine && jj < L ? (int)(((long long)jj * np) / L) : -1;
+        int src = -1, seen = 0;
+        for (int f0 = 0; f0 < W; f0 += 64) {
+            unsigned long long m = __ballot(f0 + lane < W && dv.part[min(f0 + lane, W - 1)] == p);
+            const int here = __popcll(m), t = want - seen;
+            for (int i = 0; m; ++i, m &= m - 1)                      // the i-th member of these 64 frames
+                if (t == i) src = f0 + __ffsll((long long)m) - 1;
+            seen += here;
         }
-        const int src = order[start_sh[p] + (int)(((long long)jj * np) / L)];
-        const double *s = dv.summ + ((size_t)u * dv.F + src) * D + lr * EPL;
+        if (mine) src_sh[lane] = src;
+    }
+    __syncthreads();
+    for (int i = grp; j0 + i < j1; i += kBlock / 16) {
+        const size_t j = (size_t)u * C + j0 + i;
+        const int src = src_sh[i];
+        const double *s = dv.summ + ((size_t)u * dv.F + max(src, 0)) * D + lr * EPL;
         double sq = 0.0;
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) { rj[i] = s[i]; sq += s[i] * s[i]; }
+        for (int e = 0; e < EPL; ++e) {
+            const double x = src >= 0 ? s[e] : 0.0;
+            dv.r[j * D + lr * EPL + e] = x;
+            sq += x * x;
+        }
         sq = group16_sum(sq);
-        if (lr == 0) { dv.rnorm[(size_t)u * C + j] = sqrt(sq); dv.n[(size_t)u * C + j] = 1; }
+        if (lr == 0) { dv.rnorm[j] = sqrt(sq); dv.n[j] = src >= 0 ? 1 : 0; }
     }
 }
 
 // ---------------------------------------------------------------------------
 // Partition representatives from the member lists: per unit and visual
 // partition the mean of the key summaries of the partition's frames, in
-// ascending frame order.  grid (U, P), 128 threads (thread d owns channel d).
+// ascending frame order.  grid (U, P), 128 threads (thread d owns channel d; the
+// members are listed first, then sixteen loads are in flight: 73 -> 13 us for 1024 frames).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(128) void k_partition_reps(DeviceView dv, int n_frames) {
+    constexpr int NT = 128, CH = NT * kListPer;
     const int u = blockIdx.x, p = blockIdx.y, tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     __shared__ double nsum_sh[2];
+    __shared__ int mem[CH];
+    __shared__ int wtot[NT / 64];
+    const double *sb = dv.summ + (size_t)u * dv.F * D + tid;
     double acc = 0.0;
     int count = 0;
-    for (int f = 0; f < n_frames; ++f) {
-        if (dv.part[f] != p) continue;                   // workgroup-uniform
-        if (tid < D) acc += dv.summ[((size_t)u * dv.F + f) * D + tid];
-        ++count;
+    for (int c0 = 0; c0 < n_frames; c0 += CH) {
+        const int m = list_members<NT>(dv.part, p, c0, n_frames, mem, wtot);
+        if (tid < D) acc = add_members<16>(acc, mem, m, [&](int f) { return sb[(size_t)f * D]; });
+        count += m;
     }
     double sq = 0.0;
     if (tid < D) {
@@ -1777,8 +1579,9 @@ hipError_t launch_lloyd(const DeviceView &dv, int n_frames, int iters, bool seed
     if (seed_from_warmup) {
         e = checked([&] {
             if (dv.P > 0) {
-                if (dv.D == 64) k_lloyd_seed_nested<64><<<dv.U, kBlock, 0, s>>>(dv, n_frames);
-                else k_lloyd_seed_nested<128><<<dv.U, kBlock, 0, s>>>(dv, n_frames);
+                const dim3 gs(dv.U, (dv.C + 63) / 64);
+                if (dv.D == 64) k_lloyd_seed_nested<64><<<gs, kBlock, 0, s>>>(dv, n_frames);
+                else k_lloyd_seed_nested<128><<<gs, kBlock, 0, s>>>(dv, n_frames);
             } else {
                 if (dv.D == 64) k_lloyd_seed<64><<<dv.U, kBlock, 0, s>>>(dv, n_frames);
                 else k_lloyd_seed<128><<<dv.U, kBlock, 0, s>>>(dv, n_frames);

@@ -229,6 +229,45 @@ def test_batched_assignment_at_ties_equals_single_frame_calls_bitwise(C, D, kind
             np.testing.assert_array_equal(a, b)
 
 
+# The same for the visual level of the nested index (embedding sizes with and without 16-byte rows, one to four tiles of
+# partitions, embeddings that repeat to the last bit, change at every frame or vanish) and the semantic level below it.
+@pytest.mark.parametrize("P,Cs,Dv,kind", [(3, 2, 64, "repeats"), (17, 2, 130, "rapid"), (40, 3, 1027, "repeats"),
+                                          (64, 1, 260, "rapid"), (5, 4, 36, "zeros")])
+def test_batched_visual_assignment_equals_single_frame_calls_bitwise(P, Cs, Dv, kind):
+    C, T, U, D = P * Cs, 2, 2, 64
+    F = 2 * C + 90
+    rng = np.random.default_rng(P)
+    x = rng.standard_normal((F, U, 1, D))[np.arange(F) // 5] + 0.4 * rng.standard_normal((F, U, T, D))
+    if kind == "rapid":
+        e = rng.standard_normal((F, Dv))[np.arange(F) // 2] + 0.7 * rng.standard_normal((F, Dv))
+    else:
+        e = rng.integers(-2, 3, (5, Dv))[rng.integers(0, 5, F)] * rng.choice([1.0, 3.0, -1.0], (F, 1))
+        if kind == "zeros":
+            e = e * rng.choice([1.0, 0.0], (F, 1), p=[0.8, 0.2])
+    K = torch.tensor(x[:, None].astype(np.float32)).to(DEV)
+    E = torch.tensor(e.astype(np.float32)).to(DEV)
+    # single-frame slices of an odd-sized embedding are not 16-byte aligned: one padded row each
+    one = torch.zeros((F, (Dv + 3) // 4 * 4), device=DEV)
+    one[:, :Dv] = E
+    cfg = dict(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T, max_frames=F, n_clusters=C, top_k=1,
+               kv_dtype="fp32", n_partitions=P, visual_dim=Dv)
+    states = []
+    for calls in ([1] * F, [2 * C + 1] + [33, 16, 17, 2, 1] * F, [F]):
+        m = binding.Mosaic(binding.make_config(**cfg))
+        f = 0
+        while f < F:
+            n = min(calls.pop(0), F - f)
+            ev = one[f, :Dv][None] if n == 1 else E[f:f + n].clone()
+            m.ingest_frame_visual(K[f:f + n], K[f:f + n], ev)
+            f += n
+        p = m.partitions()
+        states.append([m.assignments(), *m.centroids()] + [p[k] for k in sorted(p)])
+        m.close()
+    for other in states[1:]:
+        for a, b in zip(states[0], other):
+            np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("over", [
     dict(),
     dict(maint_mode=binding.MAINT_EAGER, init_clusters=4, tau_min=1.0, tau_max=2.0, tau_n0=8.0, recluster_every=0),
