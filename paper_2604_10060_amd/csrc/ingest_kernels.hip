@@ -247,14 +247,17 @@ __global__ __launch_bounds__(128) void k_value_reps(DeviceView dv, int n_frames)
 }
 
 // ---------------------------------------------------------------------------
-// Online assignment + Eq. 3 with the self-adaptive maintainer, frames f0..f1-1 in order.
-// grid (U), 256 threads.  The insertion procedure (Sec. VI, Alg. 1 lines 1-10) follows
-// the update: running variance (Eq. 4), threshold (Eq. 5) at the size before the
-// insertion, then absorb / split / defer.
+// Online assignment + Eq. 3, frames f0..f1-1 in order, the table read from global memory for every frame.  grid (U),
+// 256 threads.  With the maintainer, and without it for calls of one or two frames on tables of more than 256 clusters
+// (2 layers, whole calls with the page store, this / k_assign_chain: C = 1000, one frame a call 8.4 / 11.7 us, two
+// 11.2 / 12; three 14.8 / 12.9; C = 300, three 16.1 / 15.1).
 // ---------------------------------------------------------------------------
+// With MAINT the insertion procedure of the self-adaptive maintainer (Sec. VI,
+// Alg. 1 lines 1-10) follows the update: running variance (Eq. 4), threshold
+// (Eq. 5) at the size before the insertion, then absorb / split / defer.
 enum { kActAbsorb = 1, kActSplit = 2, kActDefer = 3, kActForced = 4 };
 
-template <int D>
+template <int D, bool MAINT>
 __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0, int f1) {
     constexpr int EPL = D / 16;  // elements per lane in a 16-lane row group
     const int u = blockIdx.x, tid = threadIdx.x, C = dv.C;
@@ -263,18 +266,22 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
     __shared__ double dot_sh[1024];
     __shared__ double red_v[4];
     __shared__ int red_i[4];
-    __shared__ double snorm_sh, nsum_sh[2], dsum_sh[2];
+    __shared__ double snorm_sh, nsum_sh[2], dsum_sh[2], psum_sh[2];
     __shared__ int act_sh;
-    __shared__ SplitShared<D> split_sh;
+    __shared__ SplitShared<MAINT ? D : 16> split_sh;   // (small placeholder when the maintainer is off)
     double *r = dv.r + (size_t)u * C * D;
     double *rn = dv.rnorm + (size_t)u * C;
     int *n = dv.n + (size_t)u * C;
 
+    const bool nested = dv.P > 0;
     // the summary of the next frame travels while the current frame is processed
     double s_ahead = tid < D ? dv.summ[((size_t)u * dv.F + f0) * D + tid] : 0.0;
     for (int f = f0; f < f1; ++f) {
-        // only the ids in use, [0, n_slots), can have members; the table behind them is not read
-        const int lo = 0, hi = min(C, max(dv.n_slots[u], 1));
+        // candidates: every cluster id, or (nested hierarchy, Sec. V-B) the ids of the frame's
+        // visual partition only
+        const int part_f = nested ? dv.part[f] : 0;
+        // (maintainer: only the ids in use, [0, n_slots), can have members; the table behind them is not read)
+        const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : (MAINT ? min(C, max(dv.n_slots[u], 1)) : C);
         if (tid < D) {
             s_sh[tid] = s_ahead;
             if (f + 1 < f1) s_ahead = dv.summ[((size_t)u * dv.F + f + 1) * D + tid];
@@ -282,8 +289,14 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
         __syncthreads();
         if (wave == 0) {
             double x = 0.0;
-            for (int d = lane; d < D; d += 64) x += s_sh[d] * s_sh[d];
-            x = wave_sum(x);
+            if constexpr (MAINT) {
+                for (int d = lane; d < D; d += 64) x += s_sh[d] * s_sh[d];
+                x = wave_sum(x);
+            } else {            // (in the order of the kernels that share this state)
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) x += s_sh[lr * EPL + e] * s_sh[lr * EPL + e];
+                x = row16_sum(x);
+            }
             if (lane == 0) snorm_sh = sqrt(x);
         }
         // sizes and norms of this thread's candidates (at most four: C <= 1024), fetched ahead of the rows
@@ -354,20 +367,49 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
             const double rv = __ddiv_rn(__dadd_rn(__dmul_rn(na, r[(size_t)a * D + tid]), s_sh[tid]),
                                         na + 1.0);
             r[(size_t)a * D + tid] = rv;
+            if constexpr (!MAINT) dot_sh[tid] = rv;  // (the dot products have been read)
             sq = rv * rv;
             const double t = s_sh[tid] - rv;
             dq = t * t;
         }
-        if (wave < 2) {
+        if (MAINT && wave < 2) {
             sq = wave_sum(sq);
             dq = wave_sum(dq);
             if (lane == 0) { nsum_sh[wave] = sq; dsum_sh[wave] = dq; }
         }
+        // nested hierarchy: the partition's representative in this unit's key space follows the
+        // same running mean (Eq. 3 one level up)
+        int pn_i = 0;
+        if (nested) {
+            double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
+            pn_i = dv.pn[(size_t)u * dv.P + part_f];
+            double psq = 0.0;
+            if (tid < D) {
+                const double pv = ((double)pn_i * prow[tid] + s_sh[tid]) / ((double)pn_i + 1.0);
+                prow[tid] = pv;
+                psq = pv * pv;
+            }
+            if (wave < 2) {
+                psq = wave_sum(psq);
+                if (lane == 0) psum_sh[wave] = psq;
+            }
+        }
         __syncthreads();   // all threads have read n[a] and written r before the scalars change
+        if (!MAINT && wave == 0) {      // (the norm's additions in the order of the kernels that share this state)
+            double x = 0.0;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) x += dot_sh[lr * EPL + e] * dot_sh[lr * EPL + e];
+            x = row16_sum(x);
+            if (lane == 0) nsum_sh[0] = x;
+        }
         if (tid == 0) {
-            rn[a] = sqrt(D > 64 ? nsum_sh[0] + nsum_sh[1] : nsum_sh[0]);
+            if (nested) {
+                dv.prn[(size_t)u * dv.P + part_f] = sqrt(D > 64 ? psum_sh[0] + psum_sh[1] : psum_sh[0]);
+                dv.pn[(size_t)u * dv.P + part_f] = pn_i + 1;
+            }
+            rn[a] = sqrt(MAINT && D > 64 ? nsum_sh[0] + nsum_sh[1] : nsum_sh[0]);
             int act = kActAbsorb;
-            {
+            if (MAINT) {
                 const double dist2 = D > 64 ? dsum_sh[0] + dsum_sh[1] : dsum_sh[0];
                 double *var = dv.var + (size_t)u * C;
                 const double var_new = (na * var[a] + dist2) / (na + 1.0);                          // Eq. 4
@@ -399,7 +441,7 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
             }
         }
         __syncthreads();
-        {
+        if constexpr (MAINT) {
             if (act_sh == kActSplit) {                  // workgroup-uniform
                 const int fresh = mt_split_cluster<D>(dv, u, a, f + 1, false, split_sh);
                 if (tid == 0) dv.mt_cnt[(size_t)u * 4 + (fresh >= 0 ? 0 : 3)] += 1;
@@ -710,6 +752,221 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
         }
         c0 += nc;
         __syncthreads();                            // before the next chunk overwrites the staged summaries
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Online assignment + Eq. 3 without the maintainer for calls of a few frames, tables of up to THREADS / 2 clusters, one
+// frame after the other.  grid (U), THREADS threads.  Each 16-lane group keeps its RPG rows of the unit's table
+// (row j = group + (THREADS/16) i) in registers for the whole call, sizes and norms sit in LDS, and the winner's row is
+// updated in place, so nothing in the per-frame chain waits on memory.  The operations of a similarity, of Eq. 3 and of a
+// norm are those of the one-frame kernel and of k_assign_chain's full computation, in their order.
+// What k_assign_chain pays per call whatever the number of frames -- sixteen frames' worth of matrix products, the nearest
+// clusters, slots, the check -- is more than up to four frames in turn (4 layers, 700 frames, C = 180, whole calls with the
+// page store, in turn / chain: 2 a call 11.0 / 13.4 us, 4 a call 14.9 / 16.2; 5 a call 17.2 / 17.0, 8 a call 23.3 / 20.7).
+// ---------------------------------------------------------------------------
+constexpr int kRegFrames = 4;
+
+template <int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, int f0, int f1) {
+    constexpr int EPL = D / 16, NG = THREADS / 16, RPG = 8, NW = THREADS / 64, ROWS = NG * RPG;
+    constexpr int CHUNK = kRegFrames;           // frames whose summaries are staged in LDS at a time
+    const int u = blockIdx.x, tid = threadIdx.x, C = dv.C;
+    const int lr = tid % 16, grp = tid / 16, wave = tid / 64, lane = tid % 64;
+    __shared__ __attribute__((aligned(16))) double s_sh[CHUNK][D];
+    __shared__ double dot_sh[ROWS], rn_sh[ROWS];
+    __shared__ int n_sh[ROWS];
+    __shared__ int a_out[CHUNK], p_out[CHUNK];
+    __shared__ int chg_sh[ROWS];                // 1 = the cluster's size and norm changed in this call
+    __shared__ double red_v[NW];
+    __shared__ int red_i[NW];
+    __shared__ double psum_sh[2];
+    double *r = dv.r + (size_t)u * C * D;
+    double rr[RPG][EPL];
+#pragma unroll
+    for (int i = 0; i < RPG; ++i) {
+        const double *rj = r + (size_t)min(grp + NG * i, C - 1) * D + lr * EPL;
+        if (NG * i < C) {                 // block-uniform: passes beyond the table are not loaded
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) rr[i][e] = rj[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) rr[i][e] = 0.0;
+        }
+    }
+    for (int j = tid; j < ROWS; j += THREADS) {
+        n_sh[j] = j < C ? dv.n[(size_t)u * C + j] : 0;
+        rn_sh[j] = j < C ? dv.rnorm[(size_t)u * C + j] : 0.0;
+        chg_sh[j] = 0;
+    }
+    const bool nested = dv.P > 0;
+    // The barriers inside the frame loop order LDS traffic only, and the loop touches no global memory: the
+    // call's summaries are staged in LDS a chunk at a time, the winner's row stays in registers and is written
+    // back once after the last frame, sizes and norms live in LDS, the frames' ids and ranks collect in LDS until
+    // the chunk ends.  A full __syncthreads() waits for every outstanding global access of the wavefront, and so
+    // does any wait the compiler places for a register a load is still to fill: with the next frame's summary
+    // fetched inside the loop and the winner's row written through in every frame, each frame waited once for
+    // that load, issued a moment before, and once for the store's acknowledgement.  The nested hierarchy's
+    // partition representatives and sizes do go through global memory from one frame to the next, so there the
+    // barriers stay full ones.
+    auto frame_barrier = [&]() {
+        if (nested) __syncthreads();          // workgroup-uniform
+        else lds_barrier();
+    };
+    unsigned int dirty = 0;                   // bit i: this group's row i changed in this call
+    // a one-frame call is all latency: its results go straight to memory, with no collection and no write-back pass
+    const bool single = f1 - f0 == 1;
+    for (int c0 = f0; c0 < f1; c0 += CHUNK) {
+        const int nc = min(CHUNK, f1 - c0);
+        {
+            const double *src = dv.summ + ((size_t)u * dv.F + c0) * D;
+            for (int i = tid; i < nc * D / 2; i += THREADS)
+                *reinterpret_cast<double2 *>(&s_sh[0][0] + 2 * i) = *reinterpret_cast<const double2 *>(src + 2 * i);
+        }
+        __syncthreads();
+        for (int fc = 0; fc < nc; ++fc) {
+            const int f = c0 + fc;
+            const double *sv = s_sh[fc];
+            const int part_f = nested ? dv.part[f] : 0;
+            const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : C;
+            // Dot products of the summary with the rows the group holds, four rows at a time written out side by
+            // side: four independent multiply-add chains, then their 16-lane reductions step by step in lockstep,
+            // so that one chain's latency is filled by the other three (a loop over the rows with the block-uniform
+            // test per row kept every row's chain in a basic block of its own: 2100 cycles per frame for 210
+            // instructions).  Rows beyond the table or of empty clusters give values nobody reads.  The group also
+            // forms |s|^2 from its own share of the channels, the same bits in every group.
+            double sl[EPL];
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) sl[e] = sv[lr * EPL + e];
+            double ssq = 0.0;
+#pragma unroll
+            for (int h = 0; h < RPG / 4; ++h) {
+                if (h > 0 && NG * 4 * h >= C) break;                  // block-uniform: passes beyond the table
+                double p[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) p[k] += sl[e] * rr[4 * h + k][e];
+                    if (h == 0) ssq += sl[e] * sl[e];
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor8>(p[k]);
+                if (h == 0) ssq += dpp_f64<kDppXor8>(ssq);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor7>(p[k]);
+                if (h == 0) ssq += dpp_f64<kDppXor7>(ssq);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor3>(p[k]);
+                if (h == 0) ssq += dpp_f64<kDppXor3>(ssq);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor1>(p[k]);
+                if (h == 0) ssq += dpp_f64<kDppXor1>(ssq);
+                if (lr == 0) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) dot_sh[grp + NG * (4 * h + k)] = p[k];
+                }
+            }
+            const double sn = sqrt(ssq);
+            frame_barrier();
+            // argmax of the cosine over the candidates, ties to the lowest id (THREADS >= C: at
+            // most one candidate per thread)
+            double bv = -INFINITY;
+            int bi = 0x7fffffff;
+            {
+                const int j = lo + tid;
+                if (j < hi && n_sh[j] > 0) {
+                    bv = (sn == 0.0 || rn_sh[j] == 0.0) ? 0.0 : dot_sh[j] / (sn * rn_sh[j]);
+                    bi = j;
+                }
+            }
+            wave_best_ascending(bv, bi);        // (ids ascend with the thread: j = lo + tid)
+            if (lane == 0) { red_v[wave] = bv; red_i[wave] = bi; }
+            // nested hierarchy: the partition's representative follows the same running mean
+            int pn_i = 0;
+            if (nested) {
+                double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
+                pn_i = dv.pn[(size_t)u * dv.P + part_f];
+                double psq = 0.0;
+                if (tid < D) {
+                    const double pv = ((double)pn_i * prow[tid] + sv[tid]) / ((double)pn_i + 1.0);
+                    prow[tid] = pv;
+                    psq = pv * pv;
+                }
+                if (wave < 2) {
+                    psq = wave_sum(psq);
+                    if (lane == 0) psum_sh[wave] = psq;
+                }
+            }
+            frame_barrier();
+            // every thread merges the wavefronts' winners itself (no second barrier for one thread's merge)
+            bv = red_v[0]; bi = red_i[0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w)
+                if (better(red_v[w], red_i[w], bv, bi)) { bv = red_v[w]; bi = red_i[w]; }
+            const int a = bi == 0x7fffffff ? lo : bi;
+            const int ai = __builtin_amdgcn_readfirstlane(a / NG);      // workgroup-uniform: a scalar
+            if (grp == a % NG) {                                  // the group that holds row a
+                const int na_i = n_sh[a];
+                const double na = (double)na_i;
+                const double ny = __ddiv_rn(1.0, na + 1.0);
+                double sq = 0.0;
+#pragma unroll
+                for (int i = 0; i < RPG; ++i) {
+                    if (i == ai) {                                // scalar branch: one pass runs
+#pragma unroll
+                        for (int e = 0; e < EPL; ++e) {
+                            const double rv = eq3_channel(na, ny, rr[i][e], sl[e]);
+                            rr[i][e] = rv;
+                            if (single) r[(size_t)a * D + lr * EPL + e] = rv;
+                            sq += rv * rv;
+                        }
+                    }
+                }
+                if (!single) dirty |= 1u << ai;
+                sq = row16_sum(sq);
+                if (lr == 0) {
+                    const double nr = sqrt(sq);
+                    if (single) {
+                        dv.rnorm[(size_t)u * C + a] = nr;
+                        dv.n[(size_t)u * C + a] = na_i + 1;
+                        dv.assign[(size_t)u * dv.F + f] = a;
+                        dv.pos[(size_t)u * dv.F + f] = na_i;
+                    } else {
+                        rn_sh[a] = nr;
+                        n_sh[a] = na_i + 1;
+                        chg_sh[a] = 1;
+                        a_out[fc] = a;
+                        p_out[fc] = na_i;
+                    }
+                }
+            }
+            if (nested && tid == 0) {
+                dv.prn[(size_t)u * dv.P + part_f] = sqrt(D > 64 ? psum_sh[0] + psum_sh[1] : psum_sh[0]);
+                dv.pn[(size_t)u * dv.P + part_f] = pn_i + 1;
+            }
+            if (single) return;                   // workgroup-uniform: nothing follows the only frame
+            frame_barrier();
+        }
+        // the chunk's ids and ranks (the barrier that ended its last frame made them visible)
+        if (tid < nc) {
+            dv.assign[(size_t)u * dv.F + c0 + tid] = a_out[tid];
+            dv.pos[(size_t)u * dv.F + c0 + tid] = p_out[tid];
+        }
+        __syncthreads();                          // before the next chunk overwrites the staged summaries
+    }
+    // write back what changed: rows, sizes and norms
+#pragma unroll
+    for (int i = 0; i < RPG; ++i) {
+        if ((dirty >> i) & 1u) {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) r[(size_t)(grp + NG * i) * D + lr * EPL + e] = rr[i][e];
+        }
+    }
+    for (int j = tid; j < C; j += THREADS) {
+        if (chg_sh[j]) {
+            dv.n[(size_t)u * C + j] = n_sh[j];
+            dv.rnorm[(size_t)u * C + j] = rn_sh[j];
+        }
     }
 }
 
@@ -1564,8 +1821,17 @@ hipError_t launch_fetch(const DeviceView &dv, int u0, int n_units, int max_moves
 hipError_t launch_assign_update(const DeviceView &dv, int f0, int f1, hipStream_t s) {
     return checked([&] {
         if (dv.maint_mode) {
-            if (dv.D == 64) k_assign_update<64><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
-            else k_assign_update<128><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
+            if (dv.D == 64) k_assign_update<64, true><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
+            else k_assign_update<128, true><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
+        } else if (f1 - f0 <= kRegFrames && dv.C <= 128) {
+            if (dv.D == 64) k_assign_update_reg<64, 256><<<dv.U, 256, 0, s>>>(dv, f0, f1);
+            else k_assign_update_reg<128, 256><<<dv.U, 256, 0, s>>>(dv, f0, f1);
+        } else if (f1 - f0 <= kRegFrames && dv.C <= 256) {
+            if (dv.D == 64) k_assign_update_reg<64, 512><<<dv.U, 512, 0, s>>>(dv, f0, f1);
+            else k_assign_update_reg<128, 512><<<dv.U, 512, 0, s>>>(dv, f0, f1);
+        } else if (f1 - f0 <= 2 && dv.C > 256) {
+            if (dv.D == 64) k_assign_update<64, false><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
+            else k_assign_update<128, false><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
         } else {
             if (dv.D == 64) k_assign_chain<64><<<dv.U, kChainBlock, 0, s>>>(dv, f0, f1);
             else k_assign_chain<128><<<dv.U, kChainBlock, 0, s>>>(dv, f0, f1);

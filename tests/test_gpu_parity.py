@@ -197,7 +197,8 @@ def test_single_frame_calls_equal_batched_ingest_variants(kw, over):
 # are wrong, more clusters move than a chunk has slots), tables of less than a tile, a tile and one, and more than a
 # wavefront's candidates, with calls on both sides of a chunk.
 @pytest.mark.parametrize("C,D,kind", [(1, 64, "repeats"), (5, 128, "repeats"), (16, 64, "negatives"), (17, 128, "negatives"),
-                                      (64, 64, "rapid"), (128, 128, "rapid"), (40, 128, "zeros")])
+                                      (64, 64, "rapid"), (128, 128, "rapid"), (40, 128, "zeros"), (200, 64, "rapid"),
+                                      (300, 128, "repeats"), (300, 64, "rapid")])
 def test_batched_assignment_at_ties_equals_single_frame_calls_bitwise(C, D, kind):
     F, T, U = 2 * C + 90, 3, 2
     rng = np.random.default_rng(C)
