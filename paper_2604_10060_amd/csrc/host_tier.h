@@ -53,7 +53,7 @@ struct HostTier {
     // ingest: the offload of a staged batch runs on the copy stream while the caller's stream goes on with the
     // next batch; two slab tables (host and device) used in turn, an event per table for "offload finished",
     // and the frames each still-counted offload read from the staging ring
-    hipEvent_t off_ready = nullptr, off_done[2] = {nullptr, nullptr};
+    hipEvent_t off_done[2] = {nullptr, nullptr};
     bool off_used[2] = {false, false};
     long long off_f0[2] = {0, 0}, off_f1[2] = {0, 0};
     long long off_idx = 0;

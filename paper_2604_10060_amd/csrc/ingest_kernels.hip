@@ -1711,16 +1711,24 @@ __global__ __launch_bounds__(128) void k_lloyd_update(DeviceView dv, int n_frame
 // one workgroup per page would hold the chip while it waits for the link.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_offload(DeviceView dv, int f0, int n) {
-    const int n_items = dv.U * n * 2;
-    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-        const int val = it & 1, u = (it >> 1) % dv.U, fl = (it >> 1) / dv.U, f = f0 + fl;
-        const size_t bytes = val ? dv.vpage : dv.kpage;
-        const size_t spage = (size_t)(f % dv.SN) * dv.U + u;
-        const int hp = dv.dest[(size_t)u * dv.SN + fl];        // page within the unit's host pool
-        const size_t hoff = (size_t)u * dv.h_ustride + (size_t)(hp / dv.SFh) * dv.h_bstride + (size_t)(hp % dv.SFh) * bytes;
-        const uint4 *src = reinterpret_cast<const uint4 *>((val ? dv.stage_v : dv.stage_k) + spage * bytes);
-        uint4 *dst = reinterpret_cast<uint4 *>((val ? dv.host_v : dv.host_k) + hoff);
-        for (size_t i = threadIdx.x; i < bytes / 16; i += kBlock) dst[i] = src[i];
+    // The page table is in pinned host memory: a workgroup fetches the entries of its next 256 items in one trip.
+    __shared__ int hp_sh[kBlock];
+    const int n_items = dv.U * n * 2, stride = gridDim.x;
+    for (int i0 = blockIdx.x; i0 < n_items; i0 += kBlock * stride) {
+        const long long mine = i0 + (long long)threadIdx.x * stride;
+        if (mine < n_items) hp_sh[threadIdx.x] = dv.dest[(size_t)(((int)mine >> 1) % dv.U) * dv.SN + ((int)mine >> 1) / dv.U];
+        __syncthreads();
+        for (int k = 0; k < kBlock && i0 + k * stride < n_items; ++k) {
+            const int it = i0 + k * stride, val = it & 1, u = (it >> 1) % dv.U, f = f0 + (it >> 1) / dv.U;
+            const size_t bytes = val ? dv.vpage : dv.kpage;
+            const size_t spage = (size_t)(f % dv.SN) * dv.U + u;
+            const int hp = hp_sh[k];                           // page within the unit's host pool
+            const size_t hoff = (size_t)u * dv.h_ustride + (size_t)(hp / dv.SFh) * dv.h_bstride + (size_t)(hp % dv.SFh) * bytes;
+            const uint4 *src = reinterpret_cast<const uint4 *>((val ? dv.stage_v : dv.stage_k) + spage * bytes);
+            uint4 *dst = reinterpret_cast<uint4 *>((val ? dv.host_v : dv.host_k) + hoff);
+            for (size_t i = threadIdx.x; i < bytes / 16; i += kBlock) dst[i] = src[i];
+        }
+        __syncthreads();
     }
 }
 
@@ -1801,10 +1809,10 @@ hipError_t launch_value_reps(const DeviceView &dv, int n_frames, hipStream_t s) 
 }
 
 hipError_t launch_offload(const DeviceView &dv, int f0, int n, hipStream_t s) {
-    const long long items = (long long)dv.U * n * 2;
     // 16 workgroups (posted stores keep the link full; config 3 ingest with 4 / 8 / 16 / 64 / 256 / 1024 workgroups:
     // 12.5 / 13.9 / 14.0 / 13.2 / 12.7 / 12.6 k frames/s -- the more of them, the more they slow the staging and
     // assignment kernels that run beside them)
+    const long long items = (long long)dv.U * n * 2;
     const int blocks = (int)std::min<long long>(items, 16);
     return checked([&] { k_offload<<<blocks, kBlock, 0, s>>>(dv, f0, n); });
 }

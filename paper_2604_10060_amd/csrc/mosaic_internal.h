@@ -46,7 +46,7 @@ struct DeviceView {
     size_t h_ustride, h_bstride;
     int SFh;                   // frames per host slab
     int HP;                    // host pages per unit
-    int *dest;                 // [U][SN] host page of each staged frame of the current batch
+    const int *dest;           // [U][SN] host page of each staged frame of the current batch (pinned memory)
     // fetch work lists, written by the host into pinned memory and read by k_fetch over PCIe
     const int *moves;          // [U][F][2] (host page, cache page)
     const int *n_moves;        // [U]
