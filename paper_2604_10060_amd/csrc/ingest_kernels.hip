@@ -1710,11 +1710,16 @@ __global__ __launch_bounds__(128) void k_lloyd_update(DeviceView dv, int n_frame
 // runs on the copy stream beside the next batch's staging and assignment, and
 // one workgroup per page would hold the chip while it waits for the link.
 // ---------------------------------------------------------------------------
+constexpr int kOffloadXcds = 8;
 __global__ __launch_bounds__(kBlock) void k_offload(DeviceView dv, int f0, int n) {
     // The page table is in pinned host memory: a workgroup fetches the entries of its next 256 items in one trip.
+    // Only workgroups 0, 8, 16, ... work: workgroups go to the eight XCDs in turn, so these share one XCD, and its path to
+    // the fabric is the only one that fills up with posted stores to the link.  Spread over all XCDs the same stores hold
+    // up every other kernel's memory traffic (a page store beside it 217 us instead of 12).
     __shared__ int hp_sh[kBlock];
-    const int n_items = dv.U * n * 2, stride = gridDim.x;
-    for (int i0 = blockIdx.x; i0 < n_items; i0 += kBlock * stride) {
+    if (blockIdx.x % kOffloadXcds) return;
+    const int n_items = dv.U * n * 2, stride = gridDim.x / kOffloadXcds;
+    for (int i0 = blockIdx.x / kOffloadXcds; i0 < n_items; i0 += kBlock * stride) {
         const long long mine = i0 + (long long)threadIdx.x * stride;
         if (mine < n_items) hp_sh[threadIdx.x] = dv.dest[(size_t)(((int)mine >> 1) % dv.U) * dv.SN + ((int)mine >> 1) / dv.U];
         __syncthreads();
@@ -1809,11 +1814,11 @@ hipError_t launch_value_reps(const DeviceView &dv, int n_frames, hipStream_t s) 
 }
 
 hipError_t launch_offload(const DeviceView &dv, int f0, int n, hipStream_t s) {
-    // 16 workgroups (posted stores keep the link full; config 3 ingest with 4 / 8 / 16 / 64 / 256 / 1024 workgroups:
-    // 12.5 / 13.9 / 14.0 / 13.2 / 12.7 / 12.6 k frames/s -- the more of them, the more they slow the staging and
-    // assignment kernels that run beside them)
+    // 16 working workgroups, all on one XCD (2 layers of 4 heads, 196-token pages, 16 frames a call, 512 frames, offloaded and
+    // assigned: 10.9 ms with 16 workgroups spread over the XCDs, 9.3 with 16 on one, 10.4 with 16 on two; more
+    // workgroups, or more loads in flight per thread, slow the staging and assignment kernels beside them).
     const long long items = (long long)dv.U * n * 2;
-    const int blocks = (int)std::min<long long>(items, 16);
+    const int blocks = (int)std::min<long long>(items, 16) * kOffloadXcds;
     return checked([&] { k_offload<<<blocks, kBlock, 0, s>>>(dv, f0, n); });
 }
 
