@@ -191,6 +191,15 @@ def test_single_frame_calls_equal_batched_ingest_variants(kw, over):
         np.testing.assert_array_equal(a, b)
 
 
+# page stores load four rows per thread at a time, value pages a 64-token tile ahead: pages of a batch more or less than
+# that, one token beside a tile, and several tiles, in one-frame calls (their own kernel) and batched ones
+@pytest.mark.parametrize("T,D,dtype", [(63, 128, "bf16"), (65, 128, "bf16"), (129, 64, "bf16"), (128, 64, "bf16"), (65, 128, "fp32"),
+                                       (130, 64, "fp32")])
+def test_page_store_at_batch_and_tile_edges(T, D, dtype):
+    harness.run_workload(_small(tokens_per_frame=T, head_dim=D, kv_dtype=dtype, n_frames=70, n_clusters=6, top_k=6,
+                                n_scenes=4), decode_steps=1)
+
+
 # The batched assignment decides sixteen frames at once from dot products that it carries over, and falls back to the full
 # computation where two clusters are too close: streams made of few different frames and of their multiples and
 # negatives (ties to the last bit, representatives that shrink), of new scenes every frame or two (most assumed winners
