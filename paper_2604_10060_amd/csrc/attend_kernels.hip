@@ -228,6 +228,31 @@ __device__ __forceinline__ void combine_accumulate(const DeviceView &dv, size_t 
     }
 }
 
+// One output value of row r of a tile, with the representatives' part merged in, and the row's log-sum-exp.
+// Lr: normaliser of the output (the weights the value contraction used, bf16-rounded in the MFMA kernels); Xr: the same
+// sum over the unrounded fp32 weights, for the log-sum-exp; Mr: the row's reference (log2 domain).
+template <typename E, int D>
+__device__ __forceinline__ void combine_store(const DeviceView &dv, int u, int lc, int h, int tile, int r, int dg, int col, int Tq,
+                                              float o, float Lr, float Xr, float Mr, E *out, float *lse) {
+    const int G = dv.G, Hq = dv.Hq;
+    if (dv.aug_reps) {                            // one more partial: the representatives' part
+        const size_t ae = (size_t)u * dv.nt_max + tile;
+        const float ma = dv.aug_ml[ae * 2 * kRowTile + r], la = dv.aug_ml[ae * 2 * kRowTile + kRowTile + r];
+        const float oa = dv.aug_o[(ae * kRowTile + r) * D + dg * 32 + col];
+        const float Mn = fmaxf(Mr, ma);
+        const float wa = Mr > -INFINITY ? exp2f(Mr - Mn) : 0.f, wb = ma > -INFINITY ? exp2f(ma - Mn) : 0.f;
+        o = o * wa + oa * wb;
+        Lr = Lr * wa + la * wb;
+        Xr = Xr * wa + la * wb;                   // (the representatives' weights are fp32)
+        Mr = Mn;
+    }
+    const int gr = tile * kRowTile + r, t = gr / G, g = gr % G;
+    const size_t orow = ((size_t)lc * Tq + t) * Hq + (size_t)h * G + g;
+    store_out<E>(out + orow * D + dg * 32 + col, Lr > 0.f ? o / Lr : 0.f);
+    if (dg == 0 && col == 0 && lse != nullptr)
+        lse[orow] = Xr > 0.f ? (Mr + log2f(Xr)) * 0.6931471805599453f : -INFINITY;
+}
+
 // Merge of the per-split partials (log-sum-exp weights), normalisation, output.
 // grid (D/32, NT, n_units), 256 threads.  A workgroup owns 32 output channels of
 // one row tile; its 8 groups of 32 threads share the splits, so the partial
@@ -296,25 +321,86 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
         float o = 0.f;
 #pragma unroll
         for (int q = 0; q < 8; ++q) o += red[q][rl][col];
-        // Lr: normaliser of the output (the weights the value contraction used, bf16-rounded in the
-        // MFMA kernels); Xr: the same sum over the unrounded fp32 weights, for the log-sum-exp
-        float Lr = L_sh[r], Xr = X_sh[r], Mr = M_sh[r];
-        if (dv.aug_reps) {                            // one more partial: the representatives' part
-            const size_t ae = (size_t)u * dv.nt_max + tile;
-            const float ma = dv.aug_ml[ae * 2 * kRowTile + r], la = dv.aug_ml[ae * 2 * kRowTile + kRowTile + r];
-            const float oa = dv.aug_o[(ae * kRowTile + r) * D + dg * 32 + col];
-            const float Mn = fmaxf(Mr, ma);
-            const float wa = Mr > -INFINITY ? exp2f(Mr - Mn) : 0.f, wb = ma > -INFINITY ? exp2f(ma - Mn) : 0.f;
-            o = o * wa + oa * wb;
-            Lr = Lr * wa + la * wb;
-            Xr = Xr * wa + la * wb;                   // (the representatives' weights are fp32)
-            Mr = Mn;
+        combine_store<E, D>(dv, u, lc, h, tile, r, dg, col, Tq, o, L_sh[r], X_sh[r], M_sh[r], out, lse);
+    }
+}
+
+// The merge for questions (NT > 1): many tiles, few splits each, so the chip is filled by workgroups and not by the loads
+// of one: a thread holds the sixteen rows of two splits at a time (32 registers), and several
+// workgroups per CU hide each other's latency.  The kernel above keeps 128 values per thread in flight for the one tile of
+// a decode step and is limited to two wavefronts per SIMD by them (256-token question, 448 tiles: 16.5 -> 14.2 us; 32 tokens on 28 layers, 1568 tiles:
+// 58 -> 40 us).  grid (D/32, NT, n_units), 256 threads;
+// same arithmetic, partial sums of a split group added in the same order.
+template <typename E, int D>
+__global__ __launch_bounds__(kBlock) void k_combine_question(DeviceView dv, int u0, int n_units, int Tq, int B, E *out, float *lse) {
+    const int dg = blockIdx.x, tile = blockIdx.y, uc = blockIdx.z, u = u0 + uc, NT = gridDim.y, tid = threadIdx.x;
+    const int G = dv.G, Hq = dv.Hq, lc = uc / dv.Hkv, h = u % dv.Hkv, R = Tq * G;
+    const int rows = min(kRowTile, R - tile * kRowTile);
+    const SplitSlot slot = split_slot<true>(dv.n_sel + u0, n_units, B, uc);
+    const int n_splits = slot.S;                 // 0 if the unit retrieved nothing
+    const size_t e0 = (size_t)slot.base * NT + (size_t)tile * n_splits;
+    __shared__ float w_sh[kMaxUnitSplits][kRowTile];
+    __shared__ float pm[16][kRowTile], pl[16][kRowTile], px[16][kRowTile];
+    __shared__ float red[8][kRowTile][33];
+    const int sg = tid / 32, col = tid % 32;
+    const float *po = dv.part_o + e0 * kRowTile * D + dg * 32 + col;
+    float v[2][kRowTile];                        // splits sg and sg + 8 of the pass
+    auto load_pass = [&](int s0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int s = min(s0 + sg + 8 * i, max(n_splits - 1, 0));
+#pragma unroll
+            for (int r = 0; r < kRowTile; ++r) v[i][r] = po[((size_t)s * kRowTile + min(r, rows - 1)) * D];
         }
-        const int gr = tile * kRowTile + r, t = gr / G, g = gr % G;
-        const size_t orow = ((size_t)lc * Tq + t) * Hq + (size_t)h * G + g;
-        store_out<E>(out + orow * D + dg * 32 + col, Lr > 0.f ? o / Lr : 0.f);
-        if (dg == 0 && col == 0 && lse != nullptr)
-            lse[orow] = Xr > 0.f ? (Mr + log2f(Xr)) * 0.6931471805599453f : -INFINITY;
+    };
+    load_pass(0);
+    const int row = tid % 16, part = tid / 16;
+    const float *ml = dv.part_ml + e0 * kMlRows * kRowTile + row;
+    float mx = -INFINITY;
+    for (int s = part; s < n_splits; s += 16) mx = fmaxf(mx, ml[(size_t)s * kMlRows * kRowTile]);
+    pm[part][row] = mx;
+    __syncthreads();
+    float M = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) M = fmaxf(M, pm[p][row]);
+    float ls = 0.f, xs = 0.f;
+    for (int s = part; s < n_splits; s += 16) {
+        const float *m = ml + (size_t)s * kMlRows * kRowTile;
+        const float w = M > -INFINITY ? exp2f(m[0] - M) : 0.f;
+        w_sh[s][row] = w;
+        ls += w * m[kRowTile];
+        xs += w * m[2 * kRowTile];
+    }
+    pl[part][row] = ls;
+    px[part][row] = xs;
+    __syncthreads();
+    float acc[kRowTile];
+#pragma unroll
+    for (int r = 0; r < kRowTile; ++r) acc[r] = 0.f;
+    for (int s0 = 0; s0 < n_splits; s0 += 16) {
+        if (s0 > 0) load_pass(s0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int s = s0 + sg + 8 * i;
+            if (s < n_splits) {
+#pragma unroll
+                for (int r = 0; r < kRowTile; ++r) acc[r] += w_sh[s][r] * v[i][r];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kRowTile; ++r) red[sg][r][col] = acc[r];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int r = sg + 8 * j;
+        if (r >= rows) continue;
+        float o = 0.f, Lr = 0.f, Xr = 0.f, Mr = -INFINITY;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) o += red[q][r][col];
+#pragma unroll
+        for (int p = 0; p < 16; ++p) { Lr += pl[p][r]; Xr += px[p][r]; Mr = fmaxf(Mr, pm[p][r]); }
+        combine_store<E, D>(dv, u, lc, h, tile, r, dg, col, Tq, o, Lr, Xr, Mr, out, lse);
     }
 }
 
@@ -336,6 +422,17 @@ hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int 
     const int us = uniform ? n_splits : 0;
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
     const int B = n_units * n_splits;
+    if (NT > 1) {
+        const dim3 gq(dv.D / 32, NT, n_units);
+        if (dv.esize == 4) {
+            if (dv.D == 64) k_combine_question<float, 64><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, (float *)out, lse);
+            else k_combine_question<float, 128><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, (float *)out, lse);
+        } else {
+            if (dv.D == 64) k_combine_question<unsigned short, 64><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, (unsigned short *)out, lse);
+            else k_combine_question<unsigned short, 128><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, (unsigned short *)out, lse);
+        }
+        return hipGetLastError();
+    }
     // One row tile (a decode step) of a few units: up to eight workgroups share a tile's rows, as long as the launch
     // stays within about two workgroups per CU (per-layer launch of config 2: 1075 -> 1048 / 1033 / 1027 us per step
     // with 2 / 4 / 8; the all-layers launch, 112 units, is left alone: 542 -> 562 us with 8).

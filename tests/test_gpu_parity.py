@@ -191,6 +191,17 @@ def test_single_frame_calls_equal_batched_ingest_variants(kw, over):
         np.testing.assert_array_equal(a, b)
 
 
+# the questions' merge takes a unit's splits sixteen at a time: long selections of few units (64 splits each on average,
+# unequal ones beyond that), row tiles that are not full, both page types
+@pytest.mark.parametrize("kw", [
+    dict(n_q_heads=8, n_kv_heads=2, question_tokens=9, n_clusters=12, top_k=12, n_frames=420),
+    dict(n_q_heads=3, n_kv_heads=1, question_tokens=11, n_clusters=9, top_k=3, n_frames=600, head_dim=64),
+    dict(n_q_heads=4, n_kv_heads=2, question_tokens=9, n_clusters=12, top_k=5, n_frames=420, kv_dtype="fp32"),
+])
+def test_question_merge_of_many_splits(kw):
+    harness.run_workload(_small(**kw), layer_mode="all")
+
+
 # page stores load four rows per thread at a time, value pages a 64-token tile ahead: pages of a batch more or less than
 # that, one token beside a tile, and several tiles, in one-frame calls (their own kernel) and batched ones
 @pytest.mark.parametrize("T,D,dtype", [(63, 128, "bf16"), (65, 128, "bf16"), (129, 64, "bf16"), (128, 64, "bf16"), (65, 128, "fp32"),
