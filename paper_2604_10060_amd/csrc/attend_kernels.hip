@@ -326,9 +326,9 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
 }
 
 // The merge for questions (NT > 1): many tiles, few splits each, so the chip is filled by workgroups and not by the loads
-// of one: a thread holds the sixteen rows of two splits at a time (32 registers), and several
-// workgroups per CU hide each other's latency.  The kernel above keeps 128 values per thread in flight for the one tile of
-// a decode step and is limited to two wavefronts per SIMD by them (256-token question, 448 tiles: 16.5 -> 14.2 us; 32 tokens on 28 layers, 1568 tiles:
+// of one: a thread holds the sixteen rows of two splits at a time (32 registers), and several workgroups per CU hide each
+// other's latency.  The kernel above keeps 128 values per thread in flight for the one tile of a decode step and is limited
+// to two wavefronts per SIMD by them (256-token question, 448 tiles: 16.5 -> 14.2 us; 32 tokens on 28 layers, 1568 tiles:
 // 58 -> 40 us).  grid (D/32, NT, n_units), 256 threads;
 // same arithmetic, partial sums of a split group added in the same order.
 template <typename E, int D>
