@@ -447,7 +447,7 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
         dv.h_bstride = (size_t)L.SF * (L.kpage + L.vpage);
         dv.h_ustride = (size_t)L.slabs_per_unit * dv.h_bstride;
     }
-    dv.stage_k = base + L.stage_k; dv.stage_v = base + L.stage_v; dv.dest = nullptr;
+    dv.stage_k = base + L.stage_k; dv.stage_v = base + L.stage_v; dv.dest = nullptr; dv.batch_assign = nullptr;
     dv.host_k = dv.host_v = nullptr;
     ctx->host = nullptr;
     if (cfg->tier == MOSAIC_TIER_HOST) {
@@ -485,6 +485,7 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
         ctx->h_buf_owner = (int *)((char *)cfg->host_arena + L.host_buf_owner);
         ctx->h_resident = (int *)((char *)cfg->host_arena + L.host_resident);
         dv.dest = (const int *)((char *)dptr + L.host_dest);
+        dv.batch_assign = (int *)((char *)dptr + L.host_assign);
         dv.moves = (const int *)((char *)dptr + L.host_moves);
         dv.n_moves = (const int *)((char *)dptr + L.host_nmoves);
         HostTier *ht = new (std::nothrow) HostTier();
@@ -700,12 +701,10 @@ static int offload_range(mosaic_ctx *ctx, int f0, int f1) {
         if ((e = hipEventSynchronize(ht->off_done[p])) != hipSuccess) return fail_hip(ctx, e, "hipEventSynchronize(offload)");
         ht->off_used[p] = false;
     }
-    // One copy and one wait: the link idles from here until the next offload kernel starts.  (A wait, a copy per unit, a
+    // One kernel that stores them to pinned memory, and one wait: the link idles from here until the next offload kernel starts.  (A wait, a copy per unit, a
     // second wait and the table's upload through the caller's stream took 150 us per batch of 16 frames and 8 units, half
     // as long as the offload itself.)
-    if ((e = hipMemcpy2DAsync(a, (size_t)n * 4, dv.assign + f0, (size_t)dv.F * 4, (size_t)n * 4, (size_t)dv.U,
-                              hipMemcpyDeviceToHost, ctx->stream)) != hipSuccess)
-        return fail_hip(ctx, e, "assignment read-back");
+    if ((e = launch_gather_assign(dv, f0, n, ctx->stream)) != hipSuccess) return fail_hip(ctx, e, "assignment read-back");
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return fail_hip(ctx, e, "hipStreamSynchronize");
     for (int fl = 0; fl < n; ++fl)
         for (int u = 0; u < dv.U; ++u) {
@@ -1275,12 +1274,24 @@ int32_t mosaic_get_assignments(mosaic_ctx *ctx, int32_t *frame_to_cluster) {
         for (size_t i = 0; i < nf * dv.U; ++i) frame_to_cluster[i] = -1;
         return MOSAIC_OK;
     }
-    { const int rc = join_ingest(ctx); if (rc != MOSAIC_OK) return rc; }
-    // all units' rows in one copy (a copy per unit costs 13 us each: 1.46 of the 1.9 ms that reading back the index of a
-    // 28-layer stream took)
-    const hipError_t e = hipMemcpy2DAsync(frame_to_cluster, nf * 4, dv.assign, (size_t)dv.F * 4, nf * 4, (size_t)dv.U,
-                                          hipMemcpyDeviceToHost, ctx->stream);
-    if (e != hipSuccess) return fail_hip(ctx, e, "hipMemcpy2DAsync D2H");
+    // All units' rows in one copy (a copy per unit costs 13 us each: 1.46 of the 1.9 ms that reading back the index of a
+    // 28-layer stream took): straight into the caller's array when the stream is full, else through a buffer, as long as a
+    // unit's row is worth less than a copy.  (One-dimensional copies only: an asynchronous strided copy into pageable memory
+    // was not complete when the stream was.)
+    const size_t row = (size_t)dv.F, used = ((size_t)dv.U - 1) * row + nf;
+    int32_t *all = nf == row ? frame_to_cluster : dv.F <= 32768 ? new (std::nothrow) int32_t[used] : nullptr;
+    int rc = MOSAIC_OK;
+    if (all) {
+        rc = d2h(ctx, all, dv.assign, used * 4);
+        if (rc == MOSAIC_OK) rc = sync(ctx);
+        if (all != frame_to_cluster) {
+            for (int u = 0; u < dv.U && rc == MOSAIC_OK; ++u) memcpy(frame_to_cluster + (size_t)u * nf, all + (size_t)u * row, nf * 4);
+            delete[] all;
+        }
+        return rc;
+    }
+    for (int u = 0; u < dv.U; ++u)
+        if ((rc = d2h(ctx, frame_to_cluster + (size_t)u * nf, dv.assign + (size_t)u * row, nf * 4)) != MOSAIC_OK) return rc;
     return sync(ctx);
 }
 

@@ -1737,6 +1737,12 @@ __global__ __launch_bounds__(128) void k_lloyd_update(DeviceView dv, int n_frame
 // runs on the copy stream beside the next batch's staging and assignment, and
 // one workgroup per page would hold the chip while it waits for the link.
 // ---------------------------------------------------------------------------
+// Host tier: a batch's assignments, compacted, straight into pinned host memory.  grid (U), 64 threads.
+__global__ __launch_bounds__(64) void k_gather_assign(DeviceView dv, int f0, int n) {
+    const int u = blockIdx.x;
+    for (int i = threadIdx.x; i < n; i += 64) dv.batch_assign[(size_t)u * n + i] = dv.assign[(size_t)u * dv.F + f0 + i];
+}
+
 constexpr int kOffloadXcds = 8;
 __global__ __launch_bounds__(kBlock) void k_offload(DeviceView dv, int f0, int n) {
     // The page table is in pinned host memory: a workgroup fetches the entries of its next 256 items in one trip.
@@ -1838,6 +1844,10 @@ hipError_t launch_value_reps(const DeviceView &dv, int n_frames, hipStream_t s) 
         if (dv.D == 64) k_value_reps<64><<<grid, 128, 0, s>>>(dv, n_frames);
         else k_value_reps<128><<<grid, 128, 0, s>>>(dv, n_frames);
     });
+}
+
+hipError_t launch_gather_assign(const DeviceView &dv, int f0, int n, hipStream_t s) {
+    return checked([&] { k_gather_assign<<<dv.U, 64, 0, s>>>(dv, f0, n); });
 }
 
 hipError_t launch_offload(const DeviceView &dv, int f0, int n, hipStream_t s) {
