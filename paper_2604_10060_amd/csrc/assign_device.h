@@ -51,7 +51,36 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One channel of Eq. 3, (n r + s) / (n + 1), each operation rounded separately (no contraction).  y = RN(1 / (n + 1)).
+// Sums whose last bit decides between clusters that tie to the last bit.  Several kernels share the state they go into
+// (which one runs depends on the frames per call), so every multiply-add is written out: left to the compiler, the order
+// of the first two squares and which of them is rounded by itself differed from kernel to kernel.
+//
+// Products of a lane's channels, in their order
+template <int N>
+__device__ __forceinline__ double dot_channels(const double (&a)[N], const double (&b)[N]) {
+    double p = 0.0;
+#pragma unroll
+    for (int e = 0; e < N; ++e) p = __builtin_fma(a[e], b[e], p);
+    return p;
+}
+// Squares of a lane's channels: step e of the sum, channels in their order but for the first two, whose order is a choice
+template <int N>
+__device__ __forceinline__ double square_step(double sq, const double (&x)[N], int e, bool second_first) {
+    const double v = e < 2 && second_first ? x[1 - e] : x[e];
+    return e == 0 ? v * v : __builtin_fma(v, v, sq);
+}
+template <int N>
+__device__ __forceinline__ double square_channels(const double (&x)[N], bool second_first) {
+    double sq = 0.0;
+#pragma unroll
+    for (int e = 0; e < N; ++e) sq = square_step<N>(sq, x, e, second_first);
+    return sq;
+}
+// ... which is: second first for a frame's summary, for the rows that a register kernel holds in its first pass (16
+// rows of tables of up to 128 clusters, 32 of up to 256) and for all rows of larger tables
+__device__ __forceinline__ bool row_second_first(int C, int id) { return C > 256 || id < (C > 128 ? 32 : 16); }
+
+// One channel of Eq. 3, (n r + s) / (n + 1): n r + s in one rounding, the division in another.  y = RN(1 / (n + 1)).
 // The division by n + 1, the same divisor for all channels: q = RN(x y) and two residual corrections
 // q <- RN(q + RN(x - (n + 1) q) y), each residual exact in a fused multiply-add: the first leaves q within half an ulp
 // and a little of x / (n + 1), and from such a q and a correctly rounded y the second returns the correctly rounded
@@ -59,10 +88,10 @@ __device__ __forceinline__ void wave_sync() {
 // the ends of the exponent range).  The compiler's own division hands a flag from its scaling step to its last step in
 // VCC, so the divisions of several channels run one after the other.
 __device__ __forceinline__ double eq3_channel(double n, double y, double r, double s) {
-    const double nb = n + 1.0, x = __dadd_rn(__dmul_rn(n, r), s);
-    double q = __dmul_rn(x, y);
-    q = __fma_rn(__fma_rn(-nb, q, x), y, q);
-    return __fma_rn(__fma_rn(-nb, q, x), y, q);
+    const double nb = n + 1.0, x = __builtin_fma(n, r, s);
+    double q = x * y;
+    q = __builtin_fma(__builtin_fma(-nb, q, x), y, q);
+    return __builtin_fma(__builtin_fma(-nb, q, x), y, q);
 }
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));

@@ -320,9 +320,10 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
                 for (int d = lane; d < D; d += 64) x += s_sh[d] * s_sh[d];
                 x = wave_sum(x);
             } else {            // (in the order of the kernels that share this state)
+                double sl[EPL];
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) x += s_sh[lr * EPL + e] * s_sh[lr * EPL + e];
-                x = row16_sum(x);
+                for (int e = 0; e < EPL; ++e) sl[e] = s_sh[lr * EPL + e];
+                x = row16_sum(square_channels(sl, true));
             }
             if (lane == 0) snorm_sh = sqrt(x);
         }
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
                     if (decltype(full)::value || x < passes) {
                         double p = 0.0;
 #pragma unroll
-                        for (int i = 0; i < EPL; ++i) p += s_sh[lr * EPL + i] * rv[x][i];
+                        for (int i = 0; i < EPL; ++i) p = __builtin_fma(s_sh[lr * EPL + i], rv[x][i], p);
                         p = group16_sum(p);
                         if (lr == 0 && j0 + 16 * x < hi) dot_sh[j0 + 16 * x] = p;
                     }
@@ -390,9 +391,7 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
         const double na = (double)na_i;
         double sq = 0.0, dq = 0.0;
         if (tid < D) {
-            // Eq. 3 with each operation rounded separately (no contraction)
-            const double rv = __ddiv_rn(__dadd_rn(__dmul_rn(na, r[(size_t)a * D + tid]), s_sh[tid]),
-                                        na + 1.0);
+            const double rv = __builtin_fma(na, r[(size_t)a * D + tid], s_sh[tid]) / (na + 1.0);      // Eq. 3 (as eq3_channel)
             r[(size_t)a * D + tid] = rv;
             if constexpr (!MAINT) dot_sh[tid] = rv;  // (the dot products have been read)
             sq = rv * rv;
@@ -423,11 +422,11 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
         }
         __syncthreads();   // all threads have read n[a] and written r before the scalars change
         if (!MAINT && wave == 0) {      // (the norm's additions in the order of the kernels that share this state)
-            double x = 0.0;
+            double x[EPL];
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) x += dot_sh[lr * EPL + e] * dot_sh[lr * EPL + e];
-            x = row16_sum(x);
-            if (lane == 0) nsum_sh[0] = x;
+            for (int e = 0; e < EPL; ++e) x[e] = dot_sh[lr * EPL + e];
+            const double sum = row16_sum(square_channels(x, row_second_first(C, a)));
+            if (lane == 0) nsum_sh[0] = sum;
         }
         if (tid == 0) {
             if (nested) {
@@ -493,7 +492,7 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
 //      (and |n r + ...|^2 likewise), so all frames are checked at once, a lane per (frame, slot).  Where a frame's best
 //      slot is another one than assumed, the first such frame is corrected and the rest checked again;
 //   4. with the winners known, Eq. 3 is applied to the rows themselves: a thread per (slot, channel) runs through the
-//      slot's frames in order, each operation rounded separately.
+//      slot's frames in order.
 // Decisions are exact: the similarities of steps 1 and 3 differ from those of the rows by rounding (sums of at most 17
 // products with r.s >= 0, so that no length cancels: below 1e-13 in the cosine), and they only decide where the best
 // is ahead by more than kChainMargin.  At a frame that is closer than that, or whose best slot does not exceed the
@@ -619,16 +618,16 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
         __syncthreads();
         if (!sure_sh[0]) {                          // the first frame by the full computation (workgroup-uniform)
             const int lo = lo_sh[0];
-            double sl[EPL], ssq = 0.0;
+            double sl[EPL];
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) { sl[e] = s_sh[0][lr * EPL + e]; ssq += sl[e] * sl[e]; }
-            const double sn = sqrt(row16_sum(ssq));
+            for (int e = 0; e < EPL; ++e) sl[e] = s_sh[0][lr * EPL + e];
+            const double sn = sqrt(row16_sum(square_channels(sl, true)));
             for (int cj = grp; cj < width; cj += NG) {                // (uniform within a 16-lane group)
                 const double *rj = r + (size_t)(lo + cj) * D + lr * EPL;
-                double p = 0.0;
+                double row[EPL];
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) p += sl[e] * rj[e];
-                p = row16_sum(p);
+                for (int e = 0; e < EPL; ++e) row[e] = rj[e];
+                const double p = row16_sum(dot_channels(sl, row));
                 const double rn = dv.rnorm[(size_t)u * C + lo + cj];
                 const double c = n_sh[lo + cj] <= 0 ? -INFINITY : (sn == 0.0 || rn == 0.0) ? 0.0 : p / (sn * rn);
                 if (lr == 0) sim_sh[cj] = c;
@@ -756,10 +755,10 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
             __syncthreads();
             const int kn = kb + grp;                // norm of slot kn, and its new size
             if (grp < SPB && kn < n_slot) {
-                double sq = 0.0;
+                double x[EPL];
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) { const double x = row_sh[grp][lr * EPL + e]; sq += x * x; }
-                sq = row16_sum(sq);
+                for (int e = 0; e < EPL; ++e) x[e] = row_sh[grp][lr * EPL + e];
+                const double sq = row16_sum(square_channels(x, row_second_first(C, slot_id[kn])));
                 int cnt = 0;
                 for (int fc = 0; fc < nc; ++fc) cnt += w_sh[fc] == kn;
                 if (lr == 0) {
@@ -873,8 +872,8 @@ __global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, in
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) {
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) p[k] += sl[e] * rr[4 * h + k][e];
-                    if (h == 0) ssq += sl[e] * sl[e];
+                    for (int k = 0; k < 4; ++k) p[k] = __builtin_fma(sl[e], rr[4 * h + k][e], p[k]);
+                    if (h == 0) ssq = square_step<EPL>(ssq, sl, e, true);
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor8>(p[k]);
@@ -945,8 +944,8 @@ __global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, in
                             const double rv = eq3_channel(na, ny, rr[i][e], sl[e]);
                             rr[i][e] = rv;
                             if (single) r[(size_t)a * D + lr * EPL + e] = rv;
-                            sq += rv * rv;
                         }
+                        sq = square_channels(rr[i], i == 0);                      // (row_second_first: a < NG)
                     }
                 }
                 if (!single) dirty |= 1u << ai;
@@ -1056,8 +1055,8 @@ __global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k
 #pragma unroll
         for (int e = 0; e < EPL; ++e) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) p[k] += sl[e] * rr[4 * h + k][e];
-            if (h == 0) ssq += sl[e] * sl[e];
+            for (int k = 0; k < 4; ++k) p[k] = __builtin_fma(sl[e], rr[4 * h + k][e], p[k]);
+            if (h == 0) ssq = square_step<EPL>(ssq, sl, e, true);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor8>(p[k]);
@@ -1123,10 +1122,10 @@ __global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k
             if (i == ai) {                                // scalar branch: one pass runs
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) {
-                    const double rv = eq3_channel(na, ny, rr[i][e], sl[e]);
-                    r[(size_t)a * D + lr * EPL + e] = rv;
-                    sq += rv * rv;
+                    rr[i][e] = eq3_channel(na, ny, rr[i][e], sl[e]);
+                    r[(size_t)a * D + lr * EPL + e] = rr[i][e];
                 }
+                sq = square_channels(rr[i], i == 0);                      // (row_second_first: a < NG)
             }
         }
         sq = row16_sum(sq);

@@ -250,6 +250,32 @@ def test_batched_assignment_at_ties_equals_single_frame_calls_bitwise(C, D, kind
             np.testing.assert_array_equal(a, b)
 
 
+# Ties that only the last bit of a norm decides, whatever kernel wrote it: a few directions, every frame a multiple of one
+# of them, so that several clusters lie along each and a frame's best similarities differ by rounding or not at all; ids on
+# both sides of a register kernel's first pass, tables of every kernel family and of shortened chunks (C > 512).
+@pytest.mark.parametrize("C,D", [(40, 64), (128, 128), (200, 128), (250, 64), (300, 128), (600, 64), (600, 128), (1024, 128)])
+def test_last_bit_ties_do_not_depend_on_the_split_into_calls(C, D):
+    U, T, W = 16, 4, 2 * C
+    F = W + (400 if C < 500 else 150)
+    rng = np.random.default_rng(C + D)
+    few = rng.integers(-3, 4, (6, U, T, D)).astype(np.float32)
+    x = few[rng.integers(0, 6, F)] * rng.integers(1, 4, (F, 1, 1, 1)).astype(np.float32)
+    K = torch.tensor(x[:, None]).to(DEV)
+    cfg = dict(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T, max_frames=F, n_clusters=C, top_k=1,
+               kv_dtype="fp32", lloyd_iters=2)
+    states = []
+    for per in (1, 2, 4, 5, 16, 64):
+        m = binding.Mosaic(binding.make_config(**cfg))
+        m.ingest_frame(K[:W], K[:W])
+        for f in range(W, F, per):
+            m.ingest_frame(K[f:f + per], K[f:f + per])
+        states.append((m.assignments(), *m.centroids()))
+        m.close()
+    for other in states[1:]:
+        for a, b in zip(states[0], other):
+            np.testing.assert_array_equal(a, b)
+
+
 # The same for the visual level of the nested index (embedding sizes with and without 16-byte rows, one to four tiles of
 # partitions, embeddings that repeat to the last bit, change at every frame or vanish) and the semantic level below it.
 @pytest.mark.parametrize("P,Cs,Dv,kind", [(3, 2, 64, "repeats"), (17, 2, 130, "rapid"), (40, 3, 1027, "repeats"),
