@@ -94,6 +94,15 @@ __device__ __forceinline__ double eq3_channel(double n, double y, double r, doub
     return __builtin_fma(__builtin_fma(-nb, q, x), y, q);
 }
 
+// The nested hierarchy's partition representatives follow the same running mean: eq3_channel per channel, and this per
+// wavefront for the norm, whose squares are rounded before they are added (fused into the first addition, as the compiler
+// does where it may, the two lanes of a pair get different sums)
+__device__ __forceinline__ double wave_square_sum(double x) {
+#pragma clang fp contract(off)
+    const double sq = x * x;
+    return wave64_sum(sq);
+}
+
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 

@@ -409,14 +409,13 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
         if (nested) {
             double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
             pn_i = dv.pn[(size_t)u * dv.P + part_f];
-            double psq = 0.0;
+            double pv = 0.0;
             if (tid < D) {
-                const double pv = ((double)pn_i * prow[tid] + s_sh[tid]) / ((double)pn_i + 1.0);
+                pv = eq3_channel((double)pn_i, __ddiv_rn(1.0, (double)pn_i + 1.0), prow[tid], s_sh[tid]);
                 prow[tid] = pv;
-                psq = pv * pv;
             }
             if (wave < 2) {
-                psq = wave_sum(psq);
+                const double psq = wave_square_sum(pv);
                 if (lane == 0) psum_sh[wave] = psq;
             }
         }
@@ -705,7 +704,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
 #pragma unroll
                 for (int x = 0; x < CPL; ++x) {
                     dv.pr[((size_t)u * dv.P + at) * D + lane + 64 * x] = pv[x];
-                    const double w = wave_sum(pv[x] * pv[x]);
+                    const double w = wave_square_sum(pv[x]);
                     psq = x == 0 ? w : psq + w;
                 }
                 if (lane == 0) {
@@ -722,14 +721,9 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                     for (int x = 0; x < CPL; ++x) pv[x] = dv.pr[((size_t)u * dv.P + at) * D + lane + 64 * x];
                 }
                 pn = __builtin_amdgcn_readlane(size, fc) + 1;
-                const double nb = (double)pn, ny = readlane_f64(yl, fc);
+                const double ny = readlane_f64(yl, fc);
 #pragma unroll
-                for (int x = 0; x < CPL; ++x) {     // (the quotient as in eq3_channel)
-                    const double num = __fma_rn(nb - 1.0, pv[x], s_sh[fc][lane + 64 * x]);
-                    double q = __dmul_rn(num, ny);
-                    q = __fma_rn(__fma_rn(-nb, q, num), ny, q);
-                    pv[x] = __fma_rn(__fma_rn(-nb, q, num), ny, q);
-                }
+                for (int x = 0; x < CPL; ++x) pv[x] = eq3_channel((double)(pn - 1), ny, pv[x], s_sh[fc][lane + 64 * x]);
             }
             leave();
         }
@@ -912,14 +906,13 @@ __global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, in
             if (nested) {
                 double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
                 pn_i = dv.pn[(size_t)u * dv.P + part_f];
-                double psq = 0.0;
+                double pv = 0.0;
                 if (tid < D) {
-                    const double pv = ((double)pn_i * prow[tid] + sv[tid]) / ((double)pn_i + 1.0);
+                    pv = eq3_channel((double)pn_i, __ddiv_rn(1.0, (double)pn_i + 1.0), prow[tid], sv[tid]);
                     prow[tid] = pv;
-                    psq = pv * pv;
                 }
                 if (wave < 2) {
-                    psq = wave_sum(psq);
+                    const double psq = wave_square_sum(pv);
                     if (lane == 0) psum_sh[wave] = psq;
                 }
             }
@@ -1094,14 +1087,13 @@ __global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k
     if (nested) {
         double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
         pn_i = dv.pn[(size_t)u * dv.P + part_f];
-        double psq = 0.0;
+        double pv = 0.0;
         if (tid < D) {
-            const double pv = ((double)pn_i * prow[tid] + s_sh[tid]) / ((double)pn_i + 1.0);
+            pv = eq3_channel((double)pn_i, __ddiv_rn(1.0, (double)pn_i + 1.0), prow[tid], s_sh[tid]);
             prow[tid] = pv;
-            psq = pv * pv;
         }
         if (wave < 2) {
-            psq = wave_sum(psq);
+            const double psq = wave_square_sum(pv);
             if (lane == 0) psum_sh[wave] = psq;
         }
     }

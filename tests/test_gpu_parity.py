@@ -276,6 +276,37 @@ def test_last_bit_ties_do_not_depend_on_the_split_into_calls(C, D):
             np.testing.assert_array_equal(a, b)
 
 
+# The partitions' representatives and the norms that divide their scores, written by a kernel of its own for each number of
+# frames per call: the two-stage selection's scores are the same bits.
+@pytest.mark.parametrize("P,Cs,D", [(4, 8, 64), (4, 8, 128), (6, 30, 64), (8, 50, 128)])
+def test_partition_scores_do_not_depend_on_the_split_into_calls(P, Cs, D):
+    C, T, U, Dv = P * Cs, 3, 2, 36
+    W, F = 2 * C, 2 * C + 130
+    rng = np.random.default_rng(P + D)
+    x = rng.standard_normal((F, U, 1, D))[np.arange(F) // 7] + 0.4 * rng.standard_normal((F, U, T, D))
+    K = torch.tensor(x[:, None].astype(np.float32)).to(DEV)
+    E = torch.tensor(rng.standard_normal((F, Dv)).astype(np.float32)).to(DEV)
+    q = torch.tensor(rng.standard_normal((8, 1, U, D)).astype(np.float32)).to(DEV)
+    states = []
+    for per in (1, 2, 5, 16):
+        m = binding.Mosaic(binding.make_config(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T,
+                                               max_frames=F, n_clusters=C, top_k=1, kv_dtype="fp32", n_partitions=P,
+                                               visual_dim=Dv))
+        m.ingest_frame_visual(K[:W], K[:W], E[:W])
+        for f in range(W, F, per):
+            m.ingest_frame_visual(K[f:f + per], K[f:f + per], E[f:f + per])
+        scores = []
+        for i in range(len(q)):
+            m.retrieve(0, q[i])
+            scores.append(m.partition_selection(0)[2])
+        p = m.partitions()
+        states.append([np.stack(scores), p["part_r"], p["part_n"], m.assignments()])
+        m.close()
+    for other in states[1:]:
+        for a, b in zip(states[0], other):
+            np.testing.assert_array_equal(a, b)
+
+
 # The same for the visual level of the nested index (embedding sizes with and without 16-byte rows, one to four tiles of
 # partitions, embeddings that repeat to the last bit, change at every frame or vanish) and the semantic level below it.
 @pytest.mark.parametrize("P,Cs,Dv,kind", [(3, 2, 64, "repeats"), (17, 2, 130, "rapid"), (40, 3, 1027, "repeats"),
