@@ -243,12 +243,12 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, con
         __syncthreads();
         if (!sure_sh[0]) {                  // the first frame by the full computation (workgroup-uniform)
             double en = 0.0;
-            for (int d = lane; d < Dv; d += 64) { const double v = (double)e[d]; en += v * v; }
+            for (int d = lane; d < Dv; d += 64) { const double v = (double)e[d]; en = __builtin_fma(v, v, en); }
             en = sqrt(wave_sum(en));
             for (int p = wave; p < P; p += NW) {
                 const double *rp = dv.vr + (size_t)p * Dv;
                 double x = 0.0;
-                for (int d = lane; d < Dv; d += 64) x += (double)e[d] * rp[d];
+                for (int d = lane; d < Dv; d += 64) x = __builtin_fma((double)e[d], rp[d], x);
                 x = wave_sum(x);
                 const double rn = dv.vrn[p];
                 const double c = vn_sh[p] <= 0 ? -INFINITY : (en == 0.0 || rn == 0.0) ? 0.0 : x / (en * rn);
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, con
                     for (int fc = 0; fc < FR; ++fc)
                         if (fc < nc && w_sh[fc] == k) x = eq3_channel((double)p_sh[fc], y_sh[fc], x, (double)ev[fc]);
                     dv.vr[(size_t)id * Dv + d] = x;
-                    sq += x * x;
+                    sq = __builtin_fma(x, x, sq);
                 }
                 sq = block_sum<NW>(sq, red);
                 if (tid == 0) {
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign_few(DeviceView dv,
         }
         __syncthreads();
         double en = 0.0;
-        for (int d = lane; d < Dv; d += 64) en += e_sh[d] * e_sh[d];
+        for (int d = lane; d < Dv; d += 64) en = __builtin_fma(e_sh[d], e_sh[d], en);
         en = sqrt(wave_sum(en));
         double bv = -INFINITY;
         int bi = 0x7fffffff;
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign_few(DeviceView dv,
             const double rna = dv.vrn[p], rnb = dv.vrn[p2];
             double xa = 0.0, xb = 0.0;
 #pragma unroll 8
-            for (int d = lane; d < Dv; d += 64) { xa += e_sh[d] * ra[d]; xb += e_sh[d] * rb[d]; }
+            for (int d = lane; d < Dv; d += 64) { xa = __builtin_fma(e_sh[d], ra[d], xa); xb = __builtin_fma(e_sh[d], rb[d], xb); }
             xa = wave_sum(xa);
             xb = wave_sum(xb);
             const double ca = (en == 0.0 || rna == 0.0) ? 0.0 : xa / (en * rna), cb = (en == 0.0 || rnb == 0.0) ? 0.0 : xb / (en * rnb);
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign_few(DeviceView dv,
         for (int d = tid; d < Dv; d += kVisAssign) {
             const double x = eq3_channel((double)na, y, dv.vr[(size_t)a * Dv + d], e_sh[d]);
             dv.vr[(size_t)a * Dv + d] = x;
-            sq += x * x;
+            sq = __builtin_fma(x, x, sq);
         }
         sq = block_sum<NW>(sq, red);     // (its barriers also order the reads of vn[a] before the update)
         if (tid == 0) { dv.vrn[a] = sqrt(sq); dv.vn[a] = na + 1; dv.part[f] = a; }

@@ -276,6 +276,32 @@ def test_last_bit_ties_do_not_depend_on_the_split_into_calls(C, D):
             np.testing.assert_array_equal(a, b)
 
 
+# The visual level's last-bit ties: embeddings that are multiples of a few, partitions that lie along one direction.
+@pytest.mark.parametrize("P,Dv", [(12, 64), (16, 512), (33, 1030), (64, 100)])
+def test_visual_last_bit_ties_do_not_depend_on_the_split_into_calls(P, Dv):
+    C, T, U, D = P, 1, 1, 64
+    W, F = 6 * P, 6 * P + 400
+    rng = np.random.default_rng(P + Dv)
+    K = torch.tensor(rng.standard_normal((F, 1, U, T, D)).astype(np.float32)).to(DEV)
+    e = rng.integers(-3, 4, (5, Dv))[rng.integers(0, 5, F)] * rng.integers(1, 4, (F, 1))
+    pad = torch.zeros((F, (Dv + 3) // 4 * 4), device=DEV)        # (rows that calls of any number of frames may begin with)
+    pad[:, :Dv] = torch.tensor(e.astype(np.float32)).to(DEV)
+    states = []
+    for per in (1, 2, 3, 16, 64):
+        m = binding.Mosaic(binding.make_config(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T,
+                                               max_frames=F, n_clusters=C, top_k=1, kv_dtype="fp32", n_partitions=P,
+                                               visual_dim=Dv, warmup_frames=W, lloyd_iters=1))
+        m.ingest_frame_visual(K[:W], K[:W], pad[:W, :Dv].contiguous())
+        for f in range(W, F, per):
+            m.ingest_frame_visual(K[f:f + per], K[f:f + per], pad[f:f + per, :Dv].contiguous())
+        p = m.partitions()
+        states.append([p[k] for k in sorted(p)])
+        m.close()
+    for other in states[1:]:
+        for a, b in zip(states[0], other):
+            np.testing.assert_array_equal(a, b)
+
+
 # The partitions' representatives and the norms that divide their scores, written by a kernel of its own for each number of
 # frames per call: the two-stage selection's scores are the same bits.
 @pytest.mark.parametrize("P,Cs,D", [(4, 8, 64), (4, 8, 128), (6, 30, 64), (8, 50, 128)])
