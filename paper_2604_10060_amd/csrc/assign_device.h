@@ -87,7 +87,16 @@ __device__ __forceinline__ bool row_second_first(int C, int id) { return C > 256
 // quotient (Markstein's theorem; n + 1 is a small integer, so its significand is not all ones, and nothing here is near
 // the ends of the exponent range).  The compiler's own division hands a flag from its scaling step to its last step in
 // VCC, so the divisions of several channels run one after the other.
+// Where x is infinite the residuals are not a number and the quotient is the first q.
 __device__ __forceinline__ double eq3_channel(double n, double y, double r, double s) {
+    const double nb = n + 1.0, x = __builtin_fma(n, r, s), q0 = x * y;
+    const double q1 = __builtin_fma(__builtin_fma(-nb, q0, x), y, q0);
+    const double q = __builtin_fma(__builtin_fma(-nb, q1, x), y, q1);
+    return q == q ? q : q0;
+}
+// The same in a chain of dependent updates, where the choice would lengthen every link: not a number for an infinite x,
+// which is left to the caller to see at the end and do over with eq3_channel.
+__device__ __forceinline__ double eq3_finite(double n, double y, double r, double s) {
     const double nb = n + 1.0, x = __builtin_fma(n, r, s);
     double q = x * y;
     q = __builtin_fma(__builtin_fma(-nb, q, x), y, q);

@@ -732,7 +732,8 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
             const int k = kb + tid / D, d = tid % D;                    // wave-uniform k
             int mine = 0;
             if (k < n_slot) {
-                double x = kb == 0 ? x0 : r[(size_t)slot_id[k] * D + d];
+                const double xs = kb == 0 ? x0 : r[(size_t)slot_id[k] * D + d];
+                double x = xs;
                 int w1 = w_sh[0], p1 = p_sh[0];     // (the next frame's operands are read ahead of this one's arithmetic)
                 double y1 = y_sh[0], s1 = s_sh[0][d];
                 for (int fc = 0; fc < nc; ++fc) {
@@ -740,8 +741,13 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                     const double y = y1, sv = s1;
                     w1 = w_sh[fn]; p1 = p_sh[fn]; y1 = y_sh[fn]; s1 = s_sh[fn][d];
                     if (w != k) continue;
-                    x = eq3_channel((double)p, y, x, sv);
+                    x = eq3_finite((double)p, y, x, sv);
                     ++mine;
+                }
+                if (!(x == x)) {                    // infinite states: over again
+                    x = xs;
+                    for (int fc = 0; fc < nc; ++fc)
+                        if (w_sh[fc] == k) x = eq3_channel((double)p_sh[fc], y_sh[fc], x, s_sh[fc][d]);
                 }
                 if (mine > 0) r[(size_t)slot_id[k] * D + d] = x;
                 row_sh[tid / D][d] = x;

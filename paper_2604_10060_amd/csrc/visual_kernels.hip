@@ -306,13 +306,19 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, con
             if (cnt > 0) {                  // workgroup-uniform
                 double sq = 0.0;
                 for (int d = tid; d < Dv; d += kVisAssign) {
-                    double x = dv.vr[(size_t)id * Dv + d];
+                    const double xs = dv.vr[(size_t)id * Dv + d];
+                    double x = xs;
                     float ev[FR];
 #pragma unroll
                     for (int fc = 0; fc < FR; ++fc) ev[fc] = e[(size_t)min(fc, nc - 1) * Dv + d];
 #pragma unroll
                     for (int fc = 0; fc < FR; ++fc)
-                        if (fc < nc && w_sh[fc] == k) x = eq3_channel((double)p_sh[fc], y_sh[fc], x, (double)ev[fc]);
+                        if (fc < nc && w_sh[fc] == k) x = eq3_finite((double)p_sh[fc], y_sh[fc], x, (double)ev[fc]);
+                    if (!(x == x)) {        // infinite states: over again
+                        x = xs;
+                        for (int fc = 0; fc < nc; ++fc)
+                            if (w_sh[fc] == k) x = eq3_channel((double)p_sh[fc], y_sh[fc], x, (double)e[(size_t)fc * Dv + d]);
+                    }
                     dv.vr[(size_t)id * Dv + d] = x;
                     sq = __builtin_fma(x, x, sq);
                 }

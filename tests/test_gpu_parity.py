@@ -302,6 +302,45 @@ def test_visual_last_bit_ties_do_not_depend_on_the_split_into_calls(P, Dv):
             np.testing.assert_array_equal(a, b)
 
 
+# Infinite key states (an overflowed bf16 key): Eq. 3 carries the infinity into the representative, as the oracle's division
+# does, whatever the number of frames per call; the similarity is not a number and the frame joins the first candidate.
+@pytest.mark.parametrize("C,P,D", [(40, 0, 128), (200, 0, 64), (300, 0, 128), (48, 4, 64)])
+def test_infinite_states_do_not_depend_on_the_split_into_calls(C, P, D):
+    U, T, Dv = 2, 3, 40
+    W, F = 2 * C, 2 * C + 96
+    rng = np.random.default_rng(C)
+    x = rng.standard_normal((F, 1, U, T, D)).astype(np.float32)
+    e = rng.standard_normal((F, Dv)).astype(np.float32)
+    bad = W + 21                               # inside a call of more than one frame, neither its first nor its last
+    x[bad, 0, 0, 1, 5] = np.inf
+    x[bad + 40, 0, 1, 2, D - 1] = -np.inf
+    e[bad + 3, 7] = np.inf
+    K, E = torch.tensor(x).to(DEV), torch.tensor(e).to(DEV)
+    cfg = dict(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T, max_frames=F, n_clusters=C, top_k=1,
+               kv_dtype="fp32", **(dict(n_partitions=P, visual_dim=Dv) if P else {}))
+    states = []
+    for per in (1, 2, 3, 5, 16, 64):
+        m = binding.Mosaic(binding.make_config(**cfg))
+        for f, n in [(0, W)] + [(f, min(per, F - f)) for f in range(W, F, per)]:
+            if P:
+                m.ingest_frame_visual(K[f:f + n], K[f:f + n], E[f:f + n])
+            else:
+                m.ingest_frame(K[f:f + n], K[f:f + n])
+        a, (r, n) = m.assignments(), m.centroids()
+        states.append([a, r, n] + ([m.partitions()[k] for k in ("frame_to_partition", "visual_r", "part_r")] if P else []))
+        m.close()
+    a, r, _ = states[0][:3]
+    lo = states[0][3][[bad, bad + 40]] * (C // P) if P else (0, 0)
+    assert a[0, bad] == lo[0] and a[1, bad + 40] == lo[1]
+    assert r[0, lo[0], 5] == np.inf and r[1, lo[1], D - 1] == -np.inf and np.isfinite(r).sum() == r.size - 2
+    if P:
+        assert states[0][3][bad + 3] == 0 and states[0][4][0, 7] == np.inf
+        assert np.isinf(states[0][5]).sum() == 2 and not np.isnan(states[0][5]).any()
+    for other in states[1:]:
+        for x0, x1 in zip(states[0], other):
+            np.testing.assert_array_equal(x0, x1)
+
+
 # The partitions' representatives and the norms that divide their scores, written by a kernel of its own for each number of
 # frames per call: the two-stage selection's scores are the same bits.
 @pytest.mark.parametrize("P,Cs,D", [(4, 8, 64), (4, 8, 128), (6, 30, 64), (8, 50, 128)])
