@@ -122,14 +122,15 @@ __global__ __launch_bounds__(256) void k_visual_lloyd_assign(DeviceView dv, int 
     for (int t = 0; t < kVisTiles; ++t)
 #pragma unroll
         for (int v = 0; v < 4; ++v) sim_sh[wave][4 * v + lane / 16][16 * t + lane % 16] = acc[t][v];
-    // the non-empty centroid with the largest e.r / |r| (|e| is the same factor for all of them), ties to the lowest id
+    // the non-empty centroid with the largest e.r / |r| (|e| is the same factor for all of them), ties to the lowest id;
+    // where that is infinite the cosine is not a number, and no candidate
     const bool live = lane < P && (live_all != 0 || dv.vn[min(lane, P - 1)] > 0);
     const double rn = dv.vrn[min(lane, P - 1)];
     __syncthreads();
     for (int i = wave; i < nf; i += 4) {
         const double x = (sim_sh[0][i][lane] + sim_sh[1][i][lane]) + (sim_sh[2][i][lane] + sim_sh[3][i][lane]);
         double c = rn == 0.0 ? 0.0 : x / rn;
-        if (!live || !(c == c)) c = -INFINITY;
+        if (!live || !(fabs(c) < INFINITY)) c = -INFINITY;
         int bi = c == -INFINITY ? 0x7fffffff : lane;
         wave_best_ascending(c, bi);
         if (lane == 0) dv.part[f0 + i] = bi == 0x7fffffff ? 0 : bi;

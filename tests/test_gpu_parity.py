@@ -341,6 +341,24 @@ def test_infinite_states_do_not_depend_on_the_split_into_calls(C, P, D):
             np.testing.assert_array_equal(x0, x1)
 
 
+@pytest.mark.parametrize("sign", [1, -1])
+def test_visual_kmeans_has_no_candidate_for_an_infinite_embedding(sign):
+    """The cosine of an embedding with an infinite channel is not a number for any centroid: the frame joins partition 0
+    (the rule for frames without a candidate), and no other frame follows it there once the centroid is infinite."""
+    P, C, U, T, D, Dv, W = 5, 10, 1, 1, 64, 24, 60
+    rng = np.random.default_rng(3)
+    K = torch.tensor(rng.standard_normal((W, 1, U, T, D)).astype(np.float32)).to(DEV)
+    e = (np.eye(P, Dv)[np.arange(W) % P] + 0.1 * rng.standard_normal((W, Dv))).astype(np.float32)
+    e[38, 2] = sign * np.inf                   # (its other channels are those of partition 3)
+    m = binding.Mosaic(binding.make_config(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T, max_frames=W,
+                                           n_clusters=C, top_k=1, kv_dtype="fp32", n_partitions=P, visual_dim=Dv,
+                                           warmup_frames=W, lloyd_iters=3))
+    m.ingest_frame_visual(K, K, torch.tensor(e).to(DEV))
+    part = m.partitions()["frame_to_partition"]
+    m.close()
+    assert part[38] == 0 and (part == 0).sum() == 1
+
+
 # The partitions' representatives and the norms that divide their scores, written by a kernel of its own for each number of
 # frames per call: the two-stage selection's scores are the same bits.
 @pytest.mark.parametrize("P,Cs,D", [(4, 8, 64), (4, 8, 128), (6, 30, 64), (8, 50, 128)])
