@@ -1252,10 +1252,13 @@ int32_t mosaic_decode_step(mosaic_ctx *ctx, int32_t layer, const void *q_dev, in
     return MOSAIC_OK;
 }
 
-static int d2h(mosaic_ctx *ctx, void *dst, const void *src, size_t bytes) {     // (observers: after any overlapped ingest)
+// Observers: a copy into the caller's (pageable) memory, after everything on the stream and any overlapped ingest.  The
+// blocking call, which returns when dst is written: an asynchronous copy into pageable memory is over when the runtime
+// says so, and a synchronisation of its stream does not say so.
+static int d2h(mosaic_ctx *ctx, void *dst, const void *src, size_t bytes) {
     { const int rc = join_ingest(ctx); if (rc != MOSAIC_OK) return rc; }
-    hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, ctx->stream);
-    if (e != hipSuccess) return fail_hip(ctx, e, "hipMemcpyAsync D2H");
+    hipError_t e = hipMemcpyWithStream(dst, src, bytes, hipMemcpyDeviceToHost, ctx->stream);
+    if (e != hipSuccess) return fail_hip(ctx, e, "hipMemcpyWithStream D2H");
     return MOSAIC_OK;
 }
 static int sync(mosaic_ctx *ctx) {
@@ -1276,8 +1279,7 @@ int32_t mosaic_get_assignments(mosaic_ctx *ctx, int32_t *frame_to_cluster) {
     }
     // All units' rows in one copy (a copy per unit costs 13 us each: 1.46 of the 1.9 ms that reading back the index of a
     // 28-layer stream took): straight into the caller's array when the stream is full, else through a buffer, as long as a
-    // unit's row is worth less than a copy.  (One-dimensional copies only: an asynchronous strided copy into pageable memory
-    // was not complete when the stream was.)
+    // unit's row is worth less than a copy.
     const size_t row = (size_t)dv.F, used = ((size_t)dv.U - 1) * row + nf;
     int32_t *all = nf == row ? frame_to_cluster : dv.F <= 32768 ? new (std::nothrow) int32_t[used] : nullptr;
     int rc = MOSAIC_OK;
