@@ -1734,10 +1734,12 @@ __global__ __launch_bounds__(128) void k_lloyd_update(DeviceView dv, int n_frame
 // runs on the copy stream beside the next batch's staging and assignment, and
 // one workgroup per page would hold the chip while it waits for the link.
 // ---------------------------------------------------------------------------
-// Host tier: a batch's assignments, compacted, straight into pinned host memory.  grid (U), 64 threads.
-__global__ __launch_bounds__(64) void k_gather_assign(DeviceView dv, int f0, int n) {
+// Assignments of frames f0 .. f0+n-1, compacted: a host-tier batch's straight into pinned memory, an observer's into
+// scratch.  grid (U, blocks of frames).
+__global__ __launch_bounds__(kBlock) void k_gather_assign(DeviceView dv, int f0, int n) {
     const int u = blockIdx.x;
-    for (int i = threadIdx.x; i < n; i += 64) dv.batch_assign[(size_t)u * n + i] = dv.assign[(size_t)u * dv.F + f0 + i];
+    for (int i = blockIdx.y * kBlock + threadIdx.x; i < n; i += gridDim.y * kBlock)
+        dv.batch_assign[(size_t)u * n + i] = dv.assign[(size_t)u * dv.F + f0 + i];
 }
 
 constexpr int kOffloadXcds = 8;
@@ -1844,7 +1846,8 @@ hipError_t launch_value_reps(const DeviceView &dv, int n_frames, hipStream_t s) 
 }
 
 hipError_t launch_gather_assign(const DeviceView &dv, int f0, int n, hipStream_t s) {
-    return checked([&] { k_gather_assign<<<dv.U, 64, 0, s>>>(dv, f0, n); });
+    const dim3 grid(dv.U, std::min((n + kBlock - 1) / kBlock, 1024));
+    return checked([&] { k_gather_assign<<<grid, kBlock, 0, s>>>(dv, f0, n); });
 }
 
 hipError_t launch_offload(const DeviceView &dv, int f0, int n, hipStream_t s) {

@@ -47,7 +47,7 @@ struct DeviceView {
     int SFh;                   // frames per host slab
     int HP;                    // host pages per unit
     const int *dest;           // [U][SN] host page of each staged frame of the current batch (pinned memory)
-    int *batch_assign;         // [U][frames of the batch] its assignments on their way to the host (pinned memory)
+    int *batch_assign;         // [U][n] gathered assignments: a host-tier batch's (pinned memory), an observer's (scratch)
     // fetch work lists, written by the host into pinned memory and read by k_fetch over PCIe
     const int *moves;          // [U][F][2] (host page, cache page)
     const int *n_moves;        // [U]
@@ -180,7 +180,7 @@ hipError_t launch_retrieve(const DeviceView &dv, int u0, int n_units, const void
 // deferred-split maintainer: singletons take part, residency and deferred splits follow the selection
 hipError_t launch_retrieve_deferred(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                                     int n_frames, int score_mode, hipStream_t s);
-// host tier: the assignments of frames f0..f0+n-1 of every unit to dv.batch_assign, [U][n]
+// the assignments of frames f0..f0+n-1 of every unit to dv.batch_assign, [U][n]
 hipError_t launch_gather_assign(const DeviceView &dv, int f0, int n, hipStream_t s);
 // host tier: copy staged frames f0..f0+n-1 of every unit to host page dest[u][f - f0]
 hipError_t launch_offload(const DeviceView &dv, int f0, int n, hipStream_t s);

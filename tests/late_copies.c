@@ -9,6 +9,7 @@
 typedef struct { unsigned x, y, z; } dim3;
 static struct { void *dst; const void *src; size_t n; } late[4096];
 static int n_late;
+static size_t n_bytes;
 static char scratch[1 << 12];
 
 int hipGetDevice(int *d) { *d = 0; return 0; }
@@ -30,7 +31,9 @@ int hipMemcpyAsync(void *dst, const void *src, size_t n, int kind, void *s) {
 int hipMemcpyWithStream(void *dst, const void *src, size_t n, int kind, void *s) {
     (void)kind; (void)s;
     memcpy(dst, src, n);
+    n_bytes += n;
     return 0;
 }
-/* how many copies are still to be done */
+/* how many copies are still to be done, and the bytes that others have copied since the last time */
 int late_copies_pending(void) { return n_late; }
+size_t copied_bytes(void) { const size_t n = n_bytes; n_bytes = 0; return n; }

@@ -14,6 +14,7 @@ import ctypes as C, sys
 import numpy as np
 from paper_2604_10060_amd import binding as b
 late = C.CDLL(sys.argv[1])
+late.copied_bytes.restype = C.c_size_t
 lib = b.load_library()
 PAT = 0x07
 I, D = 0x07070707, np.frombuffer(bytes([PAT] * 8), np.float64)[0]
@@ -50,7 +51,9 @@ def same(*arrays):
 U, F, CL = 6, 40, 8
 for n in (40, 23):                                   # a full stream, and one with room left
     c = Ctx(n)
+    late.copied_bytes()
     a = ints(U, n); c.ok(lib.mosaic_get_assignments(c.h, a.ctypes.data)); same(a)
+    assert late.copied_bytes() == U * n * 4         # the frames there are, however long the stream may become
     r, k = dbls(U, CL, 64), ints(U, CL); c.ok(lib.mosaic_get_centroids(c.h, r.ctypes.data, k.ctypes.data)); same(r, k)
     s = dbls(U, n, 64); c.ok(lib.mosaic_get_summaries(c.h, s.ctypes.data)); same(s)
     c.ok(lib.mosaic_retrieve(c.h, 1, c.p, 1))
