@@ -87,15 +87,17 @@ __device__ __forceinline__ bool row_second_first(int C, int id) { return C > 256
 // quotient (Markstein's theorem; n + 1 is a small integer, so its significand is not all ones, and nothing here is near
 // the ends of the exponent range).  The compiler's own division hands a flag from its scaling step to its last step in
 // VCC, so the divisions of several channels run one after the other.
-// Where x is infinite the residuals are not a number and the quotient is the first q.
+// Where x is infinite the residuals are not a number and the last instruction, that of the compiler's own division, puts
+// the infinity back.
 __device__ __forceinline__ double eq3_channel(double n, double y, double r, double s) {
-    const double nb = n + 1.0, x = __builtin_fma(n, r, s), q0 = x * y;
-    const double q1 = __builtin_fma(__builtin_fma(-nb, q0, x), y, q0);
-    const double q = __builtin_fma(__builtin_fma(-nb, q1, x), y, q1);
-    return q == q ? q : q0;
+    const double nb = n + 1.0, x = __builtin_fma(n, r, s);
+    double q = x * y;
+    q = __builtin_fma(__builtin_fma(-nb, q, x), y, q);
+    q = __builtin_fma(__builtin_fma(-nb, q, x), y, q);
+    return __builtin_amdgcn_div_fixup(q, nb, x);
 }
-// The same in a chain of dependent updates, where the choice would lengthen every link: not a number for an infinite x,
-// which is left to the caller to see at the end and do over with eq3_channel.
+// The same in a chain of dependent updates, where that instruction would lengthen every link: not a number for an infinite
+// x, which is left to the caller to see at the end and do over with eq3_channel.
 __device__ __forceinline__ double eq3_finite(double n, double y, double r, double s) {
     const double nb = n + 1.0, x = __builtin_fma(n, r, s);
     double q = x * y;
@@ -211,14 +213,16 @@ struct ChainView {
     const double *irn;                          // [cluster] 1 / |r|, 0 for a zero row
 };
 
-// Decides the frames of a chunk, at least two, whose first one joins slot w of lane 0.  One wavefront; lane (g, n) =
-// (lane / 16, lane % 16) looks at frame n and slots g, g + 4, ...  w: the slot every frame (lane n of each row of 16) is
-// assumed to join, replaced by the one it does join.  Returns the number of leading frames that are decided.
-__device__ __forceinline__ int chain_decide(const ChainView &v, int nc, int n_slot, int &w) {
+// Decides the frames of a chunk, whose first one joins slot w of lane 0.  One wavefront; lane (g, n) = (lane / 16, lane % 16)
+// looks at frame n and slots g, g + 4, ...  w: the slot every frame (lane n of each row of 16) is assumed to join (-1: it
+// has no live candidate), replaced by the one it does join.  Returns the number of leading frames that are decided, at
+// least one; tied: the frame after them is too close to call.
+__device__ __forceinline__ int chain_decide(const ChainView &v, int nc, int n_slot, int &w, bool &tied) {
     constexpr int FR = kChainFrames;
     const int lane = threadIdx.x % 64, g = lane / 16, n = lane % 16;
     const int fn = min(n, nc - 1), lo = v.lo[fn];
     const double is = v.isn[fn], sn = v.sn[fn], ss = v.ss[fn], out = v.out[fn];
+    const bool zero = ss == 0.0 && w >= 0;      // similarity 0 with every live cluster: it joins the lowest id, as assumed
     double gr[FR];                      // s_h . s_n / |s_n| of the earlier frames h
 #pragma unroll
     for (int h = 0; h < FR; ++h) gr[h] = v.gram[h][fn];
@@ -260,16 +264,28 @@ __device__ __forceinline__ int chain_decide(const ChainView &v, int nc, int n_sl
         const unsigned int odd16 = (unsigned int)(odds | odds >> 16 | odds >> 32 | odds >> 48) & 0xffffu;
         const unsigned int back16 = (unsigned int)(backs | backs >> 16 | backs >> 32 | backs >> 48) & 0xffffu;
         // (frame 0 joins slot 0 by construction)
-        const bool clear = n == 0 || n >= nc || (best - fmax(next, out) > kChainMargin && !((odd16 >> n) & 1));
+        const bool clear = n == 0 || n >= nc || zero || (best - fmax(next, out) > kChainMargin && !((odd16 >> n) & 1));
         const unsigned int vague = (unsigned int)__ballot(!clear) & 0xffffu;
-        const unsigned int other = (unsigned int)__ballot(clear && n > 0 && n < nc && bk != w) & 0xffffu;
+        const unsigned int other = (unsigned int)__ballot(clear && !zero && n > 0 && n < nc && bk != w) & 0xffffu;
         // a winner at more than a right angle shortens the representative: the rounding errors of its dot
         // products grow relative to it, so the frames after it are better taken from the rows
         const int stop = min(vague ? __ffs((int)vague) - 1 : nc, back16 ? __ffs((int)back16) : nc);
         const int at = other ? __ffs((int)other) - 1 : nc;
-        if (at >= stop) return min(stop, nc);
+        if (at >= stop) {
+            tied = stop < nc && ((vague >> stop) & 1);
+            return min(stop, nc);
+        }
         if (n == at) w = bk;            // ... that frame's winner, and once more
     }
 }
+
+// How many chunks' worth of frames are taken in turn after a chunk that met a frame too close to call: one, and twice as
+// many each time the next chunk fares no better.  A stream that ties at every frame (representatives along one direction)
+// so pays for few products whose result it cannot use.
+struct InTurn {
+    int left = 0, next = 1;
+    __device__ __forceinline__ void failed() { left = next; next = min(2 * next, 64); }
+    __device__ __forceinline__ void held() { next = 1; }
+};
 
 } // namespace mosaic

@@ -495,10 +495,13 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
 // Decisions are exact: the similarities of steps 1 and 3 differ from those of the rows by rounding (sums of at most 17
 // products with r.s >= 0, so that no length cancels: below 1e-13 in the cosine), and they only decide where the best
 // is ahead by more than kChainMargin.  At a frame that is closer than that, or whose best slot does not exceed the
-// bound of step 2, the chunk ends; the frame then comes first in the next chunk, where step 1 has its similarities
-// under the rows themselves, and if even those are too close the frame is decided by the full computation in the order
-// of operations of the one-frame kernel, ties to the lowest id.  So ids and representatives are the same bits for any
-// split of the stream into calls.
+// bound of step 2, the chunk ends, and the frames after it are taken in turn: in the order of operations of the one-frame
+// kernel, ties to the lowest id, the products of a chunk's frames with the rows formed in one pass over them and those with
+// a row that moves formed anew.  So ids and representatives are the same bits for any split of the stream into calls.  (A
+// zero summary needs no product: it has similarity 0 with every cluster.)  Frames in turn cost 2 us each, more for large
+// tables: 16 a call, page store included, on streams whose clusters lie along six directions, taken in turn by a pass over
+// the products each / now / by the kernels before this one: C = 64 67 / 46 / 33 us, C = 200 200 / 63 / 46, C = 300 186 / 74
+// / 103, C = 1000 456 / 169 / 260; on zero summaries C = 64 146 / 16 / 32 us, C = 1000 913 / 86 / 262.
 // What bounds it (16 frames, D = 128, one chunk; cycles of one workgroup): the trip to memory for table and summaries
 // 4 k (11 k while page stores saturate the memory system), the fp64 products 6-8 k, nearest clusters 3 k, decisions
 // 3.5 k, Eq. 3 on the rows 7 k (seven dependent fp64 operations per frame).  A kernel that takes the frames one after
@@ -510,16 +513,18 @@ constexpr int kChainBlock = 512, kChainSims = 8192;
 template <int D>
 __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int f0, int f1) {
     constexpr int EPL = D / 16, NG = kChainBlock / 16, NW = kChainBlock / 64, KS = D / 8, SPB = kChainBlock / D;
-    constexpr int FR = kChainFrames, kNone = 0x7fffffff;
+    constexpr int FR = kChainFrames, kNone = 0x7fffffff, TW = FR / 4;
     const int u = blockIdx.x, tid = threadIdx.x, lane = tid % 64, lr = tid % 16, grp = tid / 16, C = dv.C;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64), g = lane / 16, n = lane % 16;
     __shared__ __attribute__((aligned(16))) double s_sh[FR][D + 2];     // (row padding: 16 rows' operand reads spread over the banks)
     __shared__ double sim_sh[kChainSims];           // [frame][candidate] dot products, -inf for an empty cluster
     __shared__ double gram_sh[FR][FR + 1];          // s_f . s_g / |s_g|
-    __shared__ double irn_sh[1024];                 // 1 / |r_j|, 0 for a zero row
+    __shared__ double rn_sh[1024], irn_sh[1024];    // |r_j|; 1 / |r_j|, 0 for a zero row
     __shared__ int n_sh[1024], slot_sh[1024];       // sizes; slot of a cluster, -1
     __shared__ double ss_sh[FR], sn_sh[FR], isn_sh[FR], out_v[FR], y_sh[FR], row_sh[SPB][D];
-    __shared__ int near_sh[FR], sure_sh[FR], lo_sh[FR], w_sh[FR], p_sh[FR], slot_id[kChainSlots], n_slot_sh, nc_sh;
+    __shared__ double moved_sh[FR][D], red_v[TW];   // frames in turn: rows that moved
+    __shared__ int red_i[TW];
+    __shared__ int near_sh[FR], sure_sh[FR], lo_sh[FR], w_sh[FR], p_sh[FR], slot_id[kChainSlots], n_slot_sh, nc_sh, tied_sh;
     double *r = dv.r + (size_t)u * C * D;
     const bool nested = dv.P > 0;
     const int width = nested ? dv.Cs : C;           // candidates per frame: ids lo .. lo + width - 1
@@ -528,11 +533,60 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
     for (int j = tid; j < C; j += kChainBlock) {
         const double rn = dv.rnorm[(size_t)u * C + j];
         n_sh[j] = dv.n[(size_t)u * C + j];
+        rn_sh[j] = rn;
         irn_sh[j] = rn > 0.0 ? 1.0 / rn : 0.0;
         slot_sh[j] = -1;
     }
+    auto resize = [&](int j, int size, double norm) {               // a cluster's new size and norm
+        n_sh[j] = size;
+        rn_sh[j] = norm;
+        irn_sh[j] = norm > 0.0 ? 1.0 / norm : 0.0;
+        dv.n[(size_t)u * C + j] = size;
+        dv.rnorm[(size_t)u * C + j] = norm;
+    };
+    // nested hierarchy: the partitions' representatives in this unit's key space follow the same running mean (Eq. 3 one
+    // level up), one wavefront, two channels per lane, a partition's row in registers until another's turn comes
+    auto partition_reps = [&](int nc) {
+        constexpr int CPL = D / 64;
+        const int own = lane < nc ? lo_sh[lane] / dv.Cs : -1;
+        int size = lane < nc ? dv.pn[(size_t)u * dv.P + own] : 0;
+#pragma unroll
+        for (int h = 0; h < FR - 1; ++h) size += h < lane && __builtin_amdgcn_readlane(own, h) == own ? 1 : 0;
+        const double yl = __ddiv_rn(1.0, (double)size + 1.0);
+        double pv[CPL];
+        int at = -1, pn = 0;
+        auto leave = [&]() {
+            double psq = 0.0;
+#pragma unroll
+            for (int x = 0; x < CPL; ++x) {
+                dv.pr[((size_t)u * dv.P + at) * D + lane + 64 * x] = pv[x];
+                const double w = wave_square_sum(pv[x]);
+                psq = x == 0 ? w : psq + w;
+            }
+            if (lane == 0) {
+                dv.prn[(size_t)u * dv.P + at] = sqrt(psq);
+                dv.pn[(size_t)u * dv.P + at] = pn;
+            }
+        };
+        for (int fc = 0; fc < nc; ++fc) {
+            const int p = __builtin_amdgcn_readlane(own, fc);
+            if (p != at) {
+                if (at >= 0) leave();
+                at = p;
+#pragma unroll
+                for (int x = 0; x < CPL; ++x) pv[x] = dv.pr[((size_t)u * dv.P + at) * D + lane + 64 * x];
+            }
+            pn = __builtin_amdgcn_readlane(size, fc) + 1;
+            const double ny = readlane_f64(yl, fc);
+#pragma unroll
+            for (int x = 0; x < CPL; ++x) pv[x] = eq3_channel((double)(pn - 1), ny, pv[x], s_sh[fc][lane + 64 * x]);
+        }
+        leave();
+    };
+    InTurn turn;
     for (int c0 = f0; c0 < f1;) {
         int nc = min(NF, f1 - c0);
+        const bool in_turn = turn.left > 0;         // workgroup-uniform
         // ---- 1. the chunk against the whole table and against itself ----
         // operand layout of v_mfma_f64_16x16x4_f64: A lane (row lane%16, k lane/16), B lane (column lane%16, k lane/16),
         // result register v = (row 4v + lane/16, column lane%16); lane group k holds channels 8s + 2k, + 1 of step s
@@ -542,7 +596,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
 #pragma unroll
             for (int s = 0; s < KS; ++s) b[s] = *reinterpret_cast<const f64x2 *>(rj + 8 * s);
         };
-        if (!nested && wave < tiles) load_rows(wave);               // travels with the summaries
+        if (!nested && !in_turn && wave < tiles) load_rows(wave);   // travels with the summaries
         {
             const double *src = dv.summ + ((size_t)u * dv.F + c0) * D;
             for (int i = tid; i < nc * D / 2; i += kChainBlock)
@@ -560,7 +614,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
             }
             return acc;
         };
-        for (int t = wave; t < tiles; t += NW) {
+        for (int t = wave; t < tiles && !in_turn; t += NW) {
             if (nested) {                           // tiles that no frame of the chunk asks for are not read
                 const int lo = lo_sh[min(lane, nc - 1)];
                 if (__ballot(lo < 16 * t + 16 && lo + width > 16 * t) == 0) continue;
@@ -578,7 +632,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                 }
             }
         }
-        if (wave == NW - 1) {                       // (the wavefront with the fewest tiles)
+        if (wave == NW - 1 && !in_turn) {           // (the wavefront with the fewest tiles)
 #pragma unroll
             for (int s = 0; s < KS; ++s) b[s] = *reinterpret_cast<const f64x2 *>(&s_sh[n][8 * s + 2 * g]);
             const f64x4 acc = times_s();            // (rows and columns beyond the chunk: whatever the LDS held, never read)
@@ -592,7 +646,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
             if (g == 0) { isn_sh[n] = is; sn_sh[n] = ss_sh[n] * is; }
         }
         __syncthreads();
-        for (int fc = wave; fc < nc; fc += NW) {    // the nearest cluster under the table as it stands
+        for (int fc = wave; fc < nc && !in_turn; fc += NW) {        // the nearest cluster under the table as it stands
             const double is = isn_sh[fc];
             const int lo = lo_sh[fc];
             double bv = -INFINITY, sv = -INFINITY;
@@ -611,69 +665,161 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
             const int own_i = bi;
             wave_best_ascending(bv, bi);
             const double second = wave_max(own_i == bi ? sv : own);
-            const bool sure = __ballot(odd) == 0 && (bi == kNone || bv - second > kChainMargin);
+            bool sure = bi != kNone && __ballot(odd) == 0 && bv - second > kChainMargin;
+            if (ss_sh[fc] == 0.0) {                 // (wave-uniform) a zero summary: similarity 0 with every live cluster, the lowest id
+                int first = kNone;
+                for (int i = NI - 1; i >= 0; --i) {
+                    const int cj = lane * NI + i;
+                    if (cj < width && n_sh[lo + cj] > 0) first = lo + cj;
+                }
+                bi = __builtin_amdgcn_readlane(first, max(__ffsll((long long)__ballot(first != kNone)) - 1, 0));
+                sure = bi != kNone;
+            }
             if (lane == 0) { near_sh[fc] = bi; sure_sh[fc] = sure; out_v[fc] = second; }
         }
         __syncthreads();
-        if (!sure_sh[0]) {                          // the first frame by the full computation (workgroup-uniform)
-            const int lo = lo_sh[0];
-            double sl[EPL];
+        if (in_turn || !sure_sh[0]) {               // workgroup-uniform: the frames in turn
+            // In the one-frame kernel's order of operations, but a row is read once for all frames of the chunk: the frames'
+            // products with every row (a 16-lane group per row, four at a time), then frame by frame the search, Eq. 3 on the
+            // winner -- by a group per frame, so that each has the new row -- and the later frames' products with it.
+            if (in_turn) --turn.left;
+            else turn.failed();
+            unsigned long long parts = 0;           // partitions that the chunk asks for
+            if (nested)
+                for (int fc = 0; fc < nc; ++fc) parts |= 1ull << (lo_sh[fc] / dv.Cs);
+            auto next = [&](int j) {
+                do j += NG;
+                while (j < C && nested && !((parts >> (j / dv.Cs)) & 1));
+                return j;
+            };
+            auto fetch = [&](int j, double (&o)[EPL]) {
+                const double *rj = r + (size_t)min(j, C - 1) * D + lr * EPL;
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) sl[e] = s_sh[0][lr * EPL + e];
-            const double sn = sqrt(row16_sum(square_channels(sl, true)));
-            for (int cj = grp; cj < width; cj += NG) {                // (uniform within a 16-lane group)
-                const double *rj = r + (size_t)(lo + cj) * D + lr * EPL;
-                double row[EPL];
+                for (int e = 0; e < EPL; ++e) o[e] = rj[e];
+            };
+            auto summary = [&](int fc, double (&o)[EPL]) {
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) row[e] = rj[e];
+                for (int e = 0; e < EPL; ++e) o[e] = s_sh[fc][lr * EPL + e];
+            };
+            auto product = [&](int fc, int j, const double (&sl)[EPL], const double (&row)[EPL]) {  // (uniform within a group)
                 const double p = row16_sum(dot_channels(sl, row));
-                const double rn = dv.rnorm[(size_t)u * C + lo + cj];
-                const double c = n_sh[lo + cj] <= 0 ? -INFINITY : (sn == 0.0 || rn == 0.0) ? 0.0 : p / (sn * rn);
-                if (lr == 0) sim_sh[cj] = c;
+                const int cj = j - lo_sh[fc];
+                if (lr == 0 && cj >= 0 && cj < width) sim_sh[fc * width + cj] = p;
+            };
+            double row[EPL], sl[EPL];
+            for (int j = next(grp - NG); j < C;) {
+                constexpr int RB = 4;
+                double rows[RB][EPL];
+                int id[RB];
+#pragma unroll
+                for (int x = 0; x < RB; ++x) {
+                    id[x] = j;
+                    fetch(j, rows[x]);
+                    if (j < C) j = next(j);
+                }
+                for (int fc = 0; fc < nc; ++fc) {
+                    summary(fc, sl);
+#pragma unroll
+                    for (int x = 0; x < RB; ++x) product(fc, id[x] < C ? id[x] : -1, sl, rows[x]);
+                }
+            }
+            if (grp < nc) {
+                summary(grp, sl);
+                const double norm = sqrt(row16_sum(square_channels(sl, true)));
+                if (lr == 0) sn_sh[grp] = norm;
             }
             __syncthreads();
-            if (wave == 0) {
+            // (The loop waits for no store: moved rows stay in LDS until the chunk is done.  Four wavefronts, one per SIMD: a
+            // group per frame, and up to four consecutive candidates per thread, so that ids ascend with the thread.)
+            const int per = (width + 64 * TW - 1) / (64 * TW);
+            int a1 = -1, n1 = 0, used = 0;          // the cluster of the frame before, with its new size and norm; `row` is its row
+            double rn1 = 0.0;
+            for (int fc = 0; fc < nc; ++fc) {
+                const int lo = lo_sh[fc];
                 double bv = -INFINITY;
                 int bi = kNone;
-                for (int i = 0; i < NI; ++i) {
-                    const int cj = lane * NI + i;
-                    if (cj < width && sim_sh[cj] > bv) { bv = sim_sh[cj]; bi = lo + cj; }
+                if (wave < TW) {
+                    const double sn = sn_sh[fc];
+                    for (int cj = tid * per; cj < min(width, tid * per + per); ++cj) {
+                        const int id = lo + cj, size = id == a1 ? n1 : n_sh[id];
+                        const double rn = id == a1 ? rn1 : rn_sh[id];
+                        const double c = (sn == 0.0 || rn == 0.0) ? 0.0 : sim_sh[fc * width + cj] / (sn * rn);
+                        if (size > 0 && c > bv) { bv = c; bi = id; }
+                    }
+                    wave_best_ascending(bv, bi);
+                    if (lane == 0) { red_v[wave] = bv; red_i[wave] = bi; }
                 }
-                wave_best_ascending(bv, bi);
-                if (lane == 0) near_sh[0] = bi;
+                lds_barrier();
+                int a = lo, size = 0, slot = -1;
+                double norm = 0.0;
+                if (wave < TW) {
+                    bv = red_v[0]; bi = red_i[0];
+#pragma unroll
+                    for (int w = 1; w < TW; ++w)
+                        if (red_v[w] > bv) { bv = red_v[w]; bi = red_i[w]; }
+                    if (bi != kNone) a = bi;
+                    size = a == a1 ? n1 : n_sh[a];
+                    slot = slot_sh[a];
+                    const double y = __ddiv_rn(1.0, (double)size + 1.0);
+                    if (a != a1) {
+                        if (slot < 0) fetch(a, row);
+                        else
+#pragma unroll
+                            for (int e = 0; e < EPL; ++e) row[e] = moved_sh[slot][lr * EPL + e];
+                    }
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) row[e] = eq3_channel((double)size, y, row[e], s_sh[fc][lr * EPL + e]);
+                    if (grp > fc && grp < nc) product(grp, a, sl, row);
+                    norm = sqrt(row16_sum(square_channels(row, row_second_first(C, a))));
+                    if (slot < 0) slot = used++;
+                    a1 = a; n1 = size + 1; rn1 = norm;
+                }
+                lds_barrier();                      // the old row, size and norm have been read
+                if (grp == 0) {
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) moved_sh[slot][lr * EPL + e] = row[e];
+                    if (lr == 0) {
+                        slot_sh[a] = slot;
+                        slot_id[slot] = a;
+                        n_slot_sh = used;
+                        resize(a, size + 1, norm);
+                        dv.assign[(size_t)u * dv.F + c0 + fc] = a;
+                        dv.pos[(size_t)u * dv.F + c0 + fc] = size;
+                    }
+                }
             }
             __syncthreads();
+            for (int i = tid; i < n_slot_sh * D; i += kChainBlock) r[(size_t)slot_id[i / D] * D + i % D] = moved_sh[i / D][i % D];
+            if (tid < n_slot_sh) slot_sh[slot_id[tid]] = -1;
+            if (nested && wave == NW - 1) partition_reps(nc);
+            __syncthreads();
+            c0 += nc;
+            continue;
         }
         // ---- 2. slots ----
         if (wave == 0) {
-            // a first frame decided by the full computation, or without a live candidate, makes a chunk of its own
-            const int lim = !sure_sh[0] || near_sh[0] == kNone ? 1 : nc;
-            int mine = lane < lim ? near_sh[lane] : -1;
-            if (mine == kNone) mine = lo_sh[lane];  // (empty: the frame joins the first of its candidates)
+            int mine = lane < nc ? near_sh[lane] : -1;
+            if (mine == kNone) mine = -1;           // (no live candidate: the chunk ends before the frame)
             unsigned long long left = __ballot(mine >= 0);
             int k = 0;
-            while (left && k < kChainSlots) {
+            while (left) {
                 const int id = __builtin_amdgcn_readlane(mine, __ffsll((long long)left) - 1);
                 if (lane == 0) { slot_id[k] = id; slot_sh[id] = k; }
                 left &= ~__ballot(mine == id);
                 ++k;
             }
-            if (lane == 0) {
-                n_slot_sh = k;
-                nc_sh = left ? __ffsll((long long)left) - 1 : lim;
-            }
+            if (lane == 0) n_slot_sh = k;
         }
         __syncthreads();
-        nc = nc_sh;
         const int n_slot = n_slot_sh;
         double x0 = 0.0;                            // step 4's first rows travel meanwhile
         if (tid / D < n_slot) x0 = r[(size_t)slot_id[tid / D] * D + tid % D];
         // ---- 3. the decisions: lane (g, n) looks at frame n and slots g, g + 4, ... ----
         if (wave == 0) {
-            int w = n < nc ? slot_sh[near_sh[n] == kNone ? lo_sh[n] : near_sh[n]] : -1;       // the frame's winner, as assumed
-            int done = nc;
-            if (nc > 1)
-                done = chain_decide({sim_sh, width, lo_sh, sn_sh, isn_sh, ss_sh, out_v, gram_sh, slot_id, n_sh, irn_sh}, nc, n_slot, w);
+            int w = n < nc && near_sh[n] != kNone ? slot_sh[near_sh[n]] : -1;       // the frame's winner, as assumed
+            bool tied;
+            const int done =
+                chain_decide({sim_sh, width, lo_sh, sn_sh, isn_sh, ss_sh, out_v, gram_sh, slot_id, n_sh, irn_sh}, nc, n_slot, w, tied);
             if (lane < done) {
                 int p = n_sh[slot_id[w]];
 #pragma unroll
@@ -684,49 +830,13 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                 dv.assign[(size_t)u * dv.F + c0 + lane] = slot_id[w];
                 dv.pos[(size_t)u * dv.F + c0 + lane] = p;
             }
-            if (lane == 0) nc_sh = done;
+            if (lane == 0) { nc_sh = done; tied_sh = tied; }
         }
         __syncthreads();
         nc = nc_sh;
-        if (nested && wave == NW - 1) {
-            // nested hierarchy: the partitions' representatives in this unit's key space follow the same running mean
-            // (Eq. 3 one level up), two channels per lane, a partition's row in registers until another's turn comes
-            constexpr int CPL = D / 64;
-            const int own = lane < nc ? lo_sh[lane] / dv.Cs : -1;
-            int size = lane < nc ? dv.pn[(size_t)u * dv.P + own] : 0;
-#pragma unroll
-            for (int h = 0; h < FR - 1; ++h) size += h < lane && __builtin_amdgcn_readlane(own, h) == own ? 1 : 0;
-            const double yl = __ddiv_rn(1.0, (double)size + 1.0);
-            double pv[CPL];
-            int at = -1, pn = 0;
-            auto leave = [&]() {
-                double psq = 0.0;
-#pragma unroll
-                for (int x = 0; x < CPL; ++x) {
-                    dv.pr[((size_t)u * dv.P + at) * D + lane + 64 * x] = pv[x];
-                    const double w = wave_square_sum(pv[x]);
-                    psq = x == 0 ? w : psq + w;
-                }
-                if (lane == 0) {
-                    dv.prn[(size_t)u * dv.P + at] = sqrt(psq);
-                    dv.pn[(size_t)u * dv.P + at] = pn;
-                }
-            };
-            for (int fc = 0; fc < nc; ++fc) {
-                const int p = __builtin_amdgcn_readlane(own, fc);
-                if (p != at) {
-                    if (at >= 0) leave();
-                    at = p;
-#pragma unroll
-                    for (int x = 0; x < CPL; ++x) pv[x] = dv.pr[((size_t)u * dv.P + at) * D + lane + 64 * x];
-                }
-                pn = __builtin_amdgcn_readlane(size, fc) + 1;
-                const double ny = readlane_f64(yl, fc);
-#pragma unroll
-                for (int x = 0; x < CPL; ++x) pv[x] = eq3_channel((double)(pn - 1), ny, pv[x], s_sh[fc][lane + 64 * x]);
-            }
-            leave();
-        }
+        if (tied_sh) turn.failed();
+        else turn.held();
+        if (nested && wave == NW - 1) partition_reps(nc);
         // ---- 4. Eq. 3 on the rows ----
         for (int kb = 0; kb < n_slot; kb += SPB) {  // workgroup-uniform
             const int k = kb + tid / D, d = tid % D;                    // wave-uniform k
@@ -763,14 +873,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                 for (int fc = 0; fc < nc; ++fc) cnt += w_sh[fc] == kn;
                 if (lr == 0) {
                     const int j = slot_id[kn];
-                    if (cnt > 0) {
-                        const double rn = sqrt(sq);
-                        const int nj = n_sh[j] + cnt;
-                        n_sh[j] = nj;
-                        irn_sh[j] = rn > 0.0 ? 1.0 / rn : 0.0;
-                        dv.n[(size_t)u * C + j] = nj;
-                        dv.rnorm[(size_t)u * C + j] = rn;
-                    }
+                    if (cnt > 0) resize(j, n_sh[j] + cnt, sqrt(sq));
                     slot_sh[j] = -1;
                 }
             }

@@ -18,7 +18,6 @@ namespace mosaic {
 namespace {
 
 constexpr int kVisBlock = 1024, kVisWaves = kVisBlock / 64;
-constexpr int kVisAssign = 512;             // threads of the online kernel
 
 // (every call site has the whole wavefront active)
 __device__ __forceinline__ double wave_sum(double x) { return wave64_sum(x); }
@@ -172,13 +171,75 @@ __global__ __launch_bounds__(kVisBlock) void k_visual_lloyd_update(DeviceView dv
     if (tid == 0) { dv.vrn[p] = sqrt(sq); dv.vn[p] = count; }
 }
 
+// One frame by the full computation, all threads of a workgroup: the embedding is staged in LDS, a wavefront scores two
+// centroids at a time (their rows' loads in flight together), all threads update the winner's row.  changed(a, n, norm) is
+// called by thread 0 with the new size and norm of the row.  The caller orders calls by a barrier.
+constexpr int kVisAssign = 512;             // threads of the online kernels
+struct VisualTurnShared {
+    double e[4096], red[kVisAssign / 64], bv[kVisAssign / 64];
+    int bi[kVisAssign / 64];
+};
+template <typename Changed>
+__device__ __forceinline__ void visual_in_turn(const DeviceView &dv, const float *src, int f, VisualTurnShared &sh, Changed changed) {
+    constexpr int NW = kVisAssign / 64;
+    const int tid = threadIdx.x, lane = tid % 64, Dv = dv.Dv, P = dv.P;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    for (int d = tid; d < Dv; d += kVisAssign) {
+        const double v = (double)src[d];
+        sh.e[d] = v;
+        dv.vemb[(size_t)f * Dv + d] = v;
+    }
+    __syncthreads();
+    double en = 0.0;
+    for (int d = lane; d < Dv; d += 64) en = __builtin_fma(sh.e[d], sh.e[d], en);
+    en = sqrt(wave_sum(en));
+    double bv = -INFINITY;
+    int bi = 0x7fffffff;
+    for (int p = wave; p < P; p += 2 * NW) {
+        const int p2 = p + NW < P ? p + NW : p;
+        const double *ra = dv.vr + (size_t)p * Dv, *rb = dv.vr + (size_t)p2 * Dv;
+        const int na = dv.vn[p], nb = p2 != p ? dv.vn[p2] : 0;
+        const double rna = dv.vrn[p], rnb = dv.vrn[p2];
+        double xa = 0.0, xb = 0.0;
+#pragma unroll 8
+        for (int d = lane; d < Dv; d += 64) { xa = __builtin_fma(sh.e[d], ra[d], xa); xb = __builtin_fma(sh.e[d], rb[d], xb); }
+        xa = wave_sum(xa);
+        xb = wave_sum(xb);
+        const double ca = (en == 0.0 || rna == 0.0) ? 0.0 : xa / (en * rna), cb = (en == 0.0 || rnb == 0.0) ? 0.0 : xb / (en * rnb);
+        if (na > 0 && ca > bv) { bv = ca; bi = p; }              // (ids ascend: a strict comparison keeps the lowest)
+        if (nb > 0 && cb > bv) { bv = cb; bi = p2; }
+    }
+    if (lane == 0) { sh.bv[wave] = bv; sh.bi[wave] = bi; }
+    __syncthreads();
+    bv = -INFINITY;
+    bi = 0x7fffffff;
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+        if (sh.bv[w] > bv || (sh.bv[w] == bv && sh.bi[w] < bi)) { bv = sh.bv[w]; bi = sh.bi[w]; }
+    const int a = bi == 0x7fffffff ? 0 : bi, na = dv.vn[a];
+    const double y = __ddiv_rn(1.0, (double)na + 1.0);
+    double sq = 0.0;
+    for (int d = tid; d < Dv; d += kVisAssign) {
+        const double x = eq3_channel((double)na, y, dv.vr[(size_t)a * Dv + d], sh.e[d]);
+        dv.vr[(size_t)a * Dv + d] = x;
+        sq = __builtin_fma(x, x, sq);
+    }
+    sq = block_sum<NW>(sq, sh.red);     // (its barriers also order the reads of vn[a] before the update)
+    if (tid == 0) {
+        const double norm = sqrt(sq);
+        dv.vrn[a] = norm;
+        dv.vn[a] = na + 1;
+        dv.part[f] = a;
+        changed(a, na + 1, norm);
+    }
+}
+
 // Frames f0..f1-1: partition = most similar non-empty visual centroid, which then moves by Eq. 3.  grid (1), kVisBlock
 // threads.  e_in: the fp32 embeddings of these frames as the caller passed them; the kernel also files them in the visual
 // level's state array.  The frames are taken up to sixteen at a time, as k_assign_chain does for the semantic level (which
 // says why the decisions are exact): products of the chunk with all centroids and with itself, the channels shared out
 // over the wavefronts; the decisions from those; Eq. 3 on the rows of the centroids that the chunk moved, a thread per
-// channel.  A frame that is too close to call opens a chunk and is decided by the full computation, a wavefront per
-// centroid.  (16 frames, P = 16, Dv = 1024: 90.5 -> 26 us against one frame at a time.)
+// channel.  Where a chunk begins with a frame that is too close to call, its frames are taken in turn.  (16 frames, P = 16, Dv = 1024: 90.5 -> 26 us against one frame at a time.)
 template <bool VEC>
 __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, const float *e_in, int f0, int f1) {
     constexpr int NW = kVisAssign / 64, FR = kChainFrames, kNone = 0x7fffffff;
@@ -187,7 +248,8 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, con
     __shared__ double part_sh[NW][256];
     __shared__ double sim_sh[FR * 64], gram_sh[FR][FR + 1], red[NW], irn_sh[64];
     __shared__ double ss_sh[FR], sn_sh[FR], isn_sh[FR], out_sh[FR], y_sh[FR];
-    __shared__ int vn_sh[64], slot_sh[64], lo_sh[FR], near_sh[FR], sure_sh[FR], w_sh[FR], p_sh[FR], slot_id[kChainSlots], n_slot_sh, nc_sh;
+    __shared__ VisualTurnShared turn_sh;
+    __shared__ int vn_sh[64], slot_sh[64], lo_sh[FR], near_sh[FR], sure_sh[FR], w_sh[FR], p_sh[FR], slot_id[kChainSlots], n_slot_sh, nc_sh, tied_sh;
     if (tid < 64) {
         const double rn = tid < P ? dv.vrn[tid] : 0.0;
         vn_sh[tid] = tid < P ? dv.vn[tid] : 0;
@@ -196,94 +258,94 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, con
         if (tid < FR) lo_sh[tid] = 0;
     }
     const int share = (Dv + 16 * NW - 1) / (16 * NW) * 16, ks = min(Dv, wave * share);
+    InTurn turn;
     for (int c0 = f0; c0 < f1;) {
         int nc = min(FR, f1 - c0);
         const float *e = e_in + (size_t)(c0 - f0) * Dv;
-        // ---- products ----
-        f64x4 acc[kVisTiles + 1];
-        visual_products<float, VEC, true>(dv, e, nc, ks, min(Dv, ks + share), acc);
+        bool in_turn = turn.left > 0;       // workgroup-uniform
+        if (in_turn) {
+            --turn.left;
+        } else {
+            // ---- products ----
+            f64x4 acc[kVisTiles + 1];
+            visual_products<float, VEC, true>(dv, e, nc, ks, min(Dv, ks + share), acc);
 #pragma unroll
-        for (int t = 0; t <= kVisTiles; ++t) {
-            if (t < kVisTiles && 16 * t >= P) continue;              // workgroup-uniform
-            __syncthreads();                // (the first one also orders the tables above and the chunk before)
+            for (int t = 0; t <= kVisTiles; ++t) {
+                if (t < kVisTiles && 16 * t >= P) continue;              // workgroup-uniform
+                __syncthreads();                // (the first one also orders the tables above and the chunk before)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) part_sh[wave][(4 * v + g) * 16 + n] = acc[t][v];
-            __syncthreads();
-            if (tid < 256) {
-                double x = 0.0;
+                for (int v = 0; v < 4; ++v) part_sh[wave][(4 * v + g) * 16 + n] = acc[t][v];
+                __syncthreads();
+                if (tid < 256) {
+                    double x = 0.0;
 #pragma unroll
-                for (int w = 0; w < NW; ++w) x += part_sh[w][tid];
-                const int f = tid / 16, c = tid % 16, p = 16 * t + c;
-                if (t == kVisTiles) gram_sh[f][c] = x;
-                else if (p < P) sim_sh[f * P + p] = vn_sh[p] > 0 ? x : -INFINITY;
-            }
-        }
-        __syncthreads();
-        if (wave == 0) {
-            const double ss = n < nc ? gram_sh[n][n] : 0.0, is = fast_rsqrt(ss);
-            double x[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) x[v] = gram_sh[4 * v + g][n] * is;
-            wave_sync();
-#pragma unroll
-            for (int v = 0; v < 4; ++v) gram_sh[4 * v + g][n] = x[v];
-            if (g == 0) { ss_sh[n] = ss; sn_sh[n] = ss * is; isn_sh[n] = is; }
-        }
-        __syncthreads();
-        for (int f = wave; f < nc; f += NW) {                    // the nearest centroid under the table as it stands
-            const double d = lane < P ? sim_sh[f * P + lane] : -INFINITY;
-            double c = d == -INFINITY ? d : d * isn_sh[f] * irn_sh[lane];
-            const bool odd = __ballot(!(c == c)) != 0;
-            if (!(c == c)) c = -INFINITY;
-            double bv = c;
-            int bi = c == -INFINITY ? kNone : lane;
-            wave_best_ascending(bv, bi);
-            const double second = wave_max(lane == bi ? -INFINITY : c);
-            if (lane == 0) { near_sh[f] = bi; out_sh[f] = second; sure_sh[f] = !odd && (bi == kNone || bv - second > kChainMargin); }
-        }
-        __syncthreads();
-        if (!sure_sh[0]) {                  // the first frame by the full computation (workgroup-uniform)
-            double en = 0.0;
-            for (int d = lane; d < Dv; d += 64) { const double v = (double)e[d]; en = __builtin_fma(v, v, en); }
-            en = sqrt(wave_sum(en));
-            for (int p = wave; p < P; p += NW) {
-                const double *rp = dv.vr + (size_t)p * Dv;
-                double x = 0.0;
-                for (int d = lane; d < Dv; d += 64) x = __builtin_fma((double)e[d], rp[d], x);
-                x = wave_sum(x);
-                const double rn = dv.vrn[p];
-                const double c = vn_sh[p] <= 0 ? -INFINITY : (en == 0.0 || rn == 0.0) ? 0.0 : x / (en * rn);
-                if (lane == 0) sim_sh[p] = c;
+                    for (int w = 0; w < NW; ++w) x += part_sh[w][tid];
+                    const int f = tid / 16, c = tid % 16, p = 16 * t + c;
+                    if (t == kVisTiles) gram_sh[f][c] = x;
+                    else if (p < P) sim_sh[f * P + p] = vn_sh[p] > 0 ? x : -INFINITY;
+                }
             }
             __syncthreads();
             if (wave == 0) {
-                double bv = lane < P ? sim_sh[lane] : -INFINITY;
-                if (!(bv == bv)) bv = -INFINITY;
-                int bi = bv == -INFINITY ? kNone : lane;
-                wave_best_ascending(bv, bi);
-                if (lane == 0) near_sh[0] = bi;
+                const double ss = n < nc ? gram_sh[n][n] : 0.0, is = fast_rsqrt(ss);
+                double x[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[v] = gram_sh[4 * v + g][n] * is;
+                wave_sync();
+#pragma unroll
+                for (int v = 0; v < 4; ++v) gram_sh[4 * v + g][n] = x[v];
+                if (g == 0) { ss_sh[n] = ss; sn_sh[n] = ss * is; isn_sh[n] = is; }
             }
             __syncthreads();
+            for (int f = wave; f < nc; f += NW) {                    // the nearest centroid under the table as it stands
+                const double d = lane < P ? sim_sh[f * P + lane] : -INFINITY;
+                double c = d == -INFINITY ? d : d * isn_sh[f] * irn_sh[lane];
+                const bool odd = __ballot(!(c == c)) != 0;
+                if (!(c == c)) c = -INFINITY;
+                double bv = c;
+                int bi = c == -INFINITY ? kNone : lane;
+                wave_best_ascending(bv, bi);
+                const double second = wave_max(lane == bi ? -INFINITY : c);
+                bool sure = bi != kNone && !odd && bv - second > kChainMargin;
+                if (ss_sh[f] == 0.0) {          // (wave-uniform) a zero embedding: similarity 0 with every live centroid, the lowest id
+                    const unsigned long long live = __ballot(lane < P && vn_sh[lane] > 0);
+                    bi = live ? __ffsll((long long)live) - 1 : kNone;
+                    sure = live != 0;
+                }
+                if (lane == 0) { near_sh[f] = bi; out_sh[f] = second; sure_sh[f] = sure; }
+            }
+            __syncthreads();
+            in_turn = !sure_sh[0];
+            if (in_turn) turn.failed();
+        }
+        if (in_turn) {
+            for (int fc = 0; fc < nc; ++fc) {
+                visual_in_turn(dv, e + (size_t)fc * Dv, c0 + fc, turn_sh, [&](int a, int size, double norm) {
+                    vn_sh[a] = size;
+                    irn_sh[a] = norm > 0.0 ? 1.0 / norm : 0.0;
+                });
+                __syncthreads();
+            }
+            c0 += nc;
+            continue;
         }
         // ---- decisions ----
         if (wave == 0) {
-            const int lim = !sure_sh[0] || near_sh[0] == kNone ? 1 : nc;
-            int mine = lane < lim ? near_sh[lane] : -1;
-            if (mine == kNone) mine = 0;
+            int mine = lane < nc ? near_sh[lane] : -1;
+            if (mine == kNone) mine = -1;   // (no live candidate: the chunk ends before the frame)
             unsigned long long left = __ballot(mine >= 0);
             int k = 0;
-            while (left && k < kChainSlots) {
+            while (left) {
                 const int id = __builtin_amdgcn_readlane(mine, __ffsll((long long)left) - 1);
                 if (lane == 0) { slot_id[k] = id; slot_sh[id] = k; }
                 left &= ~__ballot(mine == id);
                 ++k;
             }
             wave_sync();
-            const int n_dec = left ? __ffsll((long long)left) - 1 : lim;
-            int w = n < n_dec ? slot_sh[near_sh[n] == kNone ? 0 : near_sh[n]] : -1;
-            int done = n_dec;
-            if (n_dec > 1)
-                done = chain_decide({sim_sh, P, lo_sh, sn_sh, isn_sh, ss_sh, out_sh, gram_sh, slot_id, vn_sh, irn_sh}, n_dec, k, w);
+            int w = n < nc && near_sh[n] != kNone ? slot_sh[near_sh[n]] : -1;
+            bool tied;
+            const int done =
+                chain_decide({sim_sh, P, lo_sh, sn_sh, isn_sh, ss_sh, out_sh, gram_sh, slot_id, vn_sh, irn_sh}, nc, k, w, tied);
             if (lane < done) {
                 const int id = slot_id[w];
                 int p = vn_sh[id];
@@ -294,10 +356,12 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, con
                 y_sh[lane] = __ddiv_rn(1.0, (double)p + 1.0);
                 dv.part[c0 + lane] = id;
             }
-            if (lane == 0) { nc_sh = done; n_slot_sh = k; }
+            if (lane == 0) { nc_sh = done; n_slot_sh = k; tied_sh = tied; }
         }
         __syncthreads();
         nc = nc_sh;
+        if (tied_sh) turn.failed();
+        else turn.held();
         const int n_slot = n_slot_sh;
         // ---- Eq. 3 on the rows; the frames' states ----
         for (int k = 0; k < n_slot; ++k) {
@@ -340,63 +404,14 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, con
     }
 }
 
-// The same for calls of at most kVisFew frames, one after the other by the full computation: per frame the embedding is
-// staged in LDS, a wavefront scores two centroids at a time (their rows' loads in flight together), all threads update
-// the winner's row.  The chunk form's products, reductions and check cost 4 us more for one frame (P = 10, Dv = 512,
-// C = 120, whole call 16.6 against 12.2 us).  Same operations in the same order as its full computation and its update.
+// The same for calls of at most kVisFew frames, all of them in turn.  The chunk form's products, reductions and check cost 4
+// us more for one frame (P = 10, Dv = 512, C = 120, whole call 16.6 against 12.2 us).
 constexpr int kVisFew = 2;
 __global__ __launch_bounds__(kVisAssign) void k_visual_assign_few(DeviceView dv, const float *e_in, int f0, int f1) {
-    constexpr int NW = kVisAssign / 64;
-    const int tid = threadIdx.x, lane = tid % 64, Dv = dv.Dv, P = dv.P;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-    __shared__ double e_sh[4096];
-    __shared__ double red[NW], bv_sh[NW];
-    __shared__ int bi_sh[NW];
+    __shared__ VisualTurnShared sh;
     for (int f = f0; f < f1; ++f) {
-        const float *src = e_in + (size_t)(f - f0) * Dv;
-        for (int d = tid; d < Dv; d += kVisAssign) {
-            const double v = (double)src[d];
-            e_sh[d] = v;
-            dv.vemb[(size_t)f * Dv + d] = v;
-        }
-        __syncthreads();
-        double en = 0.0;
-        for (int d = lane; d < Dv; d += 64) en = __builtin_fma(e_sh[d], e_sh[d], en);
-        en = sqrt(wave_sum(en));
-        double bv = -INFINITY;
-        int bi = 0x7fffffff;
-        for (int p = wave; p < P; p += 2 * NW) {
-            const int p2 = p + NW < P ? p + NW : p;
-            const double *ra = dv.vr + (size_t)p * Dv, *rb = dv.vr + (size_t)p2 * Dv;
-            const int na = dv.vn[p], nb = p2 != p ? dv.vn[p2] : 0;
-            const double rna = dv.vrn[p], rnb = dv.vrn[p2];
-            double xa = 0.0, xb = 0.0;
-#pragma unroll 8
-            for (int d = lane; d < Dv; d += 64) { xa = __builtin_fma(e_sh[d], ra[d], xa); xb = __builtin_fma(e_sh[d], rb[d], xb); }
-            xa = wave_sum(xa);
-            xb = wave_sum(xb);
-            const double ca = (en == 0.0 || rna == 0.0) ? 0.0 : xa / (en * rna), cb = (en == 0.0 || rnb == 0.0) ? 0.0 : xb / (en * rnb);
-            if (na > 0 && ca > bv) { bv = ca; bi = p; }              // (ids ascend: a strict comparison keeps the lowest)
-            if (nb > 0 && cb > bv) { bv = cb; bi = p2; }
-        }
-        if (lane == 0) { bv_sh[wave] = bv; bi_sh[wave] = bi; }
-        __syncthreads();
-        bv = -INFINITY;
-        bi = 0x7fffffff;
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-            if (bv_sh[w] > bv || (bv_sh[w] == bv && bi_sh[w] < bi)) { bv = bv_sh[w]; bi = bi_sh[w]; }
-        const int a = bi == 0x7fffffff ? 0 : bi, na = dv.vn[a];
-        const double y = __ddiv_rn(1.0, (double)na + 1.0);
-        double sq = 0.0;
-        for (int d = tid; d < Dv; d += kVisAssign) {
-            const double x = eq3_channel((double)na, y, dv.vr[(size_t)a * Dv + d], e_sh[d]);
-            dv.vr[(size_t)a * Dv + d] = x;
-            sq = __builtin_fma(x, x, sq);
-        }
-        sq = block_sum<NW>(sq, red);     // (its barriers also order the reads of vn[a] before the update)
-        if (tid == 0) { dv.vrn[a] = sqrt(sq); dv.vn[a] = na + 1; dv.part[f] = a; }
-        if (f + 1 < f1) __syncthreads();
+        if (f > f0) __syncthreads();
+        visual_in_turn(dv, e_in + (size_t)(f - f0) * dv.Dv, f, sh, [](int, int, double) {});
     }
 }
 

@@ -252,28 +252,68 @@ def test_batched_assignment_at_ties_equals_single_frame_calls_bitwise(C, D, kind
 
 # Ties that only the last bit of a norm decides, whatever kernel wrote it: a few directions, every frame a multiple of one
 # of them, so that several clusters lie along each and a frame's best similarities differ by rounding or not at all; ids on
-# both sides of a register kernel's first pass, tables of every kernel family and of shortened chunks (C > 512).
-@pytest.mark.parametrize("C,D", [(40, 64), (128, 128), (200, 128), (250, 64), (300, 128), (600, 64), (600, 128), (1024, 128)])
-def test_last_bit_ties_do_not_depend_on_the_split_into_calls(C, D):
-    U, T, W = 16, 4, 2 * C
+# both sides of a register kernel's first pass, tables of every kernel family and of shortened chunks (C > 512), the
+# nested index; and some frames whose summary is zero, which tie with every cluster.
+@pytest.mark.parametrize("C,D,P", [(40, 64, 0), (128, 128, 0), (200, 128, 0), (250, 64, 0), (300, 128, 0), (600, 64, 0),
+                                   (600, 128, 0), (1024, 128, 0), (48, 128, 6), (510, 64, 15)])
+def test_last_bit_ties_do_not_depend_on_the_split_into_calls(C, D, P):
+    U, T, W, Dv = 16, 4, 2 * C, 32
     F = W + (400 if C < 500 else 150)
     rng = np.random.default_rng(C + D)
     few = rng.integers(-3, 4, (6, U, T, D)).astype(np.float32)
     x = few[rng.integers(0, 6, F)] * rng.integers(1, 4, (F, 1, 1, 1)).astype(np.float32)
+    x[W + 200:] *= rng.integers(0, 6, (F - W, U, 1, 1))[200:] > 0
     K = torch.tensor(x[:, None]).to(DEV)
+    E = torch.tensor(rng.standard_normal((F, Dv)).astype(np.float32)).to(DEV)
     cfg = dict(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T, max_frames=F, n_clusters=C, top_k=1,
-               kv_dtype="fp32", lloyd_iters=2)
+               kv_dtype="fp32", lloyd_iters=2, **(dict(n_partitions=P, visual_dim=Dv) if P else {}))
     states = []
     for per in (1, 2, 4, 5, 16, 64):
         m = binding.Mosaic(binding.make_config(**cfg))
-        m.ingest_frame(K[:W], K[:W])
-        for f in range(W, F, per):
-            m.ingest_frame(K[f:f + per], K[f:f + per])
-        states.append((m.assignments(), *m.centroids()))
+        for f, n in [(0, W)] + [(f, min(per, F - f)) for f in range(W, F, per)]:
+            if P:
+                m.ingest_frame_visual(K[f:f + n], K[f:f + n], E[f:f + n])
+            else:
+                m.ingest_frame(K[f:f + n], K[f:f + n])
+        states.append((m.assignments(), *m.centroids()) + ((m.partitions()["part_r"],) if P else ()))
         m.close()
     for other in states[1:]:
         for a, b in zip(states[0], other):
             np.testing.assert_array_equal(a, b)
+
+
+# Frames that the batched assignment cannot decide from its products cost about what a frame costs by itself, not a pass
+# over the products each: summaries that are zero (which it does decide), and clusters along a few directions.  Against
+# streams without ties they take 0.5 and 1.5 times as long; a pass for each frame makes that 6 and 5 times.
+@pytest.mark.parametrize("kind,most", [("zeros", 2.0), ("repeats", 3.0)])
+def test_tied_streams_are_not_much_slower(kind, most):
+    C, U, T, D, per = 200, 16, 4, 128, 16
+    W, F = 2 * C, 2 * C + 640
+    g = torch.Generator().manual_seed(5)
+    few = torch.randint(-3, 4, (6, 1, U, T, D), generator=g).float()
+    tied = few[torch.randint(0, 6, (F,), generator=g)] * torch.randint(1, 4, (F, 1, 1, 1, 1), generator=g)
+    plain = torch.randn((F // 16 + 1, 1, U, 1, D), generator=g)[torch.arange(F) // 16] + 0.4 * torch.randn((F, 1, U, T, D), generator=g)
+    if kind == "zeros":
+        tied = torch.cat([plain[:W], torch.zeros((F - W, 1, U, T, D))])
+    m = binding.Mosaic(binding.make_config(n_layers=1, n_q_heads=U, n_kv_heads=U, head_dim=D, tokens_per_frame=T, max_frames=F,
+                                           n_clusters=C, top_k=1, kv_dtype="fp32", lloyd_iters=1))
+    best = []
+    for x in (plain, tied):
+        K, t = x.to(DEV), []
+        for _ in range(5):
+            m.reset()
+            m.ingest_frame(K[:W], K[:W])
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            for f in range(W, F, per):
+                m.ingest_frame(K[f:f + per], K[f:f + per])
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b))
+        best.append(min(t))
+    m.close()
+    assert best[1] <= most * best[0], best
 
 
 # The visual level's last-bit ties: embeddings that are multiples of a few, partitions that lie along one direction.
