@@ -253,10 +253,10 @@ __device__ __forceinline__ void combine_store(const DeviceView &dv, int u, int l
         lse[orow] = Xr > 0.f ? (Mr + log2f(Xr)) * 0.6931471805599453f : -INFINITY;
 }
 
-// Merge of the per-split partials (log-sum-exp weights), normalisation, output.
-// grid (D/32, NT, n_units), 256 threads.  A workgroup owns 32 output channels of
-// one row tile; its 8 groups of 32 threads share the splits, so the partial
-// buffer is read with many independent 128-byte loads in flight.
+// Merge of the per-split partials (log-sum-exp weights), normalisation, output, for one
+// row tile (a decode step).  grid (D/32 * RS, n_units), 256 threads.  A workgroup owns 32
+// output channels; its 8 groups of 32 threads share the splits, so the partial buffer is
+// read with many independent 128-byte loads in flight.
 template <typename E, int D>
 __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0, int n_units, int Tq,
                                                            int B, int uniform_S, E *out, float *lse) {
@@ -265,10 +265,9 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
     // workgroups each thread reads half as much, all of it in one pass)
     constexpr int DG = D / 32;
     const int dg = blockIdx.x % DG, rs = blockIdx.x / DG, RS = gridDim.x / DG;
-    const int tile = blockIdx.y, uc = blockIdx.z, u = u0 + uc, NT = gridDim.y;
+    const int uc = blockIdx.y, u = u0 + uc;
     const int tid = threadIdx.x;
-    const int G = dv.G, Hq = dv.Hq, lc = uc / dv.Hkv, h = u % dv.Hkv, R = Tq * G;
-    const int rows = min(kRowTile, R - tile * kRowTile);
+    const int lc = uc / dv.Hkv, h = u % dv.Hkv, rows = Tq * dv.G;
     const int rper = (rows + RS - 1) / RS, rbase = rs * rper, nr = min(rper, rows - rbase);
     if (nr <= 0) return;                         // block-uniform: no barrier reached yet
     // uniform_S > 0: every unit has exactly that many splits (the fused decode step); else the
@@ -276,7 +275,7 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
     SplitSlot slot{uc, 0, uniform_S, uc * uniform_S, 0};
     if (uniform_S <= 0) slot = split_slot<true>(dv.n_sel + u0, n_units, B, uc);
     const int n_splits = slot.S;                 // 0 if the unit retrieved nothing
-    const size_t e0 = (size_t)slot.base * NT + (size_t)tile * n_splits;
+    const size_t e0 = (size_t)slot.base;
     __shared__ float w_sh[kMaxUnitSplits][kRowTile];
     __shared__ float pm[16][kRowTile], pl[16][kRowTile], px[16][kRowTile];
     __shared__ float M_sh[kRowTile], L_sh[kRowTile], X_sh[kRowTile];
@@ -321,7 +320,7 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
         float o = 0.f;
 #pragma unroll
         for (int q = 0; q < 8; ++q) o += red[q][rl][col];
-        combine_store<E, D>(dv, u, lc, h, tile, r, dg, col, Tq, o, L_sh[r], X_sh[r], M_sh[r], out, lse);
+        combine_store<E, D>(dv, u, lc, h, 0, r, dg, col, Tq, o, L_sh[r], X_sh[r], M_sh[r], out, lse);
     }
 }
 
@@ -436,8 +435,8 @@ hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int 
     // One row tile (a decode step) of a few units: up to eight workgroups share a tile's rows, as long as the launch
     // stays within about two workgroups per CU (per-layer launch of config 2: 1075 -> 1048 / 1033 / 1027 us per step
     // with 2 / 4 / 8; the all-layers launch, 112 units, is left alone: 542 -> 562 us with 8).
-    const int RS = NT == 1 ? std::max(1, std::min(8, 512 / (n_units * (dv.D / 32)))) : 1;
-    dim3 grid(dv.D / 32 * RS, NT, n_units);
+    const int RS = std::max(1, std::min(8, 512 / (n_units * (dv.D / 32))));
+    const dim3 grid(dv.D / 32 * RS, n_units);
     if (dv.esize == 4) {
         if (dv.D == 64) k_attend_combine<float, 64><<<grid, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, us, (float *)out, lse);
         else k_attend_combine<float, 128><<<grid, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, us, (float *)out, lse);
