@@ -896,16 +896,68 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
 // ---------------------------------------------------------------------------
 constexpr int kRegFrames = 4;
 
+// Of this kernel and the one-frame kernel, whose 16-lane groups hold the table's rows in registers (rr[i]: row group + NG i).
+// Dot products of the summary (sl: this lane's channels) with the rows, into dot, four rows at a time written out side by
+// side: four independent multiply-add chains, then their 16-lane reductions step by step in lockstep, so that one chain's
+// latency is filled by the other three (a loop over the rows with the block-uniform test per row kept every row's chain in
+// a basic block of its own: 2100 cycles per frame for 210 instructions).  Rows beyond the table or of empty clusters give
+// values nobody reads.  The group also forms |s| from its own share of the channels, the same bits in every group.
+template <int EPL, int NG, int RPG>
+__device__ __forceinline__ double held_products(const double (&sl)[EPL], const double (&rr)[RPG][EPL], int C, double *dot) {
+    const int lr = threadIdx.x % 16, grp = threadIdx.x / 16;
+    double ssq = 0.0;
+#pragma unroll
+    for (int h = 0; h < RPG / 4; ++h) {
+        if (h > 0 && NG * 4 * h >= C) break;                  // block-uniform: passes beyond the table
+        double p[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] = __builtin_fma(sl[e], rr[4 * h + k][e], p[k]);
+            if (h == 0) ssq = square_step<EPL>(ssq, sl, e, true);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor8>(p[k]);
+        if (h == 0) ssq += dpp_f64<kDppXor8>(ssq);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor7>(p[k]);
+        if (h == 0) ssq += dpp_f64<kDppXor7>(ssq);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor3>(p[k]);
+        if (h == 0) ssq += dpp_f64<kDppXor3>(ssq);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor1>(p[k]);
+        if (h == 0) ssq += dpp_f64<kDppXor1>(ssq);
+        if (lr == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dot[grp + NG * (4 * h + k)] = p[k];
+        }
+    }
+    return sqrt(ssq);
+}
+// The most similar candidate of each wavefront, ties to the lowest id (at most one candidate per thread: ids lo + thread)
+__device__ __forceinline__ void held_nearest(int lo, int hi, const int *size, const double *norm, const double *dot, double sn,
+                                             double *best_v, int *best_i) {
+    const int j = lo + threadIdx.x;
+    double bv = -INFINITY;
+    int bi = 0x7fffffff;
+    if (j < hi && size[j] > 0) {
+        bv = (sn == 0.0 || norm[j] == 0.0) ? 0.0 : dot[j] / (sn * norm[j]);
+        bi = j;
+    }
+    wave_best_ascending(bv, bi);
+    if (threadIdx.x % 64 == 0) { best_v[threadIdx.x / 64] = bv; best_i[threadIdx.x / 64] = bi; }
+}
+
 template <int D, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, int f0, int f1) {
     constexpr int EPL = D / 16, NG = THREADS / 16, RPG = 8, NW = THREADS / 64, ROWS = NG * RPG;
-    constexpr int CHUNK = kRegFrames;           // frames whose summaries are staged in LDS at a time
     const int u = blockIdx.x, tid = threadIdx.x, C = dv.C;
     const int lr = tid % 16, grp = tid / 16, wave = tid / 64, lane = tid % 64;
-    __shared__ __attribute__((aligned(16))) double s_sh[CHUNK][D];
+    __shared__ __attribute__((aligned(16))) double s_sh[kRegFrames][D];
     __shared__ double dot_sh[ROWS], rn_sh[ROWS];
     __shared__ int n_sh[ROWS];
-    __shared__ int a_out[CHUNK], p_out[CHUNK];
+    __shared__ int a_out[kRegFrames], p_out[kRegFrames];
     __shared__ int chg_sh[ROWS];                // 1 = the cluster's size and norm changed in this call
     __shared__ double red_v[NW];
     __shared__ int red_i[NW];
@@ -930,9 +982,8 @@ __global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, in
     }
     const bool nested = dv.P > 0;
     // The barriers inside the frame loop order LDS traffic only, and the loop touches no global memory: the
-    // call's summaries are staged in LDS a chunk at a time, the winner's row stays in registers and is written
-    // back once after the last frame, sizes and norms live in LDS, the frames' ids and ranks collect in LDS until
-    // the chunk ends.  A full __syncthreads() waits for every outstanding global access of the wavefront, and so
+    // call's summaries are staged in LDS, the winner's row stays in registers and is written back once after the last
+    // frame, sizes and norms live in LDS, the frames' ids and ranks collect in LDS until the end.  A full __syncthreads() waits for every outstanding global access of the wavefront, and so
     // does any wait the compiler places for a register a load is still to fill: with the next frame's summary
     // fetched inside the loop and the winner's row written through in every frame, each frame waited once for
     // that load, issued a moment before, and once for the store's acknowledgement.  The nested hierarchy's
@@ -945,142 +996,95 @@ __global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, in
     unsigned int dirty = 0;                   // bit i: this group's row i changed in this call
     // a one-frame call is all latency: its results go straight to memory, with no collection and no write-back pass
     const bool single = f1 - f0 == 1;
-    for (int c0 = f0; c0 < f1; c0 += CHUNK) {
-        const int nc = min(CHUNK, f1 - c0);
-        {
-            const double *src = dv.summ + ((size_t)u * dv.F + c0) * D;
-            for (int i = tid; i < nc * D / 2; i += THREADS)
-                *reinterpret_cast<double2 *>(&s_sh[0][0] + 2 * i) = *reinterpret_cast<const double2 *>(src + 2 * i);
+    {
+        const double *src = dv.summ + ((size_t)u * dv.F + f0) * D;
+        for (int i = tid; i < (f1 - f0) * D / 2; i += THREADS)
+            *reinterpret_cast<double2 *>(&s_sh[0][0] + 2 * i) = *reinterpret_cast<const double2 *>(src + 2 * i);
+    }
+    __syncthreads();
+    for (int fc = 0; fc < f1 - f0; ++fc) {
+        const int f = f0 + fc;
+        const double *sv = s_sh[fc];
+        const int part_f = nested ? dv.part[f] : 0;
+        const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : C;
+        double sl[EPL];
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) sl[e] = sv[lr * EPL + e];
+        const double sn = held_products<EPL, NG>(sl, rr, C, dot_sh);
+        frame_barrier();
+        // argmax of the cosine over the candidates, ties to the lowest id (THREADS >= C: at
+        // most one candidate per thread)
+        held_nearest(lo, hi, n_sh, rn_sh, dot_sh, sn, red_v, red_i);
+        // nested hierarchy: the partition's representative follows the same running mean
+        int pn_i = 0;
+        if (nested) {
+            double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
+            pn_i = dv.pn[(size_t)u * dv.P + part_f];
+            double pv = 0.0;
+            if (tid < D) {
+                pv = eq3_channel((double)pn_i, __ddiv_rn(1.0, (double)pn_i + 1.0), prow[tid], sv[tid]);
+                prow[tid] = pv;
+            }
+            if (wave < 2) {
+                const double psq = wave_square_sum(pv);
+                if (lane == 0) psum_sh[wave] = psq;
+            }
         }
-        __syncthreads();
-        for (int fc = 0; fc < nc; ++fc) {
-            const int f = c0 + fc;
-            const double *sv = s_sh[fc];
-            const int part_f = nested ? dv.part[f] : 0;
-            const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : C;
-            // Dot products of the summary with the rows the group holds, four rows at a time written out side by
-            // side: four independent multiply-add chains, then their 16-lane reductions step by step in lockstep,
-            // so that one chain's latency is filled by the other three (a loop over the rows with the block-uniform
-            // test per row kept every row's chain in a basic block of its own: 2100 cycles per frame for 210
-            // instructions).  Rows beyond the table or of empty clusters give values nobody reads.  The group also
-            // forms |s|^2 from its own share of the channels, the same bits in every group.
-            double sl[EPL];
+        frame_barrier();
+        // every thread merges the wavefronts' winners itself (no second barrier for one thread's merge)
+        double bv = red_v[0];
+        int bi = red_i[0];
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) sl[e] = sv[lr * EPL + e];
-            double ssq = 0.0;
+        for (int w = 1; w < NW; ++w)
+            if (better(red_v[w], red_i[w], bv, bi)) { bv = red_v[w]; bi = red_i[w]; }
+        const int a = bi == 0x7fffffff ? lo : bi;
+        const int ai = __builtin_amdgcn_readfirstlane(a / NG);      // workgroup-uniform: a scalar
+        if (grp == a % NG) {                                  // the group that holds row a
+            const int na_i = n_sh[a];
+            const double na = (double)na_i;
+            const double ny = __ddiv_rn(1.0, na + 1.0);
+            double sq = 0.0;
 #pragma unroll
-            for (int h = 0; h < RPG / 4; ++h) {
-                if (h > 0 && NG * 4 * h >= C) break;                  // block-uniform: passes beyond the table
-                double p[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int i = 0; i < RPG; ++i) {
+                if (i == ai) {                                // scalar branch: one pass runs
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) p[k] = __builtin_fma(sl[e], rr[4 * h + k][e], p[k]);
-                    if (h == 0) ssq = square_step<EPL>(ssq, sl, e, true);
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor8>(p[k]);
-                if (h == 0) ssq += dpp_f64<kDppXor8>(ssq);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor7>(p[k]);
-                if (h == 0) ssq += dpp_f64<kDppXor7>(ssq);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor3>(p[k]);
-                if (h == 0) ssq += dpp_f64<kDppXor3>(ssq);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor1>(p[k]);
-                if (h == 0) ssq += dpp_f64<kDppXor1>(ssq);
-                if (lr == 0) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) dot_sh[grp + NG * (4 * h + k)] = p[k];
-                }
-            }
-            const double sn = sqrt(ssq);
-            frame_barrier();
-            // argmax of the cosine over the candidates, ties to the lowest id (THREADS >= C: at
-            // most one candidate per thread)
-            double bv = -INFINITY;
-            int bi = 0x7fffffff;
-            {
-                const int j = lo + tid;
-                if (j < hi && n_sh[j] > 0) {
-                    bv = (sn == 0.0 || rn_sh[j] == 0.0) ? 0.0 : dot_sh[j] / (sn * rn_sh[j]);
-                    bi = j;
-                }
-            }
-            wave_best_ascending(bv, bi);        // (ids ascend with the thread: j = lo + tid)
-            if (lane == 0) { red_v[wave] = bv; red_i[wave] = bi; }
-            // nested hierarchy: the partition's representative follows the same running mean
-            int pn_i = 0;
-            if (nested) {
-                double *prow = dv.pr + ((size_t)u * dv.P + part_f) * D;
-                pn_i = dv.pn[(size_t)u * dv.P + part_f];
-                double pv = 0.0;
-                if (tid < D) {
-                    pv = eq3_channel((double)pn_i, __ddiv_rn(1.0, (double)pn_i + 1.0), prow[tid], sv[tid]);
-                    prow[tid] = pv;
-                }
-                if (wave < 2) {
-                    const double psq = wave_square_sum(pv);
-                    if (lane == 0) psum_sh[wave] = psq;
-                }
-            }
-            frame_barrier();
-            // every thread merges the wavefronts' winners itself (no second barrier for one thread's merge)
-            bv = red_v[0]; bi = red_i[0];
-#pragma unroll
-            for (int w = 1; w < NW; ++w)
-                if (better(red_v[w], red_i[w], bv, bi)) { bv = red_v[w]; bi = red_i[w]; }
-            const int a = bi == 0x7fffffff ? lo : bi;
-            const int ai = __builtin_amdgcn_readfirstlane(a / NG);      // workgroup-uniform: a scalar
-            if (grp == a % NG) {                                  // the group that holds row a
-                const int na_i = n_sh[a];
-                const double na = (double)na_i;
-                const double ny = __ddiv_rn(1.0, na + 1.0);
-                double sq = 0.0;
-#pragma unroll
-                for (int i = 0; i < RPG; ++i) {
-                    if (i == ai) {                                // scalar branch: one pass runs
-#pragma unroll
-                        for (int e = 0; e < EPL; ++e) {
-                            const double rv = eq3_channel(na, ny, rr[i][e], sl[e]);
-                            rr[i][e] = rv;
-                            if (single) r[(size_t)a * D + lr * EPL + e] = rv;
-                        }
-                        sq = square_channels(rr[i], i == 0);                      // (row_second_first: a < NG)
+                    for (int e = 0; e < EPL; ++e) {
+                        const double rv = eq3_channel(na, ny, rr[i][e], sl[e]);
+                        rr[i][e] = rv;
+                        if (single) r[(size_t)a * D + lr * EPL + e] = rv;
                     }
-                }
-                if (!single) dirty |= 1u << ai;
-                sq = row16_sum(sq);
-                if (lr == 0) {
-                    const double nr = sqrt(sq);
-                    if (single) {
-                        dv.rnorm[(size_t)u * C + a] = nr;
-                        dv.n[(size_t)u * C + a] = na_i + 1;
-                        dv.assign[(size_t)u * dv.F + f] = a;
-                        dv.pos[(size_t)u * dv.F + f] = na_i;
-                    } else {
-                        rn_sh[a] = nr;
-                        n_sh[a] = na_i + 1;
-                        chg_sh[a] = 1;
-                        a_out[fc] = a;
-                        p_out[fc] = na_i;
-                    }
+                    sq = square_channels(rr[i], i == 0);                      // (row_second_first: a < NG)
                 }
             }
-            if (nested && tid == 0) {
-                dv.prn[(size_t)u * dv.P + part_f] = sqrt(D > 64 ? psum_sh[0] + psum_sh[1] : psum_sh[0]);
-                dv.pn[(size_t)u * dv.P + part_f] = pn_i + 1;
+            if (!single) dirty |= 1u << ai;
+            sq = row16_sum(sq);
+            if (lr == 0) {
+                const double nr = sqrt(sq);
+                if (single) {
+                    dv.rnorm[(size_t)u * C + a] = nr;
+                    dv.n[(size_t)u * C + a] = na_i + 1;
+                    dv.assign[(size_t)u * dv.F + f] = a;
+                    dv.pos[(size_t)u * dv.F + f] = na_i;
+                } else {
+                    rn_sh[a] = nr;
+                    n_sh[a] = na_i + 1;
+                    chg_sh[a] = 1;
+                    a_out[fc] = a;
+                    p_out[fc] = na_i;
+                }
             }
-            if (single) return;                   // workgroup-uniform: nothing follows the only frame
-            frame_barrier();
         }
-        // the chunk's ids and ranks (the barrier that ended its last frame made them visible)
-        if (tid < nc) {
-            dv.assign[(size_t)u * dv.F + c0 + tid] = a_out[tid];
-            dv.pos[(size_t)u * dv.F + c0 + tid] = p_out[tid];
+        if (nested && tid == 0) {
+            dv.prn[(size_t)u * dv.P + part_f] = sqrt(D > 64 ? psum_sh[0] + psum_sh[1] : psum_sh[0]);
+            dv.pn[(size_t)u * dv.P + part_f] = pn_i + 1;
         }
-        __syncthreads();                          // before the next chunk overwrites the staged summaries
+        if (single) return;                   // workgroup-uniform: nothing follows the only frame
+        frame_barrier();
+    }
+    // the frames' ids and ranks (the barrier that ended the last one made them visible)
+    if (tid < f1 - f0) {
+        dv.assign[(size_t)u * dv.F + f0 + tid] = a_out[tid];
+        dv.pos[(size_t)u * dv.F + f0 + tid] = p_out[tid];
     }
     // write back what changed: rows, sizes and norms
 #pragma unroll
@@ -1142,55 +1146,13 @@ __global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k
     const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : C;
     store_key_page<E, D>(dv, k_in, dv.k_store, u, 0, f, red, s_sh);
     __syncthreads();
-    // Dot products of the summary with the rows the group holds, four rows at a time written out side by side: four
-    // independent multiply-add chains, then their 16-lane reductions step by step in lockstep, so that one chain's
-    // latency is filled by the other three.  Rows beyond the table or of empty clusters give values nobody reads.  The
-    // group also forms |s|^2 from its own share of the channels, the same bits in every group.
     double sl[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) sl[e] = s_sh[lr * EPL + e];
-    double ssq = 0.0;
-#pragma unroll
-    for (int h = 0; h < RPG / 4; ++h) {
-        if (h > 0 && NG * 4 * h >= C) break;                  // block-uniform: passes beyond the table
-        double p[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) p[k] = __builtin_fma(sl[e], rr[4 * h + k][e], p[k]);
-            if (h == 0) ssq = square_step<EPL>(ssq, sl, e, true);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor8>(p[k]);
-        if (h == 0) ssq += dpp_f64<kDppXor8>(ssq);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor7>(p[k]);
-        if (h == 0) ssq += dpp_f64<kDppXor7>(ssq);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor3>(p[k]);
-        if (h == 0) ssq += dpp_f64<kDppXor3>(ssq);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) p[k] += dpp_f64<kDppXor1>(p[k]);
-        if (h == 0) ssq += dpp_f64<kDppXor1>(ssq);
-        if (lr == 0) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) dot_sh[grp + NG * (4 * h + k)] = p[k];
-        }
-    }
-    const double sn = sqrt(ssq);
+    const double sn = held_products<EPL, NG>(sl, rr, C, dot_sh);
     __syncthreads();
     // argmax of the cosine over the candidates, ties to the lowest id (at most one candidate per thread)
-    double bv = -INFINITY;
-    int bi = 0x7fffffff;
-    {
-        const int j = lo + tid;
-        if (j < hi && n_sh[j] > 0) {
-            bv = (sn == 0.0 || rn_sh[j] == 0.0) ? 0.0 : dot_sh[j] / (sn * rn_sh[j]);
-            bi = j;
-        }
-    }
-    wave_best_ascending(bv, bi);        // (ids ascend with the thread: j = lo + tid)
-    if (lane == 0) { red_v[wave] = bv; red_i[wave] = bi; }
+    held_nearest(lo, hi, n_sh, rn_sh, dot_sh, sn, red_v, red_i);
     // nested hierarchy: the partition's representative in this unit's key space follows the same running mean
     int pn_i = 0;
     if (nested) {
@@ -1208,7 +1170,8 @@ __global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k
     }
     __syncthreads();
     // every thread merges the wavefronts' winners itself (no second barrier for one thread's merge)
-    bv = red_v[0]; bi = red_i[0];
+    double bv = red_v[0];
+    int bi = red_i[0];
 #pragma unroll
     for (int w = 1; w < NW; ++w)
         if (better(red_v[w], red_i[w], bv, bi)) { bv = red_v[w]; bi = red_i[w]; }
