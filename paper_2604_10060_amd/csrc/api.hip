@@ -701,9 +701,9 @@ static int offload_range(mosaic_ctx *ctx, int f0, int f1) {
         if ((e = hipEventSynchronize(ht->off_done[p])) != hipSuccess) return fail_hip(ctx, e, "hipEventSynchronize(offload)");
         ht->off_used[p] = false;
     }
-    // One kernel that stores them to pinned memory, and one wait: the link idles from here until the next offload kernel starts.  (A wait, a copy per unit, a
-    // second wait and the table's upload through the caller's stream took 150 us per batch of 16 frames and 8 units, half
-    // as long as the offload itself.)
+    // One kernel that stores the assignments to pinned memory, and one wait: the link idles from here until the next offload
+    // kernel starts.  (A wait, a copy per unit, a second wait and the table's upload through the caller's stream took 150 us
+    // per batch of 16 frames and 8 units, half as long as the offload itself.)
     if ((e = launch_gather_assign(dv, f0, n, ctx->stream)) != hipSuccess) return fail_hip(ctx, e, "assignment read-back");
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return fail_hip(ctx, e, "hipStreamSynchronize");
     for (int fl = 0; fl < n; ++fl)

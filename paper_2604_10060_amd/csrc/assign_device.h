@@ -161,8 +161,17 @@ __device__ __forceinline__ double add_members(double acc, const int *mem, int m,
     return acc;
 }
 
-constexpr int kChainFrames = 16, kChainSlots = 16;
+constexpr int kChainFrames = 16;
 constexpr double kChainMargin = 1e-11;          // in the cosine
+// How far the difference of two carried-over cosines can be from that of the full computation; N: the longest chain of
+// additions in a product of a chunk's products with the rows.  With u = 2^-53, v_0 = n r and v_i the frames that joined it:
+// a product is off by at most (N + 1) u |v_i| |x|, and with what scales and adds up to 17 of them the numerator by
+// (N + 22) u |x| sum |v_i|.  Every v_i joined at no more than a right angle (chain_decide stops after a winner that did
+// not), so |sum v_i|^2 >= sum |v_i|^2 and sum |v_i| <= sqrt(17) |sum v_i|: numerators are off by sqrt(17) (N + 22) u, squared
+// lengths by 17 (N + 22) u, cosines by less than 13 (N + 24) u, a difference of two by twice that.  The rounding of the rows
+// themselves (three roundings an update) and of the full computation add less than 300 u.
+constexpr double chain_error(int n) { return (26.0 * (n + 24) + 300.0) * 0x1p-53; }
+static_assert(chain_error(128) < kChainMargin / 20, "semantic level: head sizes up to 128");
 
 // Sum / maximum over a row of 16 lanes or a wavefront of values that may be -inf but not NaN.
 __device__ __forceinline__ double row16_max(double m) {

@@ -51,8 +51,8 @@ struct HostTier {
     hipStream_t copy_stream = nullptr;   // fetch kernel, page-list upload, `ready` events
     hipEvent_t main_mark = nullptr;                 // marks the caller's stream at each retrieve
     // ingest: the offload of a staged batch runs on the copy stream while the caller's stream goes on with the
-    // next batch; two slab tables (host and device) used in turn, an event per table for "offload finished",
-    // and the frames each still-counted offload read from the staging ring
+    // next batch; two slab tables (pinned host memory, read there by the offload kernel) used in turn, an event
+    // per table for "offload finished", and the frames each still-counted offload read from the staging ring
     hipEvent_t off_done[2] = {nullptr, nullptr};
     bool off_used[2] = {false, false};
     long long off_f0[2] = {0, 0}, off_f1[2] = {0, 0};

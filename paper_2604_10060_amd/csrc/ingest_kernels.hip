@@ -492,9 +492,8 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
 //      slot is another one than assumed, the first such frame is corrected and the rest checked again;
 //   4. with the winners known, Eq. 3 is applied to the rows themselves: a thread per (slot, channel) runs through the
 //      slot's frames in order.
-// Decisions are exact: the similarities of steps 1 and 3 differ from those of the rows by rounding (sums of at most 17
-// products with r.s >= 0, so that no length cancels: below 1e-13 in the cosine), and they only decide where the best
-// is ahead by more than kChainMargin.  At a frame that is closer than that, or whose best slot does not exceed the
+// Decisions are exact: the similarities of steps 1 and 3 differ from those of the rows by rounding (chain_error: differences
+// by less than 5e-13 at D = 128), and they only decide where the best is ahead by more than kChainMargin.  At a frame that is closer than that, or whose best slot does not exceed the
 // bound of step 2, the chunk ends, and the frames after it are taken in turn: in the order of operations of the one-frame
 // kernel, ties to the lowest id, the products of a chunk's frames with the rows formed in one pass over them and those with
 // a row that moves formed anew.  So ids and representatives are the same bits for any split of the stream into calls.  (A
@@ -524,7 +523,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
     __shared__ double ss_sh[FR], sn_sh[FR], isn_sh[FR], out_v[FR], y_sh[FR], row_sh[SPB][D];
     __shared__ double moved_sh[FR][D], red_v[TW];   // frames in turn: rows that moved
     __shared__ int red_i[TW];
-    __shared__ int near_sh[FR], sure_sh[FR], lo_sh[FR], w_sh[FR], p_sh[FR], slot_id[kChainSlots], n_slot_sh, nc_sh, tied_sh;
+    __shared__ int near_sh[FR], sure_sh[FR], lo_sh[FR], w_sh[FR], p_sh[FR], slot_id[FR], n_slot_sh, nc_sh, tied_sh;
     double *r = dv.r + (size_t)u * C * D;
     const bool nested = dv.P > 0;
     const int width = nested ? dv.Cs : C;           // candidates per frame: ids lo .. lo + width - 1
@@ -1794,12 +1793,6 @@ __global__ __launch_bounds__(128) void k_lloyd_update(DeviceView dv, int n_frame
 }
 
 // ---------------------------------------------------------------------------
-// Host tier: store staged pages into their cluster's slab in pinned host memory
-// (device stores over PCIe, 16 bytes per lane, whole pages contiguous).
-// A few dozen workgroups share the (unit, frame, keys | values) items: the launch
-// runs on the copy stream beside the next batch's staging and assignment, and
-// one workgroup per page would hold the chip while it waits for the link.
-// ---------------------------------------------------------------------------
 // Assignments of frames f0 .. f0+n-1, compacted: a host-tier batch's straight into pinned memory, an observer's into
 // scratch.  grid (U, blocks of frames).
 __global__ __launch_bounds__(kBlock) void k_gather_assign(DeviceView dv, int f0, int n) {
@@ -1808,6 +1801,13 @@ __global__ __launch_bounds__(kBlock) void k_gather_assign(DeviceView dv, int f0,
         dv.batch_assign[(size_t)u * n + i] = dv.assign[(size_t)u * dv.F + f0 + i];
 }
 
+// ---------------------------------------------------------------------------
+// Host tier: store staged pages into their cluster's slab in pinned host memory
+// (device stores over PCIe, 16 bytes per lane, whole pages contiguous).
+// Sixteen workgroups share the (unit, frame, keys | values) items: the launch
+// runs on the copy stream beside the next batch's staging and assignment, and
+// one workgroup per page would hold the chip while it waits for the link.
+// ---------------------------------------------------------------------------
 constexpr int kOffloadXcds = 8;
 __global__ __launch_bounds__(kBlock) void k_offload(DeviceView dv, int f0, int n) {
     // The page table is in pinned host memory: a workgroup fetches the entries of its next 256 items in one trip.

@@ -175,8 +175,11 @@ __global__ __launch_bounds__(kVisBlock) void k_visual_lloyd_update(DeviceView dv
 // centroids at a time (their rows' loads in flight together), all threads update the winner's row.  changed(a, n, norm) is
 // called by thread 0 with the new size and norm of the row.  The caller orders calls by a barrier.
 constexpr int kVisAssign = 512;             // threads of the online kernels
+constexpr int kVisChannels = 4096;          // visual_dim at most
+static_assert(chain_error(kVisChannels / (kVisAssign / 64) + kVisAssign / 64) < kChainMargin / 5,
+              "a wavefront's share of the channels, then the wavefronts' sums");
 struct VisualTurnShared {
-    double e[4096], red[kVisAssign / 64], bv[kVisAssign / 64];
+    double e[kVisChannels], red[kVisAssign / 64], bv[kVisAssign / 64];
     int bi[kVisAssign / 64];
 };
 template <typename Changed>
@@ -234,12 +237,13 @@ __device__ __forceinline__ void visual_in_turn(const DeviceView &dv, const float
     }
 }
 
-// Frames f0..f1-1: partition = most similar non-empty visual centroid, which then moves by Eq. 3.  grid (1), kVisBlock
+// Frames f0..f1-1: partition = most similar non-empty visual centroid, which then moves by Eq. 3.  grid (1), kVisAssign
 // threads.  e_in: the fp32 embeddings of these frames as the caller passed them; the kernel also files them in the visual
 // level's state array.  The frames are taken up to sixteen at a time, as k_assign_chain does for the semantic level (which
 // says why the decisions are exact): products of the chunk with all centroids and with itself, the channels shared out
 // over the wavefronts; the decisions from those; Eq. 3 on the rows of the centroids that the chunk moved, a thread per
-// channel.  Where a chunk begins with a frame that is too close to call, its frames are taken in turn.  (16 frames, P = 16, Dv = 1024: 90.5 -> 26 us against one frame at a time.)
+// channel.  Where a chunk begins with a frame that is too close to call, its frames are taken in turn.  (16 frames, P = 16,
+// Dv = 1024: 90.5 -> 26 us against one frame at a time.)
 template <bool VEC>
 __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, const float *e_in, int f0, int f1) {
     constexpr int NW = kVisAssign / 64, FR = kChainFrames, kNone = 0x7fffffff;
@@ -249,7 +253,7 @@ __global__ __launch_bounds__(kVisAssign) void k_visual_assign(DeviceView dv, con
     __shared__ double sim_sh[FR * 64], gram_sh[FR][FR + 1], red[NW], irn_sh[64];
     __shared__ double ss_sh[FR], sn_sh[FR], isn_sh[FR], out_sh[FR], y_sh[FR];
     __shared__ VisualTurnShared turn_sh;
-    __shared__ int vn_sh[64], slot_sh[64], lo_sh[FR], near_sh[FR], sure_sh[FR], w_sh[FR], p_sh[FR], slot_id[kChainSlots], n_slot_sh, nc_sh, tied_sh;
+    __shared__ int vn_sh[64], slot_sh[64], lo_sh[FR], near_sh[FR], sure_sh[FR], w_sh[FR], p_sh[FR], slot_id[FR], n_slot_sh, nc_sh, tied_sh;
     if (tid < 64) {
         const double rn = tid < P ? dv.vrn[tid] : 0.0;
         vn_sh[tid] = tid < P ? dv.vn[tid] : 0;
