@@ -218,7 +218,9 @@ def test_page_store_at_batch_and_tile_edges(T, D, dtype):
 # wavefront's candidates, with calls on both sides of a chunk.
 @pytest.mark.parametrize("C,D,kind", [(1, 64, "repeats"), (5, 128, "repeats"), (16, 64, "negatives"), (17, 128, "negatives"),
                                       (64, 64, "rapid"), (128, 128, "rapid"), (40, 128, "zeros"), (200, 64, "rapid"),
-                                      (300, 128, "repeats"), (300, 64, "rapid")])
+                                      (300, 128, "repeats"), (300, 64, "rapid"),
+                                      # shortened chunks (C > 512: 13 frames at C = 600, eight at 1024)
+                                      (600, 128, "rapid"), (600, 64, "repeats"), (1024, 64, "rapid"), (1024, 128, "negatives")])
 def test_batched_assignment_at_ties_equals_single_frame_calls_bitwise(C, D, kind):
     F, T, U = 2 * C + 90, 3, 2
     rng = np.random.default_rng(C)
@@ -1213,6 +1215,18 @@ def test_nested_bf16_ragged_visual_dim_and_short_partitions():
                                   question_tokens=21, visual_dim=100, n_visual=5, warmup_frames=60)
     rep = harness.run_nested(wl, 6, 2, units=[(0, 0), (0, 2), (0, 3)], decode_steps=3)
     _report(rep)
+    assert rep.max_out_err <= 2e-2
+
+
+@pytest.mark.gpu
+def test_member_lists_longer_than_one_pass():
+    """The partitions' representatives and the clusters' value representatives list a unit's frames 2048 at a time."""
+    wl = inputs.CONFIGS[0].scaled(name="nested_long", n_frames=2200, n_scenes=40, tokens_per_frame=2, visual_dim=24, n_visual=4,
+                                  n_clusters=16, top_k=4, warmup_frames=2100, lloyd_iters=3)
+    harness.run_nested(wl, 4, 2, batch_pattern=(1050, 1050, 37, 20), n_questions=1, units=[(0, 1)])
+    wl = inputs.CONFIGS[1].scaled(name="aug_long", n_frames=2200, n_scenes=40, n_clusters=6, top_k=2, tokens_per_frame=2,
+                                  question_tokens=2)
+    rep = harness.run_augmented(wl, 0, True, units=[(0, 0)], ingest_between=False)
     assert rep.max_out_err <= 2e-2
 
 
