@@ -888,7 +888,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
 // frame after the other.  grid (U), THREADS threads.  Each 16-lane group keeps its RPG rows of the unit's table
 // (row j = group + (THREADS/16) i) in registers for the whole call, sizes and norms sit in LDS, and the winner's row is
 // updated in place, so nothing in the per-frame chain waits on memory.  The operations of a similarity, of Eq. 3 and of a
-// norm are those of the one-frame kernel and of k_assign_chain's full computation, in their order.
+// norm are those of the one-frame kernel and of k_assign_chain's frames in turn, in their order.
 // What k_assign_chain pays per call whatever the number of frames -- sixteen frames' worth of matrix products, the nearest
 // clusters, slots, the check -- is more than up to four frames in turn (4 layers, 700 frames, C = 180, whole calls with the
 // page store, in turn / chain: 2 a call 11.0 / 13.4 us, 4 a call 14.9 / 16.2; 5 a call 17.2 / 17.0, 8 a call 23.3 / 20.7).

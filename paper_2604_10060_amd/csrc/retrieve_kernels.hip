@@ -59,7 +59,7 @@ __device__ __forceinline__ void mean_query_partials(const E *q, int lc, int h, i
     const int c8 = tid % LPR, part = tid / LPR, R = Tq * G;
     const E *qb = q + (size_t)lc * Tq * Hq * D + (size_t)h * G * D + 8 * c8;
     double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    // (token and head of a row by increments: a division per row was half of a 256-token question's time here)
+    // (token and head of a row by increments: a division per row cost 3 of a 256-token question's 25 us in this kernel)
     const int dt = NPART / G, dg = NPART - dt * G;
     int t = part / G, g = part - t * G;
     for (int r0 = part; r0 < R; r0 += UN * NPART) {

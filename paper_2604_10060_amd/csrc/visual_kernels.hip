@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kVisBlock) void k_visual_lloyd_update(DeviceView dv
     if (tid == 0) { dv.vrn[p] = sqrt(sq); dv.vn[p] = count; }
 }
 
-// One frame by the full computation, all threads of a workgroup: the embedding is staged in LDS, a wavefront scores two
+// One frame by itself, all threads of a workgroup: the embedding is staged in LDS, a wavefront scores two
 // centroids at a time (their rows' loads in flight together), all threads update the winner's row.  changed(a, n, norm) is
 // called by thread 0 with the new size and norm of the row.  The caller orders calls by a barrier.
 constexpr int kVisAssign = 512;             // threads of the online kernels
