@@ -281,7 +281,9 @@ __device__ __forceinline__ int chain_decide(const ChainView &v, int nc, int n_sl
         const int stop = min(vague ? __ffs((int)vague) - 1 : nc, back16 ? __ffs((int)back16) : nc);
         const int at = other ? __ffs((int)other) - 1 : nc;
         if (at >= stop) {
-            tied = stop < nc && ((vague >> stop) & 1);
+            // (not a tie: a cluster outside the slots may be ahead, which the next chunk's products decide)
+            const unsigned int behind = (unsigned int)__ballot(out - best > kChainMargin) & 0xffffu;
+            tied = stop < nc && (((vague & ~behind) >> stop) & 1);
             return min(stop, nc);
         }
         if (n == at) w = bk;            // ... that frame's winner, and once more
