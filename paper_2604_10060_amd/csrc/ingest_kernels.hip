@@ -519,9 +519,10 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
     __shared__ double sim_sh[kChainSims];           // [frame][candidate] dot products, -inf for an empty cluster
     __shared__ double gram_sh[FR][FR + 1];          // s_f . s_g / |s_g|
     __shared__ double rn_sh[1024], irn_sh[1024];    // |r_j|; 1 / |r_j|, 0 for a zero row
-    __shared__ int n_sh[1024], slot_sh[1024];       // sizes; slot of a cluster, -1
+    __shared__ int n_sh[1024];                      // sizes
+    __shared__ signed char slot_sh[1024];           // slot of a cluster, -1
     __shared__ double ss_sh[FR], sn_sh[FR], isn_sh[FR], out_v[FR], y_sh[FR], row_sh[SPB][D];
-    __shared__ double moved_sh[FR][D], red_v[TW];   // frames in turn: rows that moved
+    __shared__ double red_v[TW];
     __shared__ int red_i[TW];
     __shared__ int near_sh[FR], sure_sh[FR], lo_sh[FR], w_sh[FR], p_sh[FR], slot_id[FR], n_slot_sh, nc_sh, tied_sh;
     double *r = dv.r + (size_t)u * C * D;
@@ -727,9 +728,11 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                 const double norm = sqrt(row16_sum(square_channels(sl, true)));
                 if (lr == 0) sn_sh[grp] = norm;
             }
+            if (nested && wave == NW - 1) partition_reps(nc);       // (the summaries alone decide these)
             __syncthreads();
-            // (The loop waits for no store: moved rows stay in LDS until the chunk is done.  Four wavefronts, one per SIMD: a
-            // group per frame, and up to four consecutive candidates per thread, so that ids ascend with the thread.)
+            // (The loop waits for no store: moved rows stay in LDS until the chunk is done, the k-th one in place of the summary
+            // of frame k, which has had its turn by then.  Four wavefronts, one per SIMD: a group per frame, and up to four
+            // consecutive candidates per thread, so that ids ascend with the thread.)
             const int per = (width + 64 * TW - 1) / (64 * TW);
             int a1 = -1, n1 = 0, used = 0;          // the cluster of the frame before, with its new size and norm; `row` is its row
             double rn1 = 0.0;
@@ -764,7 +767,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                         if (slot < 0) fetch(a, row);
                         else
 #pragma unroll
-                            for (int e = 0; e < EPL; ++e) row[e] = moved_sh[slot][lr * EPL + e];
+                            for (int e = 0; e < EPL; ++e) row[e] = s_sh[slot][lr * EPL + e];
                     }
 #pragma unroll
                     for (int e = 0; e < EPL; ++e) row[e] = eq3_channel((double)size, y, row[e], s_sh[fc][lr * EPL + e]);
@@ -776,7 +779,7 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                 lds_barrier();                      // the old row, size and norm have been read
                 if (grp == 0) {
 #pragma unroll
-                    for (int e = 0; e < EPL; ++e) moved_sh[slot][lr * EPL + e] = row[e];
+                    for (int e = 0; e < EPL; ++e) s_sh[slot][lr * EPL + e] = row[e];
                     if (lr == 0) {
                         slot_sh[a] = slot;
                         slot_id[slot] = a;
@@ -788,9 +791,8 @@ __global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int
                 }
             }
             __syncthreads();
-            for (int i = tid; i < n_slot_sh * D; i += kChainBlock) r[(size_t)slot_id[i / D] * D + i % D] = moved_sh[i / D][i % D];
+            for (int i = tid; i < n_slot_sh * D; i += kChainBlock) r[(size_t)slot_id[i / D] * D + i % D] = s_sh[i / D][i % D];
             if (tid < n_slot_sh) slot_sh[slot_id[tid]] = -1;
-            if (nested && wave == NW - 1) partition_reps(nc);
             __syncthreads();
             c0 += nc;
             continue;
