@@ -505,7 +505,7 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
 // 4 k (11 k while page stores saturate the memory system), the fp64 products 6-8 k, nearest clusters 3 k, decisions
 // 3.5 k, Eq. 3 on the rows 7 k (seven dependent fp64 operations per frame).  A kernel that takes the frames one after
 // the other -- table in registers, dot products, search, update, two barriers per frame -- needs 77 k.  Launch: 4 layers,
-// C = 512 in 16 partitions 48.7 -> 15.1 us, 28 layers, C = 128, beside page stores 37.1 -> 23.3 us.
+// C = 512 in 16 partitions 48.7 -> 15.6 us, 28 layers, C = 128, beside page stores 37.1 -> 22.3 us.
 // ---------------------------------------------------------------------------
 constexpr int kChainBlock = 512, kChainSims = 8192;
 
