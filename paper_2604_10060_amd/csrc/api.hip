@@ -138,7 +138,8 @@ int check_config(const mosaic_config *c, std::string &why) {
     return MOSAIC_OK;
 }
 
-Layout make_layout(const mosaic_config &c) {
+// arena_bytes: size of the device arena there is, 0: what is the size to be
+Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
     Layout L{};
     const size_t U = (size_t)c.n_layers * c.n_kv_heads, F = c.max_frames, T = c.tokens_per_frame,
                  D = c.head_dim, C = c.n_clusters, k = c.top_k;
@@ -151,7 +152,6 @@ Layout make_layout(const mosaic_config &c) {
     const int G = c.n_q_heads / c.n_kv_heads;
     const int maxq = c.max_q_tokens > 0 ? c.max_q_tokens : 256;
     const long long nt_max = ((long long)maxq * G + kRowTile - 1) / kRowTile;
-    L.part_entries = std::max<long long>(4096, (long long)U * nt_max * 2);
     L.nt_max = (int)nt_max;
     L.kpage = T * D * e;
     L.vpage = D * (L.v_transposed ? (size_t)L.Tp : T) * e;
@@ -230,9 +230,18 @@ Layout make_layout(const mosaic_config &c) {
     L.sel_pages = take(U * F * 4);
     L.n_sel = take(U * 4);
     L.tok_scratch = take((size_t)c.n_kv_heads * F * T * 4);
-    L.part_o = take((size_t)L.part_entries * kRowTile * D * 4);
-    L.part_ml = take((size_t)L.part_entries * kMlRows * kRowTile * 4);
-    L.total = off;
+    // Attention partials, the last part of the arena: two splits per unit, or what the equal shares of a question on all
+    // layers take (even_share: one per group and one more per unit, at most 4096 / NT groups).  An arena that has
+    // room for the first number only gets that, and such questions fewer shares.
+    L.part_o = off;
+    auto partials = [&](long long entries) {
+        L.part_entries = entries;
+        L.part_ml = align_up(L.part_o + (size_t)entries * kRowTile * D * 4);
+        return align_up(L.part_ml + (size_t)entries * kMlRows * kRowTile * 4);
+    };
+    const long long two = std::max<long long>(4096, (long long)U * nt_max * 2);
+    L.total = partials(std::max<long long>(two, 4096 + (long long)U * nt_max));
+    if (arena_bytes > 0 && arena_bytes < L.total) L.total = partials(two);
     L.host_k = 0;
     L.host_v = host ? (size_t)L.SF * L.kpage : 0;     // inside the first slab: [SF K pages][SF V pages]
     if (host) {
@@ -260,7 +269,8 @@ Layout make_layout(const mosaic_config &c) {
     return L;
 }
 
-// KV splits for one attend call, bounded by the partial-buffer capacity.
+// KV splits per unit for one attend call, bounded by the partial-buffer capacity (decode steps; questions that
+// choose_even_groups() leaves to it).
 int choose_splits(const mosaic_ctx *ctx, int n_units, int Tq, long long part_entries) {
     const DeviceView &dv = ctx->dv;
     const long long NT = ((long long)Tq * dv.G + kRowTile - 1) / kRowTile;
@@ -275,12 +285,9 @@ int choose_splits(const mosaic_ctx *ctx, int n_units, int Tq, long long part_ent
         // MFMA-bound multi-tile launches: every split writes 16 x D partial rows per
         // tile that the combine kernel reads back, so only as many splits as fill the
         // chip's two resident workgroups per CU once (more splits raise the attention
-        // kernel's rate a little but cost more in the combine; measured on config 4),
-        // each with at least 8 chunks; a multiple of 8 keeps the workgroups that share
-        // a (unit, split) on one XCD (workgroup ids congruent mod 8)
+        // kernel's rate a little but cost more in the combine), each with at least 8 chunks
         s = (2048 / pw + n_units * row_blocks - 1) / (n_units * row_blocks);
         s = std::min(s, std::max<long long>(1, est_chunks / 8));
-        if (s >= 8) s = s / 8 * 8;
     } else {
         // bandwidth/latency-bound: cover the chip several times over (7 x 256 workgroups:
         // measured on the all-layers launch of config 2, 1568-1792 workgroups are 3 % faster
@@ -291,6 +298,33 @@ int choose_splits(const mosaic_ctx *ctx, int n_units, int Tq, long long part_ent
     s = std::min<long long>(s, kMaxSplits);
     s = std::min(s, std::max<long long>(1, part_entries / (n_units * NT)));
     return (int)std::max<long long>(1, s);
+}
+
+// Equal shares of a question of more than one row tile (even_share), 0: choose_splits() instead.  As many as fill the chip
+// once with the workgroups that its registers hold (bf16: two per CU, fp32: two at head_dim 64, else one), so that
+// all end together.  A split count per unit leaves units of unequal size with unequal shares, and a count that does not fill
+// the chip a whole number of times leaves the last workgroups alone on it.  Attention launch, per unit / in equal shares:
+// 32 tokens on 28 layers (112 units, two splits) 941 / 584 us; 256 tokens in 4 units (eight splits) 312 / 271 us; fp32, 21
+// tokens in 8 units of D = 64 28 / 20.5 us; whole call, fp32, 32 tokens on 10 layers 1571 / 1210 us.
+// A share has at least 4 chunks (8 instead: 3 tokens in 4 units over 3 MB of pages 33.9 -> 37.1 us a call) and beyond 256
+// shares 8 (4 instead: 12 tokens over 125 MB 60.2 -> 62.7 us a call: the merge reads what more shares write).
+// Where the partial buffer holds fewer shares than the other scheme would use splits, that is the better one.
+int choose_even_groups(const mosaic_ctx *ctx, int n_units, int Tq, long long part_entries) {
+    const DeviceView &dv = ctx->dv;
+    const long long NT = ((long long)Tq * dv.G + kRowTile - 1) / kRowTile;
+    const bool fp32 = dv.esize == 4;
+    if (NT <= 1 || !(fp32 || ctx->impl == MOSAIC_ATTEND_MFMA)) return 0;
+    const long long tiles = fp32 ? kFp32Tiles : kPrefillWaves * kPrefillTiles, rb = (NT + tiles - 1) / tiles;
+    const long long est_pages = std::max<long long>(1, (ctx->n_frames * dv.k + dv.C - 1) / dv.C);
+    const long long chunks = n_units * (fp32 ? (est_pages * dv.T + kGroup - 1) / kGroup : est_pages * dv.chunks_per_page);
+    long long g = std::max<long long>(1, (fp32 && dv.D == 128 ? 256 : 512) / rb);
+    g = std::min(g, std::max({1ll, std::min(chunks / 4, 256ll), chunks / 8}));
+    const long long fit = part_entries / NT - (n_units - 1);
+    if (fit < g) {
+        g = fit;
+        if (g < (long long)n_units * choose_splits(ctx, n_units, Tq, part_entries)) return 0;
+    }
+    return (int)g;
 }
 
 __global__ __launch_bounds__(256) void k_calibration_copy(uint4 *dst, const uint4 *src, size_t n16) {
@@ -337,7 +371,7 @@ int32_t mosaic_workspace_size(const mosaic_config *cfg, size_t *dev_bytes, size_
     int rc = check_config(cfg, why);
     if (rc != MOSAIC_OK) return fail(nullptr, rc, why);
     if (!dev_bytes) return fail(nullptr, MOSAIC_EINVAL, "dev_bytes is NULL");
-    const Layout L = make_layout(*cfg);
+    const Layout L = make_layout(*cfg, 0);
     *dev_bytes = L.total;
     if (host_bytes) *host_bytes = L.host_total;
     return MOSAIC_OK;
@@ -350,7 +384,7 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
     int rc = check_config(cfg, why);
     if (rc != MOSAIC_OK) return fail(nullptr, rc, why);
     if (!out) return fail(nullptr, MOSAIC_EINVAL, "out is NULL");
-    const Layout L = make_layout(*cfg);
+    const Layout L = make_layout(*cfg, cfg->dev_arena_bytes);
     if (!cfg->dev_arena) return fail(nullptr, MOSAIC_EINVAL, "dev_arena is NULL");
     if ((uintptr_t)cfg->dev_arena % 256) return fail(nullptr, MOSAIC_EINVAL, "dev_arena must be 256-byte aligned");
     if (cfg->dev_arena_bytes < L.total) {
@@ -1118,7 +1152,8 @@ static int attend_with(mosaic_ctx *ctx, const DeviceView &dv, int32_t layer, con
                  (long long)nu * NT, dv.part_entries);
         return fail(ctx, MOSAIC_ECAPACITY, b);
     }
-    const int S = choose_splits(ctx, nu, n_q_tokens, dv.part_entries);
+    const int even = choose_even_groups(ctx, nu, n_q_tokens, dv.part_entries);
+    const int S = even > 0 ? (even + nu - 1) / nu : choose_splits(ctx, nu, n_q_tokens, dv.part_entries);
     hipError_t e;
     if (ctx->host) {
         if (layer < 0) return fail(ctx, MOSAIC_EINVAL, "the host tier attends one layer per call");
@@ -1136,12 +1171,12 @@ static int attend_with(mosaic_ctx *ctx, const DeviceView &dv, int32_t layer, con
         ctx->rv_epoch = ctx->epoch;
     }
     e = ctx->impl == MOSAIC_ATTEND_MFMA
-            ? launch_attend_mfma(dv, u0, nu, q_dev, n_q_tokens, S, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
+            ? launch_attend_mfma(dv, u0, nu, q_dev, n_q_tokens, S, even, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
         : dv.esize == 4
-            ? launch_attend_fp32(dv, u0, nu, (const float *)q_dev, n_q_tokens, S, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
+            ? launch_attend_fp32(dv, u0, nu, (const float *)q_dev, n_q_tokens, S, even, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
             : launch_attend_valu(dv, u0, nu, q_dev, n_q_tokens, S, ctx->stream, ev0, ev1);
     if (e != hipSuccess) return fail_hip(ctx, e, "attend launch");
-    e = launch_attend_combine(dv, u0, nu, n_q_tokens, S, out_dev, lse_dev, ctx->stream);
+    e = launch_attend_combine(dv, u0, nu, n_q_tokens, S, out_dev, lse_dev, ctx->stream, false, even);
     if (e != hipSuccess) return fail_hip(ctx, e, "combine launch");
     if (ctx->host) {
         if ((e = hipEventRecord(ctx->host->attend_done[layer], ctx->stream)) != hipSuccess)

@@ -17,33 +17,46 @@ namespace mosaic {
 
 namespace {
 
-// grid (B [+ n_units with the global-representative augmentation], ceil(NT / R)), 4 wavefronts.
-// split_slot() shares the B workgroups of a row block out over the units by retrieved size.  A unit's
-// tokens are one flat sequence in gather order (token i = token i % T of page i / T of the selection), taken
-// 16 at a time whatever T is, so that only the very last group is padded; wavefront w of split s takes groups
-// s + S * w + 4 * S * i.  The page ids of group i + 2 and the operands of group i + 1 are in flight while group
-// i is reduced.
+// grid B [+ n_units with the global-representative augmentation] for one row tile (R = 1), else the (group, row block) pairs in
+// xcd_run() order [+ n_units * row blocks], 4 wavefronts.  A unit's tokens are one flat sequence in gather order (token
+// i = token i % T of page i / T of the selection), taken 16 at a time whatever T is, so that only the very last group of
+// 16 is padded.  One row tile: split_slot() shares the workgroups out over the units by retrieved size, wavefront w of
+// split s takes 16s number s + S * w + 4 * S * i.  Questions: a workgroup takes a contiguous run of 16s, an equal share of all
+// units' (even_share; or a unit's split where the partial buffer is short), its wavefronts every fourth.
+// The page ids of group i + 2 and the operands of group i + 1 are in flight while group i is reduced.
 template <int D, int R, bool STREAM>
-__global__ __launch_bounds__(kBlock, R == 1 ? 2 : 1) void k_attend_fp32(DeviceView dv, int u0, int n_units, const float *q,
-                                                                        int Tq, int NT, int B) {
+__global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp32(DeviceView dv, int u0, int n_units, const float *q,
+                                                                        int Tq, int NT, int B, int n_row_blocks, int even) {
     __shared__ float lds[kF32MergeFloats<D>];
-    if ((int)blockIdx.x >= B) {     // extra columns: the global representatives' part (augmentation)
+    const int first_extra = R == 1 ? B : (B * n_row_blocks + 7) / 8 * 8;
+    if ((int)blockIdx.x >= first_extra) {      // extra workgroups: the global representatives' part (augmentation)
+        const int idx = (int)blockIdx.x - first_extra, rb = idx % n_row_blocks;
         for (int r = 0; r < R; ++r) {
-            const int tile = blockIdx.y * R + r;
-            if (tile < NT) attend_reps_partial<float, D>(dv, u0, (int)blockIdx.x - B, tile, q, Tq, lds);
+            const int tile = rb * R + r;
+            if (tile < NT) attend_reps_partial<float, D>(dv, u0, idx / n_row_blocks, tile, q, Tq, lds);
         }
         return;
     }
-    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16;
-    const SplitSlot slot = split_slot<false>(dv.n_sel + u0, n_units, B, blockIdx.x);
-    if (slot.uc < 0) return;        // block-uniform: no barrier reached yet
-    const int uc = slot.uc, u = u0 + uc, split = slot.split, S = slot.S, T = dv.T;
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16, T = dv.T;
+    int grp = (int)blockIdx.x, yb = 0;
+    if constexpr (R > 1) {
+        const int pair = xcd_run((int)blockIdx.x, B * n_row_blocks);
+        if (pair < 0) return;       // block-uniform: no barrier reached yet
+        grp = pair / n_row_blocks; yb = pair % n_row_blocks;
+    }
+    const ChunkSize<true> cs(dv);
+    ShareWalk<true> w;
+    if (!w.start(dv.n_sel + u0, n_units, cs, B, grp, R > 1 && even != 0)) return;      // block-uniform as well
+  do {
+    int n_ = n, g_ = g, t_ = tid;   // (opaque copies: what only a unit's first loads and last stores need of the lane is worked out there)
+    asm volatile("" : "+v"(n_), "+v"(g_), "+v"(t_));
+    const int uc = w.uc, u = u0 + uc, S = w.S;
     const int lc = uc / dv.Hkv, h = u % dv.Hkv;
     const int *sel = dv.sel_pages + (size_t)u * dv.F;
     const float *kb = reinterpret_cast<const float *>(k_page(dv, u, 0)), *vb = reinterpret_cast<const float *>(v_page(dv, u, 0));
-    const int n_sel = __builtin_amdgcn_readfirstlane(slot.n), N = n_sel * T;      // tokens: max_frames * T fits in 32 bits
-    const int first = __builtin_amdgcn_readfirstlane(split + S * wave), stride = __builtin_amdgcn_readfirstlane(4 * S);
-    const int groups = ((N - 1) >> 4) + 1;                                         // (0 for N = 0)
+    const int n_sel = w.n;
+    const int first = __builtin_amdgcn_readfirstlane(R == 1 ? w.split + S * wave : w.c0 + wave), stride = R == 1 ? 4 * S : 4;
+    const int groups = R == 1 ? cs.of(n_sel) : w.c1;       // (where this workgroup's end)
     const int n_my = __builtin_amdgcn_readfirstlane(first < groups ? (groups - first + stride - 1) / stride : 0);
 
     // wave-uniform cursor over the groups: page (index into the selection) and token offset of a group's first token
@@ -70,7 +83,7 @@ __global__ __launch_bounds__(kBlock, R == 1 ? 2 : 1) void k_attend_fp32(DeviceVi
     float m[R], l[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        f32_load_q<float, D>(dv, q, lc, h, Tq, ((int)blockIdx.y * R + r) * kRowTile + n, g, sl2, qf[r]);
+        f32_load_q<float, D>(dv, q, lc, h, Tq, (yb * R + r) * kRowTile + n_, g_, sl2, qf[r]);
         m[r] = -INFINITY;
         l[r] = 0.f;
 #pragma unroll
@@ -106,12 +119,12 @@ __global__ __launch_bounds__(kBlock, R == 1 ? 2 : 1) void k_attend_fp32(DeviceVi
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int tile = blockIdx.y * R + r;
+        const int tile = yb * R + r;
         if (tile >= NT) break;      // block-uniform
         float o[D / 16], M, L;
         f32_merge_waves<D>(acc[r], m[r], l[r], lds, o, M, L);
-        const int rw = tid / 16, dl = tid % 16;
-        const size_t entry = (size_t)slot.base * NT + (size_t)tile * S + split;
+        const int rw = t_ / 16, dl = t_ % 16;
+        const size_t entry = (size_t)w.base * NT + (size_t)tile * S + w.split;
         float *po = dv.part_o + (entry * kRowTile + rw) * D;
 #pragma unroll
         for (int i = 0; i < D / 16; ++i) po[dl + 16 * i] = o[i];
@@ -122,16 +135,17 @@ __global__ __launch_bounds__(kBlock, R == 1 ? 2 : 1) void k_attend_fp32(DeviceVi
             ml[2 * kRowTile + rw] = L;
         }
     }
+  } while (R > 1 && w.next(dv.n_sel + u0, cs));
 }
 
 } // namespace
 
 hipError_t launch_attend_fp32(const DeviceView &dv, int u0, int n_units, const float *q, int Tq, int n_splits,
-                              bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-    const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile, R = NT == 1 ? 1 : kFp32Tiles;
-    const int B = n_units * n_splits;
-    const dim3 grid(B + (dv.aug_reps ? n_units : 0), (NT + R - 1) / R), block(kBlock);
-    auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, B); };
+                              int even_groups, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile, R = NT == 1 ? 1 : kFp32Tiles, rb = (NT + R - 1) / R;
+    const int even = even_groups > 0, B = even ? even_groups : n_units * n_splits;
+    const dim3 grid((NT == 1 ? B : (B * rb + 7) / 8 * 8) + (dv.aug_reps ? n_units * rb : 0)), block(kBlock);
+    auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, B, rb, even); };
     if (NT == 1) {
         if (dv.D == 64) stream_kv ? go(k_attend_fp32<64, 1, true>) : go(k_attend_fp32<64, 1, false>);
         else stream_kv ? go(k_attend_fp32<128, 1, true>) : go(k_attend_fp32<128, 1, false>);

@@ -24,8 +24,6 @@ namespace mosaic {
 
 typedef float f32v4 __attribute__((ext_vector_type(4)));
 
-constexpr int kGroup = 16;          // tokens a wavefront reduces per step
-
 // See the bf16 kernels: the running reference of a row is raised only when a logit exceeds it by
 // more than this (log2 domain); weights are then at most 2^8.
 constexpr float kLazyF32 = 8.0f;

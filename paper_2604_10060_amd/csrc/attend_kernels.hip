@@ -331,14 +331,11 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
 // 58 -> 40 us).  grid (D/32, NT, n_units), 256 threads;
 // same arithmetic, partial sums of a split group added in the same order.
 template <typename E, int D>
-__global__ __launch_bounds__(kBlock) void k_combine_question(DeviceView dv, int u0, int n_units, int Tq, int B, E *out, float *lse) {
+__global__ __launch_bounds__(kBlock) void k_combine_question(DeviceView dv, int u0, int n_units, int Tq, int B, int even_groups,
+                                                             E *out, float *lse) {
     const int dg = blockIdx.x, tile = blockIdx.y, uc = blockIdx.z, u = u0 + uc, NT = gridDim.y, tid = threadIdx.x;
-    const int G = dv.G, Hq = dv.Hq, lc = uc / dv.Hkv, h = u % dv.Hkv, R = Tq * G;
-    const int rows = min(kRowTile, R - tile * kRowTile);
-    const SplitSlot slot = split_slot<true>(dv.n_sel + u0, n_units, B, uc);
-    const int n_splits = slot.S;                 // 0 if the unit retrieved nothing
-    const size_t e0 = (size_t)slot.base * NT + (size_t)tile * n_splits;
-    __shared__ float w_sh[kMaxUnitSplits][kRowTile];
+    const int lc = uc / dv.Hkv, h = u % dv.Hkv, rows = min(kRowTile, Tq * dv.G - tile * kRowTile);
+    __shared__ float w_sh[512][kRowTile];          // (equal shares: at most 512)
     __shared__ float pm[16][kRowTile], pl[16][kRowTile], px[16][kRowTile];
     __shared__ float red[8][kRowTile][33];
     const int sg = tid / 32, col = tid % 32;
@@ -417,18 +414,18 @@ hipError_t launch_attend_valu(const DeviceView &dv, int u0, int n_units, const v
 }
 
 hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int Tq, int n_splits,
-                                 void *out, float *lse, hipStream_t s, bool uniform) {
+                                 void *out, float *lse, hipStream_t s, bool uniform, int even_groups) {
     const int us = uniform ? n_splits : 0;
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
     const int B = n_units * n_splits;
     if (NT > 1) {
         const dim3 gq(dv.D / 32, NT, n_units);
         if (dv.esize == 4) {
-            if (dv.D == 64) k_combine_question<float, 64><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, (float *)out, lse);
-            else k_combine_question<float, 128><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, (float *)out, lse);
+            if (dv.D == 64) k_combine_question<float, 64><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, (float *)out, lse);
+            else k_combine_question<float, 128><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, (float *)out, lse);
         } else {
-            if (dv.D == 64) k_combine_question<unsigned short, 64><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, (unsigned short *)out, lse);
-            else k_combine_question<unsigned short, 128><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, (unsigned short *)out, lse);
+            if (dv.D == 64) k_combine_question<unsigned short, 64><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, (unsigned short *)out, lse);
+            else k_combine_question<unsigned short, 128><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, (unsigned short *)out, lse);
         }
         return hipGetLastError();
     }

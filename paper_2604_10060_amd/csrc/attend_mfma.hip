@@ -398,7 +398,7 @@ hipError_t launch_decode_fused(const DeviceView &dv, int u0, int n_units, const 
 }
 
 hipError_t launch_attend_mfma(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
-                              int n_splits, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                              int n_splits, int even_groups, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
     const unsigned short *qq = (const unsigned short *)q;
     const dim3 block(kBlock);
@@ -414,7 +414,7 @@ hipError_t launch_attend_mfma(const DeviceView &dv, int u0, int n_units, const v
             else stream_kv ? go(k_attend_decode_mfma<128, false, true>) : go(k_attend_decode_mfma<128, false, false>);
         }
     } else {
-        return launch_attend_prefill(dv, u0, n_units, qq, Tq, n_splits, s, ev0, ev1);
+        return launch_attend_prefill(dv, u0, n_units, qq, Tq, n_splits, even_groups, s, ev0, ev1);
     }
     return hipGetLastError();
 }

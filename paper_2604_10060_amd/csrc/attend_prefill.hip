@@ -36,13 +36,8 @@
 // chain LDS read -> MFMA -> softmax -> MFMA is dependent, and two wavefronts per SIMD (all that
 // two row tiles of accumulators leave room for) do not cover it.
 //
-// A group is one (unit, split) slot -- split_slot() shares the slots out over the units by
-// retrieved size -- and its n_row_blocks workgroups read the same K/V range.  Workgroups go to
-// the 8 XCDs round-robin by id and are dispatched in id order, so the 1-D grid is laid out as
-// id = 8 * (row block + n_row_blocks * (group / 8)) + group % 8: a group's workgroups share one
-// XCD (one L2) and have neighbouring dispatch slots there, which keeps them together in time --
-// also when the grid exceeds the chip or several streams' kernels interleave -- so the group's
-// K/V is fetched from memory once and found in L2 by the rest.
+// A group is a share of the retrieved chunks -- of all units' in equal parts (even_share), or where the partial buffer is short
+// a unit's split (split_slot) -- and its n_row_blocks workgroups read the same K/V range; xcd_run() says which id is which.
 #include <mutex>
 
 #include "mosaic_internal.h"
@@ -74,7 +69,7 @@ template <int D, bool AUG, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfma(DeviceView dv, int u0, int n_units,
                                                                                     const unsigned short *q, int Tq,
                                                                                     int NT, int n_groups, int n_row_blocks,
-                                                                                    int group_blocks) {
+                                                                                    int group_blocks, int even) {
     static_assert(!AUG || 64 * NW == kBlock, "the representatives' workgroups are written for kBlock threads");
     constexpr int KK = D / 32, DB = D / 16, RTW = kPrefillTiles;
     constexpr int KSEG = D / 8;                  // 16-byte pieces per key row
@@ -86,6 +81,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     constexpr int LPW = (KW + VW) / NW;          // ... per wave: loads number wave + NW i, keys first
     static_assert(LPW >= 1 && (KW + VW) % NW == 0 && 2 * (DIST - 1) * LPW < 64, "load schedule");
     constexpr int kPending = 2 * (DIST - 1) * LPW;           // loads of a wave that may stay in flight across a barrier
+    static_assert(kPending == 0, "a share's next unit starts on LDS slots that no load is on its way to");
     // LDS (dynamic): NS key slots, then NS value slots, one chunk each
     extern __shared__ __attribute__((aligned(1024))) unsigned char prefill_lds[];
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16;
@@ -97,40 +93,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
             return;
         }
     }
-    const int xcd = (int)blockIdx.x % 8, seq = (int)blockIdx.x / 8;
-    const int grp = (seq / n_row_blocks) * 8 + xcd, yb = seq % n_row_blocks;
-    if (grp >= n_groups) return;                   // block-uniform: no barrier reached yet
-    const SplitSlot slot = split_slot<false>(dv.n_sel + u0, n_units, n_groups, grp);
-    if (slot.uc < 0) return;
-    // (wave-uniform values are moved to scalar registers: page ids are then read with scalar loads,
-    // which nothing waits for until they are used a page later, and addresses are scalar arithmetic)
-    const int uc = __builtin_amdgcn_readfirstlane(slot.uc), u = u0 + uc;
-    const int split = __builtin_amdgcn_readfirstlane(slot.split), n_splits = __builtin_amdgcn_readfirstlane(slot.S);
-    const int slot_base = __builtin_amdgcn_readfirstlane(slot.base);
+    const int pair = xcd_run((int)blockIdx.x, n_groups * n_row_blocks);
+    if (pair < 0) return;                          // block-uniform: no barrier reached yet
+    const int grp = pair / n_row_blocks, yb = pair % n_row_blocks;
     const int T = dv.T, F = dv.F, cpp = dv.chunks_per_page;
-    const int lc = uc / dv.Hkv, h = u % dv.Hkv;
     const int tile0 = (yb * NW + wave) * RTW;
-    bf16x8 qf[RTW][KK];
-#pragma unroll
-    for (int r = 0; r < RTW; ++r) load_q<D>(dv, q, lc, h, Tq, (tile0 + r) * kRowTile + n, g, qf[r]);
-
-    // the page list was written by an earlier launch and is read-only here: constant address space, so
-    // that a wave-uniform read of it is a scalar load
-    const cint_ptr sel = (cint_ptr)(dv.sel_pages + (size_t)u * F);
-    const int NC = __builtin_amdgcn_readfirstlane(slot.n) * cpp;
-    const int cps = (NC + n_splits - 1) / n_splits;
-    const int c0 = __builtin_amdgcn_readfirstlane(split * cps);
-    const int c1 = __builtin_amdgcn_readfirstlane(min(NC, c0 + cps));
+    const bool idle = tile0 >= NT;                 // wave-uniform: no rows for this wave; it only fetches
     const float sl2 = 1.4426950408889634f / sqrtf((float)D);
-
-    f32x4 acc[RTW][DB], l[RTW];                    // l: row sums, kept by an all-ones MFMA
-    float m[RTW], lx[RTW], bar[RTW];               // bar: a raw logit above it raises the row's reference m
-#pragma unroll
-    for (int r = 0; r < RTW; ++r) {
-        m[r] = -INFINITY; bar[r] = -INFINITY; l[r] = f32x4{0.f, 0.f, 0.f, 0.f}; lx[r] = 0.f;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) acc[r][db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
 
     // What this lane fetches of every chunk (fixed for the kernel's life).  Load i of the wave is
     // wavefront-load number wave + NW i of the chunk: numbers below KW cover the key block, the
@@ -163,6 +132,34 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     for (int kk = 0; kk < KK; ++kk) kr_off[kk] = n * (D * 2) + (((4 * kk + g) ^ ((n / KRP) % KSEG)) * 16);
     const int vr_off = n * (kChunk * 2) + ((g ^ ((n / 4) % 4)) * 16);
 
+    // The group's chunks, unit by unit.  (Page ids are read with scalar loads, which nothing waits for until they are used a
+    // page later, and addresses are scalar arithmetic: everything of the walk is in scalar registers.)
+    const ChunkSize<false> cs(dv);
+    ShareWalk<false> w;
+    if (!w.start(dv.n_sel + u0, n_units, cs, n_groups, grp, even != 0)) return;
+  do {
+    // (opaque copies: what a unit's first loads and last stores derive from the lane is worked out there, and not kept in
+    // registers across the loop over the chunks)
+    int n_ = n, g_ = g;
+    asm volatile("" : "+v"(n_), "+v"(g_));
+    const int uc = w.uc, c0 = w.c0, c1 = w.c1, n_pages = w.n;
+    const int u = u0 + uc, lc = uc / dv.Hkv, h = u % dv.Hkv;
+    bf16x8 qf[RTW][KK];
+#pragma unroll
+    for (int r = 0; r < RTW; ++r) load_q<D>(dv, q, lc, h, Tq, (tile0 + r) * kRowTile + n_, g_, qf[r]);
+    // the page list was written by an earlier launch and is read-only here: constant address space, so
+    // that a wave-uniform read of it is a scalar load
+    const cint_ptr sel = (cint_ptr)(dv.sel_pages + (size_t)u * F);
+
+    f32x4 acc[RTW][DB], l[RTW];                    // l: row sums, kept by an all-ones MFMA
+    float m[RTW], lx[RTW], bar[RTW];               // bar: a raw logit above it raises the row's reference m
+#pragma unroll
+    for (int r = 0; r < RTW; ++r) {
+        m[r] = -INFINITY; bar[r] = -INFINITY; l[r] = f32x4{0.f, 0.f, 0.f, 0.f}; lx[r] = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) acc[r][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
     // Chunks are fetched in order by two cursors (keys run one chunk ahead of values, see below).  A cursor
     // (chunk nf = chunk cc of the pi-th selected page) advances by increments, page addresses are worked
     // out once per page, and the id of the page after the current one is read (a scalar load) a whole
@@ -170,7 +167,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     // last chunk: such loads re-read valid memory, land in slots nobody reads, and keep the number of
     // loads per barrier interval constant, which is what the partial waits count on.
     struct Cursor { int nf, pi, cc, pg_next, slot; const unsigned short *p; };
-    const int cl = c1 - 1, n_pages = NC / cpp;
+    const int cl = c1 - 1;
     const char *const kbase = dv.k_store + (size_t)u * dv.k_ustride;
     const char *const vbase = dv.v_store + (size_t)u * dv.v_ustride;
     auto page_ptr = [&](const char *base, size_t psize, int page) {
@@ -361,22 +358,23 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
         publish();                                    // K0, K1, K2, V0, V1 are in LDS
         {   // Q(0), Q(1): the first chunk's logits
             bf16x8 kf[2 * KK];
-            ldk(0, kf);
-            logits(kf, 0, S[0]);
-            logits(kf, 1, S[1]);
+            if (!idle) {
+                ldk(0, kf);
+                logits(kf, 0, S[0]);
+                logits(kf, 1, S[1]);
+            }
         }
         __syncthreads();                              // (key slot 0 is written again from the first interval on)
         for (int j = 0; j < n_chunks; j += 2) {       // barrier interval of steps j, j + 1
             fetch_v(); fetch_k();                     // V(j + 2 DIST), K(j + 2 DIST + 1): slots last read one interval ago
             fetch_v(); fetch_k();
-            step((j + 1) & (NS - 1), j & (NS - 1), next_valid(j), S, S2);
-            step((j + 2) & (NS - 1), (j + 1) & (NS - 1), next_valid(j + 1), S2, S);
+            if (!idle) {
+                step((j + 1) & (NS - 1), j & (NS - 1), next_valid(j), S, S2);
+                step((j + 2) & (NS - 1), (j + 1) & (NS - 1), next_valid(j + 1), S2, S);
+            }
             publish();
         }
     }
-#undef MOSAIC_ALTERNATE_17
-#undef MOSAIC_ALTERNATE_4
-#undef MOSAIC_ALTERNATE_1
 #pragma unroll
     for (int r = 0; r < RTW; ++r) {
         const int tile = tile0 + r;
@@ -385,24 +383,30 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
         float xr = lx[r];                              // this lane's 8 tokens per chunk: add the four lane groups
         xr += __shfl_xor(xr, 16, 64);
         xr += __shfl_xor(xr, 32, 64);
-        const size_t entry = (size_t)slot_base * NT + (size_t)tile * n_splits + split;
-        float *po = dv.part_o + (entry * kRowTile + n) * D;
+        const size_t entry = (size_t)w.base * NT + (size_t)tile * w.S + w.split;
+        float *po = dv.part_o + (entry * kRowTile + n_) * D;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
-            *reinterpret_cast<float4 *>(po + 16 * db + 4 * g) =
+            *reinterpret_cast<float4 *>(po + 16 * db + 4 * g_) =
                 make_float4(acc[r][db][0], acc[r][db][1], acc[r][db][2], acc[r][db][3]);
-        if (g == 0) {
-            dv.part_ml[entry * kMlRows * kRowTile + n] = m[r];
-            dv.part_ml[entry * kMlRows * kRowTile + kRowTile + n] = lr;
-            dv.part_ml[entry * kMlRows * kRowTile + 2 * kRowTile + n] = xr;
+        if (g_ == 0) {
+            dv.part_ml[entry * kMlRows * kRowTile + n_] = m[r];
+            dv.part_ml[entry * kMlRows * kRowTile + kRowTile + n_] = lr;
+            dv.part_ml[entry * kMlRows * kRowTile + 2 * kRowTile + n_] = xr;
         }
     }
+    // (Nothing of this unit is left in LDS or on its way there: the last interval ended with a wait for every load and a
+    // barrier.)
+  } while (w.next(dv.n_sel + u0, cs));
+#undef MOSAIC_ALTERNATE_17
+#undef MOSAIC_ALTERNATE_4
+#undef MOSAIC_ALTERNATE_1
 }
 
 } // namespace
 
 hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, const unsigned short *q, int Tq,
-                                 int n_splits, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                                 int n_splits, int even_groups, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     constexpr int NW = kPrefillWaves;
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
     // dynamic LDS: NW key slots and NW value slots of one chunk (32 x D bf16) each
@@ -415,10 +419,10 @@ hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, cons
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<128, true, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<128, false, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
     });
-    const int n_groups = n_units * n_splits, rb = (NT + NW * kPrefillTiles - 1) / (NW * kPrefillTiles);
-    const int gb = (n_groups + 7) / 8 * 8 * rb;
+    const int even = even_groups > 0, n_groups = even ? even_groups : n_units * n_splits, rb = (NT + NW * kPrefillTiles - 1) / (NW * kPrefillTiles);
+    const int gb = (n_groups * rb + 7) / 8 * 8;
     const dim3 grid(gb + (dv.aug_reps ? n_units * NT : 0)), block(64 * NW);
-    auto go = [&](auto kern) { launch_timed(kern, grid, block, lds, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, n_groups, rb, gb); };
+    auto go = [&](auto kern) { launch_timed(kern, grid, block, lds, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, n_groups, rb, gb, even); };
     if (dv.aug_reps) { if (dv.D == 64) go(k_attend_prefill_mfma<64, true, NW>); else go(k_attend_prefill_mfma<128, true, NW>); }
     else { if (dv.D == 64) go(k_attend_prefill_mfma<64, false, NW>); else go(k_attend_prefill_mfma<128, false, NW>); }
     return hipGetLastError();

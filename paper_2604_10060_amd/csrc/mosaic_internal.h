@@ -13,6 +13,7 @@ namespace mosaic {
 constexpr int kBlock = 256;       // threads per workgroup (4 wavefronts of 64)
 constexpr int kRowTile = 16;      // query rows per attention tile
 constexpr int kChunk = 32;        // tokens per attention step, always inside one page
+constexpr int kGroup = 16;        // tokens a wavefront of the fp32 attention reduces per step, across pages
 constexpr int kMaxSplits = 64;    // KV splits per (unit, row tile), average over the units of a launch
 constexpr int kMaxUnitSplits = 256; // ... and the most one unit can be given when the units retrieve unequal amounts
 constexpr int kPrefillTiles = 2;  // row tiles per wavefront in the multi-tile MFMA kernel
@@ -190,20 +191,22 @@ hipError_t launch_expand_tok_idx(const DeviceView &dv, int u0, int n_units, hipS
 // n_splits = average splits per unit chosen by the caller (B = n_units * n_splits split
 // workgroups are shared out by split_slot); partial entries needed = B * NT
 // ev0/ev1 (may be null) receive the kernel's own start/stop timestamps
+// even_groups > 0 (questions of more than one row tile): that many equal shares of the launch's chunks
+// (even_share) in place of n_splits per unit; partial entries needed = (even_groups + n_units - 1) * NT
 hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, const unsigned short *q, int Tq,
-                                 int n_splits, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+                                 int n_splits, int even_groups, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // bf16 pages on the vector ALU (MOSAIC_ATTEND_VALU)
 hipError_t launch_attend_valu(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                               int n_splits, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // fp32 pages (fp32 matrix instruction)
 hipError_t launch_attend_fp32(const DeviceView &dv, int u0, int n_units, const float *q, int Tq, int n_splits,
-                              bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+                              int even_groups, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // stream_kv: the decode-shape kernels load K/V with the non-temporal hint (stores far beyond the caches)
 hipError_t launch_attend_mfma(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
-                              int n_splits, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+                              int n_splits, int even_groups, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // uniform: every unit has exactly n_splits splits at slots unit * n_splits + split (fused decode step)
 hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int Tq, int n_splits,
-                                 void *out, float *lse, hipStream_t s, bool uniform = false);
+                                 void *out, float *lse, hipStream_t s, bool uniform = false, int even_groups = 0);
 // selection + attention of one decode step of one layer in one launch with size-proportional splits: the
 // first n_units workgroups select for one unit each and publish the result, all workgroups then share
 // out the retrieved pages (one row tile, bf16, C <= 256).  epoch: a number no earlier launch on this
@@ -384,6 +387,136 @@ __device__ __forceinline__ SplitSlot split_slot(const int *n_sel_call, int n_uni
         run += __shfl(incl, 63, 64);
     }
     return r;
+}
+
+// ---------------------------------------------------------------------------
+// Equal shares, for questions of more than one row tile.  What the units of a launch retrieved is one sequence of chunks (32
+// tokens of a page in the bf16 kernel, 16 tokens across pages in the fp32 one), in unit order; group g of G takes chunks
+// g * per .. (g + 1) * per - 1 of it, per = ceil(chunks / G), whichever units they belong to.  A group writes one partial per
+// unit that it touches: the partial of (unit i, group g) sits at slot g + i, which rises by at least one from each
+// (unit, group) pair to the next, so that slots are distinct and there are at most G + n_units - 1 of them; unit i's are
+// the S slots from base on.
+// (Chunks of a launch fit 32 bits: each has at least 4 KB of pages in GPU memory.)
+// The attention kernels call it by group, the merge by unit; every lane of the wavefront gets the result.
+// ---------------------------------------------------------------------------
+// bf16: chunks stay inside a page (per = chunks of a page); fp32: a unit's tokens are one sequence (per = tokens of a page;
+// max_frames * T fits in 32 bits)
+template <bool FP32> struct ChunkSize {
+    int per;
+    __device__ __forceinline__ explicit ChunkSize(const DeviceView &dv) : per(FP32 ? dv.T : dv.chunks_per_page) {}
+    __device__ __forceinline__ int of(int pages) const { return FP32 ? (pages * per + kGroup - 1) / kGroup : pages * per; }
+};
+struct EvenShare {
+    int uc;        // unit within the call: the group's first, or the one asked for; -1: the group has no chunks
+    int before;    // chunks of the units before it
+    int n;         // the unit's retrieved pages
+    int chunks;    // its chunks
+    int per;       // chunks per group
+    int all;       // chunks of the launch
+    __device__ __forceinline__ int base() const { return before / per + uc; }
+    __device__ __forceinline__ int splits() const { return chunks > 0 ? (before + chunks - 1) / per - before / per + 1 : 0; }
+};
+
+template <bool BY_UNIT, bool FP32>
+__device__ __forceinline__ EvenShare even_share(const int *n_sel_call, int n_units, ChunkSize<FP32> cs, int G, int key) {
+    const int lane = threadIdx.x % 64;
+    int total = 0;
+    for (int i = lane; i < n_units; i += 64) total += cs.of(n_sel_call[i]);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o, 64);
+    EvenShare r{-1, 0, 0, 0, 1, total};
+    r.per = max(1, (int)((unsigned int)(total + G - 1) / (unsigned int)G));
+    const long long want = (long long)key * r.per;          // the group's first chunk
+    int run = 0;
+    for (int i0 = 0; i0 < n_units; i0 += 64) {
+        const int i = i0 + lane;
+        const int pages = i < n_units ? n_sel_call[i] : 0, c = cs.of(pages);
+        int incl = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += t;
+        }
+        const int excl = run + incl - c;
+        const bool hit = BY_UNIT ? (i == key) : (want >= excl && want < excl + c);
+        const unsigned long long mask = __ballot(hit);
+        if (mask) {
+            const int src = __ffsll((long long)mask) - 1;
+            r.uc = i0 + src;
+            r.before = __shfl(excl, src, 64);
+            r.n = __shfl(pages, src, 64);
+            r.chunks = __shfl(c, src, 64);
+        }
+        run += __shfl(incl, 63, 64);
+    }
+    return r;
+}
+
+// The walk of one workgroup over its share, unit by unit: a group of the equal shares may end one unit and begin the next,
+// a split of split_slot() is one unit's.  Wave-uniform values are moved to scalar registers.
+template <bool FP32> struct ShareWalk {
+    int uc, n;              // unit within the call, its pages
+    int c0, c1;             // the group's range of the unit's chunks
+    int base, S, split;     // its partials: first slot and number of the unit's, which of them this is
+    int left, before, per, grp;
+    __device__ __forceinline__ void enter(int chunks) {      // equal shares: the unit (uc, n) from chunk c0 on
+        c1 = min(chunks, c0 + left);
+        left -= c1 - c0;
+        const int g0 = __builtin_amdgcn_readfirstlane(before / per);      // (the quotients are formed in vector registers)
+        base = g0 + uc;
+        S = __builtin_amdgcn_readfirstlane((before + chunks - 1) / per) - g0 + 1;
+        split = grp - g0;
+    }
+    // false: the group has no chunks.  (Both ways end in the same assignments: stores to the members in the branches were
+    // merged into one through a pointer, which put the members into memory.)
+    __device__ __forceinline__ bool start(const int *n_sel_call, int n_units, ChunkSize<FP32> cs, int G, int g, bool even) {
+        int uc_, n_, before_ = 0, per_ = 1, left_ = 0, S_ = 0, split_ = 0, base_ = 0;
+        if (even) {
+            const EvenShare sh = even_share<false, FP32>(n_sel_call, n_units, cs, G, g);
+            uc_ = sh.uc; n_ = sh.n; before_ = sh.before; per_ = sh.per;
+            left_ = min(sh.per, sh.all - g * sh.per);
+        } else {
+            const SplitSlot slot = split_slot<false>(n_sel_call, n_units, G, g);
+            uc_ = slot.uc; n_ = slot.n; S_ = slot.S; split_ = slot.split; base_ = slot.base;
+        }
+        uc = __builtin_amdgcn_readfirstlane(uc_); n = __builtin_amdgcn_readfirstlane(n_);
+        before = __builtin_amdgcn_readfirstlane(before_); per = __builtin_amdgcn_readfirstlane(per_);
+        left = __builtin_amdgcn_readfirstlane(left_); grp = g;
+        if (uc < 0) return false;
+        const int chunks = cs.of(n), first = g * per - before;
+        const int S_e = (before + chunks - 1) / per - before / per + 1;
+        const int S_u = __builtin_amdgcn_readfirstlane(even ? S_e : S_);
+        const int sp_u = __builtin_amdgcn_readfirstlane(even ? g - before / per : split_);
+        const int cps = __builtin_amdgcn_readfirstlane((chunks + S_u - 1) / S_u);
+        S = S_u;
+        split = sp_u;
+        base = __builtin_amdgcn_readfirstlane(even ? before / per + uc : base_);
+        c0 = even ? first : min(chunks, sp_u * cps);
+        c1 = min(chunks, c0 + (even ? left : cps));
+        left = even ? left - (c1 - c0) : 0;
+        return true;
+    }
+    // the group's next unit; false: there is none
+    __device__ __forceinline__ bool next(const int *n_sel_call, ChunkSize<FP32> cs) {
+        if (left <= 0) return false;
+        do {
+            before += cs.of(n);
+            n = __builtin_amdgcn_readfirstlane(n_sel_call[++uc]);
+        } while (n == 0);                                    // (chunks are left, so a later unit has some)
+        c0 = 0;
+        enter(cs.of(n));
+        return true;
+    }
+};
+
+// Workgroup w of a launch of (group, row block) pairs, w = group * row blocks + row block, for block id `id`: workgroups go to
+// the 8 XCDs round-robin by id and are dispatched in id order, so the pairs are dealt in eight contiguous runs.  A group's row
+// blocks then share one XCD and its L2 (those at a run's end: two) and have neighbouring dispatch slots there, which keeps
+// them together in time, so that the group's K/V is fetched from memory once and found in L2 by the rest; and any number of pairs
+// fills the XCDs evenly.  -1: none.  The grid has 8 * ceil(pairs / 8) ids.
+__device__ __forceinline__ int xcd_run(int id, int pairs) {
+    const int per = (pairs + 7) / 8, seq = id / 8, w = id % 8 * per + seq;
+    return seq < per && w < pairs ? w : -1;
 }
 
 } // namespace mosaic

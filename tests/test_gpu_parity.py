@@ -202,6 +202,49 @@ def test_question_merge_of_many_splits(kw):
     harness.run_workload(_small(**kw), layer_mode="all")
 
 
+# Equal shares of the retrieved chunks: shares that span several units (more than 64 of them: the scan takes two passes), units
+# that span several shares, one chunk in all and fewer chunks than shares, waves without rows beside waves with, and the merge's
+# two forms (many tiles, many splits)
+@pytest.mark.parametrize("kw", [
+    dict(n_layers=18, n_frames=60, n_scenes=6, n_clusters=6, top_k=2, tokens_per_frame=9, question_tokens=5),         # 72 units
+    dict(n_layers=2, n_frames=300, tokens_per_frame=100, head_dim=64, question_tokens=40, n_clusters=9, top_k=3),     # 4 chunks a page
+    dict(n_q_heads=6, n_kv_heads=1, n_frames=24, n_scenes=2, n_clusters=12, top_k=1, tokens_per_frame=7, question_tokens=3),
+    dict(n_layers=18, n_frames=60, n_scenes=6, n_clusters=6, top_k=2, tokens_per_frame=5, question_tokens=6, kv_dtype="fp32"),
+    dict(n_layers=3, n_frames=200, tokens_per_frame=33, question_tokens=11, kv_dtype="fp32"),
+    dict(n_q_heads=6, n_kv_heads=1, n_frames=24, n_scenes=2, n_clusters=12, top_k=1, tokens_per_frame=3, question_tokens=3, head_dim=64,
+         kv_dtype="fp32"),
+])
+def test_question_in_equal_shares(kw):
+    harness.run_workload(_small(**kw), layer_mode="all")
+
+
+def test_question_with_room_for_few_partials(monkeypatch):
+    # an arena with room for two splits per unit and no more (what a context needed before the equal shares): fewer shares
+    # or a split count per unit, the same result up to the order of the merge
+    wl = _small(n_layers=24, n_frames=96, n_clusters=8, top_k=3, question_tokens=32)       # 96 units x 14 tiles
+    st = inputs.SceneStream(wl)
+    K, V = [x.to(DEV) for x in st.frames(0, wl.n_frames)]
+    q = st.question(st.draw_scene(), 32, 0).to(DEV)
+    sizes = binding.workspace_sizes
+    more = (4096 + 96 * 14 - 4096) * (16 * 128 * 4 + 192)
+    outs = []
+    for less in (0, more):
+        monkeypatch.setattr(binding, "workspace_sizes", lambda cfg: (sizes(cfg)[0] - less, sizes(cfg)[1]))
+        m = binding.Mosaic(binding.config_for(wl, max_q_tokens=32), device=DEV)
+        m.ingest_frame(K, V)
+        m.retrieve(-1, q)
+        outs.append(m.attend(-1, q))
+        m.close()
+    (o, l), (o2, l2) = outs
+    assert (o.float() - o2.float()).abs().max().item() <= harness.OUT_TOL["bf16"]
+    assert (l - l2).abs().max().item() <= harness.LSE_TOL["bf16"]
+    # (and one with less is refused)
+    monkeypatch.setattr(binding, "workspace_sizes", lambda cfg: (sizes(cfg)[0] - more - 4096, sizes(cfg)[1]))
+    with pytest.raises(binding.MosaicError) as e:
+        binding.Mosaic(binding.config_for(wl, max_q_tokens=32), device=DEV)
+    assert e.value.code == binding.ENOMEM
+
+
 # page stores load four rows per thread at a time, value pages a 64-token tile ahead: pages of a batch more or less than
 # that, one token beside a tile, and several tiles, in one-frame calls (their own kernel) and batched ones
 @pytest.mark.parametrize("T,D,dtype", [(63, 128, "bf16"), (65, 128, "bf16"), (129, 64, "bf16"), (128, 64, "bf16"), (65, 128, "fp32"),
