@@ -8,6 +8,8 @@
 //   splits   contiguous chunk ranges; one workgroup per (split, row tile, unit)
 // Each workgroup keeps an online softmax in the log2 domain (logits are
 // multiplied by log2(e)/sqrt(D) once) and writes (max, sum, unnormalised O).
+#include <type_traits>
+
 #include "mosaic_internal.h"
 #include "attend_reps_device.h"
 
@@ -228,28 +230,30 @@ __device__ __forceinline__ void combine_accumulate(const DeviceView &dv, size_t 
     }
 }
 
-// One output value of row r of a tile, with the representatives' part merged in, and the row's log-sum-exp.
-// Lr: normaliser of the output (the weights the value contraction used, bf16-rounded in the MFMA kernels); Xr: the same
-// sum over the unrounded fp32 weights, for the log-sum-exp; Mr: the row's reference (log2 domain).
-template <typename E, int D>
-__device__ __forceinline__ void combine_store(const DeviceView &dv, int u, int lc, int h, int tile, int r, int dg, int col, int Tq,
-                                              float o, float Lr, float Xr, float Mr, E *out, float *lse) {
+// N neighbouring output values (channels ch ..) of row r of a tile, with the representatives' part merged in, and the row's
+// log-sum-exp.  Lr: normaliser of the output (the weights the value contraction used, bf16-rounded in the MFMA kernels); Xr: the
+// same sum over the unrounded fp32 weights, for the log-sum-exp; Mr: the row's reference (log2 domain).
+template <typename E, int D, int N>
+__device__ __forceinline__ void combine_store(const DeviceView &dv, int u, int lc, int h, int tile, int r, int ch, int Tq,
+                                              float (&o)[N], float Lr, float Xr, float Mr, E *out, float *lse) {
     const int G = dv.G, Hq = dv.Hq;
     if (dv.aug_reps) {                            // one more partial: the representatives' part
         const size_t ae = (size_t)u * dv.nt_max + tile;
         const float ma = dv.aug_ml[ae * 2 * kRowTile + r], la = dv.aug_ml[ae * 2 * kRowTile + kRowTile + r];
-        const float oa = dv.aug_o[(ae * kRowTile + r) * D + dg * 32 + col];
+        const float *oa = dv.aug_o + (ae * kRowTile + r) * D + ch;
         const float Mn = fmaxf(Mr, ma);
         const float wa = Mr > -INFINITY ? exp2f(Mr - Mn) : 0.f, wb = ma > -INFINITY ? exp2f(ma - Mn) : 0.f;
-        o = o * wa + oa * wb;
+#pragma unroll
+        for (int i = 0; i < N; ++i) o[i] = o[i] * wa + oa[i] * wb;
         Lr = Lr * wa + la * wb;
         Xr = Xr * wa + la * wb;                   // (the representatives' weights are fp32)
         Mr = Mn;
     }
-    const int gr = tile * kRowTile + r, t = gr / G, g = gr % G;
+    const int gr = tile * kRowTile + r, t = gr / G, g = gr - t * G;
     const size_t orow = ((size_t)lc * Tq + t) * Hq + (size_t)h * G + g;
-    store_out<E>(out + orow * D + dg * 32 + col, Lr > 0.f ? o / Lr : 0.f);
-    if (dg == 0 && col == 0 && lse != nullptr)
+#pragma unroll
+    for (int i = 0; i < N; ++i) store_out<E>(out + orow * D + ch + i, Lr > 0.f ? o[i] / Lr : 0.f);
+    if (ch == 0 && lse != nullptr)
         lse[orow] = Xr > 0.f ? (Mr + log2f(Xr)) * 0.6931471805599453f : -INFINITY;
 }
 
@@ -317,86 +321,111 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
         const int rl = sg + 8 * j;                    // row inside this workgroup's share
         if (rl >= nr) continue;
         const int r = rbase + rl;
-        float o = 0.f;
+        float o[1] = {0.f};
 #pragma unroll
-        for (int q = 0; q < 8; ++q) o += red[q][rl][col];
-        combine_store<E, D>(dv, u, lc, h, 0, r, dg, col, Tq, o, L_sh[r], X_sh[r], M_sh[r], out, lse);
+        for (int q = 0; q < 8; ++q) o[0] += red[q][rl][col];
+        combine_store<E, D, 1>(dv, u, lc, h, 0, r, dg * 32 + col, Tq, o, L_sh[r], X_sh[r], M_sh[r], out, lse);
     }
 }
 
-// The merge for questions (NT > 1): many tiles, few splits each, so the chip is filled by workgroups and not by the loads
-// of one: a thread holds the sixteen rows of two splits at a time (32 registers), and several workgroups per CU hide each
-// other's latency.  The kernel above keeps 128 values per thread in flight for the one tile of a decode step and is limited
-// to two wavefronts per SIMD by them (256-token question, 448 tiles: 16.5 -> 14.2 us; 32 tokens on 28 layers, 1568 tiles:
-// 58 -> 40 us).  grid (D/32, NT, n_units), 256 threads;
-// same arithmetic, partial sums of a split group added in the same order.
-template <typename E, int D>
-__global__ __launch_bounds__(kBlock) void k_combine_question(DeviceView dv, int u0, int n_units, int Tq, int B, int even_groups,
-                                                             E *out, float *lse) {
-    const int dg = blockIdx.x, tile = blockIdx.y, uc = blockIdx.z, u = u0 + uc, NT = gridDim.y, tid = threadIdx.x;
+// The merge for questions (NT > 1).  It reads every partial once; what bounds it is the latency of those reads, which are
+// other compute units' stores.  A workgroup merges CW channels of one tile; its SG = BLK / (4 CW) (at most 1: BLK threads own
+// the tile's 16 x CW values) split groups take every SG-th split each.  A thread owns four channels of a row (16-byte loads; the
+// lanes of a row side by side) and keeps its rows' statistics itself, kMergeBatch splits of values and statistics in flight, so that
+// up to the exchange between split groups nothing is shared and no barrier is met.
+// Many tiles: CW = D, one split group, no LDS (32 tokens on 28 layers, 1568 tiles of 2.3 splits on average
+// 49 -> 21.5 us against a workgroup per 32 channels with its weights through LDS; 256 tokens, 448 tiles of 9 splits 15.7 -> 10.6).  Few tiles with many splits: 32 channels and eight split groups
+// (28 rows in 4 units, 64 splits 13.4 -> 8.3 us; fp32, 48 tiles of
+// 21 splits 6.0).
+// grid (D / CW, NT, n_units), BLK threads.
+constexpr int kMergeBatch = 8;
+template <typename E, int D, int CW, int BLK>
+__global__ __launch_bounds__(BLK) void k_combine_question(DeviceView dv, int u0, int n_units, int Tq, int B, int even_groups,
+                                                          E *out, float *lse) {
+    constexpr int TPS = 16 * CW / 4 < BLK ? 16 * CW / 4 : BLK, SG = BLK / TPS, RPT = 16 * CW / 4 / TPS;   // threads of a split group, groups, rows per thread
+    constexpr int LPR = CW / 4, RSTEP = TPS / LPR;          // lanes of a row, rows between a thread's rows
+    const int tile = blockIdx.y, uc = blockIdx.z, u = u0 + uc, NT = gridDim.y, tid = threadIdx.x;
     const int lc = uc / dv.Hkv, h = u % dv.Hkv, rows = min(kRowTile, Tq * dv.G - tile * kRowTile);
-    __shared__ float w_sh[512][kRowTile];          // (equal shares: at most 512)
-    __shared__ float pm[16][kRowTile], pl[16][kRowTile], px[16][kRowTile];
-    __shared__ float red[8][kRowTile][33];
-    const int sg = tid / 32, col = tid % 32;
-    const float *po = dv.part_o + e0 * kRowTile * D + dg * 32 + col;
-    float v[2][kRowTile];                        // splits sg and sg + 8 of the pass
-    auto load_pass = [&](int s0) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int s = min(s0 + sg + 8 * i, max(n_splits - 1, 0));
-#pragma unroll
-            for (int r = 0; r < kRowTile; ++r) v[i][r] = po[((size_t)s * kRowTile + min(r, rows - 1)) * D];
-        }
-    };
-    load_pass(0);
-    const int row = tid % 16, part = tid / 16;
-    const float *ml = dv.part_ml + e0 * kMlRows * kRowTile + row;
-    float mx = -INFINITY;
-    for (int s = part; s < n_splits; s += 16) mx = fmaxf(mx, ml[(size_t)s * kMlRows * kRowTile]);
-    pm[part][row] = mx;
-    __syncthreads();
-    float M = -INFINITY;
-#pragma unroll
-    for (int p = 0; p < 16; ++p) M = fmaxf(M, pm[p][row]);
-    float ls = 0.f, xs = 0.f;
-    for (int s = part; s < n_splits; s += 16) {
-        const float *m = ml + (size_t)s * kMlRows * kRowTile;
-        const float w = M > -INFINITY ? exp2f(m[0] - M) : 0.f;
-        w_sh[s][row] = w;
-        ls += w * m[kRowTile];
-        xs += w * m[2 * kRowTile];
+    const int sg = tid / TPS, row0 = tid % TPS / LPR, ch = blockIdx.x * CW + tid % LPR * 4;
+    int n_splits, base;                          // n_splits is 0 if the unit retrieved nothing
+    if (even_groups > 0) {
+        const EvenShare sh = even_share<true, sizeof(E) == 4>(dv.n_sel + u0, n_units, ChunkSize<sizeof(E) == 4>(dv), even_groups, uc);
+        n_splits = sh.splits();
+        base = sh.base();
+    } else {
+        const SplitSlot slot = split_slot<true>(dv.n_sel + u0, n_units, B, uc);
+        n_splits = slot.S;
+        base = slot.base;
     }
-    pl[part][row] = ls;
-    px[part][row] = xs;
-    __syncthreads();
-    float acc[kRowTile];
+    const size_t e0 = (size_t)base * NT + (size_t)tile * n_splits;
+    const float *po = dv.part_o + (e0 * kRowTile + row0) * D + ch, *ml = dv.part_ml + e0 * kMlRows * kRowTile + row0;
+    float M[RPT], L[RPT], X[RPT], acc[RPT][4];
 #pragma unroll
-    for (int r = 0; r < kRowTile; ++r) acc[r] = 0.f;
-    for (int s0 = 0; s0 < n_splits; s0 += 16) {
-        if (s0 > 0) load_pass(s0);
+    for (int j = 0; j < RPT; ++j) {
+        M[j] = -INFINITY; L[j] = 0.f; X[j] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int s = s0 + sg + 8 * i;
-            if (s < n_splits) {
+        for (int c = 0; c < 4; ++c) acc[j][c] = 0.f;
+    }
+    const int last = n_splits - 1;
+    for (int s0 = sg; s0 < n_splits; s0 += SG * kMergeBatch) {
+        float4 v[RPT][kMergeBatch];
+        float mm[RPT][kMergeBatch], ll[RPT][kMergeBatch], xx[RPT][kMergeBatch];
 #pragma unroll
-                for (int r = 0; r < kRowTile; ++r) acc[r] += w_sh[s][r] * v[i][r];
+        for (int i = 0; i < kMergeBatch; ++i) {
+            const int s = min(s0 + SG * i, last);           // (clamped: every load is unconditional)
+#pragma unroll
+            for (int j = 0; j < RPT; ++j) {
+                v[j][i] = *reinterpret_cast<const float4 *>(po + ((size_t)s * kRowTile + RSTEP * j) * D);
+                const float *p = ml + (size_t)s * kMlRows * kRowTile + RSTEP * j;
+                mm[j][i] = p[0]; ll[j][i] = p[kRowTile]; xx[j][i] = p[2 * kRowTile];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            float mx = M[j];
+#pragma unroll
+            for (int i = 0; i < kMergeBatch; ++i) mx = fmaxf(mx, mm[j][i]);
+            const float a = M[j] > -INFINITY ? exp2f(M[j] - mx) : 0.f;
+            M[j] = mx;
+            L[j] *= a; X[j] *= a;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[j][c] *= a;
+#pragma unroll
+            for (int i = 0; i < kMergeBatch; ++i) {
+                if (s0 + SG * i <= last) {                  // (the same for a whole split group)
+                    const float w = mx > -INFINITY ? exp2f(mm[j][i] - mx) : 0.f;
+                    L[j] += w * ll[j][i]; X[j] += w * xx[j][i];
+                    acc[j][0] += w * v[j][i].x; acc[j][1] += w * v[j][i].y; acc[j][2] += w * v[j][i].z; acc[j][3] += w * v[j][i].w;
+                }
             }
         }
     }
+    if constexpr (SG > 1) {
+        static_assert(RPT == 1, "split groups exchange one row per thread");
+        __shared__ float4 o_sh[SG][TPS];
+        __shared__ float m_sh[SG][16], l_sh[SG][16], x_sh[SG][16];
+        o_sh[sg][tid % TPS] = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
+        if (tid % LPR == 0) { m_sh[sg][row0] = M[0]; l_sh[sg][row0] = L[0]; x_sh[sg][row0] = X[0]; }
+        __syncthreads();
+        if (sg != 0) return;
+        float mx = -INFINITY;
 #pragma unroll
-    for (int r = 0; r < kRowTile; ++r) red[sg][r][col] = acc[r];
-    __syncthreads();
+        for (int g = 0; g < SG; ++g) mx = fmaxf(mx, m_sh[g][row0]);
+        M[0] = mx; L[0] = 0.f; X[0] = 0.f;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int r = sg + 8 * j;
-        if (r >= rows) continue;
-        float o = 0.f, Lr = 0.f, Xr = 0.f, Mr = -INFINITY;
+        for (int c = 0; c < 4; ++c) acc[0][c] = 0.f;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) o += red[q][r][col];
+        for (int g = 0; g < SG; ++g) {
+            const float mg = m_sh[g][row0], w = mx > -INFINITY ? exp2f(mg - mx) : 0.f;
+            const float4 o = o_sh[g][tid];
+            L[0] += w * l_sh[g][row0]; X[0] += w * x_sh[g][row0];
+            acc[0][0] += w * o.x; acc[0][1] += w * o.y; acc[0][2] += w * o.z; acc[0][3] += w * o.w;
+        }
+    }
 #pragma unroll
-        for (int p = 0; p < 16; ++p) { Lr += pl[p][r]; Xr += px[p][r]; Mr = fmaxf(Mr, pm[p][r]); }
-        combine_store<E, D>(dv, u, lc, h, tile, r, dg, col, Tq, o, Lr, Xr, Mr, out, lse);
+    for (int j = 0; j < RPT; ++j) {
+        const int r = row0 + RSTEP * j;
+        if (r < rows) combine_store<E, D, 4>(dv, u, lc, h, tile, r, ch, Tq, acc[j], L[j], X[j], M[j], out, lse);
     }
 }
 
@@ -419,14 +448,17 @@ hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int 
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
     const int B = n_units * n_splits;
     if (NT > 1) {
-        const dim3 gq(dv.D / 32, NT, n_units);
-        if (dv.esize == 4) {
-            if (dv.D == 64) k_combine_question<float, 64><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, (float *)out, lse);
-            else k_combine_question<float, 128><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, (float *)out, lse);
-        } else {
-            if (dv.D == 64) k_combine_question<unsigned short, 64><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, (unsigned short *)out, lse);
-            else k_combine_question<unsigned short, 128><<<gq, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, (unsigned short *)out, lse);
-        }
+        // A workgroup per tile where that alone is one per CU or a unit has one batch of splits on average (question of 4
+        // tokens on 28 layers, 224 tiles of 2.3 splits: narrow workgroups take 16.9 us, see the kernel).
+        const bool wide = (long long)NT * n_units >= 256 || n_splits <= kMergeBatch;
+        const dim3 gq(wide ? 1 : dv.D / 32, NT, n_units);
+        auto go = [&](auto kern, int blk, auto *o) { kern<<<gq, blk, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, o, lse); };
+        auto pick = [&](auto *o) {
+            using E = std::remove_pointer_t<decltype(o)>;
+            if (dv.D == 64) wide ? go(k_combine_question<E, 64, 64, 256>, 256, o) : go(k_combine_question<E, 64, 32, 1024>, 1024, o);
+            else wide ? go(k_combine_question<E, 128, 128, 256>, 256, o) : go(k_combine_question<E, 128, 32, 1024>, 1024, o);
+        };
+        if (dv.esize == 4) pick((float *)out); else pick((unsigned short *)out);
         return hipGetLastError();
     }
     // One row tile (a decode step) of a few units: up to eight workgroups share a tile's rows, as long as the launch
