@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
     const int dq = __builtin_amdgcn_readfirstlane(stride * kGroup / T), dr = __builtin_amdgcn_readfirstlane(stride * kGroup % T);
     int cp = __builtin_amdgcn_readfirstlane(first * kGroup / T), cr = __builtin_amdgcn_readfirstlane(first * kGroup % T);
     const int inv = 65536 / T + 1;  // floor(x / T) = (x * inv) >> 16 for x < T + 16 <= 32
-    int id = 0, at = 0;             // this lane's token (token n of the cursor's group): page id, ~offset if there is none
+    int id = 0, at = 0;             // this lane's token (token n of the cursor's group): page id, ~0 for the offset if there is none
     auto lookup = [&]() {           // (past the last group: the last page again)
         int off = cr + n;
         const int d = T >= kGroup ? (off >= T ? 1 : 0) : (off * inv) >> 16;
@@ -76,7 +76,11 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
         if (cr >= T) { cr -= T; ++cp; }
         cp = min(cp, n_sel);
     };
-    auto row = [&]() { return at < 0 ? ~(id * T) : id * T + at; };
+    const size_t kstep = k_piece<float>(1, 0, T);
+    auto issue = [&](F32Operands<D> &o) {        // the cursor's group (before the next lookup)
+        const float *kr = kb + (size_t)id * T * D + k_piece<float>(0, max(at, 0), T) + 4 * g;
+        f32_issue<D, STREAM>(kr, kstep, vb, at < 0 ? ~(id * T) : id * T + at, g, n, o);
+    };
 
     const float sl2 = 1.4426950408889634f / sqrtf((float)D);
     f32v4 qf[R][D / 16], acc[R][D / 16];
@@ -92,24 +96,21 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
     F32Operands<D> oa, ob;
     if (n_my > 0) {                 // then n_sel > 0
         lookup();
-        const int r0 = row();
+        issue(oa);
         lookup();
-        f32_issue<D, STREAM>(kb, vb, r0, g, n, oa);
         int i = 0;
         for (; i + 2 < n_my; i += 2) {
-            int rn = row();
+            issue(ob);
             lookup();
-            f32_issue<D, STREAM>(kb, vb, rn, g, n, ob);
             __builtin_amdgcn_sched_barrier(0);
             f32_step<D, R>(oa, qf, acc, m, l);
-            rn = row();
+            issue(oa);
             lookup();
-            f32_issue<D, STREAM>(kb, vb, rn, g, n, oa);
             __builtin_amdgcn_sched_barrier(0);
             f32_step<D, R>(ob, qf, acc, m, l);
         }
         if (i + 2 == n_my) {
-            f32_issue<D, STREAM>(kb, vb, row(), g, n, ob);
+            issue(ob);
             __builtin_amdgcn_sched_barrier(0);
             f32_step<D, R>(oa, qf, acc, m, l);
             f32_step<D, R>(ob, qf, acc, m, l);

@@ -38,13 +38,13 @@ template <bool STREAM> __device__ __forceinline__ f32v4 ld_f32v4(const float *p)
     return STREAM ? __builtin_nontemporal_load(reinterpret_cast<const f32v4 *>(p)) : *reinterpret_cast<const f32v4 *>(p);
 }
 
-// Issues the operand loads of one group.  row_k: row of token n in the [rows][D] arrays kb and vb,
-// or ~(some valid row) if the token does not exist (it is loaded all the same and gets weight 0).
+// Issues the operand loads of one group.  kr: channels 4g of token n's key, from where 16 channels further on are kstep floats;
+// row: the token's row in the [rows][D] array vb, or ~(some valid row) if it does not exist (it is loaded all the same and gets
+// weight 0).
 template <int D, bool STREAM>
-__device__ __forceinline__ void f32_issue(const float *kb, const float *vb, int row_k, int g, int n, F32Operands<D> &o) {
-    const float *kr = kb + (size_t)(row_k < 0 ? ~row_k : row_k) * D + 4 * g;
+__device__ __forceinline__ void f32_issue(const float *kr, size_t kstep, const float *vb, int row_k, int g, int n, F32Operands<D> &o) {
 #pragma unroll
-    for (int j = 0; j < D / 16; ++j) o.k[j] = ld_f32v4<STREAM>(kr + 16 * j);
+    for (int j = 0; j < D / 16; ++j) o.k[j] = ld_f32v4<STREAM>(kr + kstep * j);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         o.row[v] = __shfl(row_k, 4 * g + v, 64);

@@ -162,9 +162,12 @@ __device__ __forceinline__ void issue_chunk(const unsigned short *kpage, const u
 #pragma unroll
     for (int tau = 0; tau < 2; ++tau) {
         const int tok = min(t0 + 8 * (n / 4) + 4 * tau + (n % 4), T - 1);
-        const unsigned short *kr = kpage + (size_t)tok * D + 8 * g;
+        const unsigned short *kr = kpage + k_piece<unsigned short>(0, tok, T) + 8 * g;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) kf[tau * KK + kk] = STREAM ? ld_frag_stream(kr + 32 * kk) : ld_frag(kr + 32 * kk);
+        for (int kk = 0; kk < KK; ++kk) {            // channels 32 kk .. + 31 are piece kk
+            const unsigned short *kp = kr + k_piece<unsigned short>(kk, 0, T);
+            kf[tau * KK + kk] = STREAM ? ld_frag_stream(kp) : ld_frag(kp);
+        }
     }
     const unsigned short *vr = vchunk + n * 32 + 8 * g;
 #pragma unroll

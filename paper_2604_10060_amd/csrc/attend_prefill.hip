@@ -107,7 +107,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     constexpr bool kWhole = KW % NW == 0;          // every wave loads keys and values (else LPW = 1: one or the other)
     static_assert(kWhole || LPW == 1, "load schedule");
     auto is_key = [&](int i) { return kWhole ? i < KW / NW : wave < KW; };
-    int ld_tok[LPW], ld_off[LPW], ld_koff[LPW], ld_dst[LPW];   // token within the chunk (keys); element offset (in the row / in the chunk); LDS byte offset in the slot
+    // token within the chunk (keys); offset in 16 bytes (of the piece, which k_piece() places / in the value chunk); LDS byte
+    // offset in the slot
+    int ld_tok[LPW], ld_dst[LPW];
+    unsigned ld_off[LPW], ld_koff[LPW];
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
         const int num = wave + NW * i;
@@ -116,13 +119,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
             const int seg = phys ^ ((row / KRP) % KSEG);
             const int tau = row / 16, rem = row % 16;
             ld_tok[i] = 8 * (rem / 4) + 4 * tau + rem % 4;
-            ld_off[i] = seg * 8;
-            ld_koff[i] = ld_tok[i] * D + seg * 8;
+            ld_off[i] = (unsigned)(seg / 4 * T) * 4 + seg % 4;
+            ld_koff[i] = ld_off[i] + 4 * ld_tok[i];
             ld_dst[i] = num * 1024;
         } else {
             const int P = (num - KW) * 64 + lane, row = P / 4, phys = P % 4;
             ld_tok[i] = 0; ld_koff[i] = 0;
-            ld_off[i] = row * kChunk + (phys ^ ((row / 4) % 4)) * 8;
+            ld_off[i] = row * (kChunk / 8) + (phys ^ ((row / 4) % 4));
             ld_dst[i] = (num - KW) * 1024;
         }
     }
@@ -200,23 +203,23 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
         unsigned char *const dst = prefill_lds + kc.slot * KBYTES;
         // (scalar base, 32-bit lane offset: the chunk's first token goes into the base, and only a page's
         // ragged last chunk clamps token numbers)
-        const unsigned short *const kp = kc.p + (size_t)t0 * D;
+        const uint4 *const kp = reinterpret_cast<const uint4 *>(kc.p + k_piece<unsigned short>(0, t0, T));
         const bool whole = t0 + kChunk <= T;           // wave-uniform
 #pragma unroll
         for (int i = 0; i < LPW; ++i)
             if (is_key(i)) {
-                const unsigned off = whole ? (unsigned)ld_koff[i] : (unsigned)((min(t0 + ld_tok[i], T - 1) - t0) * D + ld_off[i]);
+                const unsigned off = whole ? ld_koff[i] : (unsigned)(min(t0 + ld_tok[i], T - 1) - t0) * 4 + ld_off[i];
                 __builtin_amdgcn_global_load_lds((gptr_t)(kp + off), (lptr_t)(dst + ld_dst[i]), 16, 0, 0);
             }
         advance(kc, kbase, dv.kpage);
     };
     auto fetch_v = [&]() {
-        const unsigned short *vp = vc.p + (size_t)vc.cc * D * kChunk;
+        const uint4 *vp = reinterpret_cast<const uint4 *>(vc.p + (size_t)vc.cc * D * kChunk);
         unsigned char *const dst = prefill_lds + NS * KBYTES + vc.slot * VBYTES;
 #pragma unroll
         for (int i = 0; i < LPW; ++i)
             if (!is_key(i))
-                __builtin_amdgcn_global_load_lds((gptr_t)(vp + (unsigned)ld_off[i]), (lptr_t)(dst + ld_dst[i]), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((gptr_t)(vp + ld_off[i]), (lptr_t)(dst + ld_dst[i]), 16, 0, 0);
         advance(vc, vbase, dv.vpage);
     };
     // The loads are issued as the sequence K0 | V0 K1 | V1 K2 | V2 K3 | ...: a wave issues LPW loads per

@@ -103,7 +103,11 @@ __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_
     const bool host = dv.tier == MOSAIC_TIER_HOST;
     const size_t spage = host ? (size_t)(f % dv.SN) * dv.U + u : (size_t)u * dv.PU + f;
     const E *src = k_in + in_page;
-    E *dst = reinterpret_cast<E *>(kdst_base) + spage * (size_t)T * D;
+    // (a thread's eight channels lie in one piece of a row)
+    const bool pieces = sizeof(E) == 4 || dv.v_transposed;
+    E *dst = reinterpret_cast<E *>(kdst_base) + spage * (size_t)T * D +
+             (pieces ? k_piece<E>(cg * 8 / kPiece<E>, 0, T) + cg * 8 % kPiece<E> : (size_t)cg * 8);
+    const int dstep = pieces ? kPiece<E> : D;          // elements from a token to the next
     double acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.0;
@@ -119,7 +123,7 @@ __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_
             if (t0 + k * RP < T) {
                 float v[8];
                 Elem<E>::unpack(x[k], v);
-                Elem<E>::store(dst + (size_t)(t0 + k * RP) * D + cg * 8, x[k]);
+                Elem<E>::store(dst + (size_t)(t0 + k * RP) * dstep, x[k]);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) acc[i] += (double)v[i];
             }

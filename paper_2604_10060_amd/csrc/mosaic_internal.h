@@ -35,7 +35,8 @@ struct DeviceView {
     //   k_store [U][PU] K pages, v_store [U][PU] V pages.
     // HBM tier: page p = frame id (arrival order).  Host tier: page p = a slot of the unit's GPU
     //   cluster cache (slots are handed out frame by frame; a cluster's frames need not be adjacent).
-    // A K page is [T][D]; a V page is [T][D] or, for the MFMA path, [Tp/32][D][32].
+    // A K page is kept in pieces of 64 bytes of a row, [pieces of a row][T][64 bytes] (k_piece() below), or [T][D] for the
+    //   bf16 vector-ALU kernel; a V page is [T][D] or, for the bf16 MFMA path, [Tp/32][D][32].
     char *k_store;
     char *v_store;
     size_t kpage, vpage;           // bytes of one K / V page
@@ -238,6 +239,13 @@ __device__ __forceinline__ const char *k_page(const DeviceView &dv, int u, int p
 __device__ __forceinline__ const char *v_page(const DeviceView &dv, int u, int p) {
     return dv.v_store + (size_t)u * dv.v_ustride + (size_t)p * dv.vpage;
 }
+// Element offset of piece j, token t in a K page of T tokens.  A wavefront's key operand is 64 bytes from each of 16 rows: from
+// [T][D] that is 16 half cache lines per load, and a compute unit then takes in 34 GB/s where whole lines give it 44 (one of
+// 64 active ones, half of its loads keys, half values).  In pieces, the rows of an operand that are neighbours in the page are
+// neighbours in memory.  It shows where a few units' workgroups run on while the others are done: fused decode step of a layer
+// over 16 MB 19.4 -> 18.4 us; with the whole chip reading (118 MB a launch) the two are equal.
+template <typename E> constexpr int kPiece = 64 / (int)sizeof(E);
+template <typename E> __device__ __forceinline__ size_t k_piece(int j, int t, int T) { return ((size_t)j * T + t) * kPiece<E>; }
 __device__ __forceinline__ float bf16_to_f32(unsigned short h) {
     return __uint_as_float(((unsigned int)h) << 16);
 }
