@@ -92,7 +92,7 @@ typedef struct {
                                      cached per unit, least recently used evicted first; 0 -> 0.10 */
     int32_t decode_fused_max_mib; /* (any tier; sits here for alignment) mosaic_decode_step runs its single
                                      fused kernel (equal splits) while the expected K/V volume of the step is
-                                     at most this many MiB; 0 -> 48; -2: always the two calls; -1: never that
+                                     at most this many MiB (fp32: half); 0 -> 32; -2: always the two calls; -1: never that
                                      kernel but, wherever it applies, the one-launch form with proportional
                                      splits (an option kept for measurement: slower than the two calls) */
     void *host_arena;             /* HOST pointer to pinned (hipHostMalloc) memory, 256-byte aligned,
@@ -329,15 +329,15 @@ int32_t mosaic_attend_static(mosaic_ctx *ctx, int32_t layer, const void *q_dev, 
 /* One decode step in one call: mosaic_retrieve(layer, q) followed by mosaic_attend(layer, q) --
  * same arguments, errors, selection left behind (ids, scores, page list: the observers and a
  * later mosaic_attend see it) and the same output up to the order in which fp32 partial sums are
- * merged.  Where it applies -- MOSAIC_TIER_HBM, bf16 MFMA attention, layer >= 0, at most 16 query
- * rows per KV head (n_q_tokens * Hq/Hkv <= 16), n_clusters <= 256, maintainer, augmentation and
+ * merged.  Where it applies -- MOSAIC_TIER_HBM, bf16 MFMA attention or fp32 pages, layer >= 0, at most 16 query
+ * rows per KV head (n_q_tokens * Hq/Hkv <= 16), n_clusters <= 256, maintainer and
  * nested index off, and an expected K/V volume of the step (frames * top_k / n_clusters pages per
- * KV head) of at most decode_fused_max_mib (default 48) MiB, i.e. a step that is bound by launch and memory latency rather than
+ * KV head) of at most decode_fused_max_mib (default 32; fp32: half of it) MiB, i.e. a step that is bound by launch and memory latency rather than
  * by bandwidth -- the selection and the attention over the selected clusters run in ONE kernel
  * (every attention workgroup repeats its unit's selection for itself, which is cheaper than a
  * launch boundary and the dependent loads after it; KV splits are then equal per unit instead of
  * proportional to the retrieved size).  Everywhere else the call simply makes the two calls.
- * With decode_fused_max_mib = -1, under the same conditions otherwise (and n_kv_heads <= 64), the
+ * With decode_fused_max_mib = -1, under the same conditions otherwise (bf16, no augmentation, n_kv_heads <= 64), the
  * selection moves into the attention launch but is made once per unit: the launch's first Hkv
  * workgroups select for one KV head each and publish the result through memory, all workgroups
  * wait for that (a bounded wait on workgroups that are started first and wait for nobody;

@@ -19,6 +19,8 @@ namespace {
 
 thread_local std::string g_create_err = "";
 
+constexpr long long kCachedStore = 768ll << 20;      // see kv_beyond_caches()
+
 size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // Attention partials for callers that cannot allocate (mosaic_attend_static): one buffer per GPU,
@@ -61,7 +63,7 @@ struct Layout {
     size_t host_k, host_v, host_sel, host_nsel, host_ids, host_nids, host_moves, host_nmoves, host_assign, host_dest,
         host_assign_full, host_cnt, host_nbuf, host_buf_frame, host_buf_owner, host_resident, host_total;   // offsets into the pinned host arena
     long long part_entries;
-    int Tp, impl, v_transposed;
+    int Tp, impl, v_transposed, k_pieces;
     int nt_max;
     int c_init, split_iters, buf_max, W;   // maintainer (c_init = C, buf_max = 0 when off); warm-up frames
     // host tier geometry
@@ -172,6 +174,8 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
         L.PU = (int)std::max<long long>(cp, 1);
         L.SN = std::max(W, 128);                // staging ring: the warm-up, or two batches (one being offloaded, one being staged)
     }
+    // (a store that kv_beyond_caches() may find beyond the caches keeps its keys in [T][D])
+    L.k_pieces = L.v_transposed && (long long)L.PU * (long long)U * (long long)(L.kpage + L.vpage) <= kCachedStore;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     L.k_store = take(U * (size_t)L.PU * L.kpage);     // (host tier: PU = page slots of the cluster cache)
@@ -269,62 +273,53 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
     return L;
 }
 
-// KV splits per unit for one attend call, bounded by the partial-buffer capacity (decode steps; questions that
-// choose_even_groups() leaves to it).
+// KV splits per unit for a decode step (and for a question with the bf16 vector-ALU kernel), bounded by the partial-buffer
+// capacity.
 int choose_splits(const mosaic_ctx *ctx, int n_units, int Tq, long long part_entries) {
     const DeviceView &dv = ctx->dv;
     const long long NT = ((long long)Tq * dv.G + kRowTile - 1) / kRowTile;
-    const bool mfma = ctx->impl == MOSAIC_ATTEND_MFMA;
-    constexpr int pw = kPrefillWaves;
-    const int tiles = mfma ? pw * kPrefillTiles : dv.esize == 4 ? kFp32Tiles : 1;      // row tiles per workgroup
-    const long long row_blocks = (NT + tiles - 1) / tiles;
     const long long est_pages = std::max<long long>(1, (ctx->n_frames * dv.k + dv.C - 1) / dv.C);
     const long long est_chunks = est_pages * dv.chunks_per_page;
-    long long s;
-    if (NT > 1 && mfma) {
-        // MFMA-bound multi-tile launches: every split writes 16 x D partial rows per
-        // tile that the combine kernel reads back, so only as many splits as fill the
-        // chip's two resident workgroups per CU once (more splits raise the attention
-        // kernel's rate a little but cost more in the combine), each with at least 8 chunks
-        s = (2048 / pw + n_units * row_blocks - 1) / (n_units * row_blocks);
-        s = std::min(s, std::max<long long>(1, est_chunks / 8));
-    } else {
-        // bandwidth/latency-bound: cover the chip several times over (7 x 256 workgroups:
-        // measured on the all-layers launch of config 2, 1568-1792 workgroups are 3 % faster
-        // than 2128), at least 4 chunks (one per wavefront) per workgroup
-        s = (1792 + n_units * row_blocks - 1) / (n_units * row_blocks);
-        s = std::min(s, std::max<long long>(1, est_chunks / 4));
-    }
+    // bandwidth/latency-bound: cover the chip several times over (7 x 256 workgroups: measured on an all-layers launch of
+    // 112 units, 1568-1792 workgroups are 3 % faster than 2128), at least 4 chunks (one per wavefront) per workgroup,
+    // or up to two workgroups per CU with at least one.  (What a question retrieves is expected from the mean cluster, but it
+    // is about the large ones, and of units that retrieve ten times the mean the last workgroups then run on alone.  Two calls, us
+    // a layer with a chunk per wavefront / per workgroup: 15 MiB expected, 28 MiB read, 21.2 / 19.8; 1 MiB 23.1 / 18.3; 4.7 MiB
+    // fp32, 19 to 62 MiB read, 31.9 / 23.3.  More than two workgroups per CU: 22 MiB fp32 in 12 units 25.3 / 29.2 with 62 each.)
+    long long s = (1792 + n_units * NT - 1) / (n_units * NT);
+    s = std::min(s, std::max({1ll, est_chunks / 4, NT > 1 ? 1 : std::min<long long>(est_chunks, 512 / n_units)}));
     s = std::min<long long>(s, kMaxSplits);
     s = std::min(s, std::max<long long>(1, part_entries / (n_units * NT)));
     return (int)std::max<long long>(1, s);
 }
 
-// Equal shares of a question of more than one row tile (even_share), 0: choose_splits() instead.  As many as fill the chip
-// once with the workgroups that its registers hold (bf16: two per CU, fp32: two at head_dim 64, else one), so that
-// all end together.  A split count per unit leaves units of unequal size with unequal shares, and a count that does not fill
-// the chip a whole number of times leaves the last workgroups alone on it.  Attention launch, per unit / in equal shares:
-// 32 tokens on 28 layers (112 units, two splits) 941 / 584 us; 256 tokens in 4 units (eight splits) 312 / 271 us; fp32, 21
-// tokens in 8 units of D = 64 28 / 20.5 us; whole call, fp32, 32 tokens on 10 layers 1571 / 1210 us.
+// Equal shares of a question of more than one row tile (even_share).  A split count per unit leaves units of unequal size with
+// unequal shares, and a count that does not fill the chip a whole number of times leaves the last workgroups alone on it.  Attention
+// launch, per unit / in equal shares: 32 tokens on 28 layers (112 units, two splits) 941 / 584 us; 256 tokens in 4 units (eight
+// splits) 312 / 271 us; fp32, 21 tokens in 8 units of D = 64 28 / 20.5 us.
+// A workgroup walks over the units of a group, as many groups as fill the chip once with the workgroups that its registers hold
+// (bf16: two per CU, fp32: two at head_dim 64, else one), so that all end together; or it takes what one group has of one
+// unit, which spares short shares the second unit's start (query, first pages, a partial: about as long as kStart chunks), with
+// fewer and larger groups, since those workgroups too are to be on the chip at once.  Whole calls, walking / by unit: 44 tokens
+// over 3 MB in 20 units 48.7 / 43.2 us, 53 tokens over 5 MB 42.4 / 41.0; fp32 100 tokens over 34 units 369 / 840, 51 tokens over 21 MB in
+// 72 units 97.4 / 108.
 // A share has at least 4 chunks (8 instead: 3 tokens in 4 units over 3 MB of pages 33.9 -> 37.1 us a call) and beyond 256
 // shares 8 (4 instead: 12 tokens over 125 MB 60.2 -> 62.7 us a call: the merge reads what more shares write).
-// Where the partial buffer holds fewer shares than the other scheme would use splits, that is the better one.
-int choose_even_groups(const mosaic_ctx *ctx, int n_units, int Tq, long long part_entries) {
+Shares choose_shares(const mosaic_ctx *ctx, int n_units, int Tq, long long part_entries) {
     const DeviceView &dv = ctx->dv;
     const long long NT = ((long long)Tq * dv.G + kRowTile - 1) / kRowTile;
     const bool fp32 = dv.esize == 4;
-    if (NT <= 1 || !(fp32 || ctx->impl == MOSAIC_ATTEND_MFMA)) return 0;
+    const long long kStart = fp32 ? 8 : 4;
     const long long tiles = fp32 ? kFp32Tiles : kPrefillWaves * kPrefillTiles, rb = (NT + tiles - 1) / tiles;
     const long long est_pages = std::max<long long>(1, (ctx->n_frames * dv.k + dv.C - 1) / dv.C);
     const long long chunks = n_units * (fp32 ? (est_pages * dv.T + kGroup - 1) / kGroup : est_pages * dv.chunks_per_page);
-    long long g = std::max<long long>(1, (fp32 && dv.D == 128 ? 256 : 512) / rb);
-    g = std::min(g, std::max({1ll, std::min(chunks / 4, 256ll), chunks / 8}));
-    const long long fit = part_entries / NT - (n_units - 1);
-    if (fit < g) {
-        g = fit;
-        if (g < (long long)n_units * choose_splits(ctx, n_units, Tq, part_entries)) return 0;
-    }
-    return (int)g;
+    const long long fit = std::max<long long>(1, part_entries / NT - (n_units - 1));
+    const long long room = std::max<long long>(1, (fp32 && dv.D == 128 ? 256 : 512) / rb);      // groups on the chip at once
+    const long long most = std::min(fit, std::max({1ll, std::min(chunks / 4, 256ll), chunks / 8}));
+    const long long gw = std::min(room, most), gs = std::max(1ll, std::min(room - (n_units - 1), most));
+    const long long t_walk = (chunks + gw - 1) / gw + 2 * kStart;
+    const long long t_slot = std::max((chunks + gs - 1) / gs, 1ll) * std::max(1ll, (gs + n_units - 1 + room - 1) / room) + kStart;
+    return t_walk < t_slot ? Shares{(int)gw, true} : Shares{(int)gs, false};
 }
 
 __global__ __launch_bounds__(256) void k_calibration_copy(uint4 *dst, const uint4 *src, size_t n16) {
@@ -431,7 +426,7 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
     dv.G = dv.Hq / dv.Hkv; dv.D = cfg->head_dim; dv.T = cfg->tokens_per_frame; dv.Tp = L.Tp;
     dv.F = cfg->max_frames; dv.C = cfg->n_clusters; dv.k = cfg->top_k; dv.U = dv.L * dv.Hkv;
     dv.esize = cfg->kv_dtype == MOSAIC_FP32 ? 4 : 2;
-    dv.v_transposed = L.v_transposed;
+    dv.v_transposed = L.v_transposed ? 1 + L.k_pieces : 0;
     dv.chunks_per_page = (dv.T + kChunk - 1) / kChunk;
     char *base = (char *)cfg->dev_arena;
     dv.k_store = base + L.k_store; dv.v_store = base + L.v_store;
@@ -1100,7 +1095,7 @@ static bool kv_beyond_caches(const mosaic_ctx *ctx) {
     // (host tier: what the kernels read is the GPU cluster cache, PU pages per unit)
     const long long pages = ctx->host ? (long long)dv.PU : ctx->n_frames;
     const long long stored = pages * (long long)dv.U * (long long)(dv.kpage + dv.vpage);
-    return stored > (768ll << 20);
+    return stored > kCachedStore;
 }
 
 // Profiling: sum the kernel times of the event pairs used so far into prof_ms (waits for the
@@ -1132,6 +1127,16 @@ static hipError_t take_profile_events(mosaic_ctx *ctx, hipEvent_t *ev0, hipEvent
     return hipSuccess;
 }
 
+// Global representatives (Sec. V-C): the value sums, where the clustering changed since they were formed.  Their attention
+// partial is computed by extra workgroups of the attention launch.  (Its own kernel cost ~8 us per decode step; its own
+// stream, with fork/join events, more.)
+static hipError_t refresh_value_reps(mosaic_ctx *ctx, const DeviceView &dv) {
+    if (!dv.aug_reps || ctx->rv_epoch == ctx->epoch) return hipSuccess;
+    const hipError_t e = launch_value_reps(dv, (int)ctx->n_frames, ctx->stream);
+    if (e == hipSuccess) ctx->rv_epoch = ctx->epoch;
+    return e;
+}
+
 // Body of mosaic_attend and mosaic_attend_static: `dv` is the context's view with the partial
 // buffers the kernels are to use (the arena's, or the static scratch); `timed`: attach the
 // profiling events when profiling is on.
@@ -1152,8 +1157,10 @@ static int attend_with(mosaic_ctx *ctx, const DeviceView &dv, int32_t layer, con
                  (long long)nu * NT, dv.part_entries);
         return fail(ctx, MOSAIC_ECAPACITY, b);
     }
-    const int even = choose_even_groups(ctx, nu, n_q_tokens, dv.part_entries);
-    const int S = even > 0 ? (even + nu - 1) / nu : choose_splits(ctx, nu, n_q_tokens, dv.part_entries);
+    // (the bf16 vector-ALU kernel has splits per unit at any size)
+    const bool by_share = NT > 1 && (ctx->impl == MOSAIC_ATTEND_MFMA || dv.esize == 4);
+    const Shares shares = by_share ? choose_shares(ctx, nu, n_q_tokens, dv.part_entries) : Shares{};
+    const int S = by_share ? (shares.groups + nu - 1) / nu : choose_splits(ctx, nu, n_q_tokens, dv.part_entries);
     hipError_t e;
     if (ctx->host) {
         if (layer < 0) return fail(ctx, MOSAIC_EINVAL, "the host tier attends one layer per call");
@@ -1162,21 +1169,14 @@ static int attend_with(mosaic_ctx *ctx, const DeviceView &dv, int32_t layer, con
     }
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (timed && (e = take_profile_events(ctx, &ev0, &ev1)) != hipSuccess) return fail_hip(ctx, e, "kernel timing");
-    if (dv.aug_reps && ctx->rv_epoch != ctx->epoch) {
-        // global representatives (Sec. V-C): the clustering changed since the value sums were formed.
-        // Their attention partial is computed by extra workgroups of the attention launch below.
-        // (Its own kernel cost ~8 us per decode step; its own stream, with fork/join events, more.)
-        if ((e = launch_value_reps(dv, (int)ctx->n_frames, ctx->stream)) != hipSuccess)
-            return fail_hip(ctx, e, "value representatives launch");
-        ctx->rv_epoch = ctx->epoch;
-    }
+    if ((e = refresh_value_reps(ctx, dv)) != hipSuccess) return fail_hip(ctx, e, "value representatives launch");
     e = ctx->impl == MOSAIC_ATTEND_MFMA
-            ? launch_attend_mfma(dv, u0, nu, q_dev, n_q_tokens, S, even, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
+            ? launch_attend_mfma(dv, u0, nu, q_dev, n_q_tokens, S, shares, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
         : dv.esize == 4
-            ? launch_attend_fp32(dv, u0, nu, (const float *)q_dev, n_q_tokens, S, even, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
+            ? launch_attend_fp32(dv, u0, nu, (const float *)q_dev, n_q_tokens, S, shares, kv_beyond_caches(ctx), ctx->stream, ev0, ev1)
             : launch_attend_valu(dv, u0, nu, q_dev, n_q_tokens, S, ctx->stream, ev0, ev1);
     if (e != hipSuccess) return fail_hip(ctx, e, "attend launch");
-    e = launch_attend_combine(dv, u0, nu, n_q_tokens, S, out_dev, lse_dev, ctx->stream, false, even);
+    e = launch_attend_combine(dv, u0, nu, n_q_tokens, S, out_dev, lse_dev, ctx->stream, false, shares);
     if (e != hipSuccess) return fail_hip(ctx, e, "combine launch");
     if (ctx->host) {
         if ((e = hipEventRecord(ctx->host->attend_done[layer], ctx->stream)) != hipSuccess)
@@ -1216,20 +1216,25 @@ int32_t mosaic_decode_step(mosaic_ctx *ctx, int32_t layer, const void *q_dev, in
     const long long NT = ((long long)n_q_tokens * dv.G + kRowTile - 1) / kRowTile;
     // The fused kernel pays for a shorter launch chain with equal (not size-proportional) splits and a
     // selection repeated by every workgroup: it wins while the step is latency-bound, i.e. while the
-    // expected K/V volume of the launch is small (measured: 26 MB -15 %, 118 MB +7 %).
+    // expected K/V volume of the launch is small.  Measured (see the kernel): bf16 2 to 4 us a layer ahead up to 20 MiB,
+    // at 29 to 35 between 4 ahead and 2 behind; fp32 ahead up to 16, at 21 and 32 MiB 1 and 5 us behind.
     const long long est_pages = std::max<long long>(1, (ctx->n_frames * dv.k + dv.C - 1) / dv.C);
-    const long long est_bytes = (long long)dv.Hkv * est_pages * (long long)(dv.kpage + dv.vpage);
-    const bool fused = !ctx->host && ctx->impl == MOSAIC_ATTEND_MFMA && layer >= 0 && NT == 1 &&
-                       dv.maint_mode == MOSAIC_MAINT_OFF && !dv.aug_reps && !dv.aug_window && dv.P == 0 &&
+    const long long est_bytes = (long long)dv.Hkv * std::min(est_pages + dv.aug_window, std::max(ctx->n_frames, 1ll)) * (long long)(dv.kpage + dv.vpage);
+    const bool fused = !ctx->host && (ctx->impl == MOSAIC_ATTEND_MFMA || dv.esize == 4) && layer >= 0 && NT == 1 &&
+                       dv.maint_mode == MOSAIC_MAINT_OFF && dv.P == 0 &&
                        dv.C <= 256 && ctx->cfg.decode_fused_max_mib >= 0 &&
-                       est_bytes <= ((long long)(ctx->cfg.decode_fused_max_mib > 0 ? ctx->cfg.decode_fused_max_mib : 48) << 20);
+                       est_bytes <= ((long long)(ctx->cfg.decode_fused_max_mib > 0 ? ctx->cfg.decode_fused_max_mib : 32) << 20) / (dv.esize == 4 ? 2 : 1);
+    // pages of a workgroup's share at the most, which it lists in LDS (2048 entries): an equal part of the frames, and those
+    // its first and last chunk have in common with other shares
+    auto listed = [&](int splits) { return ctx->n_frames / splits + 2 + (dv.esize == 4 ? kGroup : 0); };
     int S = 0;
     if (fused) {
-        S = choose_splits(ctx, dv.Hkv, n_q_tokens, dv.part_entries);
-        // a workgroup lists the pages of its chunk range in LDS (2048 entries)
-        while (S < kMaxSplits && ctx->n_frames / S + 2 > 2048) ++S;
+        // one workgroup per CU, however little is expected (as above; the selection is repeated side by side): 36 decode draws
+        // 12 to 22 us a layer against 13 to 28 with a chunk per wavefront
+        S = std::max(1, std::min(kMaxSplits, 256 / dv.Hkv));
+        while (S < kMaxSplits && listed(S) > 2048) ++S;
     }
-    if (!fused || ctx->n_frames / std::max(S, 1) + 2 > 2048 ||
+    if (!fused || listed(std::max(S, 1)) > 2048 ||
         (long long)dv.Hkv * S > dv.part_entries) {
         // On request (decode_fused_max_mib = -1) the selection moves into the attention launch, whose first
         // workgroups select and publish, with splits proportional to the retrieved sizes.  Not the
@@ -1274,6 +1279,7 @@ int32_t mosaic_decode_step(mosaic_ctx *ctx, int32_t layer, const void *q_dev, in
     hipError_t e;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if ((e = take_profile_events(ctx, &ev0, &ev1)) != hipSuccess) return fail_hip(ctx, e, "kernel timing");
+    if ((e = refresh_value_reps(ctx, dv)) != hipSuccess) return fail_hip(ctx, e, "value representatives launch");
     e = launch_decode_fused(dv, u0, nu, q_dev, n_q_tokens, S, (int)ctx->n_frames, ctx->cfg.score_mode,
                             kv_beyond_caches(ctx), ctx->stream, ev0, ev1);
     if (e != hipSuccess) return fail_hip(ctx, e, "fused decode launch");

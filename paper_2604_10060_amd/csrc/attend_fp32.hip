@@ -22,11 +22,11 @@ namespace {
 // i = token i % T of page i / T of the selection), taken 16 at a time whatever T is, so that only the very last group of
 // 16 is padded.  One row tile: split_slot() shares the workgroups out over the units by retrieved size, wavefront w of
 // split s takes 16s number s + S * w + 4 * S * i.  Questions: a workgroup takes a contiguous run of 16s, an equal share of all
-// units' (even_share; or a unit's split where the partial buffer is short), its wavefronts every fourth.
+// units' or the part of one that lies in one unit (even_share), its wavefronts every fourth.
 // The page ids of group i + 2 and the operands of group i + 1 are in flight while group i is reduced.
 template <int D, int R, bool STREAM>
 __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp32(DeviceView dv, int u0, int n_units, const float *q,
-                                                                        int Tq, int NT, int B, int n_row_blocks, int even) {
+                                                                        int Tq, int NT, int G, int B, int n_row_blocks) {
     __shared__ float lds[kF32MergeFloats<D>];
     const int first_extra = R == 1 ? B : (B * n_row_blocks + 7) / 8 * 8;
     if ((int)blockIdx.x >= first_extra) {      // extra workgroups: the global representatives' part (augmentation)
@@ -46,7 +46,15 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
     }
     const ChunkSize<true> cs(dv);
     ShareWalk<true> w;
-    if (!w.start(dv.n_sel + u0, n_units, cs, B, grp, R > 1 && even != 0)) return;      // block-uniform as well
+    if constexpr (R == 1) {
+        const SplitSlot slot = split_slot<false>(dv.n_sel + u0, n_units, B, grp);
+        if (slot.uc < 0) return;                                                       // block-uniform as well
+        w.uc = __builtin_amdgcn_readfirstlane(slot.uc); w.n = __builtin_amdgcn_readfirstlane(slot.n);
+        w.base = __builtin_amdgcn_readfirstlane(slot.base); w.S = __builtin_amdgcn_readfirstlane(slot.S);
+        w.split = __builtin_amdgcn_readfirstlane(slot.split);
+    } else {
+        if (!w.start(dv.n_sel + u0, n_units, cs, G, grp, B == G)) return;              // (B > G: slots)
+    }
   do {
     int n_ = n, g_ = g, t_ = tid;   // (opaque copies: what only a unit's first loads and last stores need of the lane is worked out there)
     asm volatile("" : "+v"(n_), "+v"(g_), "+v"(t_));
@@ -55,7 +63,8 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
     const int *sel = dv.sel_pages + (size_t)u * dv.F;
     const float *kb = reinterpret_cast<const float *>(k_page(dv, u, 0)), *vb = reinterpret_cast<const float *>(v_page(dv, u, 0));
     const int n_sel = w.n;
-    const int first = __builtin_amdgcn_readfirstlane(R == 1 ? w.split + S * wave : w.c0 + wave), stride = R == 1 ? 4 * S : 4;
+    const int first = __builtin_amdgcn_readfirstlane(R == 1 ? w.split + S * wave : w.c0 + wave);
+    const int stride = R == 1 ? 4 * S : 4;
     const int groups = R == 1 ? cs.of(n_sel) : w.c1;       // (where this workgroup's end)
     const int n_my = __builtin_amdgcn_readfirstlane(first < groups ? (groups - first + stride - 1) / stride : 0);
 
@@ -63,7 +72,7 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
     const int dq = __builtin_amdgcn_readfirstlane(stride * kGroup / T), dr = __builtin_amdgcn_readfirstlane(stride * kGroup % T);
     int cp = __builtin_amdgcn_readfirstlane(first * kGroup / T), cr = __builtin_amdgcn_readfirstlane(first * kGroup % T);
     const int inv = 65536 / T + 1;  // floor(x / T) = (x * inv) >> 16 for x < T + 16 <= 32
-    int id = 0, at = 0;             // this lane's token (token n of the cursor's group): page id, ~0 for the offset if there is none
+    int id = 0, at = 0;             // this lane's token (token n of the cursor's group): page id, ~offset if there is none
     auto lookup = [&]() {           // (past the last group: the last page again)
         int off = cr + n;
         const int d = T >= kGroup ? (off >= T ? 1 : 0) : (off * inv) >> 16;
@@ -76,10 +85,12 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
         if (cr >= T) { cr -= T; ++cp; }
         cp = min(cp, n_sel);
     };
-    const size_t kstep = k_piece<float>(1, 0, T);
-    auto issue = [&](F32Operands<D> &o) {        // the cursor's group (before the next lookup)
-        const float *kr = kb + (size_t)id * T * D + k_piece<float>(0, max(at, 0), T) + 4 * g;
-        f32_issue<D, STREAM>(kr, kstep, vb, at < 0 ? ~(id * T) : id * T + at, g, n, o);
+    // the cursor's group; then the cursor moves on -- its page id is loaded ahead of the operands, so that waiting for it is not
+    // waiting for them (behind them: decode step of four layers over 69 MB each 133 -> 140 us)
+    auto issue = [&](F32Operands<D> &o, bool more = true) {
+        const int row = at < 0 ? ~(id * T) : id * T + at;
+        if (more) lookup();
+        f32_issue<D, STREAM>(kb, vb, row, g, n, o);
     };
 
     const float sl2 = 1.4426950408889634f / sqrtf((float)D);
@@ -93,24 +104,52 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
 #pragma unroll
         for (int b = 0; b < D / 16; ++b) acc[r][b] = f32v4{0.f, 0.f, 0.f, 0.f};
     }
+    // Questions: a share of a long one is hundreds of groups, and one fp32 sum over all of them errs with the root of their
+    // number (in equal shares, 182 tokens over 1200 frames 2.3e-5 of the output's norm, 30 over 752 8.9e-7).  So the sums of
+    // kSumGroups groups are added to a second level in LDS: 7.3e-7 and 2.0e-7 (with a split count per unit, two to six times as
+    // many, 8.4e-6 and 1.4e-7), within 1 % of the time.
+    constexpr int kSumGroups = 8;
+    __shared__ f32v4 sum_sh[R == 1 ? 1 : 4 * R * (D / 16) * 64];
+    float msum[R], lsum[R];
+    bool summed = false;            // wave-uniform
+#pragma unroll
+    for (int r = 0; r < R; ++r) { msum[r] = -INFINITY; lsum[r] = 0.f; }
+    auto sum_up = [&](bool last) {  // what acc and l hold joins the second level; last: and comes back
+        if constexpr (R > 1) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float a = msum[r] > -INFINITY ? __builtin_amdgcn_exp2f(msum[r] - m[r]) : 0.f;      // (m is no lower)
+                lsum[r] = lsum[r] * a + l[r];
+                msum[r] = m[r];
+                l[r] = last ? lsum[r] : 0.f;
+#pragma unroll
+                for (int b = 0; b < D / 16; ++b) {
+                    f32v4 *const at_sum = &sum_sh[((wave * R + r) * (D / 16) + b) * 64 + lane];
+                    f32v4 x = acc[r][b];
+                    if (summed) x = *at_sum * a + x;
+                    if (!last) *at_sum = x;
+                    acc[r][b] = last ? x : f32v4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+            summed = true;
+        }
+    };
     F32Operands<D> oa, ob;
     if (n_my > 0) {                 // then n_sel > 0
         lookup();
         issue(oa);
-        lookup();
         int i = 0;
         for (; i + 2 < n_my; i += 2) {
+            if (R > 1 && i % kSumGroups == 0 && i > 0) sum_up(false);
             issue(ob);
-            lookup();
             __builtin_amdgcn_sched_barrier(0);
             f32_step<D, R>(oa, qf, acc, m, l);
             issue(oa);
-            lookup();
             __builtin_amdgcn_sched_barrier(0);
             f32_step<D, R>(ob, qf, acc, m, l);
         }
         if (i + 2 == n_my) {
-            issue(ob);
+            issue(ob, false);
             __builtin_amdgcn_sched_barrier(0);
             f32_step<D, R>(oa, qf, acc, m, l);
             f32_step<D, R>(ob, qf, acc, m, l);
@@ -118,6 +157,7 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
             f32_step<D, R>(oa, qf, acc, m, l);
         }
     }
+    if (summed) sum_up(true);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int tile = yb * R + r;
@@ -142,11 +182,11 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
 } // namespace
 
 hipError_t launch_attend_fp32(const DeviceView &dv, int u0, int n_units, const float *q, int Tq, int n_splits,
-                              int even_groups, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                              Shares shares, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile, R = NT == 1 ? 1 : kFp32Tiles, rb = (NT + R - 1) / R;
-    const int even = even_groups > 0, B = even ? even_groups : n_units * n_splits;
+    const int B = NT == 1 ? n_units * n_splits : shares.walk ? shares.groups : shares.groups + n_units - 1;
     const dim3 grid((NT == 1 ? B : (B * rb + 7) / 8 * 8) + (dv.aug_reps ? n_units * rb : 0)), block(kBlock);
-    auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, B, rb, even); };
+    auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, shares.groups, B, rb); };
     if (NT == 1) {
         if (dv.D == 64) stream_kv ? go(k_attend_fp32<64, 1, true>) : go(k_attend_fp32<64, 1, false>);
         else stream_kv ? go(k_attend_fp32<128, 1, true>) : go(k_attend_fp32<128, 1, false>);

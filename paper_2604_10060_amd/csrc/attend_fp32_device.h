@@ -38,13 +38,13 @@ template <bool STREAM> __device__ __forceinline__ f32v4 ld_f32v4(const float *p)
     return STREAM ? __builtin_nontemporal_load(reinterpret_cast<const f32v4 *>(p)) : *reinterpret_cast<const f32v4 *>(p);
 }
 
-// Issues the operand loads of one group.  kr: channels 4g of token n's key, from where 16 channels further on are kstep floats;
-// row: the token's row in the [rows][D] array vb, or ~(some valid row) if it does not exist (it is loaded all the same and gets
-// weight 0).
+// Issues the operand loads of one group.  row_k: row of token n in the [rows][D] arrays kb and vb,
+// or ~(some valid row) if the token does not exist (it is loaded all the same and gets weight 0).
 template <int D, bool STREAM>
-__device__ __forceinline__ void f32_issue(const float *kr, size_t kstep, const float *vb, int row_k, int g, int n, F32Operands<D> &o) {
+__device__ __forceinline__ void f32_issue(const float *kb, const float *vb, int row_k, int g, int n, F32Operands<D> &o) {
+    const float *kr = kb + (size_t)(row_k < 0 ? ~row_k : row_k) * D + 4 * g;
 #pragma unroll
-    for (int j = 0; j < D / 16; ++j) o.k[j] = ld_f32v4<STREAM>(kr + kstep * j);
+    for (int j = 0; j < D / 16; ++j) o.k[j] = ld_f32v4<STREAM>(kr + 16 * j);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         o.row[v] = __shfl(row_k, 4 * g + v, 64);
@@ -114,7 +114,8 @@ __device__ __forceinline__ void f32_step(F32Operands<D> &o, const f32v4 (&qf)[R]
         if (__builtin_amdgcn_ballot_w64(cm > m[r] + kLazyF32)) {            // rare, wave-uniform
             cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
             cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
-            const float mnew = fmaxf(m[r], cm);
+            // (a whole number: the weights of partials against each other are then powers of two, and exact)
+            const float mnew = fmaxf(m[r], ceilf(cm));
             const float alpha = m[r] > -INFINITY ? __builtin_amdgcn_exp2f(m[r] - mnew) : 0.f;
             m[r] = mnew;
             l[r] *= alpha;
@@ -139,40 +140,40 @@ __device__ __forceinline__ void f32_step(F32Operands<D> &o, const f32v4 (&qf)[R]
 }
 
 // Floats of LDS that f32_merge_waves needs.
-template <int D> constexpr int kF32MergeFloats = 4 * D * (kRowTile + 1) + 2 * 4 * kRowTile;
+template <int D, int NW = 4> constexpr int kF32MergeFloats = NW * D * (kRowTile + 1) + 2 * NW * kRowTile;
 
-// Merge of the four wavefronts' running (m, l, O) of one row tile.  All 256 threads call it; thread
-// (row, dl) = (tid / 16, tid % 16) gets channels dl, dl + 16, ... of its row in o, and the row's M and L.
+// Merge of the NW wavefronts' running (m, l, O) of one row tile.  All threads call it; thread
+// (row, dl) = (tid / 16, tid % 16), row < 16, gets channels dl, dl + 16, ... of its row in o, and the row's M and L.
 // Ends with the LDS free to be written again.
-template <int D>
+template <int D, int NW = 4>
 __device__ __forceinline__ void f32_merge_waves(const f32v4 (&acc)[D / 16], float m, float l, float *lds, float (&o)[D / 16], float &M, float &L) {
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16;
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     float (*o_sh)[D][kRowTile + 1] = reinterpret_cast<float (*)[D][kRowTile + 1]>(lds);
-    float (*m_sh)[kRowTile] = reinterpret_cast<float (*)[kRowTile]>(lds + 4 * D * (kRowTile + 1)), (*l_sh)[kRowTile] = m_sh + 4;
+    float (*m_sh)[kRowTile] = reinterpret_cast<float (*)[kRowTile]>(lds + NW * D * (kRowTile + 1)), (*l_sh)[kRowTile] = m_sh + NW;
 #pragma unroll
     for (int b = 0; b < D / 16; ++b)
 #pragma unroll
         for (int i = 0; i < 4; ++i) o_sh[wave][64 * (b / 4) + 16 * g + 4 * i + b % 4][n] = acc[b][i];
     if (g == 0) { m_sh[wave][n] = m; l_sh[wave][n] = l; }
     __syncthreads();
-    const int row = tid / 16, dl = tid % 16;
+    const int row = NW == 4 ? tid / 16 : tid / 16 % kRowTile, dl = tid % 16;
     M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, m_sh[w][row]);
-    float wgt[4];
-    L = 0.f;
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, m_sh[w][row]);
+    float wgt[NW], x[NW];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < NW; ++w) {
         wgt[w] = m_sh[w][row] > -INFINITY ? __builtin_amdgcn_exp2f(m_sh[w][row] - M) : 0.f;
-        L += wgt[w] * l_sh[w][row];
+        x[w] = wgt[w] * l_sh[w][row];
     }
+    L = pair_sum<NW>(x);
 #pragma unroll
     for (int i = 0; i < D / 16; ++i) {
-        o[i] = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) o[i] += wgt[w] * o_sh[w][dl + 16 * i][row];
+        for (int w = 0; w < NW; ++w) x[w] = wgt[w] * o_sh[w][dl + 16 * i][row];
+        o[i] = pair_sum<NW>(x);
     }
     __syncthreads();
 }

@@ -321,9 +321,10 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
         const int rl = sg + 8 * j;                    // row inside this workgroup's share
         if (rl >= nr) continue;
         const int r = rbase + rl;
-        float o[1] = {0.f};
+        float o8[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) o[0] += red[q][rl][col];
+        for (int q = 0; q < 8; ++q) o8[q] = red[q][rl][col];
+        float o[1] = {pair_sum<8>(o8)};
         combine_store<E, D, 1>(dv, u, lc, h, 0, r, dg * 32 + col, Tq, o, L_sh[r], X_sh[r], M_sh[r], out, lse);
     }
 }
@@ -333,26 +334,27 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
 // the tile's 16 x CW values) split groups take every SG-th split each.  A thread owns four channels of a row (16-byte loads; the
 // lanes of a row side by side) and keeps its rows' statistics itself, kMergeBatch splits of values and statistics in flight, so that
 // up to the exchange between split groups nothing is shared and no barrier is met.
-// Many tiles: CW = D, one split group, no LDS (32 tokens on 28 layers, 1568 tiles of 2.3 splits on average
-// 49 -> 21.5 us against a workgroup per 32 channels with its weights through LDS; 256 tokens, 448 tiles of 9 splits 15.7 -> 10.6).  Few tiles with many splits: 32 channels and eight split groups
-// (28 rows in 4 units, 64 splits 13.4 -> 8.3 us; fp32, 48 tiles of
-// 21 splits 6.0).
+// Many tiles: CW = D, one split group, no LDS (32 tokens on 28 layers, 1568 tiles of 2.3 splits on average 49 -> 21.5 us against a
+// workgroup per 32 channels with its weights through LDS; 256 tokens, 448 tiles of 9 splits 15.7 -> 10.6).  Fewer tiles: 1024
+// threads, two or four split groups (160 tiles of 16 splits 10.8 -> 9.6; 240 of 11 with representatives 10.3 -> 9.5, in the narrow form
+// 13.6 and 17.3).  Few tiles with many splits: 32 channels and eight split groups (28 rows in 4 units, 64 splits 13.4 -> 8.3 us;
+// fp32, 48 tiles of 21 splits 22.5 -> 5.8).
 // grid (D / CW, NT, n_units), BLK threads.
 constexpr int kMergeBatch = 8;
 template <typename E, int D, int CW, int BLK>
-__global__ __launch_bounds__(BLK) void k_combine_question(DeviceView dv, int u0, int n_units, int Tq, int B, int even_groups,
-                                                          E *out, float *lse) {
+__global__ __launch_bounds__(BLK) void k_combine_question(DeviceView dv, int u0, int n_units, int Tq, int B, int G, E *out,
+                                                          float *lse) {
     constexpr int TPS = 16 * CW / 4 < BLK ? 16 * CW / 4 : BLK, SG = BLK / TPS, RPT = 16 * CW / 4 / TPS;   // threads of a split group, groups, rows per thread
     constexpr int LPR = CW / 4, RSTEP = TPS / LPR;          // lanes of a row, rows between a thread's rows
     const int tile = blockIdx.y, uc = blockIdx.z, u = u0 + uc, NT = gridDim.y, tid = threadIdx.x;
     const int lc = uc / dv.Hkv, h = u % dv.Hkv, rows = min(kRowTile, Tq * dv.G - tile * kRowTile);
     const int sg = tid / TPS, row0 = tid % TPS / LPR, ch = blockIdx.x * CW + tid % LPR * 4;
     int n_splits, base;                          // n_splits is 0 if the unit retrieved nothing
-    if (even_groups > 0) {
-        const EvenShare sh = even_share<true, sizeof(E) == 4>(dv.n_sel + u0, n_units, ChunkSize<sizeof(E) == 4>(dv), even_groups, uc);
+    if (G > 0) {
+        const EvenShare sh = even_share<kShareOfUnit, sizeof(E) == 4>(dv.n_sel + u0, n_units, ChunkSize<sizeof(E) == 4>(dv), G, uc);
         n_splits = sh.splits();
         base = sh.base();
-    } else {
+    } else {                                     // (the bf16 vector-ALU kernel)
         const SplitSlot slot = split_slot<true>(dv.n_sel + u0, n_units, B, uc);
         n_splits = slot.S;
         base = slot.base;
@@ -390,14 +392,18 @@ __global__ __launch_bounds__(BLK) void k_combine_question(DeviceView dv, int u0,
             L[j] *= a; X[j] *= a;
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[j][c] *= a;
+            float p[6][kMergeBatch];            // the batch's terms of L, X and the four channels, added in pairs
 #pragma unroll
             for (int i = 0; i < kMergeBatch; ++i) {
-                if (s0 + SG * i <= last) {                  // (the same for a whole split group)
-                    const float w = mx > -INFINITY ? exp2f(mm[j][i] - mx) : 0.f;
-                    L[j] += w * ll[j][i]; X[j] += w * xx[j][i];
-                    acc[j][0] += w * v[j][i].x; acc[j][1] += w * v[j][i].y; acc[j][2] += w * v[j][i].z; acc[j][3] += w * v[j][i].w;
-                }
+                const bool in = s0 + SG * i <= last;        // (the same for a whole split group)
+                const float w = in && mx > -INFINITY ? exp2f(mm[j][i] - mx) : 0.f;
+                const float t[6] = {ll[j][i], xx[j][i], v[j][i].x, v[j][i].y, v[j][i].z, v[j][i].w};
+#pragma unroll
+                for (int c = 0; c < 6; ++c) p[c][i] = in ? w * t[c] : 0.f;
             }
+            L[j] += pair_sum<kMergeBatch>(p[0]); X[j] += pair_sum<kMergeBatch>(p[1]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[j][c] += pair_sum<kMergeBatch>(p[2 + c]);
         }
     }
     if constexpr (SG > 1) {
@@ -443,22 +449,29 @@ hipError_t launch_attend_valu(const DeviceView &dv, int u0, int n_units, const v
 }
 
 hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int Tq, int n_splits,
-                                 void *out, float *lse, hipStream_t s, bool uniform, int even_groups) {
+                                 void *out, float *lse, hipStream_t s, bool uniform, Shares shares) {
     const int us = uniform ? n_splits : 0;
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
     const int B = n_units * n_splits;
     if (NT > 1) {
-        // A workgroup per tile where that alone is one per CU or a unit has one batch of splits on average (question of 4
-        // tokens on 28 layers, 224 tiles of 2.3 splits: narrow workgroups take 16.9 us, see the kernel).
-        const bool wide = (long long)NT * n_units >= 256 || n_splits <= kMergeBatch;
-        const dim3 gq(wide ? 1 : dv.D / 32, NT, n_units);
-        auto go = [&](auto kern, int blk, auto *o) { kern<<<gq, blk, 0, s>>>(dv, u0, n_units, Tq, B, even_groups, o, lse); };
-        auto pick = [&](auto *o) {
+        // A workgroup of 256 per tile where that alone is one per CU or a unit has one batch of splits on average, one of 1024
+        // for 64 tiles and more, else 1024 per 32 channels (see the kernel).
+        const long long tiles = (long long)NT * n_units;
+        const int form = tiles >= 256 || n_splits <= kMergeBatch ? 0 : tiles >= 64 ? 1 : 2;
+        const dim3 gq(form == 2 ? dv.D / 32 : 1, NT, n_units);
+        auto go = [&](auto kern, int blk, auto *o) { kern<<<gq, blk, 0, s>>>(dv, u0, n_units, Tq, B, shares.groups, o, lse); };
+        auto pick = [&](auto *o, auto d) {
             using E = std::remove_pointer_t<decltype(o)>;
-            if (dv.D == 64) wide ? go(k_combine_question<E, 64, 64, 256>, 256, o) : go(k_combine_question<E, 64, 32, 1024>, 1024, o);
-            else wide ? go(k_combine_question<E, 128, 128, 256>, 256, o) : go(k_combine_question<E, 128, 32, 1024>, 1024, o);
+            constexpr int D = decltype(d)::value;
+            if (form == 0) go(k_combine_question<E, D, D, 256>, 256, o);
+            else if (form == 1) go(k_combine_question<E, D, D, 1024>, 1024, o);
+            else go(k_combine_question<E, D, 32, 1024>, 1024, o);
         };
-        if (dv.esize == 4) pick((float *)out); else pick((unsigned short *)out);
+        auto by_d = [&](auto *o) {
+            if (dv.D == 64) pick(o, std::integral_constant<int, 64>{});
+            else pick(o, std::integral_constant<int, 128>{});
+        };
+        if (dv.esize == 4) by_d((float *)out); else by_d((unsigned short *)out);
         return hipGetLastError();
     }
     // One row tile (a decode step) of a few units: up to eight workgroups share a tile's rows, as long as the launch

@@ -154,20 +154,22 @@ __device__ __forceinline__ void chunk_step(const bf16x8 (&kf)[2 * (D / 32)], con
 // Issue the 16-byte operand loads of one chunk.  Tokens beyond the page's T are
 // clamped to the last token (valid memory, weight 0 later); the value blocks are
 // zero-padded to 32 tokens at ingest.
+// A key operand is 64 bytes from each of 16 rows: from a [T][D] page 16 half cache lines, from one in pieces four runs of
+// 256 bytes.  A compute unit takes in 44 GB/s of whole lines (64 units reading) and 34 if half its loads are of the first kind,
+// which shows where a layer's heaviest unit is read on while the others are done: fused decode step of a layer, 30 of
+// 134 MB, 16.4 -> 14.4 us.  Stores beyond the caches (STREAM) stay in [T][D]: with the whole chip reading from memory the pieces
+// are slower (118 MB a launch 33.4 -> 33.9 us; with a chunk's rows in operand order, a whole KB a load, 34.4).
 template <int D, bool STREAM>
-__device__ __forceinline__ void issue_chunk(const unsigned short *kpage, const unsigned short *vchunk,
-                                            int t0, int T, int g, int n, bf16x8 (&kf)[2 * (D / 32)],
+__device__ __forceinline__ void issue_chunk(const DeviceView &dv, const unsigned short *kpage, const unsigned short *vchunk,
+                                            int t0, int g, int n, bf16x8 (&kf)[2 * (D / 32)],
                                             bf16x8 (&vf)[D / 16]) {
     constexpr int KK = D / 32, DB = D / 16;
 #pragma unroll
     for (int tau = 0; tau < 2; ++tau) {
-        const int tok = min(t0 + 8 * (n / 4) + 4 * tau + (n % 4), T - 1);
-        const unsigned short *kr = kpage + k_piece<unsigned short>(0, tok, T) + 8 * g;
+        const int tok = min(t0 + 8 * (n / 4) + 4 * tau + (n % 4), dv.T - 1);
+        const unsigned short *kr = kpage + (size_t)tok * (STREAM ? D : dv.k_rs()) + 8 * g;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {            // channels 32 kk .. + 31 are piece kk
-            const unsigned short *kp = kr + k_piece<unsigned short>(kk, 0, T);
-            kf[tau * KK + kk] = STREAM ? ld_frag_stream(kp) : ld_frag(kp);
-        }
+        for (int kk = 0; kk < KK; ++kk) kf[tau * KK + kk] = STREAM ? ld_frag_stream(kr + 32 * kk) : ld_frag(kr + kk * dv.k_ps());
     }
     const unsigned short *vr = vchunk + n * 32 + 8 * g;
 #pragma unroll
@@ -190,19 +192,22 @@ __device__ __forceinline__ void load_q(const DeviceView &dv, const unsigned shor
     }
 }
 
-// Merge of the four wavefronts' running (m, l, O) of one row tile and store of the
+// Floats of LDS that merge_waves_store needs.
+template <int D, int NW = 4> constexpr int kMergeFloats = NW * D * (kRowTile + 1) + 3 * NW * kRowTile;
+
+// Merge of the NW wavefronts' running (m, l, O) of one row tile and store of the
 // workgroup's partial at `entry` (shared by the decode kernels).  All threads call it.
-template <int D>
+template <int D, int NW = 4>
 __device__ __forceinline__ void merge_waves_store(const DeviceView &dv, const f32x4 (&acc)[D / 16], float m, float l,
-                                                  float lx, int R, size_t entry) {
+                                                  float lx, int R, size_t entry, float *lds) {
     constexpr int DB = D / 16;
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16;
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     lx += __shfl_xor(lx, 16, 64);
     lx += __shfl_xor(lx, 32, 64);
-    __shared__ float o_sh[4][D][kRowTile + 1];
-    __shared__ float m_sh[4][kRowTile], l_sh[4][kRowTile], x_sh[4][kRowTile];
+    float (*o_sh)[D][kRowTile + 1] = reinterpret_cast<float (*)[D][kRowTile + 1]>(lds);
+    float (*m_sh)[kRowTile] = reinterpret_cast<float (*)[kRowTile]>(lds + NW * D * (kRowTile + 1)), (*l_sh)[kRowTile] = m_sh + NW, (*x_sh)[kRowTile] = m_sh + 2 * NW;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -213,10 +218,10 @@ __device__ __forceinline__ void merge_waves_store(const DeviceView &dv, const f3
     if (row >= R) return;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, m_sh[w][row]);
-    float wgt[4], Lsum = 0.f, Xsum = 0.f;
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, m_sh[w][row]);
+    float wgt[NW], Lsum = 0.f, Xsum = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < NW; ++w) {
         wgt[w] = M > -INFINITY ? __builtin_amdgcn_exp2f(m_sh[w][row] - M) : 0.f;
         Lsum += wgt[w] * l_sh[w][row];
         Xsum += wgt[w] * x_sh[w][row];
@@ -226,7 +231,7 @@ __device__ __forceinline__ void merge_waves_store(const DeviceView &dv, const f3
     for (int d = dl; d < D; d += 16) {
         float o = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) o += wgt[w] * o_sh[w][d][row];
+        for (int w = 0; w < NW; ++w) o += wgt[w] * o_sh[w][d][row];
         po[d] = o;
     }
     if (dl == 0) {

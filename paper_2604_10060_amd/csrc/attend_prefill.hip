@@ -36,8 +36,8 @@
 // chain LDS read -> MFMA -> softmax -> MFMA is dependent, and two wavefronts per SIMD (all that
 // two row tiles of accumulators leave room for) do not cover it.
 //
-// A group is a share of the retrieved chunks -- of all units' in equal parts (even_share), or where the partial buffer is short
-// a unit's split (split_slot) -- and its n_row_blocks workgroups read the same K/V range; xcd_run() says which id is which.
+// A group is an equal share of all units' retrieved chunks, or the part of one that lies in one unit (even_share); its
+// n_row_blocks workgroups read the same K/V range, and xcd_run() says which id is which.
 #include <mutex>
 
 #include "mosaic_internal.h"
@@ -68,8 +68,8 @@ __device__ __forceinline__ void wait_vmem_le() {
 template <int D, bool AUG, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfma(DeviceView dv, int u0, int n_units,
                                                                                     const unsigned short *q, int Tq,
-                                                                                    int NT, int n_groups, int n_row_blocks,
-                                                                                    int group_blocks, int even) {
+                                                                                    int NT, int G, int n_groups, int n_row_blocks,
+                                                                                    int group_blocks) {
     static_assert(!AUG || 64 * NW == kBlock, "the representatives' workgroups are written for kBlock threads");
     constexpr int KK = D / 32, DB = D / 16, RTW = kPrefillTiles;
     constexpr int KSEG = D / 8;                  // 16-byte pieces per key row
@@ -107,10 +107,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     constexpr bool kWhole = KW % NW == 0;          // every wave loads keys and values (else LPW = 1: one or the other)
     static_assert(kWhole || LPW == 1, "load schedule");
     auto is_key = [&](int i) { return kWhole ? i < KW / NW : wave < KW; };
-    // token within the chunk (keys); offset in 16 bytes (of the piece, which k_piece() places / in the value chunk); LDS byte
-    // offset in the slot
+    // token within the chunk (keys); offset in 16 bytes, in the row / in the chunk; LDS byte offset in the slot
     int ld_tok[LPW], ld_dst[LPW];
     unsigned ld_off[LPW], ld_koff[LPW];
+    const int k_rs8 = dv.k_rs() / 8;
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
         const int num = wave + NW * i;
@@ -119,8 +119,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
             const int seg = phys ^ ((row / KRP) % KSEG);
             const int tau = row / 16, rem = row % 16;
             ld_tok[i] = 8 * (rem / 4) + 4 * tau + rem % 4;
-            ld_off[i] = (unsigned)(seg / 4 * T) * 4 + seg % 4;
-            ld_koff[i] = ld_off[i] + 4 * ld_tok[i];
+            ld_off[i] = (unsigned)(seg / 4 * (dv.k_ps() / 8)) + seg % 4;
+            ld_koff[i] = ld_off[i] + ld_tok[i] * k_rs8;
             ld_dst[i] = num * 1024;
         } else {
             const int P = (num - KW) * 64 + lane, row = P / 4, phys = P % 4;
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     // page later, and addresses are scalar arithmetic: everything of the walk is in scalar registers.)
     const ChunkSize<false> cs(dv);
     ShareWalk<false> w;
-    if (!w.start(dv.n_sel + u0, n_units, cs, n_groups, grp, even != 0)) return;
+    if (!w.start(dv.n_sel + u0, n_units, cs, G, grp, n_groups == G)) return;      // (n_groups > G: they are slots)
   do {
     // (opaque copies: what a unit's first loads and last stores derive from the lane is worked out there, and not kept in
     // registers across the loop over the chunks)
@@ -203,12 +203,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
         unsigned char *const dst = prefill_lds + kc.slot * KBYTES;
         // (scalar base, 32-bit lane offset: the chunk's first token goes into the base, and only a page's
         // ragged last chunk clamps token numbers)
-        const uint4 *const kp = reinterpret_cast<const uint4 *>(kc.p + k_piece<unsigned short>(0, t0, T));
+        const uint4 *const kp = reinterpret_cast<const uint4 *>(kc.p) + (size_t)t0 * k_rs8;
         const bool whole = t0 + kChunk <= T;           // wave-uniform
 #pragma unroll
         for (int i = 0; i < LPW; ++i)
             if (is_key(i)) {
-                const unsigned off = whole ? ld_koff[i] : (unsigned)(min(t0 + ld_tok[i], T - 1) - t0) * 4 + ld_off[i];
+                const unsigned off = whole ? ld_koff[i] : (unsigned)((min(t0 + ld_tok[i], T - 1) - t0) * k_rs8) + ld_off[i];
                 __builtin_amdgcn_global_load_lds((gptr_t)(kp + off), (lptr_t)(dst + ld_dst[i]), 16, 0, 0);
             }
         advance(kc, kbase, dv.kpage);
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
 } // namespace
 
 hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, const unsigned short *q, int Tq,
-                                 int n_splits, int even_groups, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                                 Shares shares, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     constexpr int NW = kPrefillWaves;
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
     // dynamic LDS: NW key slots and NW value slots of one chunk (32 x D bf16) each
@@ -422,10 +422,10 @@ hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, cons
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<128, true, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<128, false, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
     });
-    const int even = even_groups > 0, n_groups = even ? even_groups : n_units * n_splits, rb = (NT + NW * kPrefillTiles - 1) / (NW * kPrefillTiles);
+    const int n_groups = shares.walk ? shares.groups : shares.groups + n_units - 1, rb = (NT + NW * kPrefillTiles - 1) / (NW * kPrefillTiles);
     const int gb = (n_groups * rb + 7) / 8 * 8;
     const dim3 grid(gb + (dv.aug_reps ? n_units * NT : 0)), block(64 * NW);
-    auto go = [&](auto kern) { launch_timed(kern, grid, block, lds, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, n_groups, rb, gb, even); };
+    auto go = [&](auto kern) { launch_timed(kern, grid, block, lds, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, shares.groups, n_groups, rb, gb); };
     if (dv.aug_reps) { if (dv.D == 64) go(k_attend_prefill_mfma<64, true, NW>); else go(k_attend_prefill_mfma<128, true, NW>); }
     else { if (dv.D == 64) go(k_attend_prefill_mfma<64, false, NW>); else go(k_attend_prefill_mfma<128, false, NW>); }
     return hipGetLastError();

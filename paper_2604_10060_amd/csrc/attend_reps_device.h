@@ -36,7 +36,7 @@ __device__ void attend_reps_partial(const DeviceView &dv, int u0, int uc, int ti
         const int c = grp * kGroup + n;
         nn = size[min(c, C - 1)];
         if (c >= C) nn = 0;
-        f32_issue<D, false>(rk + (size_t)min(c, C - 1) * D + 4 * g, 16, rv, min(c, C - 1), g, n, o);
+        f32_issue<D, false>(rk, rv, min(c, C - 1), g, n, o);
     };
     auto step = [&](F32Operands<D> &o, int nn) {
 #pragma unroll

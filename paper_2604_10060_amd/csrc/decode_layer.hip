@@ -281,9 +281,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_decode_layer(DeviceView dv, int u
     };
     auto issue = [&](int page, int cc_in, bf16x8 (&kf)[2 * KK], bf16x8 (&vf)[DB], int &cc) {
         cc = cc_in;
-        issue_chunk<D, STREAM>(reinterpret_cast<const unsigned short *>(k_page(dv, u, page)),
+        issue_chunk<D, STREAM>(dv, reinterpret_cast<const unsigned short *>(k_page(dv, u, page)),
                                reinterpret_cast<const unsigned short *>(v_page(dv, u, page)) + (size_t)cc * D * 32,
-                               cc * kChunk, T, g, n, kf, vf);
+                               cc * kChunk, g, n, kf, vf);
     };
     auto step = [&](const bf16x8 (&kf)[2 * KK], const bf16x8 (&vf)[DB], int cc) {
         chunk_step<D>(kf, vf, qf, min(kChunk, T - cc * kChunk), g, sl2, acc, m, l, lx);
@@ -313,7 +313,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_decode_layer(DeviceView dv, int u
             step(kA, vA, ccA);
         }
     }
-    merge_waves_store<D>(dv, acc, m, l, lx, R, (size_t)slot.base + split);
+    __shared__ float lds[kMergeFloats<D>];
+    merge_waves_store<D>(dv, acc, m, l, lx, R, (size_t)slot.base + split, lds);
 }
 
 } // namespace

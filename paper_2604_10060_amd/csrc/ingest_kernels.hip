@@ -104,10 +104,7 @@ __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_
     const size_t spage = host ? (size_t)(f % dv.SN) * dv.U + u : (size_t)u * dv.PU + f;
     const E *src = k_in + in_page;
     // (a thread's eight channels lie in one piece of a row)
-    const bool pieces = sizeof(E) == 4 || dv.v_transposed;
-    E *dst = reinterpret_cast<E *>(kdst_base) + spage * (size_t)T * D +
-             (pieces ? k_piece<E>(cg * 8 / kPiece<E>, 0, T) + cg * 8 % kPiece<E> : (size_t)cg * 8);
-    const int dstep = pieces ? kPiece<E> : D;          // elements from a token to the next
+    E *dst = reinterpret_cast<E *>(kdst_base) + spage * (size_t)T * D + cg * 8 / 32 * dv.k_ps() + cg * 8 % 32;
     double acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.0;
@@ -123,7 +120,7 @@ __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_
             if (t0 + k * RP < T) {
                 float v[8];
                 Elem<E>::unpack(x[k], v);
-                Elem<E>::store(dst + (size_t)(t0 + k * RP) * dstep, x[k]);
+                Elem<E>::store(dst + (size_t)(t0 + k * RP) * dv.k_rs(), x[k]);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) acc[i] += (double)v[i];
             }

@@ -26,7 +26,11 @@ struct DeviceView {
     // geometry
     int L, Hq, Hkv, G, D, T, Tp, F, C, k, U;
     int esize;        // bytes per KV element
-    int v_transposed; // 1: V pages stored [Tp/32][D][32] (MFMA path, Tp = T rounded up to 32); 0: [T][D]
+    int v_transposed; // not 0: V pages stored [Tp/32][D][32] (MFMA path, Tp = T rounded up to 32); 0: [T][D]
+                      // 2: and K pages in pieces of 32 channels, [D/32][T][32]; else [T][D]
+    // K pages: elements from one token to the next and from 32 channels to the next 32
+    __device__ __forceinline__ int k_rs() const { return v_transposed == 2 ? 32 : D; }
+    __device__ __forceinline__ size_t k_ps() const { return v_transposed == 2 ? (size_t)32 * T : 32; }
     int chunks_per_page;
     int tier;         // MOSAIC_TIER_*
     int PU;           // pages per unit in k_store / v_store: F (HBM tier) or the cluster-cache capacity (host tier)
@@ -35,8 +39,8 @@ struct DeviceView {
     //   k_store [U][PU] K pages, v_store [U][PU] V pages.
     // HBM tier: page p = frame id (arrival order).  Host tier: page p = a slot of the unit's GPU
     //   cluster cache (slots are handed out frame by frame; a cluster's frames need not be adjacent).
-    // A K page is kept in pieces of 64 bytes of a row, [pieces of a row][T][64 bytes] (k_piece() below), or [T][D] for the
-    //   bf16 vector-ALU kernel; a V page is [T][D] or, for the bf16 MFMA path, [Tp/32][D][32].
+    // A K page is [T][D] or, for the bf16 MFMA path on stores that the caches hold, in pieces of 32 channels, [D/32][T][32].
+    //   A V page is [T][D] or, for the bf16 MFMA path, [Tp/32][D][32].
     char *k_store;
     char *v_store;
     size_t kpage, vpage;           // bytes of one K / V page
@@ -192,29 +196,30 @@ hipError_t launch_expand_tok_idx(const DeviceView &dv, int u0, int n_units, hipS
 // n_splits = average splits per unit chosen by the caller (B = n_units * n_splits split
 // workgroups are shared out by split_slot); partial entries needed = B * NT
 // ev0/ev1 (may be null) receive the kernel's own start/stop timestamps
-// even_groups > 0 (questions of more than one row tile): that many equal shares of the launch's chunks
-// (even_share) in place of n_splits per unit; partial entries needed = (even_groups + n_units - 1) * NT
+// shares (questions of more than one row tile): groups of equal shares of the launch's chunks and what a workgroup takes of them
+// (even_share); partial entries needed = (groups + n_units - 1) * NT
+struct Shares { int groups; bool walk; };
 hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, const unsigned short *q, int Tq,
-                                 int n_splits, int even_groups, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+                                 Shares shares, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // bf16 pages on the vector ALU (MOSAIC_ATTEND_VALU)
 hipError_t launch_attend_valu(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                               int n_splits, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // fp32 pages (fp32 matrix instruction)
 hipError_t launch_attend_fp32(const DeviceView &dv, int u0, int n_units, const float *q, int Tq, int n_splits,
-                              int even_groups, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+                              Shares shares, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // stream_kv: the decode-shape kernels load K/V with the non-temporal hint (stores far beyond the caches)
 hipError_t launch_attend_mfma(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
-                              int n_splits, int even_groups, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+                              int n_splits, Shares shares, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // uniform: every unit has exactly n_splits splits at slots unit * n_splits + split (fused decode step)
 hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int Tq, int n_splits,
-                                 void *out, float *lse, hipStream_t s, bool uniform = false, int even_groups = 0);
+                                 void *out, float *lse, hipStream_t s, bool uniform = false, Shares shares = {});
 // selection + attention of one decode step of one layer in one launch with size-proportional splits: the
 // first n_units workgroups select for one unit each and publish the result, all workgroups then share
 // out the retrieved pages (one row tile, bf16, C <= 256).  epoch: a number no earlier launch on this
 // context has used.  B = total workgroups (>= n_units)
 hipError_t launch_decode_layer(const DeviceView &dv, int u0, int n_units, const void *q, int Tq, int B, int n_frames,
                                int score_mode, int epoch, bool stream_kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
-// selection + attention of one decode step in one launch (one row tile, bf16, C <= 256, uniform splits)
+// selection + attention of one decode step in one launch (one row tile, C <= 256, uniform splits)
 hipError_t launch_decode_fused(const DeviceView &dv, int u0, int n_units, const void *q, int Tq, int n_splits,
                                int n_frames, int score_mode, bool stream_kv, hipStream_t s, hipEvent_t ev0,
                                hipEvent_t ev1);
@@ -239,13 +244,6 @@ __device__ __forceinline__ const char *k_page(const DeviceView &dv, int u, int p
 __device__ __forceinline__ const char *v_page(const DeviceView &dv, int u, int p) {
     return dv.v_store + (size_t)u * dv.v_ustride + (size_t)p * dv.vpage;
 }
-// Element offset of piece j, token t in a K page of T tokens.  A wavefront's key operand is 64 bytes from each of 16 rows: from
-// [T][D] that is 16 half cache lines per load, and a compute unit then takes in 34 GB/s where whole lines give it 44 (one of
-// 64 active ones, half of its loads keys, half values).  In pieces, the rows of an operand that are neighbours in the page are
-// neighbours in memory.  It shows where a few units' workgroups run on while the others are done: fused decode step of a layer
-// over 16 MB 19.4 -> 18.4 us; with the whole chip reading (118 MB a launch) the two are equal.
-template <typename E> constexpr int kPiece = 64 / (int)sizeof(E);
-template <typename E> __device__ __forceinline__ size_t k_piece(int j, int t, int T) { return ((size_t)j * T + t) * kPiece<E>; }
 __device__ __forceinline__ float bf16_to_f32(unsigned short h) {
     return __uint_as_float(((unsigned int)h) << 16);
 }
@@ -256,6 +254,18 @@ __device__ __forceinline__ unsigned short f32_to_bf16_rne(float f) {
     return (unsigned short)(u >> 16);
 }
 
+
+// Sum of N values (a power of two) in pairs: log2 N roundings on the way of each instead of up to N - 1.
+template <int N> __device__ __forceinline__ float pair_sum(const float (&x)[N]) {
+    float y[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) y[i] = x[i];
+#pragma unroll
+    for (int h = N / 2; h >= 1; h /= 2)
+#pragma unroll
+        for (int i = 0; i < h; ++i) y[i] += y[i + h];
+    return y[0];
+}
 
 // ---------------------------------------------------------------------------
 // Reductions over the 16 lanes of a DPP row (lanes 16k .. 16k + 15) with data-parallel
@@ -399,13 +409,13 @@ __device__ __forceinline__ SplitSlot split_slot(const int *n_sel_call, int n_uni
 
 // ---------------------------------------------------------------------------
 // Equal shares, for questions of more than one row tile.  What the units of a launch retrieved is one sequence of chunks (32
-// tokens of a page in the bf16 kernel, 16 tokens across pages in the fp32 one), in unit order; group g of G takes chunks
-// g * per .. (g + 1) * per - 1 of it, per = ceil(chunks / G), whichever units they belong to.  A group writes one partial per
-// unit that it touches: the partial of (unit i, group g) sits at slot g + i, which rises by at least one from each
-// (unit, group) pair to the next, so that slots are distinct and there are at most G + n_units - 1 of them; unit i's are
-// the S slots from base on.
+// tokens of a page in the bf16 kernel, 16 tokens across pages in the fp32 one), in unit order; group g of G has chunks
+// g * per .. (g + 1) * per - 1 of it, per = ceil(chunks / G), whichever units they belong to.  The partial of (unit i,
+// group g) sits at slot g + i, which rises by at least one from each (unit, group) pair to the next, so that slots are distinct
+// and there are at most G + n_units - 1 of them; unit i's are the S slots from base on.
 // (Chunks of a launch fit 32 bits: each has at least 4 KB of pages in GPU memory.)
-// The attention kernels call it by group, the merge by unit; every lane of the wavefront gets the result.
+// A workgroup takes a group and walks over its units, or it takes one slot.  The attention kernels look up the group or the
+// slot, the merge the unit; every lane of the wavefront gets the result.
 // ---------------------------------------------------------------------------
 // bf16: chunks stay inside a page (per = chunks of a page); fp32: a unit's tokens are one sequence (per = tokens of a page;
 // max_frames * T fits in 32 bits)
@@ -414,8 +424,9 @@ template <bool FP32> struct ChunkSize {
     __device__ __forceinline__ explicit ChunkSize(const DeviceView &dv) : per(FP32 ? dv.T : dv.chunks_per_page) {}
     __device__ __forceinline__ int of(int pages) const { return FP32 ? (pages * per + kGroup - 1) / kGroup : pages * per; }
 };
+enum ShareKey { kShareOfGroup, kShareOfSlot, kShareOfUnit };
 struct EvenShare {
-    int uc;        // unit within the call: the group's first, or the one asked for; -1: the group has no chunks
+    int uc;        // unit within the call: the group's first, the slot's, or the one asked for; -1: there is none
     int before;    // chunks of the units before it
     int n;         // the unit's retrieved pages
     int chunks;    // its chunks
@@ -425,7 +436,7 @@ struct EvenShare {
     __device__ __forceinline__ int splits() const { return chunks > 0 ? (before + chunks - 1) / per - before / per + 1 : 0; }
 };
 
-template <bool BY_UNIT, bool FP32>
+template <ShareKey BY, bool FP32>
 __device__ __forceinline__ EvenShare even_share(const int *n_sel_call, int n_units, ChunkSize<FP32> cs, int G, int key) {
     const int lane = threadIdx.x % 64;
     int total = 0;
@@ -446,7 +457,10 @@ __device__ __forceinline__ EvenShare even_share(const int *n_sel_call, int n_uni
             if (lane >= o) incl += t;
         }
         const int excl = run + incl - c;
-        const bool hit = BY_UNIT ? (i == key) : (want >= excl && want < excl + c);
+        bool hit;
+        if (BY == kShareOfUnit) hit = i == key;
+        else if (BY == kShareOfGroup) hit = want >= excl && want < excl + c;
+        else hit = c > 0 && key >= excl / r.per + i && key <= (excl + c - 1) / r.per + i;
         const unsigned long long mask = __ballot(hit);
         if (mask) {
             const int src = __ffsll((long long)mask) - 1;
@@ -460,48 +474,34 @@ __device__ __forceinline__ EvenShare even_share(const int *n_sel_call, int n_uni
     return r;
 }
 
-// The walk of one workgroup over its share, unit by unit: a group of the equal shares may end one unit and begin the next,
-// a split of split_slot() is one unit's.  Wave-uniform values are moved to scalar registers.
+// What one workgroup takes, unit by unit.  Wave-uniform values are moved to scalar registers (quotients are formed in vector
+// registers).
 template <bool FP32> struct ShareWalk {
     int uc, n;              // unit within the call, its pages
-    int c0, c1;             // the group's range of the unit's chunks
+    int c0, c1;             // the range of the unit's chunks
     int base, S, split;     // its partials: first slot and number of the unit's, which of them this is
     int left, before, per, grp;
-    __device__ __forceinline__ void enter(int chunks) {      // equal shares: the unit (uc, n) from chunk c0 on
+    __device__ __forceinline__ void enter(int chunks) {      // the unit (uc, n) from chunk c0 on, in group grp
         c1 = min(chunks, c0 + left);
         left -= c1 - c0;
-        const int g0 = __builtin_amdgcn_readfirstlane(before / per);      // (the quotients are formed in vector registers)
+        const int g0 = __builtin_amdgcn_readfirstlane(before / per);
         base = g0 + uc;
         S = __builtin_amdgcn_readfirstlane((before + chunks - 1) / per) - g0 + 1;
         split = grp - g0;
     }
-    // false: the group has no chunks.  (Both ways end in the same assignments: stores to the members in the branches were
-    // merged into one through a pointer, which put the members into memory.)
-    __device__ __forceinline__ bool start(const int *n_sel_call, int n_units, ChunkSize<FP32> cs, int G, int g, bool even) {
-        int uc_, n_, before_ = 0, per_ = 1, left_ = 0, S_ = 0, split_ = 0, base_ = 0;
-        if (even) {
-            const EvenShare sh = even_share<false, FP32>(n_sel_call, n_units, cs, G, g);
-            uc_ = sh.uc; n_ = sh.n; before_ = sh.before; per_ = sh.per;
-            left_ = min(sh.per, sh.all - g * sh.per);
-        } else {
-            const SplitSlot slot = split_slot<false>(n_sel_call, n_units, G, g);
-            uc_ = slot.uc; n_ = slot.n; S_ = slot.S; split_ = slot.split; base_ = slot.base;
-        }
-        uc = __builtin_amdgcn_readfirstlane(uc_); n = __builtin_amdgcn_readfirstlane(n_);
-        before = __builtin_amdgcn_readfirstlane(before_); per = __builtin_amdgcn_readfirstlane(per_);
-        left = __builtin_amdgcn_readfirstlane(left_); grp = g;
+    // walk: key is a group, else a slot.  false: nothing to do
+    __device__ __forceinline__ bool start(const int *n_sel_call, int n_units, ChunkSize<FP32> cs, int G, int key, bool walk) {
+        EvenShare sh;
+        if (walk) sh = even_share<kShareOfGroup, FP32>(n_sel_call, n_units, cs, G, key);
+        else sh = even_share<kShareOfSlot, FP32>(n_sel_call, n_units, cs, G, key);
+        uc = __builtin_amdgcn_readfirstlane(sh.uc); n = __builtin_amdgcn_readfirstlane(sh.n);
+        before = __builtin_amdgcn_readfirstlane(sh.before); per = __builtin_amdgcn_readfirstlane(sh.per);
         if (uc < 0) return false;
-        const int chunks = cs.of(n), first = g * per - before;
-        const int S_e = (before + chunks - 1) / per - before / per + 1;
-        const int S_u = __builtin_amdgcn_readfirstlane(even ? S_e : S_);
-        const int sp_u = __builtin_amdgcn_readfirstlane(even ? g - before / per : split_);
-        const int cps = __builtin_amdgcn_readfirstlane((chunks + S_u - 1) / S_u);
-        S = S_u;
-        split = sp_u;
-        base = __builtin_amdgcn_readfirstlane(even ? before / per + uc : base_);
-        c0 = even ? first : min(chunks, sp_u * cps);
-        c1 = min(chunks, c0 + (even ? left : cps));
-        left = even ? left - (c1 - c0) : 0;
+        grp = walk ? key : key - uc;
+        c0 = max(grp * per - before, 0);                     // (grp * per is at most the launch's chunks)
+        left = min((grp + 1) * (long long)per, (long long)__builtin_amdgcn_readfirstlane(sh.all)) - before - c0;
+        enter(cs.of(n));
+        if (!walk) left = 0;
         return true;
     }
     // the group's next unit; false: there is none

@@ -1400,6 +1400,58 @@ def test_decode_step_fused_parity(kw):
     assert rep.max_out_err <= 2e-2
 
 
+# ... fp32 pages, 16 tokens at a time across page borders: pages shorter than that, beside it and ragged, one share and shares
+# without a chunk
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(),
+    dict(tokens_per_frame=1, n_frames=900, n_clusters=9, top_k=9),
+    dict(tokens_per_frame=17, head_dim=64, n_q_heads=16, n_kv_heads=1, n_clusters=200, top_k=30, n_frames=460),
+    dict(tokens_per_frame=5, n_layers=2, n_frames=30, n_clusters=12, top_k=1),
+])
+def test_decode_step_fused_parity_fp32(kw):
+    wl = _small(name="fused_fp32", kv_dtype="fp32", **kw)
+    rep = harness.run_workload(wl, n_questions=0, decode_steps=3, layer_mode="fused")
+    _report(rep)
+    assert [v for (k_, v) in rep.notes if k_ == "decode_step_fused"] == [1] * (3 * wl.n_layers)
+
+
+# ... with the local window (part of the stream, all of it, more frames than threads) and the representatives: the same selection
+# and pages as the two calls, which are compared with the oracle above, before and after more frames arrive
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw,over", [
+    (dict(), dict(aug_window_frames=7)),
+    (dict(tokens_per_frame=50), dict(aug_window_frames=1000, aug_global_reps=1)),
+    (dict(n_frames=1500, n_scenes=30, tokens_per_frame=9, n_clusters=30), dict(aug_window_frames=400)),
+    (dict(head_dim=64, n_q_heads=8, n_kv_heads=2), dict(aug_global_reps=1)),
+    (dict(kv_dtype="fp32", tokens_per_frame=20), dict(aug_window_frames=33, aug_global_reps=1)),
+    (dict(kv_dtype="fp32", head_dim=64, n_q_heads=8, n_kv_heads=2, tokens_per_frame=7), dict(aug_window_frames=1)),
+])
+def test_decode_step_fused_augmented_equals_two_calls(kw, over):
+    wl = _small(name="fused_aug", **kw)
+    st = inputs.SceneStream(wl)
+    K, V = [x.to(DEV) for x in st.frames(0, wl.n_frames)]
+    a = binding.Mosaic(binding.config_for(wl, **over), device=DEV)
+    b = binding.Mosaic(binding.config_for(wl, decode_fused_max_mib=-2, **over), device=DEV)
+    cut = wl.n_frames * 3 // 4
+    for i, (f0, f1) in enumerate(((0, cut), (cut, wl.n_frames))):
+        for m in (a, b):
+            m.ingest_frame(K[f0:f1].contiguous(), V[f0:f1].contiguous())
+        for j in range(2):
+            q = st.question(st.draw_scene(), 1, 2 * i + j).to(DEV)[0].contiguous()
+            oa, la = a.decode_step(0, q)
+            ob, lb = b.decode_step(0, q)
+            torch.cuda.synchronize()
+            assert a.stats().last_decode_fused == 1 and b.stats().last_decode_fused == 0
+            for x, y in zip(a.selection(0)[:3], b.selection(0)[:3]):
+                np.testing.assert_array_equal(x, y)
+            for x, y in zip(a.selection(0)[3], b.selection(0)[3]):
+                np.testing.assert_array_equal(x, y)
+            assert (oa.float() - ob.float()).abs().max().item() <= harness.OUT_TOL[wl.kv_dtype]
+            assert (la - lb).abs().max().item() <= harness.LSE_TOL[wl.kv_dtype]
+    a.close(); b.close()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("kw", [
     dict(),                                                          # D = 128, 4 KV heads, G = 7
