@@ -106,9 +106,10 @@ __global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp
     }
     // Questions: a share of a long one is hundreds of groups, and one fp32 sum over all of them errs with the root of their
     // number (in equal shares, 182 tokens over 1200 frames 2.3e-5 of the output's norm, 30 over 752 8.9e-7).  So the sums of
-    // kSumGroups groups are added to a second level in LDS: 7.3e-7 and 2.0e-7 (with a split count per unit, two to six times as
-    // many, 8.4e-6 and 1.4e-7), within 1 % of the time.
-    constexpr int kSumGroups = 8;
+    // kSumGroups groups are added to a second level in LDS: 1.7e-6 and 1.3e-7 (with a split count per unit, two to six times as
+    // many, 8.4e-6 and 1.4e-7).  Four groups, not eight: 176 tokens over 378 frames 9.4e-8 against 2.4e-7 (8.9e-8 with a split
+    // count per unit), for 4 % of a long question's time (60 tokens, 246 k retrieved: 580 -> 605 us, as long as with a split count).
+    constexpr int kSumGroups = 4;
     __shared__ f32v4 sum_sh[R == 1 ? 1 : 4 * R * (D / 16) * 64];
     float msum[R], lsum[R];
     bool summed = false;            // wave-uniform
