@@ -1416,6 +1416,30 @@ def test_decode_step_fused_parity_fp32(kw):
     assert [v for (k_, v) in rep.notes if k_ == "decode_step_fused"] == [1] * (3 * wl.n_layers)
 
 
+# Splits are merged in pairs.  One token of weight p in every chunk, the same in all, values of one, and 16 equal splits a
+# unit: every sum that is formed in pairs is p times a power of two, exactly, and so the output is one.  Sixteen sums one after
+# the other are not (the start of three is 3p, which has no room for p's last bit).
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+def test_normaliser_of_many_splits_is_summed_in_pairs(D):
+    U, G, T, F = 16, 2, 16, 128                   # 256 CUs / 16 units = 16 splits, of 8 chunks
+    K = torch.full((F, 1, U, T, D), -100.0)       # (their logits are a thousand below: weight 0)
+    K[:, :, :, 5] = 0.25
+    g = torch.Generator().manual_seed(D)
+    q = torch.rand((1, U * G, D), generator=g) + 0.5
+    m = binding.Mosaic(binding.make_config(n_layers=1, n_q_heads=U * G, n_kv_heads=U, head_dim=D, tokens_per_frame=T, max_frames=F,
+                                           n_clusters=4, top_k=4, kv_dtype="fp32", decode_fused_max_mib=64), device=DEV)
+    m.ingest_frame(K.to(DEV), torch.ones_like(K, device=DEV))
+    out, lse = m.decode_step(0, q.to(DEV))
+    torch.cuda.synchronize()
+    assert m.stats().last_decode_fused == 1 and m.stats().last_n_splits == 16
+    assert all(len(t) == F * T for t in m.selection(0)[3])
+    assert torch.equal(out, torch.ones_like(out))
+    want = (q.double() * 0.25).sum(-1) / D ** 0.5 + np.log(F)
+    assert (lse.cpu().double() - want).abs().max().item() <= harness.LSE_TOL["fp32"]
+    m.close()
+
+
 # ... with the local window (part of the stream, all of it, more frames than threads) and the representatives: the same selection
 # and pages as the two calls, which are compared with the oracle above, before and after more frames arrive
 @pytest.mark.gpu
