@@ -281,13 +281,17 @@ int choose_splits(const mosaic_ctx *ctx, int n_units, int Tq, long long part_ent
     const long long est_pages = std::max<long long>(1, (ctx->n_frames * dv.k + dv.C - 1) / dv.C);
     const long long est_chunks = est_pages * dv.chunks_per_page;
     // bandwidth/latency-bound: cover the chip several times over (7 x 256 workgroups: measured on an all-layers launch of
-    // 112 units, 1568-1792 workgroups are 3 % faster than 2128), at least 4 chunks (one per wavefront) per workgroup,
-    // or up to two workgroups per CU with at least one.  (What a question retrieves is expected from the mean cluster, but it
-    // is about the large ones, and of units that retrieve ten times the mean the last workgroups then run on alone.  Two calls, us
-    // a layer with a chunk per wavefront / per workgroup: 15 MiB expected, 28 MiB read, 21.2 / 19.8; 1 MiB 23.1 / 18.3; 4.7 MiB
-    // fp32, 19 to 62 MiB read, 31.9 / 23.3.  More than two workgroups per CU: 22 MiB fp32 in 12 units 25.3 / 29.2 with 62 each.)
+    // 112 units, 1568-1792 workgroups are 3 % faster than 2128), at least 4 chunks (one per wavefront) per workgroup
     long long s = (1792 + n_units * NT - 1) / (n_units * NT);
-    s = std::min(s, std::max({1ll, est_chunks / 4, NT > 1 ? 1 : std::min<long long>(est_chunks, 512 / n_units)}));
+    long long by_chunks = std::max(1ll, est_chunks / 4);
+    // ... or, of a decode step, as many with at least one chunk as fill the CUs once, or twice if they do not fit once.  (What
+    // a question retrieves is expected from the mean cluster, but it is about the large ones, and of units that retrieve ten
+    // times the mean the last workgroups then run on alone; and a second workgroup on a part of the CUs makes all wait for those.
+    // Two calls over 214 shapes of 2 to 48 KV heads, against a chunk per wavefront: 0.93 of the time in the geometric mean, none
+    // more than 2 % above; us a layer: 24 MiB expected in 12 units 51.7 -> 45.3, 1 MiB 23.1 -> 18.3.  Always twice: 16 MiB fp32 in
+    // 8 units 27.8 -> 29.5; always once: 18 MiB in 48 units 49.7 -> 64.4.)
+    if (NT == 1) by_chunks = std::max(by_chunks, std::min<long long>(est_chunks, (n_units * by_chunks <= 256 ? 256 : 512) / n_units));
+    s = std::min(s, by_chunks);
     s = std::min<long long>(s, kMaxSplits);
     s = std::min(s, std::max<long long>(1, part_entries / (n_units * NT)));
     return (int)std::max<long long>(1, s);

@@ -1512,6 +1512,32 @@ def test_decode_step_one_launch_with_proportional_splits_parity(kw):
     a.close(); b.close()
 
 
+# The two calls' splits fill the 256 CUs once, twice if a chunk per wavefront is more than once, and have a chunk at least:
+# (KV heads, frames, splits of each), 32 tokens a frame and half of the frames expected
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("hkv,F,S", [(4, 32, 16), (5, 256, 51), (8, 256, 32), (12, 256, 42), (4, 600, 64), (48, 40, 5), (48, 48, 10)])
+def test_splits_of_a_decode_step_in_two_calls(hkv, F, S, dtype):
+    wl = _small(name="two_calls", n_q_heads=hkv, n_kv_heads=hkv, head_dim=64, tokens_per_frame=32, n_frames=F, n_scenes=4, n_clusters=8,
+                top_k=4, kv_dtype=dtype)
+    st = inputs.SceneStream(wl)
+    K, V = [x.to(DEV) for x in st.frames(0, F)]
+    q = st.question(st.draw_scene(), 1, 0).to(DEV)[0].contiguous()
+    outs = []
+    for lim in (-2, 4096):
+        m = binding.Mosaic(binding.config_for(wl, decode_fused_max_mib=lim), device=DEV)
+        m.ingest_frame(K, V)
+        outs.append(m.decode_step(0, q))
+        torch.cuda.synchronize()
+        assert m.stats().last_decode_fused == (lim > 0)
+        if lim < 0:
+            assert m.stats().last_n_splits == S
+        m.close()
+    (o, l), (o2, l2) = outs
+    assert (o.float() - o2.float()).abs().max().item() <= harness.OUT_TOL[dtype]
+    assert (l - l2).abs().max().item() <= harness.LSE_TOL[dtype]
+
+
 @pytest.mark.gpu
 def test_decode_step_equals_retrieve_then_attend():
     """Same ids, scores and token lists bit for bit; outputs equal up to the merge order of the
