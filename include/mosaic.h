@@ -92,7 +92,8 @@ typedef struct {
                                      cached per unit, least recently used evicted first; 0 -> 0.10 */
     int32_t decode_fused_max_mib; /* (any tier; sits here for alignment) mosaic_decode_step runs its single
                                      fused kernel (equal splits) while the expected K/V volume of the step is
-                                     at most this many MiB (fp32: half); 0 -> 32; -2: always the two calls; -1: never that
+                                     at most this many MiB (fp32: half); 0 -> while the layer has stored at most
+                                     256 MiB of K/V (fp32: 192); -2: always the two calls; -1: never that
                                      kernel but, wherever it applies, the one-launch form with proportional
                                      splits (an option kept for measurement: slower than the two calls) */
     void *host_arena;             /* HOST pointer to pinned (hipHostMalloc) memory, 256-byte aligned,
@@ -331,9 +332,10 @@ int32_t mosaic_attend_static(mosaic_ctx *ctx, int32_t layer, const void *q_dev, 
  * later mosaic_attend see it) and the same output up to the order in which fp32 partial sums are
  * merged.  Where it applies -- MOSAIC_TIER_HBM, bf16 MFMA attention or fp32 pages, layer >= 0, at most 16 query
  * rows per KV head (n_q_tokens * Hq/Hkv <= 16), n_clusters <= 256, maintainer and
- * nested index off, and an expected K/V volume of the step (frames * top_k / n_clusters pages per
- * KV head) of at most decode_fused_max_mib (default 32; fp32: half of it) MiB, i.e. a step that is bound by launch and memory latency rather than
- * by bandwidth -- the selection and the attention over the selected clusters run in ONE kernel
+ * nested index off, and a step that is bound by launch and memory latency rather than by bandwidth, i.e. at most 256 MiB
+ * of K/V pages (fp32: 192) stored for the layer, or, with decode_fused_max_mib > 0, an expected K/V volume of the step
+ * (frames * top_k / n_clusters pages per KV head) of at most that many MiB (fp32: half of it) -- the selection and the
+ * attention over the selected clusters run in ONE kernel
  * (every attention workgroup repeats its unit's selection for itself, which is cheaper than a
  * launch boundary and the dependent loads after it; KV splits are then equal per unit instead of
  * proportional to the retrieved size).  Everywhere else the call simply makes the two calls.

@@ -1218,16 +1218,22 @@ int32_t mosaic_decode_step(mosaic_ctx *ctx, int32_t layer, const void *q_dev, in
     if (!ctx) return MOSAIC_EINVAL;
     const DeviceView &dv = ctx->dv;
     const long long NT = ((long long)n_q_tokens * dv.G + kRowTile - 1) / kRowTile;
-    // The fused kernel pays for a shorter launch chain with equal (not size-proportional) splits and a
-    // selection repeated by every workgroup: it wins while the step is latency-bound, i.e. while the
-    // expected K/V volume of the launch is small.  Measured (see the kernel): bf16 2 to 4 us a layer ahead up to 20 MiB,
-    // at 29 to 35 between 4 ahead and 2 behind; fp32 ahead up to 16, at 21 and 32 MiB 1 and 5 us behind.
+    // The fused kernel pays for a shorter launch chain with equal (not size-proportional) splits and a selection repeated by
+    // every workgroup: it wins while the step is latency-bound, i.e. while little K/V is read.  By default that is judged by what
+    // the layer has stored: a question is about the large clusters, and over 814 shapes it retrieved 13 to 55 % of the stream
+    // (nine in ten) and up to 17 times what the mean cluster leads one to expect.  Fused over two calls, geometric mean of the
+    // time with 1 to 48 KV heads and 1 to 70 MiB expected, by MiB stored: bf16 0.77 to 32, 0.79 to 64, 0.82 to 128, 0.88 to 192,
+    // 0.96 to 256, 0.99 to 300, 1.04 to 400, 1.23 to 600, 1.38 beyond; fp32 0.82, 0.85, 0.90, 0.95 to 192, 1.00 to 256, 1.07 to
+    // 400, 1.19 to 600, 1.42 beyond.  (A line at 32 MiB expected, fp32 16, left out 17.3 against 22.5 us a layer: 12 heads, 64 MiB
+    // stored, 32 expected; and took 77 against 48: 32 heads, 512 stored, 32 expected.)
+    const long long page_bytes = (long long)dv.Hkv * (long long)(dv.kpage + dv.vpage);      // a frame's, of all KV heads
     const long long est_pages = std::max<long long>(1, (ctx->n_frames * dv.k + dv.C - 1) / dv.C);
-    const long long est_bytes = (long long)dv.Hkv * std::min(est_pages + dv.aug_window, std::max(ctx->n_frames, 1ll)) * (long long)(dv.kpage + dv.vpage);
+    const long long est_bytes = page_bytes * std::min(est_pages + dv.aug_window, std::max(ctx->n_frames, 1ll));
+    const int max_mib = ctx->cfg.decode_fused_max_mib;
+    const bool small = max_mib > 0 ? est_bytes <= ((long long)max_mib << 20) / (dv.esize == 4 ? 2 : 1)
+                                   : page_bytes * ctx->n_frames <= (long long)(dv.esize == 4 ? 192 : 256) << 20;
     const bool fused = !ctx->host && (ctx->impl == MOSAIC_ATTEND_MFMA || dv.esize == 4) && layer >= 0 && NT == 1 &&
-                       dv.maint_mode == MOSAIC_MAINT_OFF && dv.P == 0 &&
-                       dv.C <= 256 && ctx->cfg.decode_fused_max_mib >= 0 &&
-                       est_bytes <= ((long long)(ctx->cfg.decode_fused_max_mib > 0 ? ctx->cfg.decode_fused_max_mib : 32) << 20) / (dv.esize == 4 ? 2 : 1);
+                       dv.maint_mode == MOSAIC_MAINT_OFF && dv.P == 0 && dv.C <= 256 && max_mib >= 0 && small;
     // pages of a workgroup's share at the most, which it lists in LDS (2048 entries): an equal part of the frames, and those
     // its first and last chunk have in common with other shares
     auto listed = [&](int splits) { return ctx->n_frames / splits + 2 + (dv.esize == 4 ? kGroup : 0); };

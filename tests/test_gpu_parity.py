@@ -649,11 +649,11 @@ def test_cfg2_full_size_sampled_units():
 @pytest.mark.parametrize("kw", [dict(n_frames=8192, n_scenes=320), dict(n_frames=13000, n_scenes=500, head_dim=64)])
 def test_decode_step_fused_on_a_store_beyond_the_caches(kw):
     """A long stream with a narrow selection: 0.85-1.07 GB of stored KV (the decode kernels then load K/V
-    with the non-temporal hint) but only ~30 MB per step, so mosaic_decode_step still takes the one-kernel
-    path -- the streaming instantiation of the fused kernel, which no benchmark configuration reaches."""
+    with the non-temporal hint) but only ~30 MB per step, for which mosaic_decode_step takes the one-kernel path if it is
+    asked to go by that -- the streaming instantiation of the fused kernel, which no benchmark configuration reaches."""
     wl = inputs.CONFIGS[1].scaled(name="long_stream_narrow_selection", top_k=2, **kw)
     rep = harness.run_full_size(wl, [(0, 0), (0, 3)], layer_modes=("fused", "per_layer"), ingest_batch=64,
-                                decode_steps=2, question=False)
+                                decode_steps=2, question=False, decode_fused_max_mib=48)
     _report(rep)
     fused = [v for (k, v) in rep.notes if k == "decode_step_fused"]
     assert fused and all(v == 1 for v in fused), fused
@@ -1536,6 +1536,46 @@ def test_splits_of_a_decode_step_in_two_calls(hkv, F, S, dtype):
     (o, l), (o2, l2) = outs
     assert (o.float() - o2.float()).abs().max().item() <= harness.OUT_TOL[dtype]
     assert (l - l2).abs().max().item() <= harness.LSE_TOL[dtype]
+
+
+# One launch or two calls by what the layer has stored, whatever is expected of a step, or by the given line: (KV heads, head size,
+# frames, clusters, top_k, line, one launch).  Either way what two contexts of different routes select is the same.
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hkv,D,F,C,k,line,fused", [
+    ("bf16", 12, 64, 345, 16, 8, 0, 1),            # 65 MiB stored, 32.4 expected
+    ("bf16", 4, 128, 2048, 128, 100, 0, 1),        # 256 stored, 200 expected
+    ("bf16", 16, 64, 1030, 64, 4, 0, 0),           # 258 stored, 16.3 expected
+    ("bf16", 16, 64, 1030, 64, 4, 20, 1),
+    ("bf16", 12, 64, 345, 16, 8, 32, 0),
+    ("fp32", 8, 64, 760, 16, 8, 0, 1),             # 190 stored, 95 expected
+    ("fp32", 8, 64, 780, 130, 2, 0, 0),            # 195 stored, 3 expected
+    ("fp32", 8, 64, 780, 130, 2, 8, 1),
+    ("fp32", 8, 64, 780, 130, 3, 8, 0),            # 4.5 expected, a line of 8 is 4
+])
+def test_route_of_a_decode_step(dtype, hkv, D, F, C, k, line, fused):
+    T, g = 64, torch.Generator(device=DEV).manual_seed(F)
+    scene = torch.randn((F // 20 + 1, 1, hkv, 1, D), generator=g, device=DEV)
+    q = (scene[3].repeat_interleave(2, dim=1)[:, :, 0] + 0.3 * torch.randn((1, 2 * hkv, D), generator=g, device=DEV)).to(torch.float32 if dtype == "fp32" else torch.bfloat16)
+    ms = [binding.Mosaic(binding.make_config(n_layers=1, n_q_heads=2 * hkv, n_kv_heads=hkv, head_dim=D, tokens_per_frame=T, max_frames=F,
+                                             n_clusters=C, top_k=k, kv_dtype=dtype, lloyd_iters=2, decode_fused_max_mib=x), device=DEV)
+          for x in (line, 4096 if not fused else -2)]
+    for f in range(0, F, 128):
+        n = min(128, F - f)
+        x = torch.randn((2, n, 1, hkv, T, D), generator=g, device=DEV).mul_(0.3)
+        x[0] += scene[torch.arange(f, f + n, device=DEV) // 20]
+        for m in ms:
+            m.ingest_frame(x[0].to(q.dtype), x[1].to(q.dtype))
+    outs = [m.decode_step(0, q) for m in ms]
+    torch.cuda.synchronize()
+    assert [m.stats().last_decode_fused for m in ms] == [fused, 1 - fused]
+    for a, b in zip(ms[0].selection(0)[:3], ms[1].selection(0)[:3]):
+        np.testing.assert_array_equal(a, b)
+    for a, b in zip(ms[0].selection(0)[3], ms[1].selection(0)[3]):
+        np.testing.assert_array_equal(a, b)
+    assert (outs[0][0].float() - outs[1][0].float()).abs().max().item() <= harness.OUT_TOL[dtype]
+    assert (outs[0][1] - outs[1][1]).abs().max().item() <= harness.LSE_TOL[dtype]
+    for m in ms:
+        m.close()
 
 
 @pytest.mark.gpu
