@@ -301,28 +301,35 @@ int choose_splits(const mosaic_ctx *ctx, int n_units, int Tq, long long part_ent
 // unequal shares, and a count that does not fill the chip a whole number of times leaves the last workgroups alone on it.  Attention
 // launch, per unit / in equal shares: 32 tokens on 28 layers (112 units, two splits) 941 / 584 us; 256 tokens in 4 units (eight
 // splits) 312 / 271 us; fp32, 21 tokens in 8 units of D = 64 28 / 20.5 us.
-// A workgroup walks over the units of a group, as many groups as fill the chip once with the workgroups that its registers hold
-// (bf16: two per CU, fp32: two at head_dim 64, else one), so that all end together; or it takes what one group has of one
-// unit, which spares short shares the second unit's start (query, first pages, a partial: about as long as kStart chunks), with
-// fewer and larger groups, since those workgroups too are to be on the chip at once.  Whole calls, walking / by unit: 44 tokens
-// over 3 MB in 20 units 48.7 / 43.2 us, 53 tokens over 5 MB 42.4 / 41.0; fp32 100 tokens over 34 units 369 / 840, 51 tokens over 21 MB in
-// 72 units 97.4 / 108.
-// A share has at least 4 chunks (8 instead: 3 tokens in 4 units over 3 MB of pages 33.9 -> 37.1 us a call) and beyond 256
-// shares 8 (4 instead: 12 tokens over 125 MB 60.2 -> 62.7 us a call: the merge reads what more shares write).
+// A workgroup walks over the units of a group, so that all end together; or it takes what one group has of one unit, which spares
+// short shares the second unit's start (query, first pages, a partial: about as long as kStart chunks), with fewer and larger
+// groups, since those workgroups too are to be on the chip at once.  Whole calls, walking / by unit: 44 tokens over 3 MB in 20
+// units 48.7 / 43.2 us, 53 tokens over 5 MB 42.4 / 41.0; fp32 100 tokens over 34 units 369 / 840, 51 tokens over 21 MB in 72 units 97.4 / 108.
+// As many groups as have one workgroup per CU, or two (the registers of the fp32 kernel at head_dim 128 hold one) where a share
+// then still has kTwice chunks: a second one on a part of the CUs makes all wait for those.  What is retrieved is taken to be at
+// least a fifth of the stream (see mosaic_decode_step).  Whole calls, by 4 chunks of the mean cluster's a share and up to 256 groups /
+// so: fp32, 24 tokens in 24 units (279 workgroups / 255) 46.8 / 38.2 us, bf16 64 tokens in 4 units (316 / 256) 39.7 / 35.6, 3 tokens in one
+// unit 37.3 / 24.4; 353 shapes 0.97 in the geometric mean; against a split count per unit, 9 of them were 3 to 11 % slower, now one by
+// 3 %.  kTwice 4 and 10 instead of 6: 1.004 and 1.001 of the time, 24 and 40 instead of 32: 1.001 and 1.003; 0.15 and 0.3 instead of a
+// fifth: 1.002 and 1.001.
 Shares choose_shares(const mosaic_ctx *ctx, int n_units, int Tq, long long part_entries) {
     const DeviceView &dv = ctx->dv;
     const long long NT = ((long long)Tq * dv.G + kRowTile - 1) / kRowTile;
-    const bool fp32 = dv.esize == 4;
-    const long long kStart = fp32 ? 8 : 4;
+    const bool fp32 = dv.esize == 4, two = !(fp32 && dv.D == 128);
+    const long long kStart = fp32 ? 8 : 4, kTwice = fp32 ? 32 : 6;
     const long long tiles = fp32 ? kFp32Tiles : kPrefillWaves * kPrefillTiles, rb = (NT + tiles - 1) / tiles;
     const long long est_pages = std::max<long long>(1, (ctx->n_frames * dv.k + dv.C - 1) / dv.C);
-    const long long chunks = n_units * (fp32 ? (est_pages * dv.T + kGroup - 1) / kGroup : est_pages * dv.chunks_per_page);
+    auto chunks_of = [&](long long pages) { return fp32 ? (pages * dv.T + kGroup - 1) / kGroup : pages * dv.chunks_per_page; };
+    const long long chunks = n_units * std::max(chunks_of(est_pages), chunks_of(ctx->n_frames) / 5);
     const long long fit = std::max<long long>(1, part_entries / NT - (n_units - 1));
-    const long long room = std::max<long long>(1, (fp32 && dv.D == 128 ? 256 : 512) / rb);      // groups on the chip at once
-    const long long most = std::min(fit, std::max({1ll, std::min(chunks / 4, 256ll), chunks / 8}));
-    const long long gw = std::min(room, most), gs = std::max(1ll, std::min(room - (n_units - 1), most));
+    auto groups = [&](long long extra) {        // extra: slots beside one per group
+        auto fill = [&](long long wgs) { return std::max(1ll, wgs / rb - extra); };
+        const long long g = two && chunks / fill(512) >= kTwice ? fill(512) : std::min(fill(256), std::max(1ll, chunks / 4));
+        return std::min(g, fit);
+    };
+    const long long gw = groups(0), gs = groups(n_units - 1), room = std::max(1ll, (two ? 512 : 256) / rb);      // on the chip at once
     const long long t_walk = (chunks + gw - 1) / gw + 2 * kStart;
-    const long long t_slot = std::max((chunks + gs - 1) / gs, 1ll) * std::max(1ll, (gs + n_units - 1 + room - 1) / room) + kStart;
+    const long long t_slot = (chunks + gs - 1) / gs * ((gs + n_units - 1 + room - 1) / room) + kStart;
     return t_walk < t_slot ? Shares{(int)gw, true} : Shares{(int)gs, false};
 }
 

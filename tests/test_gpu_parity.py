@@ -218,6 +218,40 @@ def test_question_in_equal_shares(kw):
     harness.run_workload(_small(**kw), layer_mode="all")
 
 
+# How many groups, and what a workgroup takes of one (the mean number of splits a unit tells both): one workgroup per CU, a chunk or
+# two of a fifth of a long stream, two workgroups per CU; 72 units walked over (by unit it would be one split fewer), in groups of
+# more than two units, with second-level sums, row blocks and LDS used again for the next unit
+@pytest.mark.parametrize("S,kw", [
+    (16, dict(n_frames=300, n_scenes=10, n_clusters=32, question_tokens=64)),                                     # 61 groups, 4 units
+    (10, dict(n_q_heads=12, n_kv_heads=12, n_layers=2, head_dim=64, tokens_per_frame=16, n_frames=150, n_clusters=8, question_tokens=24,
+              kv_dtype="fp32")),                                                                                  # 233, 24
+    (51, dict(n_q_heads=8, n_kv_heads=1, tokens_per_frame=32, n_frames=1024, n_scenes=30, n_clusters=64, question_tokens=3)),
+    (64, dict(n_q_heads=8, n_kv_heads=8, head_dim=64, tokens_per_frame=20, n_frames=800, n_scenes=20, n_clusters=8, question_tokens=20)),
+    (2, dict(question_tokens=9, head_dim=64, kv_dtype="fp32")),
+    (2, dict(question_tokens=9, kv_dtype="fp32")),
+    (3, dict(question_tokens=40, head_dim=64)),
+    (3, dict(question_tokens=40)),
+    (1, dict(question_tokens=40, head_dim=64, kv_dtype="fp32")),                                                  # 28 groups
+    (1, dict(question_tokens=40, kv_dtype="fp32")),
+    (1, dict(question_tokens=140)),                                                                               # 64 groups
+])
+def test_groups_of_a_question(S, kw):
+    if S <= 3:
+        kw = dict(n_layers=18, n_frames=90, n_scenes=6, n_clusters=6, top_k=2, tokens_per_frame=9, **kw)
+    wl = _small(**kw)
+    L, H = wl.n_layers, wl.n_kv_heads
+    units = sorted({(l, h) for l in (0, L // 2, L - 1) for h in (0, H // 2, H - 1)})
+    st, rep = inputs.SceneStream(wl), harness.Report()
+    K, V = st.frames(0, wl.n_frames)
+    m = binding.Mosaic(binding.config_for(wl), device=DEV)
+    oracles = harness.ingest_with_parity(m, wl, K.to(DEV), V.to(DEV), units, rep, batch_pattern=(16, 3))
+    for i in range(2):
+        q = st.question(st.draw_scene(), wl.question_tokens, i).to(DEV)
+        harness.query_with_parity(m, wl, q, oracles, K, V, rep, "all")
+        assert m.stats().last_n_splits == S
+    m.close()
+
+
 def test_question_with_room_for_few_partials(monkeypatch):
     # an arena with room for two splits per unit and no more (what a context needed before the equal shares): fewer shares
     # or a split count per unit, the same result up to the order of the merge
