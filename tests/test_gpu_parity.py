@@ -1474,6 +1474,30 @@ def test_normaliser_of_many_splits_is_summed_in_pairs(D):
     m.close()
 
 
+# ... and so are the eight split groups of a question's merge: one token of weight p in every chunk again, 64 splits of four chunks, and
+# values of one in the splits of every other four.  The output is a half, exactly.
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+def test_split_groups_of_a_question_are_summed_in_pairs(D):
+    G, T, F, Tq = 7, 16, 256, 4
+    K = torch.full((F, 1, 1, T, D), -100.0)
+    K[:, :, :, 5] = 0.25
+    V = torch.zeros_like(K)
+    V[[f for f in range(F) if f // 4 % 8 < 4]] = 1.0
+    g = torch.Generator().manual_seed(D)
+    q = torch.rand((1, Tq, G, D), generator=g) + 0.5
+    m = binding.Mosaic(binding.make_config(n_layers=1, n_q_heads=G, n_kv_heads=1, head_dim=D, tokens_per_frame=T, max_frames=F,
+                                           n_clusters=4, top_k=4, kv_dtype="fp32"), device=DEV)
+    m.ingest_frame(K.to(DEV), V.to(DEV))
+    m.retrieve(-1, q.to(DEV))
+    out, lse = m.attend(-1, q.to(DEV))
+    torch.cuda.synchronize()
+    assert m.stats().last_n_splits == 64
+    np.testing.assert_array_equal(m.selection(0)[3][0], np.arange(F * T))       # (one cluster: pages in order of arrival)
+    assert torch.equal(out, torch.full_like(out, 0.5))
+    m.close()
+
+
 # ... with the local window (part of the stream, all of it, more frames than threads) and the representatives: the same selection
 # and pages as the two calls, which are compared with the oracle above, before and after more frames arrive
 @pytest.mark.gpu
