@@ -162,9 +162,10 @@ __global__ __launch_bounds__((kFusedBlock<E, D, AUG>), AUG ? 2 : 1) void k_decod
             const double p = sc_sh[tid], nr = rn_sh[tid];
             sc = score_mode == 1 ? p : (nr == 0.0 ? 0.0 : p / nr);
         }
+        if (split == 0) dv.scores[(size_t)u * dv.SC + tid] = sc;
+        if (n_sh[tid] > 0) sc = rank_score(sc);
         sc_sh[tid] = sc;
         key_sh[tid] = (float)sc;          // fp32 rounding for the pair count below
-        if (split == 0) dv.scores[(size_t)u * dv.SC + tid] = sc;
     }
     __syncthreads();
     // ---- ranks by (score descending, id ascending) among the non-empty clusters ----

@@ -119,9 +119,10 @@ __device__ __forceinline__ void leader_select(const DeviceView &dv, int u, int l
             const double p = sc_sh[tid], nr = rn_sh[tid];
             sc = score_mode == 1 ? p : (nr == 0.0 ? 0.0 : p / nr);
         }
+        dv.scores[(size_t)u * dv.SC + tid] = sc;
+        if (n_sh[tid] > 0) sc = rank_score(sc);
         sc_sh[tid] = sc;
         key_sh[tid] = (float)sc;          // fp32 rounding for the pair count below
-        dv.scores[(size_t)u * dv.SC + tid] = sc;
     }
     __syncthreads();
     // ---- ranks by (score descending, id ascending) among the non-empty clusters: pairs compared on

@@ -255,6 +255,11 @@ __device__ __forceinline__ unsigned short f32_to_bf16_rne(float f) {
 }
 
 
+// A score as the rankings order it.  What is not above the lowest number (no number at all, or minus infinity: a question that
+// overflowed) counts as that, so that the live entries' ranks are distinct and an empty entry's minus infinity stays below them: a
+// rank that two entries shared would leave another without one, and what lies there would be read as an id.
+__device__ __forceinline__ double rank_score(double s) { return s > -1.7976931348623157e308 ? s : -1.7976931348623157e308; }
+
 // Sum of N values (a power of two) in pairs: log2 N roundings on the way of each instead of up to N - 1.
 template <int N> __device__ __forceinline__ float pair_sum(const float (&x)[N]) {
     float y[N];

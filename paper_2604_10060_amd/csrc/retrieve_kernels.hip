@@ -306,6 +306,7 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve(DeviceView dv, int u0, 
     __syncthreads();
     // ranks of the k best non-empty clusters by (score descending, id ascending); empty and
     // pruned clusters have n_sh = 0 and take no part
+    const double score = tid < C ? sc_sh[tid] : 0.0;       // (as it goes to memory; the ranking may replace it)
     const int n_live = topk_rank(sc_sh, n_sh, C, k, rank_sh, ids_sh, cnt_sh, off_sh, tk_sh);
     const int n_ids = min(k, n_live);
     int run = 0;
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve(DeviceView dv, int u0, 
         if (write_pages) dv.n_sel[u] = run + (n_frames - w0);
     }
     for (int i = tid; i < k; i += BLK) dv.ids[(size_t)u * k + i] = i < n_ids ? ids_sh[i] : -1;
-    if (tid < C) dv.scores[(size_t)u * C + tid] = sc_sh[tid];
+    if (tid < C) dv.scores[(size_t)u * C + tid] = score;
     if (!write_pages) return;     // host tier: the host maps clusters to cache slots
     // page list: clusters in selection order, member frames ascending
     int *sel = dv.sel_pages + (size_t)u * dv.F;

@@ -17,7 +17,7 @@
 // same as that of the full comparison, whatever the score distribution (if all
 // scores fall into one bin the candidates are simply all live entries).
 #pragma once
-#include <hip/hip_runtime.h>
+#include "mosaic_internal.h"
 
 namespace mosaic {
 
@@ -30,17 +30,19 @@ struct TopkShared {
     int bstar, n_live, n_cand;
 };
 
+// sc_sh: a live entry's score that is no number or minus infinity is replaced by the lowest one (rank_score).
 // cnt_sh, cand_sh: 1024 ints of scratch each (contents destroyed).  R <= 1024.
 // All 1024 threads of the workgroup must call it; it contains barriers.
 // Precondition (saves a barrier on the small-table path): cnt_sh[0..R) and
 // sh.n_live were set to zero by the caller before its latest barrier.
-__device__ __forceinline__ int topk_rank(const double *sc_sh, const int *n_sh, int R, int k,
+__device__ __forceinline__ int topk_rank(double *sc_sh, const int *n_sh, int R, int k,
                                          int *rank_sh, int *ids_sh, int *cnt_sh, int *cand_sh,
                                          TopkShared &sh) {
     constexpr int BLK = 1024;
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     const bool live = tid < R && n_sh[tid] > 0;
-    const double s = live ? sc_sh[tid] : 0.0;
+    const double s = live ? rank_score(sc_sh[tid]) : 0.0;
+    if (live) sc_sh[tid] = s;               // (others read it behind the next barrier)
     if (R <= 128) {
         // Small tables: the direct count over all pairs, 2^pl threads per entry (the largest power of
         // two that fits the workgroup: shifts instead of integer divisions).  The pairs are compared

@@ -1795,3 +1795,48 @@ def test_topk_scores_that_collide_in_fp32_are_ordered_exactly(higher_id_wins, n_
     ids, n_ids, scores, toks = m.selection(0)
     assert n_ids[0] == 1 and int(ids[0, 0]) == int(ids_o[0])
     m.close()
+
+
+@pytest.mark.parametrize("n_clusters,route,dtype", [(12, 4096, "bf16"), (12, -2, "bf16"), (12, -1, "bf16"), (12, 4096, "fp32"), (160, -2, "fp32"),
+                                                    (160, 4096, "bf16"), (300, -2, "bf16"), (12, "deferred", "bf16")])
+def test_questions_that_overflowed_select_existing_clusters(n_clusters, route, dtype):
+    """Scores that are infinite or no number still give every live cluster a rank of its own (no number like minus infinity;
+    equal ones by id): k different clusters, their frames once each, and the other heads as without."""
+    C, k = n_clusters, 4
+    over = dict(maint_mode=binding.MAINT_DEFERRED, init_clusters=C, tau_min=1e9, tau_max=1e9, tau_n0=1.0) if route == "deferred" else \
+        dict(decode_fused_max_mib=route)
+    wl = _small(name="overflow", kv_dtype=dtype, n_frames=2 * C + 60, n_scenes=max(6, C // 3), n_clusters=C, top_k=k, tokens_per_frame=5)
+    st = inputs.SceneStream(wl)
+    K, V = [x.to(DEV) for x in st.frames(0, wl.n_frames)]
+    m = binding.Mosaic(binding.config_for(wl, **over), device=DEV)
+    m.ingest_frame(K, V)
+    clean = st.question(st.draw_scene(), 1, 0).to(DEV)[0].contiguous()
+    q, G = clean.clone(), wl.group
+    q[0, 1, 5] = float("nan")                 # a head of the first KV head
+    q[0, G, 7] = float("-inf")                # ... of the second
+    q[0, 2 * G + 1, 3:5] = torch.tensor([float("inf"), float("-inf")])
+    want = m.decode_step(0, clean)
+    clean_sel = m.selection(0)
+    got = m.decode_step(0, q)
+    torch.cuda.synchronize()
+    if not isinstance(route, str):
+        assert m.stats().last_decode_fused == {4096: 1, -2: 0, -1: 2}[route]
+    ids, n_ids, scores, toks = m.selection(0)
+    r, n = m.centroids()
+    A = m.assignments()
+    for h in range(wl.n_kv_heads):
+        live = np.flatnonzero(n[h] > 0)
+        assert n_ids[h] == min(k, len(live))
+        chosen = ids[h, :n_ids[h]]
+        s = scores[h][live]
+        if h < 3:
+            assert [np.isnan(s).all(), np.isinf(s).all() and len(set(s)) == 2, not np.isfinite(s).any()][h]
+            key = np.maximum(np.nan_to_num(s, nan=-np.inf, posinf=np.inf, neginf=-np.inf), -np.finfo(np.float64).max)
+            np.testing.assert_array_equal(chosen, live[np.argsort(-key, kind="stable")][:k])
+        else:
+            np.testing.assert_array_equal(chosen, clean_sel[0][h, :n_ids[h]])
+        frames = np.concatenate([np.flatnonzero(A[h] == c) for c in chosen])
+        np.testing.assert_array_equal(toks[h], (frames[:, None] * 5 + np.arange(5)).ravel())
+    last = slice(3 * G, 4 * G)
+    assert torch.equal(got[0][..., last, :], want[0][..., last, :]) and torch.equal(got[1][..., last], want[1][..., last])
+    m.close()
