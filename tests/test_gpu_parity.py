@@ -191,7 +191,7 @@ def test_single_frame_calls_equal_batched_ingest_variants(kw, over):
         np.testing.assert_array_equal(a, b)
 
 
-# the questions' merge takes a unit's splits sixteen at a time: long selections of few units (64 splits each on average,
+# the questions' merge takes eight splits at a time per split group: long selections of few units (many splits each on average,
 # unequal ones beyond that), row tiles that are not full, both page types
 @pytest.mark.parametrize("kw", [
     dict(n_q_heads=8, n_kv_heads=2, question_tokens=9, n_clusters=12, top_k=12, n_frames=420),
@@ -202,9 +202,8 @@ def test_question_merge_of_many_splits(kw):
     harness.run_workload(_small(**kw), layer_mode="all")
 
 
-# Equal shares of the retrieved chunks: shares that span several units (more than 64 of them: the scan takes two passes), units
-# that span several shares, one chunk in all and fewer chunks than shares, waves without rows beside waves with, and the merge's
-# two forms (many tiles, many splits)
+# Equal shares of the retrieved chunks: more than 64 units (the scan takes two passes), units that span several shares, one chunk in
+# all and fewer chunks than shares, waves without rows beside waves with, and the merge's forms (many tiles, fewer, many splits)
 @pytest.mark.parametrize("kw", [
     dict(n_layers=18, n_frames=60, n_scenes=6, n_clusters=6, top_k=2, tokens_per_frame=9, question_tokens=5),         # 72 units
     dict(n_layers=2, n_frames=300, tokens_per_frame=100, head_dim=64, question_tokens=40, n_clusters=9, top_k=3),     # 4 chunks a page
@@ -253,8 +252,8 @@ def test_groups_of_a_question(S, kw):
 
 
 def test_question_with_room_for_few_partials(monkeypatch):
-    # an arena with room for two splits per unit and no more (what a context needed before the equal shares): fewer shares
-    # or a split count per unit, the same result up to the order of the merge
+    # an arena with room for two splits per unit and no more (what a context needed before the equal shares): fewer shares, the
+    # same result up to the order of the merge
     wl = _small(n_layers=24, n_frames=96, n_clusters=8, top_k=3, question_tokens=32)       # 96 units x 14 tiles
     st = inputs.SceneStream(wl)
     K, V = [x.to(DEV) for x in st.frames(0, wl.n_frames)]
@@ -692,6 +691,76 @@ def test_decode_step_fused_on_a_store_beyond_the_caches(kw):
     fused = [v for (k, v) in rep.notes if k == "decode_step_fused"]
     assert fused and all(v == 1 for v in fused), fused
     assert rep.max_out_err <= 2e-2
+
+
+# ... and its streaming instantiations with fp32 pages, by default: layers that have stored little each, 800 MiB in all
+@pytest.mark.parametrize("kw", [dict(n_frames=700), dict(n_frames=1400, head_dim=64)])
+def test_fp32_decode_step_fused_on_a_store_beyond_the_caches(kw):
+    wl = inputs.CONFIGS[1].scaled(name="fp32_layers", n_layers=5, kv_dtype="fp32", **kw)
+    rep = harness.run_full_size(wl, [(0, 0), (4, 3)], layer_modes=("fused",), ingest_batch=64, decode_steps=2, question=False)
+    _report(rep)
+    assert [v for (k, v) in rep.notes if k == "decode_step_fused"] == [1] * 10
+    assert rep.max_out_err <= 1e-4
+
+
+# ... and with the augmentation, beside the two calls
+@pytest.mark.parametrize("dtype,F,D", [("bf16", 1700, 128), ("bf16", 3400, 64), ("fp32", 700, 128), ("fp32", 1400, 64)])
+def test_decode_step_fused_augmented_on_a_store_beyond_the_caches(dtype, F, D):
+    wl = inputs.CONFIGS[1].scaled(name="aug_layers", n_layers=4 if dtype == "bf16" else 5, n_frames=F, head_dim=D, kv_dtype=dtype)
+    st = inputs.SceneStream(wl, device=DEV)
+    ms = [binding.Mosaic(binding.config_for(wl, aug_window_frames=16, aug_global_reps=1, decode_fused_max_mib=x), device=DEV)
+          for x in (0, -2)]
+    for f in range(0, F, 64):
+        K, V = st.frames(f, min(f + 64, F))
+        for m in ms:
+            m.ingest_frame(K, V)
+    for l in (0, wl.n_layers - 1):
+        q = st.question(st.draw_scene(), 1, l)[l].contiguous()
+        (oa, la), (ob, lb) = [m.decode_step(l, q) for m in ms]
+        torch.cuda.synchronize()
+        assert [m.stats().last_decode_fused for m in ms] == [1, 0]
+        for x, y in zip(ms[0].selection(l)[3], ms[1].selection(l)[3]):
+            np.testing.assert_array_equal(x, y)
+        assert (oa.float() - ob.float()).abs().max().item() <= harness.OUT_TOL[dtype]
+        assert (la - lb).abs().max().item() <= harness.LSE_TOL[dtype]
+    for m in ms:
+        m.close()
+
+
+# Keys of a context with room for more than 768 MiB lie in [T][D] from its first frame on, while the loads that go with it carry the
+# non-temporal hint only once that much is stored: every decode kernel and the questions on both sides of that, on one context each
+@pytest.mark.parametrize("D,F", [(128, 1100), (64, 2200)])
+def test_keys_in_rows_before_and_after_the_store_is_beyond_the_caches(D, F):
+    L, early = 6, 200
+    wl = inputs.CONFIGS[1].scaled(name="rows", n_layers=L, n_frames=F, head_dim=D, question_tokens=20)
+    st, rep, units = inputs.SceneStream(wl, device=DEV), harness.Report(), [(0, 1), (L - 1, 3)]
+    K, V = st.frames(0, F)
+    ms = [binding.Mosaic(binding.config_for(wl, decode_fused_max_mib=x), device=DEV) for x in (0, -2, -1)]
+    oracles = {u: harness.orc.OracleUnit(wl.n_clusters, D, wl.tokens_per_frame, F, wl.warmup_frames, wl.lloyd_iters, 0) for u in units}
+    for f0, f1 in ((0, early), (early, F)):
+        for f in range(f0, f1, 64):
+            for m in ms:
+                m.ingest_frame(K[f:min(f + 64, f1)].contiguous(), V[f:min(f + 64, f1)].contiguous())
+        A = ms[0].assignments()
+        for (l, h), o in oracles.items():
+            pages = inputs.unit_pages(K[f0:f1], l, h)
+            for f in range(f0, f1):
+                got, force = int(A[l * wl.n_kv_heads + h, f]), -1
+                if o.ready:
+                    dec = o.peek(pages[f - f0])
+                    if got != dec.winner:
+                        assert dec.gap < harness.NEAR_TIE and got == dec.runner_up
+                        force = got
+                o.ingest(pages[f - f0], force)
+        for m, route in zip(ms, (1, 0, 2)):
+            q = st.question(st.draw_scene(), 1, f1 + route)
+            harness.query_with_parity(m, wl, q, oracles, K, V, rep, "fused")
+            assert m.stats().last_decode_fused == route
+            q = st.question(st.draw_scene(), wl.question_tokens, f1 + route)
+            harness.query_with_parity(m, wl, q, oracles, K, V, rep, "per_layer" if route else "all")
+    _report(rep)
+    for m in ms:
+        m.close()
 
 
 @pytest.mark.parametrize("stream_id", [0, 5])
@@ -1671,9 +1740,13 @@ def test_decode_step_equals_retrieve_then_attend():
 
 @pytest.mark.gpu
 def test_decode_step_falls_back_where_the_fused_kernel_does_not_apply():
-    # fp32 KV (vector-ALU attention), a multi-token question, all layers at once, the host tier
+    # (fp32 pages: it applies)
     rep = harness.run_workload(inputs.CONFIGS[0], n_questions=1, decode_steps=2, layer_mode="fused")
     assert rep.max_out_err <= 1e-4
+    # bf16 on the vector ALU, more than one row tile, nothing ingested yet (a layer that has stored too much: the routes above)
+    rep = harness.run_workload(_small(name="fused_fallback_valu"), n_questions=0, decode_steps=2, layer_mode="fused",
+                               attend_impl=binding.ATTEND_VALU)
+    assert [v for (k_, v) in rep.notes if k_ == "decode_step_fused"] == [0, 0]
     wl = _small(name="fused_fallback", question_tokens=5)
     rep = harness.run_workload(wl, n_questions=2, decode_steps=0, layer_mode="fused")
     assert rep.max_out_err <= 2e-2
