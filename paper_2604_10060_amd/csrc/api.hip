@@ -1246,8 +1246,8 @@ int32_t mosaic_decode_step(mosaic_ctx *ctx, int32_t layer, const void *q_dev, in
     auto listed = [&](int splits) { return ctx->n_frames / splits + 2 + (dv.esize == 4 ? kGroup : 0); };
     int S = 0;
     if (fused) {
-        // one workgroup per CU, however little is expected (as above; the selection is repeated side by side): 36 decode draws
-        // 12 to 22 us a layer against 13 to 28 with a chunk per wavefront
+        // one workgroup per CU, or 64 per KV head (one and two heads), however little is expected (as above; the selection is
+        // repeated side by side): 36 decode draws 12 to 22 us a layer against 13 to 28 with a chunk per wavefront
         S = std::max(1, std::min(kMaxSplits, 256 / dv.Hkv));
         while (S < kMaxSplits && listed(S) > 2048) ++S;
     }

@@ -36,7 +36,7 @@ constexpr int kFusedMaxC = 256, kFusedList = 2048;
 // Threads of a workgroup, one workgroup per CU.  Eight wavefronts halve the selection's and the pages' trips (bf16, 1 to 36 MiB a
 // layer: 0.4 to 0.9 us less than four; fp32 at D = 64 1 us less).  Four where a wavefront's accumulators are large and there
 // are more of them to merge (fp32 at D = 128: 16 to 38 us a layer with four, 1 to 2 us more with eight), and with the
-// representatives, whose workgroups have to find a place beside the others.
+// representatives, whose workgroups have to find a place beside the others (a window alone takes the same instantiation).
 template <typename E, int D, bool AUG> constexpr int kFusedBlock = AUG || (sizeof(E) == 4 && D == 128) ? 256 : 512;
 
 __device__ __forceinline__ double group16_sum_f64(double x) { return row16_sum(x); }   // as in k_retrieve
@@ -47,6 +47,8 @@ __global__ __launch_bounds__((kFusedBlock<E, D, AUG>), AUG ? 2 : 1) void k_decod
     constexpr bool FP32 = sizeof(E) == 4;
     constexpr int BLK = kFusedBlock<E, D, AUG>, NW = BLK / 64;
     constexpr int KK = D / 32, DB = D / 16, EPL = D / 16, NG = BLK / 16, RPF = 128 / NG, FPT = 2048 / BLK;
+    static_assert(BLK >= kFusedMaxC && BLK >= D, "a thread per table entry and per channel");
+    static_assert(128 % NG == 0 && 1024 % BLK == 0, "whole passes of prefetched rows, frames and window frames");
     __shared__ float lds[FP32 || (AUG && kF32MergeFloats<D> > kMergeFloats<D, kFusedBlock<E, D, AUG> / 64>)
                              ? kF32MergeFloats<D, kFusedBlock<E, D, AUG> / 64> : kMergeFloats<D, kFusedBlock<E, D, AUG> / 64>];
     if constexpr (AUG) {
@@ -188,7 +190,7 @@ __global__ __launch_bounds__((kFusedBlock<E, D, AUG>), AUG ? 2 : 1) void k_decod
         }
     }
     __syncthreads();
-    {   // C <= 256 = BLK: thread j owns entry j; live entries counted with one atomic per wavefront
+    {   // C <= kFusedMaxC <= BLK: thread j owns entry j; live entries counted with one atomic per wavefront
         const bool live = tid < C && n_sh[tid] > 0;
         int rk = -1;
         if (live) {
