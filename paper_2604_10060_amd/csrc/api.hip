@@ -174,7 +174,8 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
         L.PU = (int)std::max<long long>(cp, 1);
         L.SN = std::max(W, 128);                // staging ring: the warm-up, or two batches (one being offloaded, one being staged)
     }
-    // (a store that kv_beyond_caches() may find beyond the caches keeps its keys in [T][D])
+    // (a store that kv_beyond_caches() may find beyond the caches keeps its keys in [T][D]; below that pieces win at every size, see
+    // issue_chunk())
     L.k_pieces = L.v_transposed && (long long)L.PU * (long long)U * (long long)(L.kpage + L.vpage) <= kCachedStore;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };

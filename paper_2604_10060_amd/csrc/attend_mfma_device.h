@@ -157,8 +157,10 @@ __device__ __forceinline__ void chunk_step(const bf16x8 (&kf)[2 * (D / 32)], con
 // A key operand is 64 bytes from each of 16 rows: from a [T][D] page 16 half cache lines, from one in pieces four runs of
 // 256 bytes.  A compute unit takes in 44 GB/s of whole lines (64 units reading) and 34 if half its loads are of the first kind,
 // which shows where a layer's heaviest unit is read on while the others are done: fused decode step of a layer, 30 of
-// 134 MB, 16.4 -> 14.4 us.  Stores beyond the caches (STREAM) stay in [T][D]: with the whole chip reading from memory the pieces
-// are slower (118 MB a launch 33.4 -> 33.9 us; with a chunk's rows in operand order, a whole KB a load, 34.4).
+// 134 MB, 16.4 -> 14.4 us.  Decode steps on larger stores, another question every step, rows / pieces: 268 MB 25.6 / 23.9 us, 403 35.1 /
+// 33.6, 537 40.4 / 39.0, 760 51.4 / 49.8, 28 layers of 26 MB 381 / 376; questions of 32 to 256 tokens alike within 1 %.  Stores beyond that
+// (STREAM) stay in [T][D]: with the whole chip reading from memory the pieces are slower (118 MB a launch 33.4 -> 33.9 us; with a chunk's
+// rows in operand order, a whole KB a load, 34.4).
 template <int D, bool STREAM>
 __device__ __forceinline__ void issue_chunk(const DeviceView &dv, const unsigned short *kpage, const unsigned short *vchunk,
                                             int t0, int g, int n, bf16x8 (&kf)[2 * (D / 32)],

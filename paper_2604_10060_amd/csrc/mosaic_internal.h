@@ -39,7 +39,7 @@ struct DeviceView {
     //   k_store [U][PU] K pages, v_store [U][PU] V pages.
     // HBM tier: page p = frame id (arrival order).  Host tier: page p = a slot of the unit's GPU
     //   cluster cache (slots are handed out frame by frame; a cluster's frames need not be adjacent).
-    // A K page is [T][D] or, for the bf16 MFMA path on stores that the caches hold, in pieces of 32 channels, [D/32][T][32].
+    // A K page is [T][D] or, for the bf16 MFMA path on stores of at most 768 MiB, in pieces of 32 channels, [D/32][T][32].
     //   A V page is [T][D] or, for the bf16 MFMA path, [Tp/32][D][32].
     char *k_store;
     char *v_store;
