@@ -272,7 +272,8 @@ int32_t mosaic_ingest_frame_visual(mosaic_ctx *ctx, const void *k_dev, const voi
  * q_dev is [L][Tq][Hq][D].  q_dev: device pointer, kv_dtype.
  * Per unit: mean query over the Tq tokens and the unit's G query heads;
  * score_j = (mean query . r_j)/|r_j| for non-empty clusters; the top_k best by
- * (score descending, id ascending); then the page list of those clusters
+ * (score descending, id ascending; one that is no number or minus infinity
+ * ranks as the lowest number); then the page list of those clusters
  * (clusters in selection order, member frames ascending).  The selection stays
  * in the context until the next retrieve for that layer or the next ingest.
  * Errors: ENOTREADY before W frames are in; EINVAL (layer, n_q_tokens out of

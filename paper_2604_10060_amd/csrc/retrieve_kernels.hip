@@ -222,8 +222,8 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve(DeviceView dv, int u0, 
                     sc = score_mode == 1 ? p : (prn_pre == 0.0 ? 0.0 : p / prn_pre);
                     atomicAdd(&p_live_sh, 1);
                 }
-                ps_sh[row0] = sc;
                 dv.pscores[(size_t)u * P + row0] = sc;
+                ps_sh[row0] = pn_pre > 0 ? rank_score(sc) : sc;
             }
         }
         __syncthreads();

@@ -1913,3 +1913,30 @@ def test_questions_that_overflowed_select_existing_clusters(n_clusters, route, d
     last = slice(3 * G, 4 * G)
     assert torch.equal(got[0][..., last, :], want[0][..., last, :]) and torch.equal(got[1][..., last], want[1][..., last])
     m.close()
+
+
+def test_nested_question_that_overflowed_keeps_the_first_partitions():
+    """... and in the first stage every non-empty partition: the first ones are kept, as many as asked for."""
+    P, C, H, D, T, F, Dv = 6, 24, 2, 64, 3, 200, 16
+    g = torch.Generator(device=DEV).manual_seed(7)
+    K, V = torch.randn((2, F, 1, H, T, D), generator=g, device=DEV)
+    m = binding.Mosaic(binding.make_config(n_layers=1, n_q_heads=2 * H, n_kv_heads=H, head_dim=D, tokens_per_frame=T, max_frames=F,
+                                           n_clusters=C, top_k=7, kv_dtype="fp32", n_partitions=P, visual_dim=Dv, top_partitions=2), device=DEV)
+    m.ingest_frame_visual(K, V, torch.randn((F, Dv), generator=g, device=DEV))
+    q = torch.randn((1, 2 * H, D), generator=g, device=DEV)
+    q[0, 0, 3] = float("nan")
+    m.retrieve(0, q)
+    part, n_part, ps = m.partition_selection(0)
+    ids, n_ids, scores, toks = m.selection(0)
+    np.testing.assert_array_equal(n_part, [2, 2])
+    assert np.isnan(ps[0]).all() and np.isfinite(ps[1]).all()
+    np.testing.assert_array_equal(part[0], [0, 1])
+    np.testing.assert_array_equal(part[1], np.argsort(-ps[1], kind="stable")[:2])
+    A, (r, n) = m.assignments(), m.centroids()
+    for h in range(H):
+        live = [c for c in range(C) if n[h][c] > 0 and c // (C // P) in part[h]]
+        chosen = list(ids[h, :n_ids[h]])
+        assert len(set(chosen)) == n_ids[h] == min(7, len(live)) and set(chosen) <= set(live)
+        frames = np.concatenate([np.flatnonzero(A[h] == c) for c in chosen])
+        np.testing.assert_array_equal(toks[h], (frames[:, None] * T + np.arange(T)).ravel())
+    m.close()
