@@ -251,6 +251,35 @@ def test_groups_of_a_question(S, kw):
     m.close()
 
 
+# Logits that rise from page to page by more or less than what makes a question's kernel raise a row's reference, and fall again: in shares of
+# one chunk up to seven, ragged pages and whole ones, rows in one wavefront and in all.  A single cluster, so that every page is
+# read in order.  Weights and outputs are bf16, logits fp32 sums (1e-6 of the largest).
+@pytest.mark.parametrize("T,D,tq,frames,rise", [(9, 128, 5, 3, 14.0), (32, 128, 40, 40, 5.0), (40, 64, 256, 61, 14.0), (64, 128, 256, 50, 2.0),
+                                                (33, 128, 256, 47, 30.0), (96, 64, 40, 37, -9.0)])
+def test_question_whose_weights_outgrow_their_reference(T, D, tq, frames, rise):
+    wl = _small(tokens_per_frame=T, head_dim=D, n_frames=frames, n_clusters=1, top_k=1, question_tokens=tq, warmup_frames=2)
+    g = torch.Generator().manual_seed(T)
+    U, H, Hq = wl.n_kv_heads, wl.n_kv_heads, wl.n_q_heads
+    along = torch.nn.functional.normalize(torch.randn(U, 1, D, generator=g), dim=-1)
+    at = (torch.arange(frames) % 31 + 1).view(-1, 1, 1, 1) * rise * D ** 0.5 / 8.0
+    k = (0.1 * torch.randn(frames, U, T, D, generator=g) + at * along).to(torch.bfloat16)
+    v = torch.randn(frames, U, T, D, generator=g).to(torch.bfloat16)
+    q = (8.0 * along.repeat_interleave(Hq // H, 0).transpose(0, 1) + 0.1 * torch.randn(tq, Hq, D, generator=g)).to(torch.bfloat16)
+    m = binding.Mosaic(binding.config_for(wl, max_q_tokens=tq), device=DEV)
+    m.ingest_frame(k.view(frames, 1, U, T, D).to(DEV), v.view(frames, 1, U, T, D).to(DEV))
+    m.retrieve(-1, q.view(1, tq, Hq, D).to(DEV))
+    o, lse = m.attend(-1, q.view(1, tq, Hq, D).to(DEV))
+    m.close()
+    for h in range(H):
+        rows = q.view(tq, H, Hq // H, D)[:, h].double().reshape(-1, D)
+        logit = rows @ k[:, h].double().reshape(-1, D).t() / D ** 0.5
+        ref = torch.softmax(logit, 1) @ v[:, h].double().reshape(-1, D)
+        got = o.cpu().view(tq, H, Hq // H, D)[:, h].double().reshape(-1, D)
+        got_lse = lse.cpu().view(tq, H, Hq // H)[:, h].double().reshape(-1)
+        assert (got - ref).abs().max().item() <= harness.OUT_TOL["bf16"]
+        assert (got_lse - torch.logsumexp(logit, 1)).abs().max().item() <= 1e-6 * logit.abs().max().item() + harness.LSE_TOL["bf16"]
+
+
 def test_question_with_room_for_few_partials(monkeypatch):
     # an arena with room for two splits per unit and no more (what a context needed before the equal shares): fewer shares, the
     # same result up to the order of the merge
