@@ -56,7 +56,7 @@ int fail_hip(mosaic_ctx *ctx, hipError_t e, const char *what) {
 }
 
 struct Layout {
-    size_t k_store, v_store, summ, r, rnorm, n, assign, pos, lloyd_moved, lloyd_delta, lloyd_ub, lloyd_lb, lloyd_live, sel_flag, sync_err, scores, ids, n_ids, sel_pages, n_sel,
+    size_t k_store, v_store, summ, r, rnorm, n, assign, pos, lloyd_moved, lloyd_delta, lloyd_bounds, sel_flag, sync_err, scores, ids, n_ids, sel_pages, n_sel,
         tok_scratch, part_o, part_ml, stage_k, stage_v, var, lazy, resident, n_slots, buf_frame,
         buf_owner, n_buf, mt_cnt, mt_mem, mt_side, mt_nrm, vsumm, rvsum, rep_k, rep_v, aug_o, aug_ml,
         vemb, vr, vrn, vn, part, pr, prn, pn, pscores, pids, n_pids, total;
@@ -189,11 +189,9 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
     L.n = take(U * C * 4);
     L.assign = take(U * F * 4);
     L.pos = take(U * F * 4);
-    L.lloyd_moved = take(U * 6 * 4 + U * C * 4);      // + the live-row counters and the clusters' changed flags
-    L.lloyd_live = take(U * ((F + 15) / 16) * 4);
+    L.lloyd_moved = take(U * 3 * 4 + U * C * 4);      // + the clusters' changed flags
     L.lloyd_delta = take(U * C * 8);
-    L.lloyd_ub = take(U * F * 8);
-    L.lloyd_lb = take(U * F * 8);
+    L.lloyd_bounds = take(U * F * 16);
     L.sel_flag = take(U * 8);
     L.sync_err = take(4);
     L.c_init = init_clusters_of(c); L.buf_max = buffer_max_of(c); L.W = warmup_of(c);
@@ -445,10 +443,9 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
     dv.summ = (double *)(base + L.summ); dv.r = (double *)(base + L.r);
     dv.rnorm = (double *)(base + L.rnorm); dv.n = (int *)(base + L.n);
     dv.assign = (int *)(base + L.assign); dv.pos = (int *)(base + L.pos);
-    dv.lloyd_moved = (int *)(base + L.lloyd_moved); dv.lloyd_changed = dv.lloyd_moved + (size_t)dv.U * 6;
-    dv.lloyd_live = (int *)(base + L.lloyd_live);
+    dv.lloyd_moved = (int *)(base + L.lloyd_moved); dv.lloyd_changed = dv.lloyd_moved + (size_t)dv.U * 3;
     dv.lloyd_delta = (double *)(base + L.lloyd_delta);
-    dv.lloyd_ub = (double *)(base + L.lloyd_ub); dv.lloyd_lb = (double *)(base + L.lloyd_lb);
+    dv.lloyd_bounds = (ChordBounds *)(base + L.lloyd_bounds);
     dv.sel_flag = (long long *)(base + L.sel_flag); dv.sync_err = (int *)(base + L.sync_err);
     ctx->launch_epoch = 0;
     dv.scores = (double *)(base + L.scores); dv.ids = (int *)(base + L.ids);
@@ -1344,7 +1341,7 @@ int32_t mosaic_get_assignments(mosaic_ctx *ctx, int32_t *frame_to_cluster) {
     int rc = join_ingest(ctx);
     if (rc != MOSAIC_OK) return rc;
     DeviceView out = dv;
-    out.batch_assign = reinterpret_cast<int *>(dv.lloyd_ub);
+    out.batch_assign = reinterpret_cast<int *>(dv.lloyd_bounds);
     const hipError_t e = launch_gather_assign(out, 0, (int)nf, ctx->stream);
     if (e != hipSuccess) return fail_hip(ctx, e, "assignment gather launch");
     return d2h(ctx, frame_to_cluster, out.batch_assign, nf * dv.U * 4);

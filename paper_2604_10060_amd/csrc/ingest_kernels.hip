@@ -1390,116 +1390,86 @@ __global__ __launch_bounds__(kBlock) void k_exact_var(DeviceView dv, int n_frame
 // The slot of the round after is cleared by this launch, which neither reads nor counts in it.
 //
 // Frames whose assignment cannot change are skipped as well, by the distance bounds of accelerated
-// K-means (Hamerly, SDM 2010) taken on the unit sphere, where the largest cosine is the smallest chord
-// d(s, r) = |s/|s| - r/|r|| = sqrt(2 - 2 cos): a round that computes a frame's similarities leaves
-// ub = d(own representative) and lb = d(best other candidate); an update that moves representative j by
-// delta_j = d(old r_j, new r_j) can shrink any frame's distance to it by at most delta_j, so after it
-// ub + delta_own still bounds the own distance from above and lb - max_{j != own} delta_j the others from
-// below (triangle inequality).  While ub + 1e-6 < lb the own representative wins by a margin far above
-// the rounding of the similarities (> 5e-13 in the cosine) and the full computation would return the same
-// id: a row of 16 frames (what one wavefront multiplies) whose frames all pass only gets the moved bounds
-// stored (k_lloyd_bounds); any other is recomputed in full and leaves exact bounds again.  Round 0 computes
-// everything.  After the first round a handful of frames per unit keeps moving and a few representatives with
-// them, so most rows pass.  The assignments are the same as without the test, by construction.
-constexpr double kBoundMargin = 1e-6;
+// K-means (Hamerly, SDM 2010; bounds by groups of representatives: Ding et al., ICML 2015) taken on the unit sphere, where the largest
+// cosine is the smallest chord d(s, r) = |s/|s| - r/|r|| = sqrt(2 - 2 cos): a round that computes a frame's similarities leaves
+// ub = d(own representative) and, for each group of representatives, lb = the least d to one of the group other than its own; an update that
+// moves representative j by delta_j = d(old r_j, new r_j) can change any frame's distance to it by at most delta_j, so after it
+// ub + delta_own still bounds the own distance from above and lb - max delta_j over the group the others from below (triangle
+// inequality).  While ub < lb for every group, by more than the rounding of the similarities (> 5e-13 in the cosine), the own representative
+// wins and the full computation would return the same id: such a frame only gets the moved bounds stored.  Any other is computed again
+// against the groups that fail and its own, whose bounds are then exact again.  Round 0 computes everything.
+// The assignments are the same as without the test, by construction: a similarity is the same sum whichever others are formed beside it.
+// Bounds are whole multiples of 2^-14, rounded outwards: ub < lb then means a distance of at least that.  A frame's eight, 16 bytes: ub, then
+// seven groups' lb.  (One lb for all other representatives, sixteen consecutive frames at a time: a representative that jumps far made every row of its unit live
+// again, 45 % of the frame-candidate pairs of the second round of 112 units x 1536 frames and 10 to 60 % of those after it; by groups and single
+// frames 3 and 0.1 to 3 %.)
+constexpr int kChordOne = 1 << 14, kChordNever = 65534, kChordNone = 65535;    // 1.0; an ub no lb exceeds; the lb of a group without candidates
+__device__ __forceinline__ int chord_up(double d) { return d < 2.0 ? (int)(d * kChordOne) + 1 : 2 * kChordOne; }          // (also where d is no number)
+__device__ __forceinline__ int chord_down(double d) { return d > 0.0 ? (int)fmin(d * kChordOne, 2.0 * kChordOne) : 0; }
 
-// The bound test of a round it >= 1, for all frames of a unit: grid (U, ceil(F/1024)), 256 threads, a lane per
-// frame, sixteen consecutive frames (what one wavefront of k_lloyd_assign multiplies) per 16-lane row.  A row
-// whose frames all pass stores their moved bounds; any other is appended to the unit's list of live rows
-// (order of arrival: every frame's result is independent of it), which k_lloyd_assign then works through
-// four rows per workgroup, so that the few rows still alive fill whole workgroups.
-__global__ __launch_bounds__(kBlock) void k_lloyd_bounds(DeviceView dv, int n_frames, int it) {
-    const int u = blockIdx.x, tid = threadIdx.x, wave = tid / 64, lane = tid % 64, C = dv.C;
-    int *n_live = dv.lloyd_moved + (size_t)dv.U * 3 + (size_t)u * 3;
-    if (blockIdx.y == 0 && tid == 0) n_live[(it + 1) % 3] = 0;
-    if (dv.lloyd_moved[(size_t)u * 3 + (it - 1) % 3] == 0) return;      // converged (as in k_lloyd_assign)
-    __shared__ double top_v[4][2];
-    __shared__ int top_j[4];
-    // largest and second largest movement of a representative in the last update, and whose the largest was
-    const double *delta = dv.lloyd_delta + (size_t)u * C;
-    double d1 = 0.0, d2 = 0.0;
-    int j1 = -1;
-    for (int j = tid; j < C; j += kBlock) {
-        const double dj = delta[j];
-        if (dj > d1) { d2 = d1; d1 = dj; j1 = j; }
-        else if (dj > d2) d2 = dj;
+// The groups: a frame's candidates span `span` tiles of 16 ids at most, counted from the tile of its first candidate; group g has
+// tiles lo(g) .. lo(g + 1) - 1 of them.
+struct LloydGroups {
+    int span;
+    __device__ __forceinline__ explicit LloydGroups(const DeviceView &dv)
+        : span(dv.P > 0 ? (dv.Cs % 16 == 0 ? dv.Cs / 16 : (dv.Cs + 14) / 16 + 1) : (dv.C + 15) / 16) {}
+    __device__ __forceinline__ int lo(int g) const { return span <= kLloydGroups ? min(g, span) : (g * span + kLloydGroups - 1) / kLloydGroups; }
+    __device__ __forceinline__ int of(int t) const { return span <= kLloydGroups ? t : t * kLloydGroups / span; }
+    // tiles of group g of a frame whose candidates lie in tiles t0 .. t1 - 1, as a mask
+    __device__ __forceinline__ unsigned long long tiles(int g, int t0, int t1) const {
+        const int a = t0 + lo(g), b = min(t0 + lo(g + 1), t1);
+        return a < b ? (~0ull >> (64 - (b - a))) << a : 0ull;
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const double o1 = __shfl_xor(d1, o, 64), o2 = __shfl_xor(d2, o, 64);
-        const int oj = __shfl_xor(j1, o, 64);
-        if (o1 > d1) { d2 = fmax(d1, o2); d1 = o1; j1 = oj; }
-        else d2 = fmax(d2, o1);
-    }
-    if (lane == 0) { top_v[wave][0] = d1; top_v[wave][1] = d2; top_j[wave] = j1; }
-    __syncthreads();
-    d1 = top_v[0][0]; d2 = top_v[0][1]; j1 = top_j[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w) {
-        const double o1 = top_v[w][0], o2 = top_v[w][1];
-        if (o1 > d1) { d2 = fmax(d1, o2); d1 = o1; j1 = top_j[w]; }
-        else d2 = fmax(d2, o1);
-    }
-    const int fend = min(n_frames, (int)(blockIdx.y + 1) * 1024);
-    for (int f0 = blockIdx.y * 1024 + wave * 64; f0 < fend; f0 += kBlock) {
-        const int f = f0 + lane;
-        bool safe = true;
-        double ubn = 0.0, lbn = 0.0;
-        if (f < n_frames) {
-            const int a_old = dv.assign[(size_t)u * dv.F + f];
-            ubn = dv.lloyd_ub[(size_t)u * dv.F + f] + delta[a_old];
-            lbn = dv.lloyd_lb[(size_t)u * dv.F + f] - (a_old == j1 ? d2 : d1);
-            safe = ubn + kBoundMargin < lbn;
-        }
-        const unsigned long long unsafe = __ballot(!safe);
-        const bool row_live = ((unsafe >> (lane & 48)) & 0xffffull) != 0ull;
-        if (!row_live && f < n_frames) {
-            dv.lloyd_ub[(size_t)u * dv.F + f] = ubn;
-            dv.lloyd_lb[(size_t)u * dv.F + f] = lbn;
-        }
-        // the wavefront's live rows (at most four) take consecutive slots of the list
-        unsigned int rows = 0;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) rows |= (((unsafe >> (16 * g)) & 0xffffull) != 0ull ? 1u : 0u) << g;
-        if (rows) {
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&n_live[it % 3], __popc(rows));
-            base = __shfl(base, 0, 64);
-            const int g = lane / 16;
-            if ((lane & 15) == 0 && ((rows >> g) & 1u))
-                dv.lloyd_live[(size_t)u * ((dv.F + 15) / 16) + base + __popc(rows & ((1u << g) - 1u))] = f0 / 16 + g;
-        }
-    }
+};
+
+// (written out: the compiler's own fmaxf first makes a quiet number of every operand that comes from another lane)
+__device__ __forceinline__ float max_f32(float a, float b) { float r; asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
+__device__ __forceinline__ float min_f32(float a, float b) { float r; asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
+__device__ __forceinline__ float max3_f32(float a, float b, float c) { float r; asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
+template <int CTRL> __device__ __forceinline__ float dpp_f32(float x) { return __int_as_float(dpp_i32<CTRL>(__float_as_int(x))); }
+// largest and second largest of x over the 16 lanes of a row, in every lane
+__device__ __forceinline__ void row16_top2(float x, float &m1, float &m2) {
+    float o = dpp_f32<kDppXor8>(x);
+    m2 = min_f32(x, o);
+    m1 = max_f32(x, o);
+    o = dpp_f32<kDppXor7>(m1);
+    m2 = max3_f32(m2, dpp_f32<kDppXor7>(m2), min_f32(m1, o));
+    m1 = max_f32(m1, o);
+    o = dpp_f32<kDppXor3>(m1);
+    m2 = max3_f32(m2, dpp_f32<kDppXor3>(m2), min_f32(m1, o));
+    m1 = max_f32(m1, o);
+    o = dpp_f32<kDppXor1>(m1);
+    m2 = max3_f32(m2, dpp_f32<kDppXor1>(m2), min_f32(m1, o));
+    m1 = max_f32(m1, o);
+}
+template <int CTRL> __device__ __forceinline__ unsigned int or_step(unsigned int x) { return x | (unsigned int)dpp_i32<CTRL>((int)x); }
+__device__ __forceinline__ unsigned int row16_or(unsigned int x) {
+    return or_step<kDppXor1>(or_step<kDppXor3>(or_step<kDppXor7>(or_step<kDppXor8>(x))));
 }
 
-// LATER: the instantiation for the rounds after the first.  Their launches are mostly workgroups that find nothing to
-// do and lone tasks that are all latency, so it may use more registers (two wavefronts per SIMD are plenty) to start
-// every independent load at once: both round counters and the wavefront's list entry together, the frames' old ids
-// with the operands, the table built while the operands travel; and its bounds take their roots in fp32.
-template <int D, bool LATER>
+// Round 0: grid (U, ceil(F/64)), a workgroup's four wavefronts take 16 consecutive frames each.  LATER, the instantiation for the rounds after
+// it: grid (U, ceil(F/128)); a workgroup tests 128 frames, a thread each, and its wavefronts then take the live ones 16 at a time, in order,
+// so that those taken together mostly ask for the same tiles.  A tile of 16 representatives that no frame of a wavefront asks for is not multiplied, one that
+// none of the workgroup's asks for is not staged.  (256 frames a workgroup: where most are live its tasks follow one another, 10 us longer.)
+// 112 units, C = 128, 512 to 1536 frames, a later round on average, nothing beside it: rows of sixteen consecutive frames, live or not by one bound, in a
+// list that a launch of its own made, all tiles for each: 7.6 + 57 us; now 35 us (18 us where little is live).  4 units of C = 512 in 16
+// partitions: 6.1 + 39.5 us; now 16 us; round 0, where tiles of other partitions are no longer multiplied, 59 -> 40 us.
+constexpr int kLloydTest = 128;
+template <int D, bool LATER, bool NESTED>
 __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(DeviceView dv, int n_frames, int it) {
     constexpr int KS = D / 8;
-    const int u = blockIdx.x, tid = threadIdx.x, wave = tid / 64, lane = tid % 64, C = dv.C;
+    static_assert(kLloydTest <= kBlock && kLloydTest % 64 == 0, "a thread per frame, whole wavefronts");
+    const int u = blockIdx.x, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, C = dv.C;
     const int row = lane % 16, kq = lane / 16;
     int *moved = dv.lloyd_moved + (size_t)u * 3;
     if (blockIdx.y == 0 && tid == 0) moved[(it + 1) % 3] = 0;
-    // Round 0: one task per workgroup, wavefront w of workgroup y takes frames 64 y + 16 w ...  Later rounds:
-    // task t = rows 4 t .. 4 t + 3 of the unit's list of live rows, the workgroups of a unit taking tasks in turn.
-    const int n_rows = (dv.F + 15) / 16;
-    const int *live_list = dv.lloyd_live + (size_t)u * n_rows;
-    int cnt = 0, first_row = 0;
-    if constexpr (LATER) {
-        const int moved_before = moved[(it - 1) % 3];
-        cnt = dv.lloyd_moved[(size_t)dv.U * 3 + (size_t)u * 3 + it % 3];
-        first_row = live_list[min((int)blockIdx.y * 4 + wave, n_rows - 1)];
-        if (moved_before == 0) return;                         // workgroup-uniform: converged in an earlier round
-        if ((int)blockIdx.y * 4 >= cnt) return;                // workgroup-uniform
-    }
     const double *r = dv.r + (size_t)u * C * D;
     const int n_tiles = (C + 15) / 16;
+    const LloydGroups groups(dv);
+    ChordBounds *bounds = dv.lloyd_bounds + (size_t)u * dv.F;
     // A tile of 16 representatives is shared by the four wavefronts through LDS (each row is read
     // from L2 once per workgroup); rows are padded by 16 bytes so that the 16 lanes of a k group hit
-    // 16 different 16-byte bank groups.  Tile ct+1 travels global -> registers while tile ct is used.
+    // 16 different 16-byte bank groups.  The next tile travels global -> registers while one is used.
     constexpr int LROW = D + 2, PPT = 16 * D / 2 / kBlock;        // doubles per LDS row; 16-byte pieces per thread
     __shared__ __attribute__((aligned(16))) double b_lds[2][16][LROW];
     f64x2 stg[PPT];
@@ -1527,44 +1497,140 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(DeviceVi
     // (all 0) do.
     __shared__ __attribute__((aligned(16))) f64x2 scale_sh[1024 + 16];    // the cluster-count limit of a context, rounded up to tiles
     __shared__ double sn_sh[4][16];
-    auto build_table = [&]() {
-        for (int j = tid; j < 16 * n_tiles; j += kBlock) {
-            f64x2 e = {0.0, -INFINITY};
-            if (j < C && dv.n[(size_t)u * C + j] > 0) {
-                const double rnj = dv.rnorm[(size_t)u * C + j];
-                e.x = rnj == 0.0 ? 0.0 : 1.0 / rnj;
-                e.y = 0.0;
-            }
-            scale_sh[j] = e;
+    __shared__ unsigned long long tiles_sh[4];
+    __shared__ unsigned char group_sh[64];                                // group of a tile, counted from the frame's first
+    // LATER: a tile's largest movement of a representative * 16 + 15 - whose, and its second largest; the live frames, and the tiles they ask for
+    __shared__ unsigned short delta_sh[LATER ? 1024 + 16 : 1];            // what the last update moved a representative by, at most
+    __shared__ int top_sh[LATER ? 64 : 1], second_sh[LATER ? 64 : 1], live_sh[LATER ? 4 : 1];
+    __shared__ unsigned char list_sh[LATER ? kLloydTest : 1];
+    __shared__ unsigned long long need_sh[LATER ? kLloydTest : 1];
+    const int f0 = blockIdx.y * (LATER ? kLloydTest : 64);
+    int n_live = min(64, n_frames - f0);
+    ChordBounds cb{};
+    int own = 0, plo_t = 0, moved_before = 1;
+    // (loads without a condition, before anything waits for one)
+    int nj = dv.n[(size_t)u * C + min(tid, C - 1)];
+    double rnj = dv.rnorm[(size_t)u * C + min(tid, C - 1)], dj = 0.0;
+    if constexpr (LATER) {
+        const int f = min(f0 + tid, n_frames - 1);
+        dj = dv.lloyd_delta[(size_t)u * C + min(tid, C - 1)];
+        cb = bounds[f];
+        own = dv.assign[(size_t)u * dv.F + f];
+        if constexpr (NESTED) plo_t = dv.part[f] * dv.Cs;
+        moved_before = moved[(it - 1) % 3];
+        if (moved_before == 0) return;                         // workgroup-uniform: converged in an earlier round
+    }
+    for (int j = tid; j < 16 * n_tiles; j += kBlock) {
+        if (j >= kBlock) {
+            nj = dv.n[(size_t)u * C + min(j, C - 1)];
+            rnj = dv.rnorm[(size_t)u * C + min(j, C - 1)];
+            if constexpr (LATER) dj = dv.lloyd_delta[(size_t)u * C + min(j, C - 1)];
         }
-    };
-    if constexpr (!LATER) build_table();
-    const bool nested = dv.P > 0;
-    for (int task = blockIdx.y;; task += gridDim.y) {
-        int fbase = task * 64 + wave * 16;
-        bool live = true;
+        f64x2 e = {0.0, -INFINITY};
+        if (j < C && nj > 0) {
+            e.x = rnj == 0.0 ? 0.0 : 1.0 / rnj;
+            e.y = 0.0;
+        }
+        scale_sh[j] = e;
         if constexpr (LATER) {
-            if (task * 4 >= cnt) break;                         // workgroup-uniform
-            live = task * 4 + wave < cnt;
-            fbase = !live ? 0 : 16 * (task == (int)blockIdx.y ? first_row : live_list[task * 4 + wave]);
+            if (j >= C) dj = 0.0;
+            const int d = dj == 0.0 ? 0 : chord_up(dj);
+            delta_sh[j] = (unsigned short)d;
+            int top = 16 * d + 15 - row;
+            top = max(top, dpp_i32<kDppXor8>(top));
+            top = max(top, dpp_i32<kDppXor7>(top));
+            top = max(top, dpp_i32<kDppXor3>(top));
+            top = max(top, dpp_i32<kDppXor1>(top));
+            int second = row == 15 - top % 16 ? 0 : d;
+            second = max(second, dpp_i32<kDppXor8>(second));
+            second = max(second, dpp_i32<kDppXor7>(second));
+            second = max(second, dpp_i32<kDppXor3>(second));
+            second = max(second, dpp_i32<kDppXor1>(second));
+            if (row == 0) { top_sh[j / 16] = top; second_sh[j / 16] = second; }
         }
-        fetch_tile(0);
+    }
+    if (tid < groups.span) group_sh[tid] = (unsigned char)groups.of(tid);
+    if constexpr (LATER) {
+        // the test
+        __syncthreads();
+        const int t0 = plo_t / 16, t1 = (NESTED ? plo_t + dv.Cs - 1 : C - 1) / 16 + 1;
+        const bool in = tid < kLloydTest && f0 + tid < n_frames;
+        const int ub = min((int)cb.ub + (int)delta_sh[own], kChordNever);
+        unsigned long long need = 0;
+#pragma unroll
+        for (int g = 0; g < kLloydGroups; ++g) {
+            int d = 0;
+            for (int t = groups.lo(g); t < groups.lo(g + 1); ++t) {         // (uniform)
+                const int tt = min(t0 + t, n_tiles - 1), top = top_sh[tt];
+                const int dt = tt == own / 16 && top % 16 == 15 - own % 16 ? second_sh[tt] : top / 16;
+                d = t0 + t < t1 ? max(d, dt) : d;
+            }
+            const int lb = cb.lb[g] == kChordNone ? kChordNone : max(0, (int)cb.lb[g] - d);
+            cb.lb[g] = (unsigned short)lb;
+            if (ub >= lb) need |= groups.tiles(g, t0, t1);
+        }
+        cb.ub = (unsigned short)ub;
+        if (in) bounds[f0 + tid] = cb;
+        const bool live = in && need != 0;
+        if (live) need |= groups.tiles(group_sh[own / 16 - t0], t0, t1);    // the own group: the exact own distance, and its bound if the frame leaves
+        if (tid < kLloydTest) need_sh[tid] = need;
+        const unsigned long long lv = __ballot(live);
+        if (lane == 0) live_sh[wave] = __popcll(lv);
+        __syncthreads();
+        int at = __popcll(lv & ((1ull << lane) - 1));
+        n_live = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) { at += w < wave ? live_sh[w] : 0; n_live += live_sh[w]; }
+        if (n_live == 0) return;                                // workgroup-uniform
+        if (live) list_sh[at] = (unsigned char)tid;
+        __syncthreads();
+    }
+    for (int task = 0; task < n_live; task += 64) {
+        const int k0 = task + 16 * wave;                        // this wavefront's frames: k0 .. of the live ones
+        const bool busy = k0 < n_live;
+        auto frame = [&](int i) {                               // the i-th of them (the last live one past the end)
+            const int k = min(k0 + i, n_live - 1);
+            return f0 + (LATER ? (int)list_sh[k] : k);
+        };
         f64x2 a[KS];
-        int a_old[4] = {0, 0, 0, 0};     // LATER: the frames' ids before this round, for the lane that finishes them
-        if (live) {
-            const int f = min(fbase + row, n_frames - 1);
+        unsigned long long mine = 0;                            // tiles that the frames of this lane's row ask for
+        if (busy) {
+            const int f = frame(row);
             const double *sp = dv.summ + ((size_t)u * dv.F + f) * D + 2 * kq;
 #pragma unroll
             for (int s = 0; s < KS; ++s) a[s] = *reinterpret_cast<const f64x2 *>(sp + 8 * s);
-            if constexpr (LATER) {
+            if constexpr (LATER) mine = need_sh[f - f0];
+            else {
+                const int lo = NESTED ? dv.part[f] * dv.Cs : 0, hi = NESTED ? lo + dv.Cs : C;
+                mine = (~0ull >> (63 - (hi - 1) / 16 + lo / 16)) << (lo / 16);
+            }
+            mine = ((unsigned long long)row16_or((unsigned int)(mine >> 32)) << 32) | row16_or((unsigned int)mine);
+        }
+        mine = ((unsigned long long)(unsigned int)__builtin_amdgcn_readfirstlane((int)(mine >> 32)) << 32) |
+               (unsigned int)__builtin_amdgcn_readfirstlane((int)mine);
+        if (lane == 0) tiles_sh[wave] = mine;
+        int fv[4], plo[4], phi[4], bi[4];
+        double bv[4];
+        float g1[4], g2[4];              // of group `row`: largest and second largest similarity (times |s|)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) a_old[v] = dv.assign[(size_t)u * dv.F + min(fbase + 4 * v + kq, n_frames - 1)];
+        for (int v = 0; v < 4; ++v) {    // the four result rows of this lane
+            bv[v] = -INFINITY; bi[v] = 0x7fffffff; g1[v] = -INFINITY; g2[v] = -INFINITY;
+            fv[v] = frame(4 * v + kq); plo[v] = 0; phi[v] = C;
+            if constexpr (NESTED) {        // nested hierarchy: only the ids of the frame's visual partition are candidates
+                plo[v] = dv.part[fv[v]] * dv.Cs;
+                phi[v] = plo[v] + dv.Cs;
             }
         }
-        if constexpr (LATER) {
-            if (task == (int)blockIdx.y) build_table();        // once, while the summaries are on their way
-        }
-        if (live) {
+        __syncthreads();
+        unsigned long long left = tiles_sh[0] | tiles_sh[1] | tiles_sh[2] | tiles_sh[3];
+        left = ((unsigned long long)(unsigned int)__builtin_amdgcn_readfirstlane((int)(left >> 32)) << 32) |
+               (unsigned int)__builtin_amdgcn_readfirstlane((int)left);
+        int ct = __ffsll((long long)left) - 1, buf = 0;
+        fetch_tile(ct);
+        int a_was[4] = {0, 0, 0, 0};     // the frames' ids before this round, for the lane that finishes them
+        if (busy) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) a_was[v] = dv.assign[(size_t)u * dv.F + fv[v]];
             double sq = 0.0;
 #pragma unroll
             for (int s = 0; s < KS; ++s) sq += a[s].x * a[s].x + a[s].y * a[s].y;
@@ -1572,27 +1638,16 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(DeviceVi
             sq += __shfl_xor(sq, 32, 64);
             if (kq == 0) sn_sh[wave][row] = sqrt(sq);
         }
-        // the four result rows of this lane: frames fbase + 4v + kq; best and second best similarity (times |s|)
-        double bv[4], sv[4];
-        int plo[4], phi[4], bi[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            bv[v] = -INFINITY; sv[v] = -INFINITY; bi[v] = 0x7fffffff;
-            plo[v] = 0; phi[v] = C;
-            if (nested) {        // nested hierarchy: only the ids of the frame's visual partition are candidates
-                plo[v] = dv.part[min(fbase + 4 * v + kq, n_frames - 1)] * dv.Cs;
-                phi[v] = plo[v] + dv.Cs;
-            }
-        }
         stage_tile(0);
         __syncthreads();
-        for (int ct = 0; ct < n_tiles; ++ct) {
-            const int ctn = min(ct + 1, n_tiles - 1);
-            fetch_tile(ctn);
-            if (live) {
+        for (;;) {
+            left &= left - 1;
+            const int next = left ? __ffsll((long long)left) - 1 : ct;
+            fetch_tile(next);
+            if ((mine >> ct) & 1) {                             // wave-uniform
                 f64x2 b[KS];
 #pragma unroll
-                for (int s = 0; s < KS; ++s) b[s] = *reinterpret_cast<const f64x2 *>(&b_lds[ct & 1][row][8 * s + 2 * kq]);
+                for (int s = 0; s < KS; ++s) b[s] = *reinterpret_cast<const f64x2 *>(&b_lds[buf][row][8 * s + 2 * kq]);
                 const f64x2 sc = scale_sh[16 * ct + row];
                 // one accumulator chain: back-to-back matrix instructions on the same accumulator sustain 70 TFLOP/s
                 // in a probe of nothing else, two alternating accumulators 66, four 58
@@ -1603,79 +1658,67 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(DeviceVi
                     acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s].y, b[s].y, acc, 0, 0, 0);
                 }
                 const int j = 16 * ct + row;
-                // A lane meets its candidates in ascending id order, so a strict comparison keeps the lowest id of
-                // equals; the second best is kept for the bounds.
-                if (nested) {
+                // A lane meets its candidates in ascending id order, so a strict comparison keeps the lowest id of equals.
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        double c = __builtin_fma(acc[v], sc.x, sc.y);
-                        if (j < plo[v] || j >= phi[v]) c = -INFINITY;
-                        bi[v] = c > bv[v] ? j : bi[v];
-                        sv[v] = max_f64(sv[v], min_f64(bv[v], c));
-                        bv[v] = max_f64(bv[v], c);
-                    }
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const double c = __builtin_fma(acc[v], sc.x, sc.y);
-                        bi[v] = c > bv[v] ? j : bi[v];
-                        sv[v] = max_f64(sv[v], min_f64(bv[v], c));
-                        bv[v] = max_f64(bv[v], c);
-                    }
+                for (int v = 0; v < 4; ++v) {
+                    double c = __builtin_fma(acc[v], sc.x, sc.y);
+                    if (NESTED && (j < plo[v] || j >= phi[v])) c = -INFINITY;
+                    bi[v] = c > bv[v] ? j : bi[v];
+                    bv[v] = max_f64(bv[v], c);
+                    // the tile's two largest join those of its group (lane `row` keeps group `row`)
+                    const int t = ct - plo[v] / 16;
+                    const bool here = row == (int)group_sh[NESTED ? min(max(t, 0), groups.span - 1) : ct];
+                    float m1, m2;
+                    row16_top2((float)c, m1, m2);
+                    m1 = here ? m1 : -INFINITY;                 // (no branch: the four rows' chains interleave)
+                    m2 = here ? m2 : -INFINITY;
+                    g2[v] = max3_f32(g2[v], m2, min_f32(g1[v], m1));
+                    g1[v] = max_f32(g1[v], m1);
                 }
             }
-            stage_tile((ct + 1) & 1);       // the other buffer: last read before the previous barrier
+            if (left == 0) break;                               // workgroup-uniform
+            stage_tile(buf ^ 1);            // the other buffer: last read before the previous barrier
             __syncthreads();
+            ct = next;
+            buf ^= 1;
         }
-        if (live) {
-            // best and second best over the 16 columns a lane group covers (lanes 16k .. 16k + 15)
+        if (busy) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-#pragma unroll
-                for (int o = 8; o >= 1; o >>= 1) {
-                    const double ov = __shfl_xor(bv[v], o, 16), os = __shfl_xor(sv[v], o, 16);
-                    const int oi = __shfl_xor(bi[v], o, 16);
-                    if (better(ov, oi, bv[v], bi[v])) { sv[v] = max_f64(bv[v], os); bv[v] = ov; bi[v] = oi; }
-                    else sv[v] = max_f64(sv[v], ov);
+                // best over the 16 columns a lane group covers (lanes 16k .. 16k + 15)
+                best_step<kDppXor8>(bv[v], bi[v]);
+                best_step<kDppXor7>(bv[v], bi[v]);
+                best_step<kDppXor3>(bv[v], bi[v]);
+                best_step<kDppXor1>(bv[v], bi[v]);
+                if (k0 + 4 * v + kq >= n_live) continue;
+                const int f = fv[v];
+                const bool none = bv[v] == -INFINITY;            // no candidate at all: the first id of the range
+                const int a_new = none ? plo[v] : bi[v];
+                if (row == 0 && a_was[v] != a_new) {
+                    dv.assign[(size_t)u * dv.F + f] = a_new;
+                    atomicAdd(&moved[it % 3], 1);
+                    // both clusters' sums change; every other cluster's update is skipped (round 0 updates all)
+                    dv.lloyd_changed[(size_t)u * C + a_new] = 1;
+                    if (a_was[v] >= 0 && a_was[v] < C) dv.lloyd_changed[(size_t)u * C + a_was[v]] = 1;
                 }
-                const int f = fbase + 4 * v + kq;
-                if (row == 0 && f < n_frames) {
-                    const bool none = bv[v] == -INFINITY;            // no candidate at all: the first id of the range
-                    const int a_new = none ? plo[v] : bi[v];
-                    int *slot = dv.assign + (size_t)u * dv.F + f;
-                    const int a_was = LATER ? a_old[v] : *slot;
-                    if (a_was != a_new) {
-                        *slot = a_new;
-                        atomicAdd(&moved[it % 3], 1);
-                        // both clusters' sums change; every other cluster's update is skipped (round 0 updates all)
-                        dv.lloyd_changed[(size_t)u * C + a_new] = 1;
-                        if (a_was >= 0 && a_was < C) dv.lloyd_changed[(size_t)u * C + a_was] = 1;
-                    }
-                    // chords to the winner and to the best other candidate (a frame without a winner, or an all-zero
-                    // summary, whose cosines are all 0, is never skipped)
-                    const double sn = sn_sh[wave][4 * v + kq];
-                    double ubn = 2.0, lbn = 0.0;
-                    if (!none && sn > 0.0) {
-                        if constexpr (LATER) {
-                            // They only have to bound: roots in fp32 (relative error below 2e-7 with the conversion),
-                            // pushed outwards by 1e-6 relative and 1e-9 absolute; an fp64 root is a dozen instructions
-                            // and, like the fp64 division, keeps a flag in VCC, so a lane's eight ran one after the other.
-                            const double inv = 1.0 / sn;
-                            ubn = (double)sqrtf((float)fmax(0.0, 2.0 - 2.0 * (bv[v] * inv))) * (1.0 + 1e-6) + 1e-9;
-                            lbn = sv[v] == -INFINITY
-                                      ? INFINITY
-                                      : fmax(0.0, (double)sqrtf((float)fmax(0.0, 2.0 - 2.0 * (sv[v] * inv))) * (1.0 - 1e-6) - 1e-9);
-                        } else {
-                            ubn = sqrt(fmax(0.0, 2.0 - 2.0 * (bv[v] / sn)));
-                            lbn = sv[v] == -INFINITY ? INFINITY : sqrt(fmax(0.0, 2.0 - 2.0 * (sv[v] / sn)));
-                        }
-                    }
-                    dv.lloyd_ub[(size_t)u * dv.F + f] = ubn;
-                    dv.lloyd_lb[(size_t)u * dv.F + f] = lbn;
-                }
+                // Chords to the winner (lane 7) and to the best other candidate of group `row` (a frame without a winner, or whose
+                // summary is all zeros or nearly, is never skipped).  Roots in fp32, pushed outwards (relative error below 2e-7 with the
+                // conversion); a similarity that has been rounded to fp32 is pushed upwards first.
+                const double sn = sn_sh[wave][4 * v + kq], inv = 1.0 / sn;
+                const bool sound = !none && sn > 1e-30 && sn < 1e30;         // (what fp32 similarities hold)
+                const int t0 = plo[v] / 16, t1 = (phi[v] - 1) / 16 + 1;
+                const unsigned long long gt = row < kLloydGroups ? groups.tiles(row, t0, t1) : 0ull;
+                const float sim = row == (int)group_sh[sound ? a_new / 16 - t0 : 0] ? g2[v] : g1[v];
+                const double cos = row == 7 ? bv[v] * inv : ((double)sim + fabs((double)sim) * 1.2e-7) * inv;
+                const double chord = (double)sqrtf((float)fmax(0.0, 2.0 - 2.0 * cos));
+                unsigned short *o = reinterpret_cast<unsigned short *>(bounds + f);
+                if (row == 7) o[0] = (unsigned short)(sound ? chord_up(chord * (1.0 + 1e-6) + 1e-9) : kChordNever);
+                else if (row < kLloydGroups && (mine & gt) == gt)
+                    o[1 + row] = (unsigned short)(!sound ? 0 : sim == -INFINITY ? kChordNone : chord_down(chord * (1.0 - 1e-6) - 1e-9));
             }
         }
         if constexpr (!LATER) break;
+        __syncthreads();                                        // (the buffers and masks are written again)
     }
 }
 
@@ -1974,26 +2017,26 @@ hipError_t launch_lloyd(const DeviceView &dv, int n_frames, int iters, bool seed
         });
         if (e != hipSuccess) return e;
     }
-    dim3 ga(dv.U, (n_frames + 63) / 64), gu(dv.U, dv.C);
-    // the rounds' moved-frame counters, live-row counters and, behind them, the clusters' changed flags
-    if ((e = hipMemsetAsync(dv.lloyd_moved, 0, ((size_t)dv.U * 6 + (size_t)dv.U * dv.C) * 4, s)) != hipSuccess) return e;
+    const dim3 gu(dv.U, dv.C);
+    // the rounds' moved-frame counters and, behind them, the clusters' changed flags
+    if ((e = hipMemsetAsync(dv.lloyd_moved, 0, ((size_t)dv.U * 3 + (size_t)dv.U * dv.C) * 4, s)) != hipSuccess) return e;
     for (int it = 0; it < iters; ++it) {
-        if (it > 0) {
-            e = checked([&] { k_lloyd_bounds<<<dim3(dv.U, (n_frames + 1023) / 1024), kBlock, 0, s>>>(dv, n_frames, it); });
-            if (e != hipSuccess) return e;
-        }
-        // (later rounds: a workgroup per task of four live rows, the rest of the grid exits at once; fewer
-        // workgroups that take tasks in turn were slower, 80 against 59 us per round: a unit whose rows mostly
-        // stay alive then keeps its few workgroups busy for several tasks)
-        const dim3 gi = ga;
         e = checked([&] {
-            if (it == 0) {
-                if (dv.D == 64) k_lloyd_assign<64, false><<<gi, kBlock, 0, s>>>(dv, n_frames, it);
-                else k_lloyd_assign<128, false><<<gi, kBlock, 0, s>>>(dv, n_frames, it);
-            } else {
-                if (dv.D == 64) k_lloyd_assign<64, true><<<gi, kBlock, 0, s>>>(dv, n_frames, it);
-                else k_lloyd_assign<128, true><<<gi, kBlock, 0, s>>>(dv, n_frames, it);
-            }
+            const int per = it == 0 ? 64 : kLloydTest;
+            const dim3 g(dv.U, (n_frames + per - 1) / per);
+            auto go = [&](auto kern) { kern<<<g, kBlock, 0, s>>>(dv, n_frames, it); };
+            auto pick = [&](auto d, auto later) {
+                constexpr int D = decltype(d)::value;
+                constexpr bool LATER = decltype(later)::value;
+                if (dv.P > 0) go(k_lloyd_assign<D, LATER, true>);
+                else go(k_lloyd_assign<D, LATER, false>);
+            };
+            auto by_d = [&](auto later) {
+                if (dv.D == 64) pick(std::integral_constant<int, 64>{}, later);
+                else pick(std::integral_constant<int, 128>{}, later);
+            };
+            if (it == 0) by_d(std::false_type{});
+            else by_d(std::true_type{});
         });
         if (e != hipSuccess) return e;
         e = checked([&] {

@@ -129,6 +129,63 @@ def test_recluster_rounds_with_skipped_frames_parity(kw):
     assert rep.lloyd_runs >= 2 * 4
 
 
+# Bounds are kept by groups of tiles of representatives: as many tiles as groups, one more, groups of two to nine tiles; frames on both
+# sides of a workgroup's 128; partitions whose ids begin and end inside a tile, and of more tiles than groups; and summaries that are zero,
+# equal, or far too small for the bounds' fp32 similarities
+@pytest.mark.parametrize("kw", [
+    dict(n_clusters=112, warmup_frames=128, n_frames=400, recluster_every=129),
+    dict(n_clusters=113, warmup_frames=226, n_frames=400, recluster_every=127, head_dim=64),
+    dict(n_clusters=200, warmup_frames=200, n_frames=520, recluster_every=256),
+    dict(n_clusters=1024, warmup_frames=1024, n_frames=1300, recluster_every=1280, tokens_per_frame=2, lloyd_iters=4),
+])
+def test_recluster_bounds_by_groups_parity(kw):
+    wl = _small(**{**dict(scene_model="rapid", noise=0.8, drift=0.0, lloyd_iters=10, tokens_per_frame=4, n_kv_heads=1, n_q_heads=7), **kw})
+    rep = harness.run_workload(wl, decode_steps=1)
+    _report(rep)
+
+
+@pytest.mark.parametrize("P,C,W,D", [(5, 60, 200, 64), (3, 120, 300, 128), (1, 200, 260, 64), (2, 500, 600, 64)])
+def test_nested_bounds_by_groups_parity(P, C, W, D):
+    wl = inputs.CONFIGS[1].scaled(name="nested_groups", n_frames=W + 20, scene_model="rapid", noise=0.8, n_clusters=C, top_k=5, head_dim=D,
+                                  tokens_per_frame=3, question_tokens=2, visual_dim=20, n_visual=P, warmup_frames=W, lloyd_iters=10)
+    rep = harness.run_nested(wl, P, 1, units=[(0, 0), (0, 3)], batch_pattern=(64, 16), n_questions=1, decode_steps=1)
+    _report(rep)
+
+
+@pytest.mark.parametrize("kind", ["zeros", "equal", "tiny"])
+def test_recluster_of_summaries_without_usable_bounds(kind):
+    """K-means rounds whose frames may not be skipped end where rounds that skip nothing end: 64-bit rounds on the CPU."""
+    F, C, D, iters = 300, 24, 64, 6
+    g = torch.Generator().manual_seed(7)
+    s = torch.randn(F, D, generator=g)
+    if kind == "zeros": s[::3] = 0.0
+    if kind == "equal": s[1::4] = s[:1]
+    if kind == "tiny": s *= 1e-36
+    wl = _small(n_frames=F, n_clusters=C, warmup_frames=F, lloyd_iters=iters, head_dim=D, tokens_per_frame=1, n_kv_heads=1, n_q_heads=2, top_k=2,
+                kv_dtype="fp32")
+    m = binding.Mosaic(binding.config_for(wl), device=DEV)
+    k = s.view(F, 1, 1, 1, D).contiguous().to(DEV)
+    m.ingest_frame(k, k)
+    got = m.assignments()[0]
+    m.close()
+    x = s.double()
+    r = x[torch.arange(C) * F // C].clone()
+    live = torch.ones(C, dtype=torch.bool)
+    for _ in range(iters):
+        rn = r.norm(dim=1)
+        cos = torch.where(rn > 0, (x @ r.t()) / torch.where(rn > 0, rn, 1.0), 0.0)
+        cos[:, ~live] = -float("inf")
+        a = cos.argmax(1)
+        for f in range(F):                       # equal representatives: the lowest id (their products have the same bits on the device)
+            j = int(a[f])
+            a[f] = next(i for i in range(j + 1) if live[i] and (i == j or torch.equal(r[i], r[j]) or cos[f].abs().max() == 0.0))
+        n = torch.bincount(a, minlength=C)
+        for j in range(C):
+            if n[j]: r[j] = x[a == j].sum(0) / n[j]
+        live = n > 0
+    assert (torch.as_tensor(got).long() == a).all()
+
+
 def test_low_coherence_stream():
     wl = inputs.cfg4_stream(5).scaled(n_frames=192, n_clusters=16, top_k=5, question_tokens=8)
     rep = harness.run_workload(wl)
