@@ -785,7 +785,7 @@ static int ingest_host(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, in
         const int nb = (int)(f < W ? std::min(end, W) - f : std::min<long long>(end - f, 64));
         if ((rc = wait_for_ring(ctx, f, f + nb)) != MOSAIC_OK) return rc;
         e = launch_store_summary(dv, (const char *)k_dev + done * frame_bytes,
-                                 (const char *)v_dev + done * frame_bytes, (int)f, nb, ctx->stream);
+                                 (const char *)v_dev + done * frame_bytes, (int)f, nb, false, ctx->stream);
         if (e != hipSuccess) return fail_hip(ctx, e, "store_summary launch");
         if (f < W) {
             f += nb;
@@ -813,6 +813,7 @@ static int ingest_host(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, in
 
 static int ingest_frames(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, const float *e_dev,
                          int32_t n_frames);
+static bool kv_beyond_caches(const mosaic_ctx *ctx);
 
 int32_t mosaic_ingest_frame(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, int32_t n_frames) {
     if (!ctx) return MOSAIC_EINVAL;
@@ -860,7 +861,7 @@ static int ingest_frames(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, 
         const int nb = std::min(n_frames - done, 32768);
         const size_t in_off = (size_t)done * dv.U * dv.T * dv.D * dv.esize;
         e = launch_store_summary(dv, (const char *)k_dev + in_off, (const char *)v_dev + in_off,
-                                 (int)ctx->n_frames + done, nb, ctx->stream);
+                                 (int)ctx->n_frames + done, nb, n_frames > 1 && kv_beyond_caches(ctx), ctx->stream);
         if (e != hipSuccess) return fail_hip(ctx, e, "store_summary launch");
         // embeddings of warm-up frames are only filed; later ones are filed by the visual assignment
         const long long first = ctx->n_frames + done, n_warm = std::min<long long>(first + nb, ctx->W) - first;

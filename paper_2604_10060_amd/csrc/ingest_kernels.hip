@@ -12,40 +12,12 @@
 #include <algorithm>
 #include "mosaic_internal.h"
 #include "maintain_device.h"
+#include "page_store_device.h"
 #include "assign_device.h"
 
 namespace mosaic {
 
 namespace {
-
-template <typename E> struct Elem;
-template <> struct Elem<float> {
-    struct Row { float4 a, b; };                     // 8 elements
-    static __device__ __forceinline__ Row load(const float *p) {
-        return {*reinterpret_cast<const float4 *>(p), *reinterpret_cast<const float4 *>(p + 4)};
-    }
-    static __device__ __forceinline__ void store(float *p, const Row &r) {
-        *reinterpret_cast<float4 *>(p) = r.a;
-        *reinterpret_cast<float4 *>(p + 4) = r.b;
-    }
-    static __device__ __forceinline__ void unpack(const Row &r, float (&v)[8]) {
-        v[0] = r.a.x; v[1] = r.a.y; v[2] = r.a.z; v[3] = r.a.w;
-        v[4] = r.b.x; v[5] = r.b.y; v[6] = r.b.z; v[7] = r.b.w;
-    }
-};
-template <> struct Elem<unsigned short> {
-    typedef uint4 Row;
-    static __device__ __forceinline__ Row load(const unsigned short *p) { return *reinterpret_cast<const uint4 *>(p); }
-    static __device__ __forceinline__ void store(unsigned short *p, const Row &r) { *reinterpret_cast<uint4 *>(p) = r; }
-    static __device__ __forceinline__ void unpack(const Row &r, float (&v)[8]) {
-        const unsigned int w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[2 * i] = __uint_as_float(w[i] << 16);
-            v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
-    }
-};
 
 // (every call site has all 16 lanes of the group active)
 __device__ __forceinline__ double group16_sum(double x) { return row16_sum(x); }
@@ -85,163 +57,16 @@ __device__ __forceinline__ void wave_best(double &bv, int &bi) {
 }
 
 // ---------------------------------------------------------------------------
-// Page store + summaries.  store_key_page / store_value_page are run by one
-// 256-thread workgroup per (unit, frame): the page goes to the arena's store (HBM
-// tier) or the staging ring (host tier); the key summary (mean of the frame's T key
-// vectors, fp64) goes to dv.summ and, if s_out is given, to that LDS array too.
-// red: kBlock / (D / 8) rows of D doubles of LDS scratch.
-// ---------------------------------------------------------------------------
-template <typename E, int D>
-__device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_in, char *kdst_base, int u, int fl,
-                                               int f, double (&red)[kBlock / (D / 8)][D], double *s_out) {
-    constexpr int LPR = D / 8;          // lanes per row, 8 elements each
-    constexpr int RP = kBlock / LPR;    // rows per pass
-    const int tid = threadIdx.x, cg = tid % LPR, r0 = tid / LPR;
-    const int T = dv.T;
-    const size_t in_page = ((size_t)fl * dv.U + u) * (size_t)T * D;
-    const size_t page = (size_t)u * dv.F + f;          // summary slot
-    const bool host = dv.tier == MOSAIC_TIER_HOST;
-    const size_t spage = host ? (size_t)(f % dv.SN) * dv.U + u : (size_t)u * dv.PU + f;
-    const E *src = k_in + in_page;
-    // (a thread's eight channels lie in one piece of a row)
-    E *dst = reinterpret_cast<E *>(kdst_base) + spage * (size_t)T * D + cg * 8 / 32 * dv.k_ps() + cg * 8 % 32;
-    double acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-    // four rows' loads in flight (row clamped, loads unconditional): one row at a time, a load waits for the store before
-    // it, which may alias it for all the compiler knows, and a 64-token page is four trips to memory instead of one (28
-    // layers, one frame a call: 12.2 -> 9.0 us a frame; 64 a call, C = 20: 6.5 -> 4.9)
-    for (int t0 = r0; t0 < T; t0 += 4 * RP) {
-        typename Elem<E>::Row x[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = Elem<E>::load(src + (size_t)min(t0 + k * RP, T - 1) * D + cg * 8);
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (t0 + k * RP < T) {
-                float v[8];
-                Elem<E>::unpack(x[k], v);
-                Elem<E>::store(dst + (size_t)(t0 + k * RP) * dv.k_rs(), x[k]);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[i] += (double)v[i];
-            }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) red[r0][cg * 8 + i] = acc[i];
-    __syncthreads();
-    if (tid < D) {
-        double sm = 0.0;
-        for (int rr = 0; rr < RP; ++rr) sm += red[rr][tid];
-        sm /= (double)T;
-        dv.summ[page * D + tid] = sm;
-        if (s_out) s_out[tid] = sm;
-    }
-}
-
-template <typename E, int D>
-__device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *v_in, char *vdst_base, int u, int fl,
-                                                 int f, double (&red)[kBlock / (D / 8)][D]) {
-    constexpr int LPR = D / 8, RP = kBlock / LPR;
-    const int tid = threadIdx.x, cg = tid % LPR, r0 = tid / LPR;
-    const int T = dv.T;
-    const size_t in_page = ((size_t)fl * dv.U + u) * (size_t)T * D;
-    const size_t page = (size_t)u * dv.F + f;
-    const bool host = dv.tier == MOSAIC_TIER_HOST;
-    const size_t spage = host ? (size_t)(f % dv.SN) * dv.U + u : (size_t)u * dv.PU + f;
-    // With the global-representative augmentation on, the frame's value summary (mean of
-    // its T value vectors, fp64) is formed next to the copy, like the key summary.
-    const E *src = v_in + in_page;
-    if (!dv.v_transposed) {
-        E *dst = reinterpret_cast<E *>(vdst_base) + spage * (size_t)T * D;
-        double acc[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-        for (int t0 = r0; t0 < T; t0 += 4 * RP) {      // (as in store_key_page)
-            typename Elem<E>::Row x[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) x[k] = Elem<E>::load(src + (size_t)min(t0 + k * RP, T - 1) * D + cg * 8);
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (t0 + k * RP < T) {
-                    Elem<E>::store(dst + (size_t)(t0 + k * RP) * D + cg * 8, x[k]);
-                    if (dv.vsumm) {
-                        float v[8];
-                        Elem<E>::unpack(x[k], v);
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) acc[i] += (double)v[i];
-                    }
-                }
-        }
-        if (dv.vsumm) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) red[r0][cg * 8 + i] = acc[i];
-            __syncthreads();
-            if (tid < D) {
-                double sv = 0.0;
-                for (int rr = 0; rr < RP; ++rr) sv += red[rr][tid];
-                dv.vsumm[page * D + tid] = sv / (double)T;
-            }
-        }
-        return;
-    }
-    // Transposed, chunk-blocked value page [Tp/32][D][32] (2-byte elements only):
-    // 8 consecutive tokens of one channel form one 16-byte operand of the PV
-    // contraction, and the 16 channels x 32 tokens a wavefront loads at once
-    // are one contiguous KiB.  Tokens T..Tp-1 are written as zeros.
-    if constexpr (sizeof(E) == 2) {
-        constexpr int TC = 64;                       // tokens per LDS tile (two chunks)
-        __shared__ unsigned short tile[TC][D + 2];
-        const int Tp = dv.Tp;
-        double vacc = 0.0;
-        unsigned short *dst = reinterpret_cast<unsigned short *>(vdst_base) + spage * (size_t)D * Tp;
-        // a tile's rows are loaded together (row clamped, loads unconditional), the next tile's while this one is written out
-        constexpr int RPT = TC / RP;                 // rows per thread and tile
-        uint4 w[RPT];
-        auto load_tile = [&](int tc0) {
-#pragma unroll
-            for (int k = 0; k < RPT; ++k)
-                w[k] = *reinterpret_cast<const uint4 *>(src + (size_t)min(tc0 + r0 + k * RP, T - 1) * D + cg * 8);
-        };
-        load_tile(0);
-        for (int tc0 = 0; tc0 < Tp; tc0 += TC) {
-#pragma unroll
-            for (int k = 0; k < RPT; ++k) {
-                const bool in = tc0 + r0 + k * RP < T;
-                unsigned int *row = reinterpret_cast<unsigned int *>(&tile[r0 + k * RP][cg * 8]);
-                row[0] = in ? w[k].x : 0u; row[1] = in ? w[k].y : 0u; row[2] = in ? w[k].z : 0u; row[3] = in ? w[k].w : 0u;
-            }
-            if (tc0 + TC < Tp) load_tile(tc0 + TC);
-            __syncthreads();
-            if (dv.vsumm && tid < D) {
-                const int nt = min(TC, T - tc0);     // real tokens in this tile
-                for (int t = 0; t < nt; ++t) vacc += (double)bf16_to_f32(tile[t][tid]);
-            }
-            const int ntg = (min(TC, Tp - tc0)) / 8;  // token groups of 8 in this tile
-            for (int id = tid; id < D * ntg; id += kBlock) {
-                const int d = id / ntg, tg = id % ntg;
-                unsigned int o[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    o[j] = (unsigned int)tile[tg * 8 + 2 * j][d] |
-                           ((unsigned int)tile[tg * 8 + 2 * j + 1][d] << 16);
-                const int tok = tc0 + tg * 8;         // first of the 8 tokens
-                *reinterpret_cast<uint4 *>(dst + ((size_t)(tok / kChunk) * D + d) * kChunk + tok % kChunk) =
-                    make_uint4(o[0], o[1], o[2], o[3]);
-            }
-            __syncthreads();
-        }
-        if (dv.vsumm && tid < D) dv.vsumm[page * D + tid] = vacc / (double)T;
-    }
-}
-
+// Page store + summaries: page_store_device.h.
 // grid (U, n_frames, 2): z = 0 keys, z = 1 values.
-template <typename E, int D>
-__global__ __launch_bounds__(kBlock) void k_store_summary(DeviceView dv, const E *k_in,
+template <typename E, int D, bool BEYOND>
+__global__ __launch_bounds__(kStoreBlock) void k_store_summary(DeviceView dv, const E *k_in,
                                                           const E *v_in, int f0) {
-    __shared__ double red[kBlock / (D / 8)][D];
+    __shared__ double red[kStoreRows<D>][D];
     const int u = blockIdx.x, fl = blockIdx.y;
     const bool host = dv.tier == MOSAIC_TIER_HOST;
-    if (blockIdx.z == 0) store_key_page<E, D>(dv, k_in, host ? dv.stage_k : dv.k_store, u, fl, f0 + fl, red, nullptr);
-    else store_value_page<E, D>(dv, v_in, host ? dv.stage_v : dv.v_store, u, fl, f0 + fl, red);
+    if (blockIdx.z == 0) store_key_page<E, D, kStoreBlock, BEYOND>(dv, k_in, host ? dv.stage_k : dv.k_store, u, fl, f0 + fl, red, nullptr);
+    else store_value_page<E, D, kStoreBlock, BEYOND>(dv, v_in, host ? dv.stage_v : dv.v_store, u, fl, f0 + fl, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -1106,17 +931,18 @@ __global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, in
 
 // ---------------------------------------------------------------------------
 // One frame in one launch (maintainer off, C <= 128, HBM tier, online phase).
-// grid (U, 2), 256 threads: y = 0 key page + summary + assignment + Eq. 3, y = 1 value page.
+// grid (U, 2), kOneBlock threads: y = 0 key page + summary + assignment + Eq. 3, y = 1 value page.
 // The table is in flight -- eight rows per 16-lane group -- before the page store begins; what follows it runs out of
-// registers and LDS.  The same operations on the same operands as k_assign_chain, element by element.
+// registers and LDS.  (The page's loads first, so that it could be summed while the table is on its way: 5.90 -> 7.28 us.)  The same operations on the same operands as k_assign_chain, element by element.
 // ---------------------------------------------------------------------------
+constexpr int kOneBlock = 256;
 template <typename E, int D>
-__global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k_in, const E *v_in, int f) {
-    constexpr int EPL = D / 16, NG = kBlock / 16, RPG = 8, NW = kBlock / 64, ROWS = NG * RPG;
-    __shared__ double red[kBlock / (D / 8)][D];
+__global__ __launch_bounds__(kOneBlock) void k_ingest_one(DeviceView dv, const E *k_in, const E *v_in, int f) {
+    constexpr int EPL = D / 16, NG = kOneBlock / 16, RPG = 128 / NG, NW = kOneBlock / 64, ROWS = NG * RPG;
+    __shared__ double red[kStoreRows<D>][D];
     const int u = blockIdx.x;
     if (blockIdx.y == 1) {
-        store_value_page<E, D>(dv, v_in, dv.v_store, u, 0, f, red);         // HBM tier only
+        store_value_page<E, D, kOneBlock, false>(dv, v_in, dv.v_store, u, 0, f, red);         // HBM tier only
         return;
     }
     const int tid = threadIdx.x, C = dv.C;
@@ -1146,7 +972,7 @@ __global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k
     const bool nested = dv.P > 0;
     const int part_f = nested ? dv.part[f] : 0;
     const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : C;
-    store_key_page<E, D>(dv, k_in, dv.k_store, u, 0, f, red, s_sh);
+    store_key_page<E, D, kOneBlock, false>(dv, k_in, dv.k_store, u, 0, f, red, s_sh);
     __syncthreads();
     double sl[EPL];
 #pragma unroll
@@ -1191,7 +1017,7 @@ __global__ __launch_bounds__(kBlock) void k_ingest_one(DeviceView dv, const E *k
                     rr[i][e] = eq3_channel(na, ny, rr[i][e], sl[e]);
                     r[(size_t)a * D + lr * EPL + e] = rr[i][e];
                 }
-                sq = square_channels(rr[i], i == 0);                      // (row_second_first: a < NG)
+                sq = square_channels(rr[i], row_second_first(C, a));
             }
         }
         sq = row16_sum(sq);
@@ -1923,16 +1749,22 @@ template <typename F> hipError_t checked(F &&launch) {
 } // namespace
 
 hipError_t launch_store_summary(const DeviceView &dv, const void *k_in, const void *v_in, int f0,
-                                int n_frames, hipStream_t s) {
-    dim3 grid(dv.U, n_frames, 2);
+                                int n_frames, bool beyond, hipStream_t s) {
+    const dim3 grid(dv.U, n_frames, 2);
+    auto go = [&](auto kern, auto *k) { kern<<<grid, kStoreBlock, 0, s>>>(dv, k, (decltype(k))v_in, f0); };
+    auto pick = [&](auto *k, auto d) {
+        using E = std::remove_const_t<std::remove_pointer_t<decltype(k)>>;
+        constexpr int D = decltype(d)::value;
+        if (beyond) go(k_store_summary<E, D, true>, k);
+        else go(k_store_summary<E, D, false>, k);
+    };
     return checked([&] {
-        if (dv.esize == 4) {
-            if (dv.D == 64) k_store_summary<float, 64><<<grid, kBlock, 0, s>>>(dv, (const float *)k_in, (const float *)v_in, f0);
-            else k_store_summary<float, 128><<<grid, kBlock, 0, s>>>(dv, (const float *)k_in, (const float *)v_in, f0);
-        } else {
-            if (dv.D == 64) k_store_summary<unsigned short, 64><<<grid, kBlock, 0, s>>>(dv, (const unsigned short *)k_in, (const unsigned short *)v_in, f0);
-            else k_store_summary<unsigned short, 128><<<grid, kBlock, 0, s>>>(dv, (const unsigned short *)k_in, (const unsigned short *)v_in, f0);
-        }
+        auto by_d = [&](auto *k) {
+            if (dv.D == 64) pick(k, std::integral_constant<int, 64>{});
+            else pick(k, std::integral_constant<int, 128>{});
+        };
+        if (dv.esize == 4) by_d((const float *)k_in);
+        else by_d((const unsigned short *)k_in);
     });
 }
 
@@ -1940,11 +1772,11 @@ hipError_t launch_ingest_one(const DeviceView &dv, const void *k_in, const void 
     dim3 grid(dv.U, 2);
     return checked([&] {
         if (dv.esize == 4) {
-            if (dv.D == 64) k_ingest_one<float, 64><<<grid, kBlock, 0, s>>>(dv, (const float *)k_in, (const float *)v_in, f);
-            else k_ingest_one<float, 128><<<grid, kBlock, 0, s>>>(dv, (const float *)k_in, (const float *)v_in, f);
+            if (dv.D == 64) k_ingest_one<float, 64><<<grid, kOneBlock, 0, s>>>(dv, (const float *)k_in, (const float *)v_in, f);
+            else k_ingest_one<float, 128><<<grid, kOneBlock, 0, s>>>(dv, (const float *)k_in, (const float *)v_in, f);
         } else {
-            if (dv.D == 64) k_ingest_one<unsigned short, 64><<<grid, kBlock, 0, s>>>(dv, (const unsigned short *)k_in, (const unsigned short *)v_in, f);
-            else k_ingest_one<unsigned short, 128><<<grid, kBlock, 0, s>>>(dv, (const unsigned short *)k_in, (const unsigned short *)v_in, f);
+            if (dv.D == 64) k_ingest_one<unsigned short, 64><<<grid, kOneBlock, 0, s>>>(dv, (const unsigned short *)k_in, (const unsigned short *)v_in, f);
+            else k_ingest_one<unsigned short, 128><<<grid, kOneBlock, 0, s>>>(dv, (const unsigned short *)k_in, (const unsigned short *)v_in, f);
         }
     });
 }

@@ -166,8 +166,9 @@ struct Ctx {
 };
 
 // ---- launchers (each checks its own launch; returns hipError_t) ----
+// beyond: the pages go to a store far beyond the caches
 hipError_t launch_store_summary(const DeviceView &dv, const void *k_in, const void *v_in,
-                                int f0, int n_frames, hipStream_t s);
+                                int f0, int n_frames, bool beyond, hipStream_t s);
 // pages, summary, assignment and Eq. 3 of one frame in one launch (HBM tier, maintainer off,
 // C <= 128, frame f beyond the warm-up)
 hipError_t launch_ingest_one(const DeviceView &dv, const void *k_in, const void *v_in, int f, hipStream_t s);
