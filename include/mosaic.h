@@ -352,7 +352,9 @@ int32_t mosaic_decode_step(mosaic_ctx *ctx, int32_t layer, const void *q_dev, in
 
 /* Observers for parity checks: the clustering state of Sec. V-B / Sec. VI (frame -> cluster
  * map, representatives of Eq. 1 / Eq. 3, per-frame states) as the library holds it.  All
- * outputs are HOST pointers, caller-allocated; each call synchronises the stream.  NULL
+ * outputs are HOST pointers, caller-allocated; each call synchronises the stream.  An array of 2 MiB or more
+ * is read through 8 MiB of pinned host memory that the context allocates with the first one and frees when it
+ * is destroyed, with a few threads that live as long as the call (without either, it is copied directly).  NULL
  * outputs are skipped. */
 
 /* frame_to_cluster [L*Hkv][n_frames_ingested] (row stride = frames ingested);

@@ -123,6 +123,7 @@ struct DeviceView {
 };
 
 struct HostTier;   // host_tier.hip
+constexpr int kReadPieces = 4;      // pinned pieces that large read-backs go through
 
 struct Ctx {
     mosaic_config cfg;
@@ -157,6 +158,9 @@ struct Ctx {
     hipStream_t assign_stream;
     hipEvent_t stored, assigned;
     bool assign_pending;
+    // large read-backs (null until the first one)
+    char *read_buf;
+    hipEvent_t read_done[kReadPieces];
     // profiling
     bool profile;
     std::vector<hipEvent_t> ev;      // pool of pairs, created by mosaic_profile_enable
