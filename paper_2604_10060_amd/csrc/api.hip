@@ -789,7 +789,7 @@ static int ingest_host(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, in
         const int nb = (int)(f < W ? std::min(end, W) - f : std::min<long long>(end - f, 64));
         if ((rc = wait_for_ring(ctx, f, f + nb)) != MOSAIC_OK) return rc;
         e = launch_store_summary(dv, (const char *)k_dev + done * frame_bytes,
-                                 (const char *)v_dev + done * frame_bytes, (int)f, nb, false, ctx->stream);
+                                 (const char *)v_dev + done * frame_bytes, (int)f, nb, false, nullptr, 0, ctx->stream);
         if (e != hipSuccess) return fail_hip(ctx, e, "store_summary launch");
         if (f < W) {
             f += nb;
@@ -859,20 +859,23 @@ static int ingest_frames(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, 
     const bool overlap = ctx->assign_stream != nullptr && n_frames > 1;
     if (!overlap) { const int rc = join_ingest(ctx); if (rc != MOSAIC_OK) return rc; }
     const hipStream_t dep = overlap ? ctx->assign_stream : ctx->stream;
+    // Nested hierarchy, frames of the online phase: the visual level decides them beside their page stores.
+    const bool with_visual = e_dev && ctx->n_frames >= ctx->W && !one_launch && store_visual_assign_takes(dv, n_frames);
+    if (with_visual) {
+        e = launch_store_visual_assign(dv, k_dev, v_dev, e_dev, (int)ctx->n_frames, (int)ctx->n_frames + n_frames, kv_beyond_caches(ctx), ctx->stream);
+        if (e != hipSuccess) return fail_hip(ctx, e, "store and visual assignment launch");
+    }
     // pages + summaries of the whole batch (independent across frames); the grid's
     // y dimension is limited to 65535 frames per launch
-    for (int done = 0; done < n_frames && !one_launch;) {
+    for (int done = 0; done < n_frames && !one_launch && !with_visual;) {
         const int nb = std::min(n_frames - done, 32768);
         const size_t in_off = (size_t)done * dv.U * dv.T * dv.D * dv.esize;
-        e = launch_store_summary(dv, (const char *)k_dev + in_off, (const char *)v_dev + in_off,
-                                 (int)ctx->n_frames + done, nb, n_frames > 1 && kv_beyond_caches(ctx), ctx->stream);
-        if (e != hipSuccess) return fail_hip(ctx, e, "store_summary launch");
         // embeddings of warm-up frames are only filed; later ones are filed by the visual assignment
-        const long long first = ctx->n_frames + done, n_warm = std::min<long long>(first + nb, ctx->W) - first;
-        if (e_dev && n_warm > 0) {
-            e = launch_visual_store(dv, e_dev + (size_t)done * dv.Dv, (int)first, (int)n_warm, ctx->stream);
-            if (e != hipSuccess) return fail_hip(ctx, e, "visual_store launch");
-        }
+        const long long first = ctx->n_frames + done, n_warm = e_dev ? std::min<long long>(first + nb, ctx->W) - first : 0;
+        e = launch_store_summary(dv, (const char *)k_dev + in_off, (const char *)v_dev + in_off, (int)first, nb,
+                                 n_frames > 1 && kv_beyond_caches(ctx), e_dev ? e_dev + (size_t)done * dv.Dv : nullptr,
+                                 (int)std::max<long long>(n_warm, 0), ctx->stream);
+        if (e != hipSuccess) return fail_hip(ctx, e, "store_summary launch");
         done += nb;
     }
     if (overlap) {
@@ -903,7 +906,7 @@ static int ingest_frames(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, 
         }
         long long seg_end = end;
         if (every > 0) seg_end = std::min(end, (f / every + 1) * every);
-        if (dv.P > 0) {
+        if (dv.P > 0 && !with_visual) {
             e = launch_visual_assign(dv, e_dev + (size_t)(f - ctx->n_frames) * dv.Dv, (int)f, (int)seg_end, dep);
             if (e != hipSuccess) return fail_hip(ctx, e, "visual assignment launch");
         }

@@ -58,15 +58,18 @@ __device__ __forceinline__ void wave_best(double &bv, int &bi) {
 
 // ---------------------------------------------------------------------------
 // Page store + summaries: page_store_device.h.
-// grid (U, n_frames, 2): z = 0 keys, z = 1 values.
+// grid (U, n_frames, 2 or 3): z = 0 keys, z = 1 values, z = 2 the embeddings e_in of the n_emb first frames (nested hierarchy, warm-up), into the
+// visual level's fp64 state array.  (A launch of their own cost 3.6 us.)
 template <typename E, int D, bool BEYOND>
 __global__ __launch_bounds__(kStoreBlock) void k_store_summary(DeviceView dv, const E *k_in,
-                                                          const E *v_in, int f0) {
-    __shared__ double red[kStoreRows<D>][D];
+                                                          const E *v_in, int f0, const float *e_in, int n_emb) {
+    __shared__ StoreShared<D> store_sh;
     const int u = blockIdx.x, fl = blockIdx.y;
     const bool host = dv.tier == MOSAIC_TIER_HOST;
-    if (blockIdx.z == 0) store_key_page<E, D, kStoreBlock, BEYOND>(dv, k_in, host ? dv.stage_k : dv.k_store, u, fl, f0 + fl, red, nullptr);
-    else store_value_page<E, D, kStoreBlock, BEYOND>(dv, v_in, host ? dv.stage_v : dv.v_store, u, fl, f0 + fl, red);
+    if (blockIdx.z == 0) store_key_page<E, D, kStoreBlock, BEYOND>(dv, k_in, host ? dv.stage_k : dv.k_store, u, fl, f0 + fl, store_sh, nullptr);
+    else if (blockIdx.z == 1) store_value_page<E, D, kStoreBlock, BEYOND>(dv, v_in, host ? dv.stage_v : dv.v_store, u, fl, f0 + fl, store_sh);
+    else if (fl < n_emb)
+        for (int d = u * kStoreBlock + threadIdx.x; d < dv.Dv; d += dv.U * kStoreBlock) dv.vemb[(size_t)(f0 + fl) * dv.Dv + d] = (double)e_in[(size_t)fl * dv.Dv + d];
 }
 
 // ---------------------------------------------------------------------------
@@ -939,10 +942,10 @@ constexpr int kOneBlock = 256;
 template <typename E, int D>
 __global__ __launch_bounds__(kOneBlock) void k_ingest_one(DeviceView dv, const E *k_in, const E *v_in, int f) {
     constexpr int EPL = D / 16, NG = kOneBlock / 16, RPG = 128 / NG, NW = kOneBlock / 64, ROWS = NG * RPG;
-    __shared__ double red[kStoreRows<D>][D];
+    __shared__ StoreShared<D> store_sh;
     const int u = blockIdx.x;
     if (blockIdx.y == 1) {
-        store_value_page<E, D, kOneBlock, false>(dv, v_in, dv.v_store, u, 0, f, red);         // HBM tier only
+        store_value_page<E, D, kOneBlock, false>(dv, v_in, dv.v_store, u, 0, f, store_sh);         // HBM tier only
         return;
     }
     const int tid = threadIdx.x, C = dv.C;
@@ -972,7 +975,7 @@ __global__ __launch_bounds__(kOneBlock) void k_ingest_one(DeviceView dv, const E
     const bool nested = dv.P > 0;
     const int part_f = nested ? dv.part[f] : 0;
     const int lo = nested ? part_f * dv.Cs : 0, hi = nested ? lo + dv.Cs : C;
-    store_key_page<E, D, kOneBlock, false>(dv, k_in, dv.k_store, u, 0, f, red, s_sh);
+    store_key_page<E, D, kOneBlock, false>(dv, k_in, dv.k_store, u, 0, f, store_sh, s_sh);
     __syncthreads();
     double sl[EPL];
 #pragma unroll
@@ -1749,9 +1752,9 @@ template <typename F> hipError_t checked(F &&launch) {
 } // namespace
 
 hipError_t launch_store_summary(const DeviceView &dv, const void *k_in, const void *v_in, int f0,
-                                int n_frames, bool beyond, hipStream_t s) {
-    const dim3 grid(dv.U, n_frames, 2);
-    auto go = [&](auto kern, auto *k) { kern<<<grid, kStoreBlock, 0, s>>>(dv, k, (decltype(k))v_in, f0); };
+                                int n_frames, bool beyond, const float *e_in, int n_emb, hipStream_t s) {
+    const dim3 grid(dv.U, n_frames, n_emb > 0 ? 3 : 2);
+    auto go = [&](auto kern, auto *k) { kern<<<grid, kStoreBlock, 0, s>>>(dv, k, (decltype(k))v_in, f0, e_in, n_emb); };
     auto pick = [&](auto *k, auto d) {
         using E = std::remove_const_t<std::remove_pointer_t<decltype(k)>>;
         constexpr int D = decltype(d)::value;

@@ -170,21 +170,24 @@ struct Ctx {
 };
 
 // ---- launchers (each checks its own launch; returns hipError_t) ----
-// beyond: the pages go to a store far beyond the caches
+// beyond: the pages go to a store far beyond the caches; e_in: the embeddings of these frames, of which the n_emb first are filed in the visual
+// level's state array (nested hierarchy, warm-up)
 hipError_t launch_store_summary(const DeviceView &dv, const void *k_in, const void *v_in,
-                                int f0, int n_frames, bool beyond, hipStream_t s);
+                                int f0, int n_frames, bool beyond, const float *e_in, int n_emb, hipStream_t s);
 // pages, summary, assignment and Eq. 3 of one frame in one launch (HBM tier, maintainer off,
 // C <= 128, frame f beyond the warm-up)
 hipError_t launch_ingest_one(const DeviceView &dv, const void *k_in, const void *v_in, int f, hipStream_t s);
 hipError_t launch_assign_update(const DeviceView &dv, int f0, int f1, hipStream_t s);
 hipError_t launch_lloyd(const DeviceView &dv, int n_frames, int iters, bool seed_from_warmup,
                         hipStream_t s);
-// nested hierarchy: embeddings of frames f0.. into the visual level's state array
-hipError_t launch_visual_store(const DeviceView &dv, const float *e_in, int f0, int n_frames, hipStream_t s);
 // visual level: initial P-means over the first W embeddings / greedy assignment of frames f0..f1-1
 hipError_t launch_visual_lloyd(const DeviceView &dv, int W, int iters, hipStream_t s);
 // (e_in: fp32 embeddings of frames f0..f1-1, which the kernel also files in the state array)
 hipError_t launch_visual_assign(const DeviceView &dv, const float *e_in, int f0, int f1, hipStream_t s);
+// ... with the page stores of the same frames in the same launch (calls that it takes)
+bool store_visual_assign_takes(const DeviceView &dv, int n_frames);
+hipError_t launch_store_visual_assign(const DeviceView &dv, const void *k_in, const void *v_in, const float *e_in, int f0, int f1, bool beyond,
+                                      hipStream_t s);
 // per-unit partition representatives recomputed from the member lists (after a K-means run)
 hipError_t launch_partition_reps(const DeviceView &dv, int n_frames, hipStream_t s);
 // write_pages = false (host tier): only scores and ids; the page list comes from the host

@@ -13,6 +13,12 @@ namespace mosaic {
 constexpr int kStoreBlock = 512;
 template <int D> constexpr int kStoreRows = 2048 / D;
 
+constexpr int kStoreTile = 64;          // tokens of a value page transposed at a time (two chunks)
+template <int D> union StoreShared {    // LDS of a page store
+    double red[kStoreRows<D>][D];
+    unsigned short tile[kStoreTile][D + 2];
+};
+
 // BEYOND: the store is far beyond the caches (see issue_chunk() for the loads of such pages), and so its pages are written with the hint, too.
 // Re-clustered ingest of 28 layers, page stores beside the K-means rounds of the batch before: a round's assignment 34.7 -> 32.4 us, its
 // update 27.1 -> 22.8 us on average, a page store 26.8 -> 25.8.  Not in one-frame calls (5.83 -> 6.06 us), nor where the next question finds the pages in a cache.
@@ -41,10 +47,9 @@ template <typename E, int N> struct RowPiece {
     }
 };
 
-// red: LDS scratch.
 template <typename E, int D, int NT, bool BEYOND>
 __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_in, char *kdst_base, int u, int fl,
-                                               int f, double (&red)[kStoreRows<D>][D], double *s_out) {
+                                               int f, StoreShared<D> &sh, double *s_out) {
     constexpr int RP = kStoreRows<D>, LPR = NT / RP, N = D / LPR;      // rows per pass, lanes per row, elements each
     const int tid = threadIdx.x, c0 = tid % LPR * N, r0 = tid / LPR;
     const int T = dv.T;
@@ -76,11 +81,11 @@ __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_
             }
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) red[r0][c0 + i] = acc[i];
+    for (int i = 0; i < N; ++i) sh.red[r0][c0 + i] = acc[i];
     __syncthreads();
     if (tid < D) {
         double sm = 0.0;
-        for (int rr = 0; rr < RP; ++rr) sm += red[rr][tid];
+        for (int rr = 0; rr < RP; ++rr) sm += sh.red[rr][tid];
         sm /= (double)T;
         dv.summ[page * D + tid] = sm;
         if (s_out) s_out[tid] = sm;
@@ -89,7 +94,7 @@ __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_
 
 template <typename E, int D, int NT, bool BEYOND>
 __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *v_in, char *vdst_base, int u, int fl,
-                                                 int f, double (&red)[kStoreRows<D>][D]) {
+                                                 int f, StoreShared<D> &sh) {
     constexpr int RP = kStoreRows<D>, LPR = NT / RP, N = D / LPR;
     const int tid = threadIdx.x, c0 = tid % LPR * N, r0 = tid / LPR;
     const int T = dv.T;
@@ -123,11 +128,11 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
         }
         if (dv.vsumm) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) red[r0][c0 + i] = acc[i];
+            for (int i = 0; i < N; ++i) sh.red[r0][c0 + i] = acc[i];
             __syncthreads();
             if (tid < D) {
                 double sv = 0.0;
-                for (int rr = 0; rr < RP; ++rr) sv += red[rr][tid];
+                for (int rr = 0; rr < RP; ++rr) sv += sh.red[rr][tid];
                 dv.vsumm[page * D + tid] = sv / (double)T;
             }
         }
@@ -138,8 +143,7 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
     // contraction, and the 16 channels x 32 tokens a wavefront loads at once
     // are one contiguous KiB.  Tokens T..Tp-1 are written as zeros.
     if constexpr (sizeof(E) == 2) {
-        constexpr int TC = 64;                       // tokens per LDS tile (two chunks)
-        __shared__ unsigned short tile[TC][D + 2];
+        constexpr int TC = kStoreTile;
         const int Tp = dv.Tp;
         double vacc = 0.0;
         unsigned short *dst = reinterpret_cast<unsigned short *>(vdst_base) + spage * (size_t)D * Tp;
@@ -155,7 +159,7 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
 #pragma unroll
             for (int k = 0; k < RPT; ++k) {
                 const bool in = tc0 + r0 + k * RP < T;
-                unsigned int *row = reinterpret_cast<unsigned int *>(&tile[r0 + k * RP][c0]);
+                unsigned int *row = reinterpret_cast<unsigned int *>(&sh.tile[r0 + k * RP][c0]);
 #pragma unroll
                 for (int i = 0; i < RowPiece<E, N>::W; ++i) row[i] = in ? w[k].w[i] : 0u;
             }
@@ -163,7 +167,7 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
             __syncthreads();
             if (dv.vsumm && tid < D) {
                 const int nt = min(TC, T - tc0);     // real tokens in this tile
-                for (int t = 0; t < nt; ++t) vacc += (double)bf16_to_f32(tile[t][tid]);
+                for (int t = 0; t < nt; ++t) vacc += (double)bf16_to_f32(sh.tile[t][tid]);
             }
             const int ntg = (min(TC, Tp - tc0)) / 8;  // token groups of 8 in this tile
             for (int id = tid; id < D * ntg; id += NT) {
@@ -171,8 +175,8 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
                 unsigned int o[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    o[j] = (unsigned int)tile[tg * 8 + 2 * j][d] |
-                           ((unsigned int)tile[tg * 8 + 2 * j + 1][d] << 16);
+                    o[j] = (unsigned int)sh.tile[tg * 8 + 2 * j][d] |
+                           ((unsigned int)sh.tile[tg * 8 + 2 * j + 1][d] << 16);
                 const int tok = tc0 + tg * 8;         // first of the 8 tokens
                 typedef unsigned int Words __attribute__((ext_vector_type(4)));
                 keep_words<BEYOND>(reinterpret_cast<Words *>(dst + ((size_t)(tok / kChunk) * D + d) * kChunk + tok % kChunk), Words{o[0], o[1], o[2], o[3]});

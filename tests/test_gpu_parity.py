@@ -186,6 +186,17 @@ def test_recluster_of_summaries_without_usable_bounds(kind):
     assert (torch.as_tensor(got).long() == a).all()
 
 
+# Embeddings of a workgroup's channels in the visual K-means update and of more, of one block of channels per thread in the online
+# assignment and of more; one to four tiles of partitions; batches stored beside the visual level
+@pytest.mark.parametrize("P,Dv,dtype", [(5, 256, "bf16"), (18, 260, "fp32"), (4, 1020, "bf16"), (7, 1100, "fp32"), (33, 2052, "bf16")])
+def test_nested_visual_blocks_of_channels_parity(P, Dv, dtype):
+    W = 4 * P + 20
+    wl = inputs.CONFIGS[1].scaled(name="visual_blocks", n_frames=W + 60, n_scenes=12, n_clusters=2 * P, top_k=3, tokens_per_frame=40, kv_dtype=dtype,
+                                  question_tokens=2, visual_dim=Dv, n_visual=P, warmup_frames=W)
+    rep = harness.run_nested(wl, P, 2, units=[(0, 1)], batch_pattern=(16, 5, 1, 3, 17), n_questions=1, decode_steps=1)
+    _report(rep)
+
+
 def test_low_coherence_stream():
     wl = inputs.cfg4_stream(5).scaled(n_frames=192, n_clusters=16, top_k=5, question_tokens=8)
     rep = harness.run_workload(wl)
