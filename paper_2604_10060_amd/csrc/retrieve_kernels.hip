@@ -2,6 +2,8 @@
 // one workgroup per unit computes the mean query, scores every representative
 // of the GPU-resident index, ranks them, and lists the pages of the chosen
 // clusters.  Nothing is copied: attention later reads the pages in place.
+#include <algorithm>
+
 #include "mosaic_internal.h"
 #include "maintain_device.h"
 #include "topk_device.h"
@@ -51,12 +53,12 @@ template <> __device__ __forceinline__ void load8_f64<unsigned short>(const unsi
     }
 }
 
-template <typename E, int D>
-__device__ __forceinline__ void mean_query_partials(const E *q, int lc, int h, int Tq, int G, int Hq,
-                                                    double (*wpart)[D]) {
-    constexpr int BLK = kRetrBlock, LPR = D / 8, NPART = BLK / LPR, UN = 8;
+template <typename E, int D, int BLK>
+__device__ __forceinline__ void mean_query_partials(const E *q, int lc, int h, int Tq, int G, int Hq, int row0, int R,
+                                                    double (*wpart)[D]) {      // rows row0 .. R - 1
+    constexpr int LPR = D / 8, NPART = BLK / LPR, UN = 8;
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-    const int c8 = tid % LPR, part = tid / LPR, R = Tq * G;
+    const int c8 = tid % LPR, part = row0 + tid / LPR;
     const E *qb = q + (size_t)lc * Tq * Hq * D + (size_t)h * G * D + 8 * c8;
     double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     // (token and head of a row by increments: a division per row cost 3 of a 256-token question's 25 us in this kernel)
@@ -91,12 +93,41 @@ __device__ __forceinline__ void mean_query_partials(const E *q, int lc, int h, i
     }
 }
 
+// A long question's rows, kMeanRows of each unit per workgroup: sums to dv.part_o, [unit of the call][workgroup][D] doubles.  grid (n_units,
+// mean_query_parts()), 256 threads.  One workgroup per unit is bound by what its CU takes in and converts: 1792 rows of 128 channels cost k_retrieve 10 us of
+// its 22.9 (256 tokens, 7 heads a unit, 4 units, bf16); here they take 4.8, and k_retrieve 13.1.
+constexpr int kMeanBlock = 256, kMeanRows = 128;
+template <typename E, int D>
+__global__ __launch_bounds__(kMeanBlock) void k_mean_query(DeviceView dv, int u0, const E *q, int Tq) {
+    const int uc = blockIdx.x, u = u0 + uc, tid = threadIdx.x, row0 = blockIdx.y * kMeanRows;
+    __shared__ double wpart[kMeanBlock / 64][D];
+    mean_query_partials<E, D, kMeanBlock>(q, uc / dv.Hkv, u % dv.Hkv, Tq, dv.G, dv.Hq, row0, min(Tq * dv.G, row0 + kMeanRows), wpart);
+    __syncthreads();
+    if (tid < D) {
+        double a = 0.0;
+#pragma unroll
+        for (int w = 0; w < kMeanBlock / 64; ++w) a += wpart[w][tid];
+        reinterpret_cast<double *>(dv.part_o)[((size_t)uc * gridDim.y + blockIdx.y) * D + tid] = a;
+    }
+}
+
+// Sums of how many workgroups k_retrieve finds (0: it sums the rows itself).  The launch costs less than it saves from about 900 rows a unit (fp32: 500) on,
+// unless the units fill the chip by themselves.  Calls of mosaic_retrieve in us, rows summed in k_retrieve / before it: bf16, 4 units 560 rows 10.8 / 11.6,
+// 896 12.1 / 12.3, 1344 14.2 / 11.9, 1792 16.3 / 11.7; 16 units 1792 rows 16.5 / 12.4; 112 units 1792 rows 18.5 / 19.0; fp32, 4 units 448 rows
+// 12.1 / 12.1, 560 13.2 / 12.3, 1792 18.1 / 12.2; 112 units 1792 rows 25.4 / 26.3.  The sums lie in the attention partials, which the context's one
+// stream uses after them (the host tier selects on another stream).
+int mean_query_parts(const DeviceView &dv, int n_units, int Tq) {
+    const long long rows = (long long)Tq * dv.G, parts = (rows + kMeanRows - 1) / kMeanRows;
+    const long long room = dv.part_entries * kRowTile / 2 / n_units;           // rows of D doubles in the attention partials
+    return rows >= (dv.esize == 4 ? 640 : 1024) && n_units <= 64 && dv.tier == MOSAIC_TIER_HBM && parts <= std::min<long long>(room, 4096) ? (int)parts : 0;
+}
+
 // NESTED (paper Sec. V-C "Two-Stage Retrieval"): the mean query is first scored against the
 // unit's P partition representatives; only the clusters of the top_p best partitions are then
 // scored (the rest count as empty: their rows are never read) and ranked.
 template <typename E, int D, bool NESTED>
 __global__ __launch_bounds__(kRetrBlock) void k_retrieve(DeviceView dv, int u0, const E *q, int Tq,
-                                                         int n_frames, int score_mode, bool write_pages) {
+                                                         int n_frames, int score_mode, int mean_parts, bool write_pages) {
     constexpr int BLK = kRetrBlock;
     constexpr int EPL = D / 16;        // doubles per lane in a 16-lane row group
     constexpr int RPP = BLK / 16;      // representative rows per pass
@@ -196,9 +227,26 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve(DeviceView dv, int u0, 
         if (tid < C) { n_sh[tid] = n_reg; rn_sh[tid] = rn_reg; cnt_sh[tid] = 0; wcnt_sh[tid] = 0; }
         __syncthreads();
         if (wa >= 0) atomicAdd(&wcnt_sh[wa], 1);         // (read after the scores' barrier at the earliest)
+    } else if (mean_parts > 0) {            // (k_mean_query has summed the rows)
+        if (tid < D) {
+            const double *qb = reinterpret_cast<const double *>(dv.part_o) + (size_t)uc * mean_parts * D + tid;
+            double acc = 0.0;
+            for (int p0 = 0; p0 < mean_parts; p0 += 16) {
+                double v[16];
+#pragma unroll
+                for (int x = 0; x < 16; ++x) v[x] = qb[(size_t)min(p0 + x, mean_parts - 1) * D];
+#pragma unroll
+                for (int x = 0; x < 16; ++x)
+                    if (p0 + x < mean_parts) acc += v[x];
+            }
+            qbar[tid] = acc / (double)R;
+        }
+        if (tid < C) { n_sh[tid] = n_reg; rn_sh[tid] = rn_reg; cnt_sh[tid] = 0; wcnt_sh[tid] = 0; }
+        __syncthreads();
+        if (wa >= 0) atomicAdd(&wcnt_sh[wa], 1);
     } else {
         if (tid < C) { n_sh[tid] = n_reg; rn_sh[tid] = rn_reg; cnt_sh[tid] = 0; wcnt_sh[tid] = 0; }
-        mean_query_partials<E, D>(q, lc, h, Tq, G, Hq, qpart);
+        mean_query_partials<E, D, BLK>(q, lc, h, Tq, G, Hq, 0, R, qpart);
         __syncthreads();
         if (wa >= 0) atomicAdd(&wcnt_sh[wa], 1);
         if (tid < D) {
@@ -391,7 +439,7 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve_deferred(DeviceView dv,
 
     for (int j = tid; j < 1024; j += BLK) { n_sh[j] = j < C ? n[j] : (j < R ? 1 : 0); cnt_sh[j] = 0; }
     if (tid == 0) tk_sh.n_live = 0;
-    mean_query_partials<E, D>(q, lc, h, Tq, G, Hq, qpart);
+    mean_query_partials<E, D, BLK>(q, lc, h, Tq, G, Hq, 0, Tq * G, qpart);
     __syncthreads();
     if (tid < D) {
         double acc = 0.0;
@@ -493,12 +541,23 @@ __global__ __launch_bounds__(kBlock) void k_expand_tok_idx(DeviceView dv, int u0
 template <bool NESTED>
 static void launch_retrieve_t(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                               int n_frames, int score_mode, bool write_pages, hipStream_t s) {
+    const int parts = mean_query_parts(dv, n_units, Tq);
+    if (parts > 0) {
+        auto sums = [&](auto kern, auto *qq) { kern<<<dim3(n_units, parts), kMeanBlock, 0, s>>>(dv, u0, qq, Tq); };
+        if (dv.esize == 4) {
+            if (dv.D == 64) sums(k_mean_query<float, 64>, (const float *)q);
+            else sums(k_mean_query<float, 128>, (const float *)q);
+        } else {
+            if (dv.D == 64) sums(k_mean_query<unsigned short, 64>, (const unsigned short *)q);
+            else sums(k_mean_query<unsigned short, 128>, (const unsigned short *)q);
+        }
+    }
     if (dv.esize == 4) {
-        if (dv.D == 64) k_retrieve<float, 64, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const float *)q, Tq, n_frames, score_mode, write_pages);
-        else k_retrieve<float, 128, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const float *)q, Tq, n_frames, score_mode, write_pages);
+        if (dv.D == 64) k_retrieve<float, 64, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const float *)q, Tq, n_frames, score_mode, parts, write_pages);
+        else k_retrieve<float, 128, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const float *)q, Tq, n_frames, score_mode, parts, write_pages);
     } else {
-        if (dv.D == 64) k_retrieve<unsigned short, 64, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const unsigned short *)q, Tq, n_frames, score_mode, write_pages);
-        else k_retrieve<unsigned short, 128, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const unsigned short *)q, Tq, n_frames, score_mode, write_pages);
+        if (dv.D == 64) k_retrieve<unsigned short, 64, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const unsigned short *)q, Tq, n_frames, score_mode, parts, write_pages);
+        else k_retrieve<unsigned short, 128, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const unsigned short *)q, Tq, n_frames, score_mode, parts, write_pages);
     }
 }
 

@@ -348,6 +348,14 @@ def test_question_whose_weights_outgrow_their_reference(T, D, tq, frames, rise):
         assert (got_lse - torch.logsumexp(logit, 1)).abs().max().item() <= 1e-6 * logit.abs().max().item() + harness.LSE_TOL["bf16"]
 
 
+# Rows of a long question are summed by workgroups of 128 rows each in a launch of its own: the least it takes, a row more than a workgroup's
+# share, sixteen of them and one, and one row less than it takes
+@pytest.mark.parametrize("tq,kw", [(147, dict()), (183, dict()), (147, dict(head_dim=64, n_layers=3)), (80, dict(n_q_heads=32, kv_dtype="fp32")),
+                                   (129, dict(n_q_heads=64)), (146, dict()), (79, dict(n_q_heads=32, kv_dtype="fp32"))])
+def test_mean_query_of_a_long_question(tq, kw):
+    harness.run_workload(_small(**{**dict(question_tokens=tq, n_frames=40, n_clusters=9, top_k=2, tokens_per_frame=6), **kw}), layer_mode="all")
+
+
 def test_question_with_room_for_few_partials(monkeypatch):
     # an arena with room for two splits per unit and no more (what a context needed before the equal shares): fewer shares, the
     # same result up to the order of the merge
