@@ -9,9 +9,11 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmosaic.so")
 SOURCES = ("api.hip", "host_tier.hip", "ingest_kernels.hip", "visual_kernels.hip",
            "retrieve_kernels.hip", "attend_kernels.hip", "attend_mfma.hip", "decode_fused.hip", "decode_layer.hip", "attend_prefill.hip", "attend_fp32.hip")
-# Packed-FP32 instructions are switched off for all device code.
+# Packed-FP32 instructions are switched off for all device code.  Kernel arguments come in registers (sixteen at the most) instead of by a load that
+# every wavefront would wait for first.
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wall", "-Wno-unused-function"]
 
 

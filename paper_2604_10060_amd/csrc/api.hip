@@ -59,7 +59,7 @@ int fail_hip(mosaic_ctx *ctx, hipError_t e, const char *what) {
 
 struct Layout {
     size_t k_store, v_store, summ, r, rnorm, n, assign, pos, lloyd_moved, lloyd_delta, lloyd_bounds, sel_flag, sync_err, scores, ids, n_ids, sel_pages, n_sel,
-        tok_scratch, part_o, part_ml, stage_k, stage_v, var, lazy, resident, n_slots, buf_frame,
+        tok_scratch, views, part_o, part_ml, stage_k, stage_v, var, lazy, resident, n_slots, buf_frame,
         buf_owner, n_buf, mt_cnt, mt_mem, mt_side, mt_nrm, vsumm, rvsum, rep_k, rep_v, aug_o, aug_ml,
         vemb, vr, vrn, vn, part, pr, prn, pn, pscores, pids, n_pids, total;
     size_t host_k, host_v, host_sel, host_nsel, host_ids, host_nids, host_moves, host_nmoves, host_assign, host_dest,
@@ -196,6 +196,7 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
     L.lloyd_bounds = take(U * F * 16);
     L.sel_flag = take(U * 8);
     L.sync_err = take(4);
+    L.views = take(2 * sizeof(DeviceView));
     L.c_init = init_clusters_of(c); L.buf_max = buffer_max_of(c); L.W = warmup_of(c);
     L.split_iters = c.split_iters > 0 ? c.split_iters : 4;
     const bool mt = c.maint_mode != MOSAIC_MAINT_OFF;
@@ -272,6 +273,28 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
         L.host_total = 0;
     }
     return L;
+}
+
+// The copy of a view that kernels read, where the view says it is.  One workgroup; a launch, so that it stands in the context's stream (and in a capture
+// of it) before every launch that reads it.
+__global__ __launch_bounds__(128) void k_set_view(DeviceView v) {
+    unsigned long long w[sizeof(DeviceView) / 8];
+    __builtin_memcpy(w, &v, sizeof v);
+    unsigned long long *dst = (unsigned long long *)v.self;
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (size_t i = 0; i < sizeof(DeviceView) / 8; ++i) dst[i] = w[i];
+}
+
+// The same view with the attention partials in the library's static buffer instead of the arena: [entries][16][D] outputs, then [entries][3][16]
+// statistics; every entry a launch reads was written by that launch, so nothing has to be cleared between calls
+DeviceView static_view(const mosaic_ctx *ctx) {
+    DeviceView dv = ctx->dv;
+    const size_t per_entry = (size_t)kRowTile * dv.D * 4 + (size_t)kMlRows * kRowTile * 4;
+    dv.part_entries = (long long)(kStaticScratchBytes / per_entry);
+    dv.part_o = (float *)ctx->static_scratch;
+    dv.part_ml = dv.part_o + (size_t)dv.part_entries * kRowTile * dv.D;
+    return dv;
 }
 
 // KV splits per unit for a decode step (and for a question with the bf16 vector-ALU kernel), bounded by the partial-buffer
@@ -548,7 +571,15 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
                 (e = hipEventCreateWithFlags(&ht->attend_done[l], hipEventDisableTiming)) != hipSuccess)
                 return bail(MOSAIC_EHIP, std::string("host tier event creation: ") + hipGetErrorString(e));
     }
-    if (clear_maintainer(ctx) != hipSuccess) {     // (no context to keep a message in: the code says it)
+    // the kernels' views: [0] with the arena's attention partials, [1] with the static ones (mosaic_attend_static)
+    DeviceView *views = (DeviceView *)(base + L.views);
+    for (int i = 0; i < 2; ++i) {
+        DeviceView v = i ? static_view(ctx) : dv;
+        v.self = views + i;
+        k_set_view<<<1, 128, 0, ctx->stream>>>(v);
+    }
+    dv.self = views;
+    if (hipGetLastError() != hipSuccess || clear_maintainer(ctx) != hipSuccess) {     // (no context to keep a message in: the code says it)
         (void)mosaic_destroy(ctx);
         *out = nullptr;
         return MOSAIC_EHIP;
@@ -746,7 +777,7 @@ static int offload_range(mosaic_ctx *ctx, int f0, int f1) {
     // One kernel that stores the assignments to pinned memory, and one wait: the link idles from here until the next offload
     // kernel starts.  (A wait, a copy per unit, a second wait and the table's upload through the caller's stream took 150 us
     // per batch of 16 frames and 8 units, half as long as the offload itself.)
-    if ((e = launch_gather_assign(dv, f0, n, ctx->stream)) != hipSuccess) return fail_hip(ctx, e, "assignment read-back");
+    if ((e = launch_gather_assign(dv, dv.batch_assign, f0, n, ctx->stream)) != hipSuccess) return fail_hip(ctx, e, "assignment read-back");
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return fail_hip(ctx, e, "hipStreamSynchronize");
     for (int fl = 0; fl < n; ++fl)
         for (int u = 0; u < dv.U; ++u) {
@@ -760,9 +791,8 @@ static int offload_range(mosaic_ctx *ctx, int f0, int f1) {
         }
     // The offload goes to the copy stream, so that the caller's stream can stage and assign the next batch meanwhile; the
     // batch is staged (the wait above), and the kernel reads its table where the host has written it.
-    DeviceView d2 = dv;
-    d2.dest = dv.dest + (size_t)p * dv.U * dv.SN;
-    if ((e = launch_offload(d2, f0, n, ht->copy_stream)) != hipSuccess) return fail_hip(ctx, e, "offload launch");
+    const int *dest_dev = dv.dest + (size_t)p * dv.U * dv.SN;
+    if ((e = launch_offload(dv, dest_dev, f0, n, ht->copy_stream)) != hipSuccess) return fail_hip(ctx, e, "offload launch");
     if ((e = hipEventRecord(ht->off_done[p], ht->copy_stream)) != hipSuccess) return fail_hip(ctx, e, "hipEventRecord(offload)");
     ht->off_used[p] = true; ht->off_f0[p] = f0; ht->off_f1[p] = f1;
     ht->off_idx += 1;
@@ -1215,14 +1245,8 @@ int32_t mosaic_attend_static(mosaic_ctx *ctx, int32_t layer, const void *q_dev, 
                              void *out_dev, float *lse_dev) {
     if (!ctx) return MOSAIC_EINVAL;
     if (!ctx->static_scratch) return fail(ctx, MOSAIC_EHIP, "the static scratch buffer has no device address");
-    // the same kernels, with their split partials in the library's static buffer instead of the arena:
-    // [entries][16][D] outputs, then [entries][3][16] statistics; every entry a launch reads was written
-    // by that launch, so nothing has to be cleared between calls
-    DeviceView dv = ctx->dv;
-    const size_t per_entry = (size_t)kRowTile * dv.D * 4 + (size_t)kMlRows * kRowTile * 4;
-    dv.part_entries = (long long)(kStaticScratchBytes / per_entry);
-    dv.part_o = (float *)ctx->static_scratch;
-    dv.part_ml = dv.part_o + (size_t)dv.part_entries * kRowTile * dv.D;
+    DeviceView dv = static_view(ctx);
+    dv.self = ctx->dv.self + 1;
     return attend_with(ctx, dv, layer, q_dev, n_q_tokens, out_dev, lse_dev, false);
 }
 
@@ -1430,11 +1454,10 @@ int32_t mosaic_get_assignments(mosaic_ctx *ctx, int32_t *frame_to_cluster) {
     if (nf == (size_t)dv.F) return d2h(ctx, frame_to_cluster, dv.assign, nf * dv.U * 4);
     int rc = join_ingest(ctx);
     if (rc != MOSAIC_OK) return rc;
-    DeviceView out = dv;
-    out.batch_assign = reinterpret_cast<int *>(dv.lloyd_bounds);
-    const hipError_t e = launch_gather_assign(out, 0, (int)nf, ctx->stream);
+    int *rows = reinterpret_cast<int *>((ChordBounds *)dv.lloyd_bounds);
+    const hipError_t e = launch_gather_assign(dv, rows, 0, (int)nf, ctx->stream);
     if (e != hipSuccess) return fail_hip(ctx, e, "assignment gather launch");
-    return d2h(ctx, frame_to_cluster, out.batch_assign, nf * dv.U * 4);
+    return d2h(ctx, frame_to_cluster, rows, nf * dv.U * 4);
 }
 
 int32_t mosaic_get_centroids(mosaic_ctx *ctx, double *r, int32_t *n) {

@@ -25,8 +25,9 @@ namespace {
 // units' or the part of one that lies in one unit (even_share), its wavefronts every fourth.
 // The page ids of group i + 2 and the operands of group i + 1 are in flight while group i is reduced.
 template <int D, int R, bool STREAM>
-__global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp32(DeviceView dv, int u0, int n_units, const float *q,
+__global__ __launch_bounds__(kBlock, R == 1 || D == 64 ? 2 : 1) void k_attend_fp32(const DeviceView *self, int u0, int n_units, const float *q,
                                                                         int Tq, int NT, int G, int B, int n_row_blocks) {
+    const DeviceView dv = device_view<0, 1, 2, 8>(self);
     __shared__ float lds[kF32MergeFloats<D>];
     const int first_extra = R == 1 ? B : (B * n_row_blocks + 7) / 8 * 8;
     if ((int)blockIdx.x >= first_extra) {      // extra workgroups: the global representatives' part (augmentation)
@@ -187,7 +188,7 @@ hipError_t launch_attend_fp32(const DeviceView &dv, int u0, int n_units, const f
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile, R = NT == 1 ? 1 : kFp32Tiles, rb = (NT + R - 1) / R;
     const int B = NT == 1 ? n_units * n_splits : shares.walk ? shares.groups : shares.groups + n_units - 1;
     const dim3 grid((NT == 1 ? B : (B * rb + 7) / 8 * 8) + (dv.aug_reps ? n_units * rb : 0)), block(kBlock);
-    auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, shares.groups, B, rb); };
+    auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv.self, u0, n_units, q, Tq, NT, shares.groups, B, rb); };
     if (NT == 1) {
         if (dv.D == 64) stream_kv ? go(k_attend_fp32<64, 1, true>) : go(k_attend_fp32<64, 1, false>);
         else stream_kv ? go(k_attend_fp32<128, 1, true>) : go(k_attend_fp32<128, 1, false>);

@@ -46,8 +46,9 @@ __device__ __forceinline__ float group16_sumf(float x) {
 // grid (n_units * n_splits [+ n_units with the global-representative augmentation], NT), 256 threads:
 // thread (row = tid/16, tl = tid%16)
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_attend_valu(DeviceView dv, int u0, int n_units, const unsigned short *q,
+__global__ __launch_bounds__(kBlock) void k_attend_valu(const DeviceView *self, int u0, int n_units, const unsigned short *q,
                                                         int Tq, int B) {
+    const DeviceView dv = device_view(self);
     typedef unsigned short E;
     constexpr int DPT = D / 16;   // output channels per thread
     constexpr int CG = D / 8;     // 8-element groups per token row
@@ -265,8 +266,9 @@ __device__ __forceinline__ void combine_store(const DeviceView &dv, int u, int l
 // output channels; its 8 groups of 32 threads share the splits, so the partial buffer is
 // read with many independent 128-byte loads in flight.
 template <typename E, int D>
-__global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0, int n_units, int Tq,
+__global__ __launch_bounds__(kBlock) void k_attend_combine(const DeviceView *self, int u0, int n_units, int Tq,
                                                            int B, int uniform_S, E *out, float *lse) {
+    const DeviceView dv = device_view<0, 2, 8>(self);
     // grid.x = (D / 32) * RS: RS workgroups share a tile's rows (a decode step's heaviest unit has up to 256
     // partials to merge, and the launch lasts as long as that unit's workgroups: with its rows shared by two
     // workgroups each thread reads half as much, all of it in one pass)
@@ -345,8 +347,9 @@ __global__ __launch_bounds__(kBlock) void k_attend_combine(DeviceView dv, int u0
 // grid (D / CW, NT, n_units), BLK threads.
 constexpr int kMergeBatch = 8;
 template <typename E, int D, int CW, int BLK>
-__global__ __launch_bounds__(BLK) void k_combine_question(DeviceView dv, int u0, int n_units, int Tq, int B, int G, E *out,
+__global__ __launch_bounds__(BLK) void k_combine_question(const DeviceView *self, int u0, int n_units, int Tq, int B, int G, E *out,
                                                           float *lse) {
+    const DeviceView dv = device_view(self);
     constexpr int TPS = 16 * CW / 4 < BLK ? 16 * CW / 4 : BLK, SG = BLK / TPS, RPT = 16 * CW / 4 / TPS;   // threads of a split group, groups, rows per thread
     constexpr int LPR = CW / 4, RSTEP = TPS / LPR;          // lanes of a row, rows between a thread's rows
     const int tile = blockIdx.y, uc = blockIdx.z, u = u0 + uc, NT = gridDim.y, tid = threadIdx.x;
@@ -451,8 +454,8 @@ hipError_t launch_attend_valu(const DeviceView &dv, int u0, int n_units, const v
     const int B = n_units * n_splits;
     const dim3 grid(B + (dv.aug_reps ? n_units : 0), NT), block(kBlock);
     const unsigned short *qq = (const unsigned short *)q;
-    if (dv.D == 64) launch_timed((k_attend_valu<64>), grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B);
-    else launch_timed((k_attend_valu<128>), grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B);
+    if (dv.D == 64) launch_timed((k_attend_valu<64>), grid, block, 0, s, ev0, ev1, dv.self, u0, n_units, qq, Tq, B);
+    else launch_timed((k_attend_valu<128>), grid, block, 0, s, ev0, ev1, dv.self, u0, n_units, qq, Tq, B);
     return hipGetLastError();
 }
 
@@ -467,7 +470,7 @@ hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int 
         const long long tiles = (long long)NT * n_units;
         const int form = tiles >= 256 || n_splits <= kMergeBatch ? 0 : tiles >= 64 ? 1 : 2;
         const dim3 gq(form == 2 ? dv.D / 32 : 1, NT, n_units);
-        auto go = [&](auto kern, int blk, auto *o) { kern<<<gq, blk, 0, s>>>(dv, u0, n_units, Tq, B, shares.groups, o, lse); };
+        auto go = [&](auto kern, int blk, auto *o) { kern<<<gq, blk, 0, s>>>(dv.self, u0, n_units, Tq, B, shares.groups, o, lse); };
         auto pick = [&](auto *o, auto d) {
             using E = std::remove_pointer_t<decltype(o)>;
             constexpr int D = decltype(d)::value;
@@ -488,11 +491,11 @@ hipError_t launch_attend_combine(const DeviceView &dv, int u0, int n_units, int 
     const int RS = std::max(1, std::min(8, 512 / (n_units * (dv.D / 32))));
     const dim3 grid(dv.D / 32 * RS, n_units);
     if (dv.esize == 4) {
-        if (dv.D == 64) k_attend_combine<float, 64><<<grid, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, us, (float *)out, lse);
-        else k_attend_combine<float, 128><<<grid, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, us, (float *)out, lse);
+        if (dv.D == 64) k_attend_combine<float, 64><<<grid, kBlock, 0, s>>>(dv.self, u0, n_units, Tq, B, us, (float *)out, lse);
+        else k_attend_combine<float, 128><<<grid, kBlock, 0, s>>>(dv.self, u0, n_units, Tq, B, us, (float *)out, lse);
     } else {
-        if (dv.D == 64) k_attend_combine<unsigned short, 64><<<grid, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, us, (unsigned short *)out, lse);
-        else k_attend_combine<unsigned short, 128><<<grid, kBlock, 0, s>>>(dv, u0, n_units, Tq, B, us, (unsigned short *)out, lse);
+        if (dv.D == 64) k_attend_combine<unsigned short, 64><<<grid, kBlock, 0, s>>>(dv.self, u0, n_units, Tq, B, us, (unsigned short *)out, lse);
+        else k_attend_combine<unsigned short, 128><<<grid, kBlock, 0, s>>>(dv.self, u0, n_units, Tq, B, us, (unsigned short *)out, lse);
     }
     return hipGetLastError();
 }

@@ -33,8 +33,9 @@ namespace {
 // in flight while the current one is reduced.
 // ---------------------------------------------------------------------------
 template <int D, bool AUG, bool STREAM>
-__global__ __launch_bounds__(kBlock, 2) void k_attend_decode_mfma(DeviceView dv, int u0, int n_units,
+__global__ __launch_bounds__(kBlock, 2) void k_attend_decode_mfma(const DeviceView *self, int u0, int n_units,
                                                                   const unsigned short *q, int Tq, int B) {
+    const DeviceView dv = device_view(self);
     constexpr int KK = D / 32, DB = D / 16;
     if constexpr (AUG) {
         if ((int)blockIdx.x >= B) {   // extra workgroups: the global representatives' part (augmentation)
@@ -135,7 +136,7 @@ hipError_t launch_attend_mfma(const DeviceView &dv, int u0, int n_units, const v
     if (NT == 1) {
         const int B = n_units * n_splits;
         const dim3 grid(B + (dv.aug_reps ? n_units : 0));
-        auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B); };
+        auto go = [&](auto kern) { launch_timed(kern, grid, block, 0, s, ev0, ev1, dv.self, u0, n_units, qq, Tq, B); };
         if (dv.aug_reps) {
             if (dv.D == 64) stream_kv ? go(k_attend_decode_mfma<64, true, true>) : go(k_attend_decode_mfma<64, true, false>);
             else stream_kv ? go(k_attend_decode_mfma<128, true, true>) : go(k_attend_decode_mfma<128, true, false>);

@@ -62,10 +62,11 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 }
 
 template <int D, bool AUG, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfma(DeviceView dv, int u0, int n_units,
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfma(const DeviceView *self, int u0, int n_units,
                                                                                     const unsigned short *q, int Tq,
                                                                                     int NT, int G, int n_groups, int n_row_blocks,
                                                                                     int group_blocks) {
+    const DeviceView dv = device_view(self);
     static_assert(!AUG || 64 * NW == kBlock, "the representatives' workgroups are written for kBlock threads");
     constexpr int KK = D / 32, DB = D / 16, RTW = kPrefillTiles;
     constexpr int KSEG = D / 8;                  // 16-byte pieces per key row
@@ -410,7 +411,7 @@ hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, cons
     const int n_groups = shares.walk ? shares.groups : shares.groups + n_units - 1, rb = (NT + NW * kPrefillTiles - 1) / (NW * kPrefillTiles);
     const int gb = (n_groups * rb + 7) / 8 * 8;
     const dim3 grid(gb + (dv.aug_reps ? n_units * NT : 0)), block(64 * NW);
-    auto go = [&](auto kern) { launch_timed(kern, grid, block, lds, s, ev0, ev1, dv, u0, n_units, q, Tq, NT, shares.groups, n_groups, rb, gb); };
+    auto go = [&](auto kern) { launch_timed(kern, grid, block, lds, s, ev0, ev1, dv.self, u0, n_units, q, Tq, NT, shares.groups, n_groups, rb, gb); };
     if (dv.aug_reps) { if (dv.D == 64) go(k_attend_prefill_mfma<64, true, NW>); else go(k_attend_prefill_mfma<128, true, NW>); }
     else { if (dv.D == 64) go(k_attend_prefill_mfma<64, false, NW>); else go(k_attend_prefill_mfma<128, false, NW>); }
     return hipGetLastError();

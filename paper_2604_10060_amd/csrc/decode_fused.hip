@@ -42,8 +42,9 @@ template <typename E, int D, bool AUG> constexpr int kFusedBlock = AUG || (sizeo
 __device__ __forceinline__ double group16_sum_f64(double x) { return row16_sum(x); }   // as in k_retrieve
 
 template <typename E, int D, bool AUG, bool STREAM>
-__global__ __launch_bounds__((kFusedBlock<E, D, AUG>), AUG ? 2 : 1) void k_decode_fused(DeviceView dv, int u0, int n_units, const E *q, int Tq,
+__global__ __launch_bounds__((kFusedBlock<E, D, AUG>), AUG ? 2 : 1) void k_decode_fused(const DeviceView *self, int u0, int n_units, const E *q, int Tq,
                                                          int S, int n_frames, int score_mode) {
+    const DeviceView dv = device_view<0, 1, 2, 3>(self);
     constexpr bool FP32 = sizeof(E) == 4;
     constexpr int BLK = kFusedBlock<E, D, AUG>, NW = BLK / 64;
     constexpr int KK = D / 32, DB = D / 16, EPL = D / 16, NG = BLK / 16, RPF = 128 / NG, FPT = 2048 / BLK;
@@ -375,7 +376,7 @@ hipError_t launch_decode_fused(const DeviceView &dv, int u0, int n_units, const 
                                hipEvent_t ev1) {
     const bool aug = dv.aug_reps || dv.aug_window > 0;
     const dim3 grid(n_units * n_splits + (dv.aug_reps ? n_units : 0));
-    auto go = [&](auto kern, int blk, auto *qq) { launch_timed(kern, grid, dim3(blk), 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, n_splits, n_frames, score_mode); };
+    auto go = [&](auto kern, int blk, auto *qq) { launch_timed(kern, grid, dim3(blk), 0, s, ev0, ev1, dv.self, u0, n_units, qq, Tq, n_splits, n_frames, score_mode); };
     auto pick = [&](auto *qq, auto d) {
         using E = std::remove_const_t<std::remove_pointer_t<decltype(qq)>>;
         constexpr int D = decltype(d)::value, A = kFusedBlock<E, D, true>, P = kFusedBlock<E, D, false>;

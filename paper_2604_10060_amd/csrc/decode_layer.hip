@@ -211,8 +211,9 @@ __device__ __forceinline__ void leader_select(const DeviceView &dv, int u, int l
 }
 
 template <int D, bool STREAM>
-__global__ __launch_bounds__(kBlock, 2) void k_decode_layer(DeviceView dv, int u0, int n_units, const unsigned short *q,
+__global__ __launch_bounds__(kBlock, 2) void k_decode_layer(const DeviceView *self, int u0, int n_units, const unsigned short *q,
                                                             int Tq, int B, int n_frames, int score_mode, int epoch) {
+    const DeviceView dv = device_view(self);
     constexpr int KK = D / 32, DB = D / 16;
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, g = lane / 16, n = lane % 16;
     __shared__ int ok_sh, pub_sh, nsel_sh[64];
@@ -325,11 +326,11 @@ hipError_t launch_decode_layer(const DeviceView &dv, int u0, int n_units, const 
     const dim3 grid(B), block(kBlock);
     const unsigned short *qq = (const unsigned short *)q;
     if (stream_kv) {
-        if (dv.D == 64) launch_timed(k_decode_layer<64, true>, grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B, n_frames, score_mode, epoch);
-        else launch_timed(k_decode_layer<128, true>, grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B, n_frames, score_mode, epoch);
+        if (dv.D == 64) launch_timed(k_decode_layer<64, true>, grid, block, 0, s, ev0, ev1, dv.self, u0, n_units, qq, Tq, B, n_frames, score_mode, epoch);
+        else launch_timed(k_decode_layer<128, true>, grid, block, 0, s, ev0, ev1, dv.self, u0, n_units, qq, Tq, B, n_frames, score_mode, epoch);
     } else {
-        if (dv.D == 64) launch_timed(k_decode_layer<64, false>, grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B, n_frames, score_mode, epoch);
-        else launch_timed(k_decode_layer<128, false>, grid, block, 0, s, ev0, ev1, dv, u0, n_units, qq, Tq, B, n_frames, score_mode, epoch);
+        if (dv.D == 64) launch_timed(k_decode_layer<64, false>, grid, block, 0, s, ev0, ev1, dv.self, u0, n_units, qq, Tq, B, n_frames, score_mode, epoch);
+        else launch_timed(k_decode_layer<128, false>, grid, block, 0, s, ev0, ev1, dv.self, u0, n_units, qq, Tq, B, n_frames, score_mode, epoch);
     }
     return hipGetLastError();
 }

@@ -61,8 +61,9 @@ __device__ __forceinline__ void wave_best(double &bv, int &bi) {
 // grid (U, n_frames, 2 or 3): z = 0 keys, z = 1 values, z = 2 the embeddings e_in of the n_emb first frames (nested hierarchy, warm-up), into the
 // visual level's fp64 state array.  (A launch of their own cost 3.6 us.)
 template <typename E, int D, bool BEYOND>
-__global__ __launch_bounds__(kStoreBlock) void k_store_summary(DeviceView dv, const E *k_in,
+__global__ __launch_bounds__(kStoreBlock) void k_store_summary(const DeviceView *self, const E *k_in,
                                                           const E *v_in, int f0, const float *e_in, int n_emb) {
+    const DeviceView dv = device_view(self);
     __shared__ StoreShared<D> store_sh;
     const int u = blockIdx.x, fl = blockIdx.y;
     const bool host = dv.tier == MOSAIC_TIER_HOST;
@@ -82,7 +83,8 @@ __global__ __launch_bounds__(kStoreBlock) void k_store_summary(DeviceView dv, co
 // the pseudo-token tables (zero rows for empty clusters).
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(128) void k_value_reps(DeviceView dv, int n_frames) {
+__global__ __launch_bounds__(128) void k_value_reps(const DeviceView *self, int n_frames) {
+    const DeviceView dv = device_view(self);
     constexpr int NT = 128, CH = NT * kListPer;
     const int u = blockIdx.x, j = blockIdx.y, tid = threadIdx.x, C = dv.C;
     __shared__ int mem[CH];
@@ -114,7 +116,8 @@ __global__ __launch_bounds__(128) void k_value_reps(DeviceView dv, int n_frames)
 enum { kActAbsorb = 1, kActSplit = 2, kActDefer = 3, kActForced = 4 };
 
 template <int D, bool MAINT>
-__global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0, int f1) {
+__global__ __launch_bounds__(kBlock) void k_assign_update(const DeviceView *self, int f0, int f1) {
+    const DeviceView dv = device_view(self);
     constexpr int EPL = D / 16;  // elements per lane in a 16-lane row group
     const int u = blockIdx.x, tid = threadIdx.x, C = dv.C;
     const int lr = tid % 16, row0 = tid / 16, wave = tid / 64, lane = tid % 64;
@@ -339,7 +342,8 @@ __global__ __launch_bounds__(kBlock) void k_assign_update(DeviceView dv, int f0,
 constexpr int kChainBlock = 512, kChainSims = 8192;
 
 template <int D>
-__global__ __launch_bounds__(kChainBlock) void k_assign_chain(DeviceView dv, int f0, int f1) {
+__global__ __launch_bounds__(kChainBlock) void k_assign_chain(const DeviceView *self, int f0, int f1) {
+    const DeviceView dv = device_view(self);
     constexpr int EPL = D / 16, NG = kChainBlock / 16, NW = kChainBlock / 64, KS = D / 8, SPB = kChainBlock / D;
     constexpr int FR = kChainFrames, kNone = 0x7fffffff, TW = FR / 4;
     const int u = blockIdx.x, tid = threadIdx.x, lane = tid % 64, lr = tid % 16, grp = tid / 16, C = dv.C;
@@ -780,7 +784,8 @@ __device__ __forceinline__ void held_nearest(int lo, int hi, const int *size, co
 }
 
 template <int D, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, int f0, int f1) {
+__global__ __launch_bounds__(THREADS) void k_assign_update_reg(const DeviceView *self, int f0, int f1) {
+    const DeviceView dv = device_view(self);
     constexpr int EPL = D / 16, NG = THREADS / 16, RPG = 8, NW = THREADS / 64, ROWS = NG * RPG;
     const int u = blockIdx.x, tid = threadIdx.x, C = dv.C;
     const int lr = tid % 16, grp = tid / 16, wave = tid / 64, lane = tid % 64;
@@ -940,7 +945,8 @@ __global__ __launch_bounds__(THREADS) void k_assign_update_reg(DeviceView dv, in
 // ---------------------------------------------------------------------------
 constexpr int kOneBlock = 256;
 template <typename E, int D>
-__global__ __launch_bounds__(kOneBlock) void k_ingest_one(DeviceView dv, const E *k_in, const E *v_in, int f) {
+__global__ __launch_bounds__(kOneBlock) void k_ingest_one(const DeviceView *self, const E *k_in, const E *v_in, int f) {
+    const DeviceView dv = device_view<0, 1, 3>(self);
     constexpr int EPL = D / 16, NG = kOneBlock / 16, RPG = 128 / NG, NW = kOneBlock / 64, ROWS = NG * RPG;
     __shared__ StoreShared<D> store_sh;
     const int u = blockIdx.x;
@@ -1045,7 +1051,8 @@ __global__ __launch_bounds__(kOneBlock) void k_ingest_one(DeviceView dv, const E
 // With the maintainer on only the first c_init ids are seeded (the rest of the
 // table is empty until splits fill it) and the maintainer's state is cleared.
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_lloyd_seed(DeviceView dv, int W) {
+__global__ __launch_bounds__(kBlock) void k_lloyd_seed(const DeviceView *self, int W) {
+    const DeviceView dv = device_view(self);
     constexpr int EPL = D / 16;
     const int u = blockIdx.x, tid = threadIdx.x, C = dv.C;
     const int Cl = dv.maint_mode ? dv.c_init : C;
@@ -1087,7 +1094,8 @@ __global__ __launch_bounds__(kBlock) void k_lloyd_seed(DeviceView dv, int W) {
 // at a time for all ids of a unit (W = 1024, P = 16, C = 512: 250 -> 24 us).
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_lloyd_seed_nested(DeviceView dv, int W) {
+__global__ __launch_bounds__(kBlock) void k_lloyd_seed_nested(const DeviceView *self, int W) {
+    const DeviceView dv = device_view(self);
     constexpr int EPL = D / 16;
     const int u = blockIdx.x, tid = threadIdx.x, lane = tid % 64, C = dv.C, Cs = dv.Cs;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lr = tid % 16, grp = tid / 16;
@@ -1134,7 +1142,8 @@ __global__ __launch_bounds__(kBlock) void k_lloyd_seed_nested(DeviceView dv, int
 // members are listed first, then sixteen loads are in flight: 73 -> 13 us for 1024 frames).
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(128) void k_partition_reps(DeviceView dv, int n_frames) {
+__global__ __launch_bounds__(128) void k_partition_reps(const DeviceView *self, int n_frames) {
+    const DeviceView dv = device_view(self);
     constexpr int NT = 128, CH = NT * kListPer;
     const int u = blockIdx.x, p = blockIdx.y, tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     __shared__ double nsum_sh[2];
@@ -1169,7 +1178,8 @@ __global__ __launch_bounds__(128) void k_partition_reps(DeviceView dv, int n_fra
 // group partials are added in a fixed order.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_exact_var(DeviceView dv, int n_frames) {
+__global__ __launch_bounds__(kBlock) void k_exact_var(const DeviceView *self, int n_frames) {
+    const DeviceView dv = device_view(self);
     constexpr int EPL = D / 16, NG = kBlock / 16;
     const int u = blockIdx.x, j = blockIdx.y, tid = threadIdx.x, C = dv.C;
     const int lr = tid % 16, grp = tid / 16;
@@ -1285,7 +1295,8 @@ __device__ __forceinline__ unsigned int row16_or(unsigned int x) {
 // partitions: 6.1 + 39.5 us; now 16 us; round 0, where tiles of other partitions are no longer multiplied, 59 -> 40 us.
 constexpr int kLloydTest = 128;
 template <int D, bool LATER, bool NESTED>
-__global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(DeviceView dv, int n_frames, int it) {
+__global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const DeviceView *self, int n_frames, int it) {
+    const DeviceView dv = device_view(self);
     constexpr int KS = D / 8;
     static_assert(kLloydTest <= kBlock && kLloydTest % 64 == 0, "a thread per frame, whole wavefronts");
     const int u = blockIdx.x, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, C = dv.C;
@@ -1562,7 +1573,8 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(DeviceVi
 // unit: 470 MB at 112 units x 4096 frames), which is what bounds it.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(128) void k_lloyd_update(DeviceView dv, int n_frames, int it) {
+__global__ __launch_bounds__(128) void k_lloyd_update(const DeviceView *self, int n_frames, int it) {
+    const DeviceView dv = device_view(self);
     constexpr int NT = 128, FPT = 16, CH = NT * FPT;
     const int u = blockIdx.x, j = blockIdx.y, tid = threadIdx.x, C = dv.C;
     // (a round that moved no frame would rebuild the same sums: see k_lloyd_assign)
@@ -1670,10 +1682,11 @@ __global__ __launch_bounds__(128) void k_lloyd_update(DeviceView dv, int n_frame
 // ---------------------------------------------------------------------------
 // Assignments of frames f0 .. f0+n-1, compacted: a host-tier batch's straight into pinned memory, an observer's into
 // scratch.  grid (U, blocks of frames).
-__global__ __launch_bounds__(kBlock) void k_gather_assign(DeviceView dv, int f0, int n) {
+__global__ __launch_bounds__(kBlock) void k_gather_assign(const DeviceView *self, int *rows, int f0, int n) {
+    const DeviceView dv = device_view(self);
     const int u = blockIdx.x;
     for (int i = blockIdx.y * kBlock + threadIdx.x; i < n; i += gridDim.y * kBlock)
-        dv.batch_assign[(size_t)u * n + i] = dv.assign[(size_t)u * dv.F + f0 + i];
+        rows[(size_t)u * n + i] = dv.assign[(size_t)u * dv.F + f0 + i];
 }
 
 // ---------------------------------------------------------------------------
@@ -1684,7 +1697,8 @@ __global__ __launch_bounds__(kBlock) void k_gather_assign(DeviceView dv, int f0,
 // one workgroup per page would hold the chip while it waits for the link.
 // ---------------------------------------------------------------------------
 constexpr int kOffloadXcds = 8;
-__global__ __launch_bounds__(kBlock) void k_offload(DeviceView dv, int f0, int n) {
+__global__ __launch_bounds__(kBlock) void k_offload(const DeviceView *self, const int *dest, int f0, int n) {
+    const DeviceView dv = device_view(self);
     // The page table is in pinned host memory: a workgroup fetches the entries of its next 256 items in one trip.
     // Only workgroups 0, 8, 16, ... work: workgroups go to the eight XCDs in turn, so these share one XCD, and its path to
     // the fabric is the only one that fills up with posted stores to the link.  Spread over all XCDs the same stores hold
@@ -1694,7 +1708,7 @@ __global__ __launch_bounds__(kBlock) void k_offload(DeviceView dv, int f0, int n
     const int n_items = dv.U * n * 2, stride = gridDim.x / kOffloadXcds;
     for (int i0 = blockIdx.x / kOffloadXcds; i0 < n_items; i0 += kBlock * stride) {
         const long long mine = i0 + (long long)threadIdx.x * stride;
-        if (mine < n_items) hp_sh[threadIdx.x] = dv.dest[(size_t)(((int)mine >> 1) % dv.U) * dv.SN + ((int)mine >> 1) / dv.U];
+        if (mine < n_items) hp_sh[threadIdx.x] = dest[(size_t)(((int)mine >> 1) % dv.U) * dv.SN + ((int)mine >> 1) / dv.U];
         __syncthreads();
         for (int k = 0; k < kBlock && i0 + k * stride < n_items; ++k) {
             const int it = i0 + k * stride, val = it & 1, u = (it >> 1) % dv.U, f = f0 + (it >> 1) / dv.U;
@@ -1717,7 +1731,8 @@ __global__ __launch_bounds__(kBlock) void k_offload(DeviceView dv, int f0, int n
 // rate of a large DMA copy and costs one launch instead of one runtime call per
 // slab.  grid: a few dozen workgroups that share the (unit, page, keys | values) items.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_fetch(DeviceView dv, int u0, int n_units, int max_moves) {
+__global__ __launch_bounds__(kBlock) void k_fetch(const DeviceView *self, int u0, int n_units, int max_moves) {
+    const DeviceView dv = device_view(self);
     // items = (unit, move, keys | values), dealt round-robin to a SMALL fixed number of workgroups: the link
     // needs ~150 KB in flight, and workgroups parked on PCIe loads would otherwise hold the wave slots and
     // registers that the attention and selection kernels of the neighbouring layers are waiting for
@@ -1754,7 +1769,7 @@ template <typename F> hipError_t checked(F &&launch) {
 hipError_t launch_store_summary(const DeviceView &dv, const void *k_in, const void *v_in, int f0,
                                 int n_frames, bool beyond, const float *e_in, int n_emb, hipStream_t s) {
     const dim3 grid(dv.U, n_frames, n_emb > 0 ? 3 : 2);
-    auto go = [&](auto kern, auto *k) { kern<<<grid, kStoreBlock, 0, s>>>(dv, k, (decltype(k))v_in, f0, e_in, n_emb); };
+    auto go = [&](auto kern, auto *k) { kern<<<grid, kStoreBlock, 0, s>>>(dv.self, k, (decltype(k))v_in, f0, e_in, n_emb); };
     auto pick = [&](auto *k, auto d) {
         using E = std::remove_const_t<std::remove_pointer_t<decltype(k)>>;
         constexpr int D = decltype(d)::value;
@@ -1775,11 +1790,11 @@ hipError_t launch_ingest_one(const DeviceView &dv, const void *k_in, const void 
     dim3 grid(dv.U, 2);
     return checked([&] {
         if (dv.esize == 4) {
-            if (dv.D == 64) k_ingest_one<float, 64><<<grid, kOneBlock, 0, s>>>(dv, (const float *)k_in, (const float *)v_in, f);
-            else k_ingest_one<float, 128><<<grid, kOneBlock, 0, s>>>(dv, (const float *)k_in, (const float *)v_in, f);
+            if (dv.D == 64) k_ingest_one<float, 64><<<grid, kOneBlock, 0, s>>>(dv.self, (const float *)k_in, (const float *)v_in, f);
+            else k_ingest_one<float, 128><<<grid, kOneBlock, 0, s>>>(dv.self, (const float *)k_in, (const float *)v_in, f);
         } else {
-            if (dv.D == 64) k_ingest_one<unsigned short, 64><<<grid, kOneBlock, 0, s>>>(dv, (const unsigned short *)k_in, (const unsigned short *)v_in, f);
-            else k_ingest_one<unsigned short, 128><<<grid, kOneBlock, 0, s>>>(dv, (const unsigned short *)k_in, (const unsigned short *)v_in, f);
+            if (dv.D == 64) k_ingest_one<unsigned short, 64><<<grid, kOneBlock, 0, s>>>(dv.self, (const unsigned short *)k_in, (const unsigned short *)v_in, f);
+            else k_ingest_one<unsigned short, 128><<<grid, kOneBlock, 0, s>>>(dv.self, (const unsigned short *)k_in, (const unsigned short *)v_in, f);
         }
     });
 }
@@ -1787,23 +1802,23 @@ hipError_t launch_ingest_one(const DeviceView &dv, const void *k_in, const void 
 hipError_t launch_value_reps(const DeviceView &dv, int n_frames, hipStream_t s) {
     const dim3 grid(dv.U, dv.C);
     return checked([&] {
-        if (dv.D == 64) k_value_reps<64><<<grid, 128, 0, s>>>(dv, n_frames);
-        else k_value_reps<128><<<grid, 128, 0, s>>>(dv, n_frames);
+        if (dv.D == 64) k_value_reps<64><<<grid, 128, 0, s>>>(dv.self, n_frames);
+        else k_value_reps<128><<<grid, 128, 0, s>>>(dv.self, n_frames);
     });
 }
 
-hipError_t launch_gather_assign(const DeviceView &dv, int f0, int n, hipStream_t s) {
+hipError_t launch_gather_assign(const DeviceView &dv, int *rows, int f0, int n, hipStream_t s) {
     const dim3 grid(dv.U, std::min((n + kBlock - 1) / kBlock, 1024));
-    return checked([&] { k_gather_assign<<<grid, kBlock, 0, s>>>(dv, f0, n); });
+    return checked([&] { k_gather_assign<<<grid, kBlock, 0, s>>>(dv.self, rows, f0, n); });
 }
 
-hipError_t launch_offload(const DeviceView &dv, int f0, int n, hipStream_t s) {
+hipError_t launch_offload(const DeviceView &dv, const int *dest, int f0, int n, hipStream_t s) {
     // 16 working workgroups, all on one XCD (2 layers of 4 heads, 196-token pages, 16 frames a call, 512 frames, offloaded and
     // assigned: 10.9 ms with 16 workgroups spread over the XCDs, 9.3 with 16 on one, 10.4 with 16 on two; more
     // workgroups, or more loads in flight per thread, slow the staging and assignment kernels beside them).
     const long long items = (long long)dv.U * n * 2;
     const int blocks = (int)std::min<long long>(items, 16) * kOffloadXcds;
-    return checked([&] { k_offload<<<blocks, kBlock, 0, s>>>(dv, f0, n); });
+    return checked([&] { k_offload<<<blocks, kBlock, 0, s>>>(dv.self, dest, f0, n); });
 }
 
 hipError_t launch_fetch(const DeviceView &dv, int u0, int n_units, int max_moves, hipStream_t s) {
@@ -1812,26 +1827,26 @@ hipError_t launch_fetch(const DeviceView &dv, int u0, int n_units, int max_moves
     // decode step of 6.15 / 6.19 / 6.01 / 6.28 / 6.25 / 6.53 / 6.71 ms and 53.4 .. 55.2 GB/s over the link)
     const long long items = (long long)n_units * max_moves * 2;
     const int blocks = (int)std::min<long long>(items, 64);
-    return checked([&] { k_fetch<<<blocks, kBlock, 0, s>>>(dv, u0, n_units, max_moves); });
+    return checked([&] { k_fetch<<<blocks, kBlock, 0, s>>>(dv.self, u0, n_units, max_moves); });
 }
 
 hipError_t launch_assign_update(const DeviceView &dv, int f0, int f1, hipStream_t s) {
     return checked([&] {
         if (dv.maint_mode) {
-            if (dv.D == 64) k_assign_update<64, true><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
-            else k_assign_update<128, true><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
+            if (dv.D == 64) k_assign_update<64, true><<<dv.U, kBlock, 0, s>>>(dv.self, f0, f1);
+            else k_assign_update<128, true><<<dv.U, kBlock, 0, s>>>(dv.self, f0, f1);
         } else if (f1 - f0 <= kRegFrames && dv.C <= 128) {
-            if (dv.D == 64) k_assign_update_reg<64, 256><<<dv.U, 256, 0, s>>>(dv, f0, f1);
-            else k_assign_update_reg<128, 256><<<dv.U, 256, 0, s>>>(dv, f0, f1);
+            if (dv.D == 64) k_assign_update_reg<64, 256><<<dv.U, 256, 0, s>>>(dv.self, f0, f1);
+            else k_assign_update_reg<128, 256><<<dv.U, 256, 0, s>>>(dv.self, f0, f1);
         } else if (f1 - f0 <= kRegFrames && dv.C <= 256) {
-            if (dv.D == 64) k_assign_update_reg<64, 512><<<dv.U, 512, 0, s>>>(dv, f0, f1);
-            else k_assign_update_reg<128, 512><<<dv.U, 512, 0, s>>>(dv, f0, f1);
+            if (dv.D == 64) k_assign_update_reg<64, 512><<<dv.U, 512, 0, s>>>(dv.self, f0, f1);
+            else k_assign_update_reg<128, 512><<<dv.U, 512, 0, s>>>(dv.self, f0, f1);
         } else if (f1 - f0 <= 2 && dv.C > 256) {
-            if (dv.D == 64) k_assign_update<64, false><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
-            else k_assign_update<128, false><<<dv.U, kBlock, 0, s>>>(dv, f0, f1);
+            if (dv.D == 64) k_assign_update<64, false><<<dv.U, kBlock, 0, s>>>(dv.self, f0, f1);
+            else k_assign_update<128, false><<<dv.U, kBlock, 0, s>>>(dv.self, f0, f1);
         } else {
-            if (dv.D == 64) k_assign_chain<64><<<dv.U, kChainBlock, 0, s>>>(dv, f0, f1);
-            else k_assign_chain<128><<<dv.U, kChainBlock, 0, s>>>(dv, f0, f1);
+            if (dv.D == 64) k_assign_chain<64><<<dv.U, kChainBlock, 0, s>>>(dv.self, f0, f1);
+            else k_assign_chain<128><<<dv.U, kChainBlock, 0, s>>>(dv.self, f0, f1);
         }
     });
 }
@@ -1843,11 +1858,11 @@ hipError_t launch_lloyd(const DeviceView &dv, int n_frames, int iters, bool seed
         e = checked([&] {
             if (dv.P > 0) {
                 const dim3 gs(dv.U, (dv.C + 63) / 64);
-                if (dv.D == 64) k_lloyd_seed_nested<64><<<gs, kBlock, 0, s>>>(dv, n_frames);
-                else k_lloyd_seed_nested<128><<<gs, kBlock, 0, s>>>(dv, n_frames);
+                if (dv.D == 64) k_lloyd_seed_nested<64><<<gs, kBlock, 0, s>>>(dv.self, n_frames);
+                else k_lloyd_seed_nested<128><<<gs, kBlock, 0, s>>>(dv.self, n_frames);
             } else {
-                if (dv.D == 64) k_lloyd_seed<64><<<dv.U, kBlock, 0, s>>>(dv, n_frames);
-                else k_lloyd_seed<128><<<dv.U, kBlock, 0, s>>>(dv, n_frames);
+                if (dv.D == 64) k_lloyd_seed<64><<<dv.U, kBlock, 0, s>>>(dv.self, n_frames);
+                else k_lloyd_seed<128><<<dv.U, kBlock, 0, s>>>(dv.self, n_frames);
             }
         });
         if (e != hipSuccess) return e;
@@ -1859,7 +1874,7 @@ hipError_t launch_lloyd(const DeviceView &dv, int n_frames, int iters, bool seed
         e = checked([&] {
             const int per = it == 0 ? 64 : kLloydTest;
             const dim3 g(dv.U, (n_frames + per - 1) / per);
-            auto go = [&](auto kern) { kern<<<g, kBlock, 0, s>>>(dv, n_frames, it); };
+            auto go = [&](auto kern) { kern<<<g, kBlock, 0, s>>>(dv.self, n_frames, it); };
             auto pick = [&](auto d, auto later) {
                 constexpr int D = decltype(d)::value;
                 constexpr bool LATER = decltype(later)::value;
@@ -1875,16 +1890,16 @@ hipError_t launch_lloyd(const DeviceView &dv, int n_frames, int iters, bool seed
         });
         if (e != hipSuccess) return e;
         e = checked([&] {
-            if (dv.D == 64) k_lloyd_update<64><<<gu, 128, 0, s>>>(dv, n_frames, it);
-            else k_lloyd_update<128><<<gu, 128, 0, s>>>(dv, n_frames, it);
+            if (dv.D == 64) k_lloyd_update<64><<<gu, 128, 0, s>>>(dv.self, n_frames, it);
+            else k_lloyd_update<128><<<gu, 128, 0, s>>>(dv.self, n_frames, it);
         });
         if (e != hipSuccess) return e;
     }
     if (dv.maint_mode) {
         const dim3 gv(dv.U, dv.c_init);
         e = checked([&] {
-            if (dv.D == 64) k_exact_var<64><<<gv, kBlock, 0, s>>>(dv, n_frames);
-            else k_exact_var<128><<<gv, kBlock, 0, s>>>(dv, n_frames);
+            if (dv.D == 64) k_exact_var<64><<<gv, kBlock, 0, s>>>(dv.self, n_frames);
+            else k_exact_var<128><<<gv, kBlock, 0, s>>>(dv.self, n_frames);
         });
     }
     return e;
@@ -1893,8 +1908,8 @@ hipError_t launch_lloyd(const DeviceView &dv, int n_frames, int iters, bool seed
 hipError_t launch_partition_reps(const DeviceView &dv, int n_frames, hipStream_t s) {
     const dim3 g(dv.U, dv.P);
     return checked([&] {
-        if (dv.D == 64) k_partition_reps<64><<<g, 128, 0, s>>>(dv, n_frames);
-        else k_partition_reps<128><<<g, 128, 0, s>>>(dv, n_frames);
+        if (dv.D == 64) k_partition_reps<64><<<g, 128, 0, s>>>(dv.self, n_frames);
+        else k_partition_reps<128><<<g, 128, 0, s>>>(dv.self, n_frames);
     });
 }
 

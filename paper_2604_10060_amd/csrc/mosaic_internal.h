@@ -25,8 +25,22 @@ constexpr int kLloydGroups = 7;   // groups of representatives that a frame keep
 // A frame's K-means bounds, in units of 2^-14: its chord to its own representative from above, to the others of each group from below
 struct __attribute__((aligned(16))) ChordBounds { unsigned short ub, lb[kLloydGroups]; };
 
+// A pointer that the GPU loads from memory and uses as one to global memory (the compiler knows that of a kernel's arguments only)
+#ifdef __HIP_DEVICE_COMPILE__
+#define MOSAIC_GLOBAL __attribute__((address_space(1)))
+#else
+#define MOSAIC_GLOBAL
+#endif
+template <typename T> struct DevPtr {
+    MOSAIC_GLOBAL T *p;
+    DevPtr() = default;
+    __host__ __device__ __forceinline__ DevPtr(T *q) : p((MOSAIC_GLOBAL T *)q) {}
+    __host__ __device__ __forceinline__ operator T *() const { return (T *)p; }
+};
+
 // Device-side view of one context: plain pointers into the caller's arena.
-struct DeviceView {
+struct alignas(64) DeviceView {
+    const DeviceView *self;     // the copy of this struct that kernels read (in the arena)
     // geometry
     int L, Hq, Hkv, G, D, T, Tp, F, C, k, U;
     int esize;        // bytes per KV element
@@ -39,88 +53,118 @@ struct DeviceView {
     int tier;         // MOSAIC_TIER_*
     int PU;           // pages per unit in k_store / v_store: F (HBM tier) or the cluster-cache capacity (host tier)
     int SN;           // host tier: frames in the staging ring
+    int SC;           // score columns per unit: C + buf_max
     // KV pages the attention kernels read, addressed through k_page()/v_page() below: two arrays,
     //   k_store [U][PU] K pages, v_store [U][PU] V pages.
     // HBM tier: page p = frame id (arrival order).  Host tier: page p = a slot of the unit's GPU
     //   cluster cache (slots are handed out frame by frame; a cluster's frames need not be adjacent).
     // A K page is [T][D] or, for the bf16 MFMA path on stores of at most 768 MiB, in pieces of 32 channels, [D/32][T][32].
     //   A V page is [T][D] or, for the bf16 MFMA path, [Tp/32][D][32].
-    char *k_store;
-    char *v_store;
+    DevPtr<char> k_store;
+    DevPtr<char> v_store;
     size_t kpage, vpage;           // bytes of one K / V page
     size_t k_ustride, v_ustride;   // bytes between units, K array / V array
+    // latest selection per unit
+    DevPtr<double> scores;   // [U][SC]
+    DevPtr<int> ids;         // [U][k]
+    DevPtr<int> n_ids;       // [U]
+    DevPtr<int> sel_pages;   // [U][F]      frames of the selected clusters, gather order
+    DevPtr<int> n_sel;       // [U]         number of selected frames
+    // attention partials: entry e = base_slot(unit)*NT + tile*S(unit) + split, see split_slot()
+    DevPtr<float> part_o;    // [entries][16][D]
+    DevPtr<float> part_ml;   // [entries][3][16]  running max (log2 domain), sum of the weights the value contraction
+                      //                   used (bf16-rounded in the MFMA kernels), sum of the unrounded weights
+    int aug_reps, aug_window;       // retrieval augmentation (paper Sec. V-C); both 0 = off
+    // clustering state (decision arithmetic in fp64)
+    DevPtr<double> summ;     // [U][F][D]   per-frame key summaries
+    DevPtr<double> r;        // [U][C][D]   representatives
+    DevPtr<double> rnorm;    // [U][C]      |r_j|
+    DevPtr<int> n;           // [U][C]      sizes in frames
+    DevPtr<int> assign;      // [U][F]      frame -> cluster
+    DevPtr<int> pos;         // [U][F]      rank of the frame among its cluster's members (ascending frame order)
+    int maint_mode;          // self-adaptive maintainer (paper Sec. VI), 0 = off
+    int P, Cs, top_p;        // nested visual-semantic hierarchy (paper Sec. V-B, V-C); P = 0: flat index
+    // (what decode and questions read ends here: four lines of 64 bytes)
     // host tier: staging ring the ingest kernel writes (frame f at slot f % SN), and the
     // device-visible address of the pinned host pools the offload kernel writes
-    char *stage_k, *stage_v;   // [SN][U][page]
-    char *host_k, *host_v;     // pinned pools: [U][HP/SFh] slabs of [SFh K pages][SFh V pages]
+    DevPtr<char> stage_k, stage_v;   // [SN][U][page]
+    DevPtr<char> host_k, host_v;     // pinned pools: [U][HP/SFh] slabs of [SFh K pages][SFh V pages]
     size_t h_ustride, h_bstride;
     int SFh;                   // frames per host slab
     int HP;                    // host pages per unit
-    const int *dest;           // [U][SN] host page of each staged frame of the current batch (pinned memory)
-    int *batch_assign;         // [U][n] gathered assignments: a host-tier batch's (pinned memory), an observer's (scratch)
+    DevPtr<const int> dest;           // [2][U][SN] host page of each staged frame of a batch, two tables in turn (pinned memory)
+    DevPtr<int> batch_assign;         // [U][n] a host-tier batch's gathered assignments (pinned memory)
     // fetch work lists, written by the host into pinned memory and read by k_fetch over PCIe
-    const int *moves;          // [U][F][2] (host page, cache page)
-    const int *n_moves;        // [U]
-    // clustering state (decision arithmetic in fp64)
-    double *summ;     // [U][F][D]   per-frame key summaries
-    double *r;        // [U][C][D]   representatives
-    double *rnorm;    // [U][C]      |r_j|
-    int *n;           // [U][C]      sizes in frames
-    int *assign;      // [U][F]      frame -> cluster
-    int *pos;         // [U][F]      rank of the frame among its cluster's members (ascending frame order)
-    long long *sel_flag;   // [U]    (launch number << 32 | retrieved pages) of the unit's last selection published inside a launch (k_decode_layer)
-    int *sync_err;    // [1]         set if a bounded in-kernel wait ever ran out
-    int *lloyd_moved; // [U][3]      frames moved by the K-means rounds it-1, it, it+1 (mod 3): converged units skip the rest
-    int *lloyd_changed; // [U][C]    1 = a frame entered or left the cluster in the current round (its sums must be rebuilt)
-    double *lloyd_delta; // [U][C]   chord by which the last update moved the representative's direction
-    ChordBounds *lloyd_bounds; // [U][F]
-    // self-adaptive maintainer (paper Sec. VI); maint_mode 0 = off (the arrays are then empty)
-    int maint_mode, c_init, split_iters, buf_max;
-    int SC;           // score columns per unit: C + buf_max
+    DevPtr<const int> moves;          // [U][F][2] (host page, cache page)
+    DevPtr<const int> n_moves;        // [U]
+    DevPtr<long long> sel_flag;   // [U]    (launch number << 32 | retrieved pages) of the unit's last selection published inside a launch (k_decode_layer)
+    DevPtr<int> sync_err;    // [1]         set if a bounded in-kernel wait ever ran out
+    DevPtr<int> lloyd_moved; // [U][3]      frames moved by the K-means rounds it-1, it, it+1 (mod 3): converged units skip the rest
+    DevPtr<int> lloyd_changed; // [U][C]    1 = a frame entered or left the cluster in the current round (its sums must be rebuilt)
+    DevPtr<double> lloyd_delta; // [U][C]   chord by which the last update moved the representative's direction
+    DevPtr<ChordBounds> lloyd_bounds; // [U][F]
+    // self-adaptive maintainer (paper Sec. VI; empty arrays when it is off)
+    int c_init, split_iters, buf_max;
     double tau_min, tau_max, tau_n0;
-    double *var;      // [U][C]      running intra-cluster variance (Eq. 2 / Eq. 4)
-    int *lazy;        // [U][C]      lazy-split flag
-    int *resident;    // [U][C]      1 = selected by the unit's latest retrieval
-    int *n_slots;     // [U]         cluster ids in use: [0, n_slots)
-    int *buf_frame;   // [U][buf_max] buffered singletons: frame
-    int *buf_owner;   // [U][buf_max]                       cluster they were assigned to
-    int *n_buf;       // [U]
-    long long *mt_cnt;// [U][4]      splits on insertion, deferred splits, buffered inserts, forced absorbs
-    int *mt_mem, *mt_side;   // [U][F] scratch of Split
-    double *mt_nrm;          // [U][F]
-    // retrieval augmentation (paper Sec. V-C); both 0 = off
-    int aug_reps, aug_window, nt_max;
-    double *vsumm;    // [U][F][D]   per-frame value summaries (mean of the frame's T value vectors)
-    double *rvsum;    // [U][C][D]   per-cluster sums of them (value representative = rvsum / n)
-    float *rep_k, *rep_v;   // [U][C][D] fp32 pseudo-token tables: representative, value representative
-    float *aug_o;     // [U][nt_max][16][D]  partial of the representatives' part, same form as part_o
-    float *aug_ml;    // [U][nt_max][2][16]
-    // nested visual-semantic hierarchy (paper Sec. V-B, V-C); P = 0: flat index
-    int P, Cs, Dv, top_p;
-    double *vemb;     // [F][Dv]     visual embeddings of the frames (the visual level's states)
-    double *vr;       // [P][Dv]     visual centroids
-    double *vrn;      // [P]         their norms
-    int *vn;          // [P]         their sizes in frames
-    int *part;        // [F]         frame -> visual partition (shared by all units)
-    double *pr;       // [U][P][D]   partition representatives in the unit's key space
-    double *prn;      // [U][P]
-    int *pn;          // [U][P]
-    double *pscores;  // [U][P]      first-stage scores of the latest retrieval
-    int *pids;        // [U][top_p]  partitions it kept
-    int *n_pids;      // [U]
-    // latest selection per unit
-    double *scores;   // [U][SC]
-    int *ids;         // [U][k]
-    int *n_ids;       // [U]
-    int *sel_pages;   // [U][F]      frames of the selected clusters, gather order
-    int *n_sel;       // [U]         number of selected frames
-    int *tok_scratch; // [Hkv][F*T]  token-index expansion for the observer
-    // attention partials: entry e = base_slot(unit)*NT + tile*S(unit) + split, see split_slot()
-    float *part_o;    // [entries][16][D]
-    float *part_ml;   // [entries][3][16]  running max (log2 domain), sum of the weights the value contraction
-                      //                   used (bf16-rounded in the MFMA kernels), sum of the unrounded weights
+    DevPtr<double> var;      // [U][C]      running intra-cluster variance (Eq. 2 / Eq. 4)
+    DevPtr<int> lazy;        // [U][C]      lazy-split flag
+    DevPtr<int> resident;    // [U][C]      1 = selected by the unit's latest retrieval
+    DevPtr<int> n_slots;     // [U]         cluster ids in use: [0, n_slots)
+    DevPtr<int> buf_frame;   // [U][buf_max] buffered singletons: frame
+    DevPtr<int> buf_owner;   // [U][buf_max]                       cluster they were assigned to
+    DevPtr<int> n_buf;       // [U]
+    DevPtr<long long> mt_cnt;// [U][4]      splits on insertion, deferred splits, buffered inserts, forced absorbs
+    DevPtr<int> mt_mem, mt_side;   // [U][F] scratch of Split
+    DevPtr<double> mt_nrm;          // [U][F]
+    // retrieval augmentation (paper Sec. V-C)
+    int nt_max;
+    DevPtr<double> vsumm;    // [U][F][D]   per-frame value summaries (mean of the frame's T value vectors)
+    DevPtr<double> rvsum;    // [U][C][D]   per-cluster sums of them (value representative = rvsum / n)
+    DevPtr<float> rep_k, rep_v;   // [U][C][D] fp32 pseudo-token tables: representative, value representative
+    DevPtr<float> aug_o;     // [U][nt_max][16][D]  partial of the representatives' part, same form as part_o
+    DevPtr<float> aug_ml;    // [U][nt_max][2][16]
+    // nested visual-semantic hierarchy (paper Sec. V-B, V-C)
+    int Dv;
+    DevPtr<double> vemb;     // [F][Dv]     visual embeddings of the frames (the visual level's states)
+    DevPtr<double> vr;       // [P][Dv]     visual centroids
+    DevPtr<double> vrn;      // [P]         their norms
+    DevPtr<int> vn;          // [P]         their sizes in frames
+    DevPtr<int> part;        // [F]         frame -> visual partition (shared by all units)
+    DevPtr<double> pr;       // [U][P][D]   partition representatives in the unit's key space
+    DevPtr<double> prn;      // [U][P]
+    DevPtr<int> pn;          // [U][P]
+    DevPtr<double> pscores;  // [U][P]      first-stage scores of the latest retrieval
+    DevPtr<int> pids;        // [U][top_p]  partitions it kept
+    DevPtr<int> n_pids;      // [U]
+    DevPtr<int> tok_scratch; // [Hkv][F*T]  token-index expansion for the observer
     long long part_entries;
 };
+
+static_assert(sizeof(DeviceView) % 8 == 0, "loaded by words");
+
+static_assert(offsetof(DeviceView, tier) == 64 && offsetof(DeviceView, scores) == 128 && offsetof(DeviceView, summ) == 192 &&
+              offsetof(DeviceView, stage_k) == 256 && offsetof(DeviceView, nt_max) / 64 == 8 && offsetof(DeviceView, aug_ml) / 64 == 8, "lines of what decode reads");
+
+// A kernel's view: the fields that it uses, by scalar loads.  A launch carries the address, which lies in registers when a wavefront starts (the build asks
+// for that).  With the struct itself as an argument a launch of a few us is longer by 0.2 us and more, and so is the way to it: a token through 28 layers
+// (84 launches) 846 -> 828 us, four fp32 layers 95.7 -> 92.5, 768 frames one by one (784 launches) 5.20 -> 4.95 ms.
+// LINES of it are fetched at once: the compiler loads a field where it is first used, which is one more trip to the L2 on a kernel's chain.
+template <int... LINES>
+__device__ __forceinline__ DeviceView device_view(const DeviceView *self) {
+    typedef __attribute__((address_space(4))) const unsigned long long Word;
+    constexpr int N = sizeof(DeviceView) / 8;
+    const Word *w = (const Word *)(unsigned long long)self;
+    unsigned long long a[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) a[i] = w[i];
+    if constexpr (sizeof...(LINES) > 0) {
+        const unsigned long long t = (0 | ... | a[LINES * 8]);
+        asm volatile("" ::"s"(t));
+    }
+    DeviceView v;
+    __builtin_memcpy(&v, a, sizeof v);
+    return v;
+}
 
 struct HostTier;   // host_tier.hip
 constexpr int kReadPieces = 4;      // pinned pieces that large read-backs go through
@@ -196,10 +240,10 @@ hipError_t launch_retrieve(const DeviceView &dv, int u0, int n_units, const void
 // deferred-split maintainer: singletons take part, residency and deferred splits follow the selection
 hipError_t launch_retrieve_deferred(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                                     int n_frames, int score_mode, hipStream_t s);
-// the assignments of frames f0..f0+n-1 of every unit to dv.batch_assign, [U][n]
-hipError_t launch_gather_assign(const DeviceView &dv, int f0, int n, hipStream_t s);
+// the assignments of frames f0..f0+n-1 of every unit to rows, [U][n]
+hipError_t launch_gather_assign(const DeviceView &dv, int *rows, int f0, int n, hipStream_t s);
 // host tier: copy staged frames f0..f0+n-1 of every unit to host page dest[u][f - f0]
-hipError_t launch_offload(const DeviceView &dv, int f0, int n, hipStream_t s);
+hipError_t launch_offload(const DeviceView &dv, const int *dest, int f0, int n, hipStream_t s);
 // host tier: move the pages listed in moves[u0..u0+n_units) from the pinned slabs into the cache
 hipError_t launch_fetch(const DeviceView &dv, int u0, int n_units, int max_moves, hipStream_t s);
 hipError_t launch_expand_tok_idx(const DeviceView &dv, int u0, int n_units, hipStream_t s);

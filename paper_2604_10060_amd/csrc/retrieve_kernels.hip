@@ -98,7 +98,8 @@ __device__ __forceinline__ void mean_query_partials(const E *q, int lc, int h, i
 // its 22.9 (256 tokens, 7 heads a unit, 4 units, bf16); here they take 4.8, and k_retrieve 13.1.
 constexpr int kMeanBlock = 256, kMeanRows = 128;
 template <typename E, int D>
-__global__ __launch_bounds__(kMeanBlock) void k_mean_query(DeviceView dv, int u0, const E *q, int Tq) {
+__global__ __launch_bounds__(kMeanBlock) void k_mean_query(const DeviceView *self, int u0, const E *q, int Tq) {
+    const DeviceView dv = device_view(self);
     const int uc = blockIdx.x, u = u0 + uc, tid = threadIdx.x, row0 = blockIdx.y * kMeanRows;
     __shared__ double wpart[kMeanBlock / 64][D];
     mean_query_partials<E, D, kMeanBlock>(q, uc / dv.Hkv, u % dv.Hkv, Tq, dv.G, dv.Hq, row0, min(Tq * dv.G, row0 + kMeanRows), wpart);
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(kMeanBlock) void k_mean_query(DeviceView dv, int u0
         double a = 0.0;
 #pragma unroll
         for (int w = 0; w < kMeanBlock / 64; ++w) a += wpart[w][tid];
-        reinterpret_cast<double *>(dv.part_o)[((size_t)uc * gridDim.y + blockIdx.y) * D + tid] = a;
+        reinterpret_cast<double *>((float *)dv.part_o)[((size_t)uc * gridDim.y + blockIdx.y) * D + tid] = a;
     }
 }
 
@@ -125,9 +126,11 @@ int mean_query_parts(const DeviceView &dv, int n_units, int Tq) {
 // NESTED (paper Sec. V-C "Two-Stage Retrieval"): the mean query is first scored against the
 // unit's P partition representatives; only the clusters of the top_p best partitions are then
 // scored (the rest count as empty: their rows are never read) and ranked.
-template <typename E, int D, bool NESTED>
-__global__ __launch_bounds__(kRetrBlock) void k_retrieve(DeviceView dv, int u0, const E *q, int Tq,
-                                                         int n_frames, int score_mode, int mean_parts, bool write_pages) {
+// SUMMED: k_mean_query has summed the question's rows (kernels of their own: an argument and a branch more cost each of decode's launches 0.3 us).
+template <typename E, int D, bool NESTED, bool SUMMED>
+__global__ __launch_bounds__(kRetrBlock) void k_retrieve(const DeviceView *self, int u0, const E *q, int Tq,
+                                                         int n_frames, int score_mode, bool write_pages) {
+    const DeviceView dv = device_view<0, 2, 3>(self);
     constexpr int BLK = kRetrBlock;
     constexpr int EPL = D / 16;        // doubles per lane in a 16-lane row group
     constexpr int RPP = BLK / 16;      // representative rows per pass
@@ -227,9 +230,10 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve(DeviceView dv, int u0, 
         if (tid < C) { n_sh[tid] = n_reg; rn_sh[tid] = rn_reg; cnt_sh[tid] = 0; wcnt_sh[tid] = 0; }
         __syncthreads();
         if (wa >= 0) atomicAdd(&wcnt_sh[wa], 1);         // (read after the scores' barrier at the earliest)
-    } else if (mean_parts > 0) {            // (k_mean_query has summed the rows)
+    } else if (SUMMED) {
         if (tid < D) {
-            const double *qb = reinterpret_cast<const double *>(dv.part_o) + (size_t)uc * mean_parts * D + tid;
+            const int mean_parts = (R + kMeanRows - 1) / kMeanRows;
+            const double *qb = reinterpret_cast<const double *>((const float *)dv.part_o) + (size_t)uc * mean_parts * D + tid;
             double acc = 0.0;
             for (int p0 = 0; p0 < mean_parts; p0 += 16) {
                 double v[16];
@@ -410,8 +414,9 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve(DeviceView dv, int u0, 
 // in selection order.  grid (n_units), kRetrBlock threads; C + buf_max <= 1024.
 // ---------------------------------------------------------------------------
 template <typename E, int D>
-__global__ __launch_bounds__(kRetrBlock) void k_retrieve_deferred(DeviceView dv, int u0, const E *q, int Tq,
+__global__ __launch_bounds__(kRetrBlock) void k_retrieve_deferred(const DeviceView *self, int u0, const E *q, int Tq,
                                                                   int n_frames, int score_mode) {
+    const DeviceView dv = device_view(self);
     constexpr int BLK = kRetrBlock;
     constexpr int EPL = D / 16, RPP = BLK / 16;
     const int uc = blockIdx.x, u = u0 + uc, tid = threadIdx.x;
@@ -527,7 +532,8 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve_deferred(DeviceView dv,
 }
 
 // Token-index expansion of the page lists (observer only).  grid (n_units).
-__global__ __launch_bounds__(kBlock) void k_expand_tok_idx(DeviceView dv, int u0) {
+__global__ __launch_bounds__(kBlock) void k_expand_tok_idx(const DeviceView *self, int u0) {
+    const DeviceView dv = device_view(self);
     const int uc = blockIdx.x, u = u0 + uc, T = dv.T;
     const long long total = (long long)dv.n_sel[u] * T;
     const int *sel = dv.sel_pages + (size_t)u * dv.F;
@@ -542,22 +548,18 @@ template <bool NESTED>
 static void launch_retrieve_t(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                               int n_frames, int score_mode, bool write_pages, hipStream_t s) {
     const int parts = mean_query_parts(dv, n_units, Tq);
-    if (parts > 0) {
-        auto sums = [&](auto kern, auto *qq) { kern<<<dim3(n_units, parts), kMeanBlock, 0, s>>>(dv, u0, qq, Tq); };
-        if (dv.esize == 4) {
-            if (dv.D == 64) sums(k_mean_query<float, 64>, (const float *)q);
-            else sums(k_mean_query<float, 128>, (const float *)q);
-        } else {
-            if (dv.D == 64) sums(k_mean_query<unsigned short, 64>, (const unsigned short *)q);
-            else sums(k_mean_query<unsigned short, 128>, (const unsigned short *)q);
-        }
-    }
+    auto run = [&](auto sums, auto summed, auto kern, auto *qq) {
+        if (parts > 0) sums<<<dim3(n_units, parts), kMeanBlock, 0, s>>>(dv.self, u0, qq, Tq);
+        (parts > 0 ? summed : kern)<<<n_units, kRetrBlock, 0, s>>>(dv.self, u0, qq, Tq, n_frames, score_mode, write_pages);
+    };
     if (dv.esize == 4) {
-        if (dv.D == 64) k_retrieve<float, 64, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const float *)q, Tq, n_frames, score_mode, parts, write_pages);
-        else k_retrieve<float, 128, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const float *)q, Tq, n_frames, score_mode, parts, write_pages);
+        const float *qq = (const float *)q;
+        if (dv.D == 64) run(k_mean_query<float, 64>, k_retrieve<float, 64, NESTED, true>, k_retrieve<float, 64, NESTED, false>, qq);
+        else run(k_mean_query<float, 128>, k_retrieve<float, 128, NESTED, true>, k_retrieve<float, 128, NESTED, false>, qq);
     } else {
-        if (dv.D == 64) k_retrieve<unsigned short, 64, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const unsigned short *)q, Tq, n_frames, score_mode, parts, write_pages);
-        else k_retrieve<unsigned short, 128, NESTED><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const unsigned short *)q, Tq, n_frames, score_mode, parts, write_pages);
+        const unsigned short *qq = (const unsigned short *)q;
+        if (dv.D == 64) run(k_mean_query<unsigned short, 64>, k_retrieve<unsigned short, 64, NESTED, true>, k_retrieve<unsigned short, 64, NESTED, false>, qq);
+        else run(k_mean_query<unsigned short, 128>, k_retrieve<unsigned short, 128, NESTED, true>, k_retrieve<unsigned short, 128, NESTED, false>, qq);
     }
 }
 
@@ -571,17 +573,17 @@ hipError_t launch_retrieve(const DeviceView &dv, int u0, int n_units, const void
 hipError_t launch_retrieve_deferred(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                                     int n_frames, int score_mode, hipStream_t s) {
     if (dv.esize == 4) {
-        if (dv.D == 64) k_retrieve_deferred<float, 64><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const float *)q, Tq, n_frames, score_mode);
-        else k_retrieve_deferred<float, 128><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const float *)q, Tq, n_frames, score_mode);
+        if (dv.D == 64) k_retrieve_deferred<float, 64><<<n_units, kRetrBlock, 0, s>>>(dv.self, u0, (const float *)q, Tq, n_frames, score_mode);
+        else k_retrieve_deferred<float, 128><<<n_units, kRetrBlock, 0, s>>>(dv.self, u0, (const float *)q, Tq, n_frames, score_mode);
     } else {
-        if (dv.D == 64) k_retrieve_deferred<unsigned short, 64><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const unsigned short *)q, Tq, n_frames, score_mode);
-        else k_retrieve_deferred<unsigned short, 128><<<n_units, kRetrBlock, 0, s>>>(dv, u0, (const unsigned short *)q, Tq, n_frames, score_mode);
+        if (dv.D == 64) k_retrieve_deferred<unsigned short, 64><<<n_units, kRetrBlock, 0, s>>>(dv.self, u0, (const unsigned short *)q, Tq, n_frames, score_mode);
+        else k_retrieve_deferred<unsigned short, 128><<<n_units, kRetrBlock, 0, s>>>(dv.self, u0, (const unsigned short *)q, Tq, n_frames, score_mode);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_expand_tok_idx(const DeviceView &dv, int u0, int n_units, hipStream_t s) {
-    k_expand_tok_idx<<<n_units, kBlock, 0, s>>>(dv, u0);
+    k_expand_tok_idx<<<n_units, kBlock, 0, s>>>(dv.self, u0);
     return hipGetLastError();
 }
 

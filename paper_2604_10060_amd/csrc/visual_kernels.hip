@@ -119,7 +119,8 @@ __device__ __forceinline__ double visual_norm(const DeviceView &dv, int p) {
 //   k_visual_lloyd_update  grid (P, 4), 256 threads: members listed, then summed in ascending frame order with 32 loads in flight
 //                          (159 us with a test per frame and channel, 38 with a workgroup of 1024 per centroid, whose CU takes in
 //                          what it can, now 17)
-__global__ __launch_bounds__(kVisBlock) void k_visual_seed(DeviceView dv, int W) {
+__global__ __launch_bounds__(kVisBlock) void k_visual_seed(const DeviceView *self, int W) {
+    const DeviceView dv = device_view(self);
     const int tid = threadIdx.x, p = blockIdx.x, Dv = dv.Dv;
     const double *src = dv.vemb + (size_t)(((long long)p * W) / dv.P) * Dv;
     double sq = 0.0;
@@ -130,12 +131,14 @@ __global__ __launch_bounds__(kVisBlock) void k_visual_seed(DeviceView dv, int W)
 }
 
 // the norms of all centroids from their parts.  grid (1), 64 threads
-__global__ __launch_bounds__(64) void k_visual_norms(DeviceView dv) {
+__global__ __launch_bounds__(64) void k_visual_norms(const DeviceView *self) {
+    const DeviceView dv = device_view(self);
     if ((int)threadIdx.x < dv.P) dv.vrn[threadIdx.x] = visual_norm(dv, threadIdx.x);
 }
 
 template <bool VEC, int TILES>
-__global__ __launch_bounds__(256) void k_visual_lloyd_assign(DeviceView dv, int W, int live_all) {
+__global__ __launch_bounds__(256) void k_visual_lloyd_assign(const DeviceView *self, int W, int live_all) {
+    const DeviceView dv = device_view(self);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, P = dv.P, Dv = dv.Dv;
     const int f0 = blockIdx.x * 16, nf = min(16, W - f0);
     __shared__ double sim_sh[4][16][64];
@@ -162,7 +165,8 @@ __global__ __launch_bounds__(256) void k_visual_lloyd_assign(DeviceView dv, int 
 }
 
 constexpr int kVisUpdate = 256;             // threads; workgroup y has channels 256 y .. 256 y + 255, and those 1024, 2048, 3072 further on
-__global__ __launch_bounds__(kVisUpdate) void k_visual_lloyd_update(DeviceView dv, int W) {
+__global__ __launch_bounds__(kVisUpdate) void k_visual_lloyd_update(const DeviceView *self, int W) {
+    const DeviceView dv = device_view(self);
     constexpr int CH = kVisUpdate * kListPer;
     const int tid = threadIdx.x, p = blockIdx.x, Dv = dv.Dv, c = blockIdx.y * kVisUpdate + tid;
     __shared__ int mem[CH];
@@ -496,7 +500,8 @@ __device__ __forceinline__ void visual_assign(const DeviceView &dv, const float 
     }
 }
 
-__global__ __launch_bounds__(kVisAssign, 2) void k_visual_assign(DeviceView dv, const float *e_in, int f0, int f1) {
+__global__ __launch_bounds__(kVisAssign, 2) void k_visual_assign(const DeviceView *self, const float *e_in, int f0, int f1) {
+    const DeviceView dv = device_view(self);
     __shared__ VisualShared sh;
     visual_assign(dv, e_in, f0, f1, sh);
 }
@@ -504,8 +509,9 @@ __global__ __launch_bounds__(kVisAssign, 2) void k_visual_assign(DeviceView dv, 
 // The page stores of the same frames beside it (the visual level reads nothing that they write): grid (1 + 2 U n), workgroup 0 the visual
 // level, the others a page each.  (16 frames, 4 layers of 4 heads, T = 64: 5.4 + 25.2 us in two launches, now 21.6; of 28 layers of 4 heads a call of 16 frames, assignment included, 65.3 -> 51.7.)
 template <typename E, int D>
-__global__ __launch_bounds__(kVisAssign, 2) void k_store_visual_assign(DeviceView dv, const E *k_in, const E *v_in, const float *e_in, int f0, int f1,
+__global__ __launch_bounds__(kVisAssign, 2) void k_store_visual_assign(const DeviceView *self, const E *k_in, const E *v_in, const float *e_in, int f0, int f1,
                                                                        int beyond) {
+    const DeviceView dv = device_view(self);
     static_assert(kStoreBlock == kVisAssign, "one workgroup size");
     __shared__ union { VisualShared visual; StoreShared<D> store; } sh;
     if (blockIdx.x == 0) {
@@ -525,7 +531,8 @@ __global__ __launch_bounds__(kVisAssign, 2) void k_store_visual_assign(DeviceVie
 // The same for calls of at most kVisFew frames, all of them in turn.  The chunk form's products, reductions and check cost 4
 // us more for one frame (P = 10, Dv = 512, C = 120, whole call 16.6 against 12.2 us).
 constexpr int kVisFew = 2;
-__global__ __launch_bounds__(kVisAssign) void k_visual_assign_few(DeviceView dv, const float *e_in, int f0, int f1) {
+__global__ __launch_bounds__(kVisAssign) void k_visual_assign_few(const DeviceView *self, const float *e_in, int f0, int f1) {
+    const DeviceView dv = device_view(self);
     __shared__ VisualTurnShared sh;
     for (int f = f0; f < f1; ++f) {
         if (f > f0) __syncthreads();
@@ -540,10 +547,10 @@ hipError_t after_launch() {
 } // namespace
 
 hipError_t launch_visual_lloyd(const DeviceView &dv, int W, int iters, hipStream_t s) {
-    k_visual_seed<<<dv.P, kVisBlock, 0, s>>>(dv, W);
+    k_visual_seed<<<dv.P, kVisBlock, 0, s>>>(dv.self, W);
     hipError_t e = after_launch();
     for (int it = 0; it < iters && e == hipSuccess; ++it) {
-        auto go = [&](auto kern) { kern<<<(W + 15) / 16, 256, 0, s>>>(dv, W, it == 0); };
+        auto go = [&](auto kern) { kern<<<(W + 15) / 16, 256, 0, s>>>(dv.self, W, it == 0); };
         auto by_tiles = [&](auto vec) {
             constexpr bool VEC = decltype(vec)::value;
             if (dv.P <= 16) go(k_visual_lloyd_assign<VEC, 1>);
@@ -553,19 +560,19 @@ hipError_t launch_visual_lloyd(const DeviceView &dv, int W, int iters, hipStream
         if (dv.Dv % 4 == 0) by_tiles(std::true_type{});
         else by_tiles(std::false_type{});
         if ((e = after_launch()) != hipSuccess) break;
-        k_visual_lloyd_update<<<dim3(dv.P, kVisBlock / kVisUpdate), kVisUpdate, 0, s>>>(dv, W);
+        k_visual_lloyd_update<<<dim3(dv.P, kVisBlock / kVisUpdate), kVisUpdate, 0, s>>>(dv.self, W);
         e = after_launch();
     }
     if (e == hipSuccess) {
-        k_visual_norms<<<1, 64, 0, s>>>(dv);
+        k_visual_norms<<<1, 64, 0, s>>>(dv.self);
         e = after_launch();
     }
     return e;
 }
 
 hipError_t launch_visual_assign(const DeviceView &dv, const float *e_in, int f0, int f1, hipStream_t s) {
-    if (f1 - f0 <= kVisFew) k_visual_assign_few<<<1, kVisAssign, 0, s>>>(dv, e_in, f0, f1);
-    else k_visual_assign<<<1, kVisAssign, 0, s>>>(dv, e_in, f0, f1);
+    if (f1 - f0 <= kVisFew) k_visual_assign_few<<<1, kVisAssign, 0, s>>>(dv.self, e_in, f0, f1);
+    else k_visual_assign<<<1, kVisAssign, 0, s>>>(dv.self, e_in, f0, f1);
     return after_launch();
 }
 
@@ -576,7 +583,7 @@ bool store_visual_assign_takes(const DeviceView &dv, int n_frames) {
 hipError_t launch_store_visual_assign(const DeviceView &dv, const void *k_in, const void *v_in, const float *e_in, int f0, int f1, bool beyond,
                                       hipStream_t s) {
     const int grid = 1 + 2 * dv.U * (f1 - f0);
-    auto go = [&](auto kern, auto *k) { kern<<<grid, kVisAssign, 0, s>>>(dv, k, (decltype(k))v_in, e_in, f0, f1, beyond); };
+    auto go = [&](auto kern, auto *k) { kern<<<grid, kVisAssign, 0, s>>>(dv.self, k, (decltype(k))v_in, e_in, f0, f1, beyond); };
     if (dv.esize == 4) {
         if (dv.D == 64) go(k_store_visual_assign<float, 64>, (const float *)k_in);
         else go(k_store_visual_assign<float, 128>, (const float *)k_in);
