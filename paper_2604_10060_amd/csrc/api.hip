@@ -70,7 +70,8 @@ struct Layout {
     int c_init, split_iters, buf_max, W;   // maintainer (c_init = C, buf_max = 0 when off); warm-up frames
     // host tier geometry
     int SF, slabs_per_unit, HP, PU, SN, max_clusters;
-    size_t kpage, vpage;
+    size_t kpage, vpage, hvpage;
+    int htail;
 };
 
 // resolved defaults of the maintainer fields and of the warm-up length
@@ -159,6 +160,9 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
     L.nt_max = (int)nt_max;
     L.kpage = T * D * e;
     L.vpage = D * (L.v_transposed ? (size_t)L.Tp : T) * e;
+    // host pools: the last block of a V page in units of 4 tokens, if that is less than the block
+    L.htail = L.v_transposed && (T % 32 + 3) / 4 < 8 ? (int)(T % 32 + 3) / 4 : 0;
+    L.hvpage = L.htail ? D * (T / 32 * 32 + (size_t)L.htail * 4) * e : L.vpage;
     const bool host = c.tier == MOSAIC_TIER_HOST;
     L.PU = (int)F; L.SN = 1;
     if (host) {
@@ -251,7 +255,7 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
     L.host_k = 0;
     L.host_v = host ? (size_t)L.SF * L.kpage : 0;     // inside the first slab: [SF K pages][SF V pages]
     if (host) {
-        size_t ho = align_up(U * (size_t)L.HP * (L.kpage + L.vpage));
+        size_t ho = align_up(U * (size_t)L.HP * (L.kpage + L.hvpage));
         auto htake = [&](size_t bytes) { size_t o = ho; ho = align_up(ho + bytes); return o; };
         L.host_sel = htake(U * F * 4);      // page lists on their way to the device
         L.host_nsel = htake(U * 4);
@@ -504,10 +508,10 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
     dv.kpage = L.kpage; dv.vpage = L.vpage;
     dv.k_ustride = (size_t)L.PU * L.kpage;
     dv.v_ustride = (size_t)L.PU * L.vpage;
-    dv.SFh = 1; dv.h_bstride = dv.h_ustride = 0;
+    dv.SFh = 1; dv.h_bstride = dv.h_ustride = 0; dv.hvpage = L.hvpage; dv.htail = L.htail;
     if (cfg->tier == MOSAIC_TIER_HOST) {
         dv.SFh = L.SF;
-        dv.h_bstride = (size_t)L.SF * (L.kpage + L.vpage);
+        dv.h_bstride = (size_t)L.SF * (L.kpage + L.hvpage);
         dv.h_ustride = (size_t)L.slabs_per_unit * dv.h_bstride;
     }
     dv.stage_k = base + L.stage_k; dv.stage_v = base + L.stage_v; dv.dest = nullptr; dv.batch_assign = nullptr;

@@ -1712,13 +1712,21 @@ __global__ __launch_bounds__(kBlock) void k_offload(const DeviceView *self, cons
         __syncthreads();
         for (int k = 0; k < kBlock && i0 + k * stride < n_items; ++k) {
             const int it = i0 + k * stride, val = it & 1, u = (it >> 1) % dv.U, f = f0 + (it >> 1) / dv.U;
-            const size_t bytes = val ? dv.vpage : dv.kpage;
+            const size_t bytes = val ? dv.vpage : dv.kpage, hbytes = val ? dv.hvpage : dv.kpage;
             const size_t spage = (size_t)(f % dv.SN) * dv.U + u;
             const int hp = hp_sh[k];                           // page within the unit's host pool
-            const size_t hoff = (size_t)u * dv.h_ustride + (size_t)(hp / dv.SFh) * dv.h_bstride + (size_t)(hp % dv.SFh) * bytes;
+            const size_t hoff = (size_t)u * dv.h_ustride + (size_t)(hp / dv.SFh) * dv.h_bstride + (size_t)(hp % dv.SFh) * hbytes;
             const uint4 *src = reinterpret_cast<const uint4 *>((val ? dv.stage_v : dv.stage_k) + spage * bytes);
             uint4 *dst = reinterpret_cast<uint4 *>((val ? dv.host_v : dv.host_k) + hoff);
-            for (size_t i = threadIdx.x; i < bytes / 16; i += kBlock) dst[i] = src[i];
+            const int tail = val ? dv.htail : 0;
+            const size_t n16 = (hbytes - (size_t)dv.D * tail * 8) / 16;
+            for (size_t i = threadIdx.x; i < n16; i += kBlock) dst[i] = src[i];
+            // (the last block: the first units of 8 bytes of each channel's 64, two units a store)
+            const uint2 *s2 = reinterpret_cast<const uint2 *>(src + n16);
+            for (int i = threadIdx.x; i < dv.D * tail / 2; i += kBlock) {
+                const uint2 a = s2[2 * i / tail * 8 + 2 * i % tail], b = s2[(2 * i + 1) / tail * 8 + (2 * i + 1) % tail];
+                dst[n16 + i] = make_uint4(a.x, a.y, b.x, b.y);
+            }
         }
         __syncthreads();
     }
@@ -1741,13 +1749,25 @@ __global__ __launch_bounds__(kBlock) void k_fetch(const DeviceView *self, int u0
         const int val = it & 1, i = (it >> 1) % max_moves, u = u0 + (it >> 1) / max_moves;
         if (i >= dv.n_moves[u]) continue;                                   // block-uniform
         const int hp = dv.moves[((size_t)u * dv.F + i) * 2], cp = dv.moves[((size_t)u * dv.F + i) * 2 + 1];
-        const size_t bytes = val ? dv.vpage : dv.kpage;
+        const size_t bytes = val ? dv.vpage : dv.kpage, hbytes = val ? dv.hvpage : dv.kpage;
         const char *src = (val ? dv.host_v : dv.host_k) + (size_t)u * dv.h_ustride +
-                          (size_t)(hp / dv.SFh) * dv.h_bstride + (size_t)(hp % dv.SFh) * bytes;
+                          (size_t)(hp / dv.SFh) * dv.h_bstride + (size_t)(hp % dv.SFh) * hbytes;
         char *dst = (val ? dv.v_store + (size_t)u * dv.v_ustride : dv.k_store + (size_t)u * dv.k_ustride) + (size_t)cp * bytes;
         const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
         uint4 *d4 = reinterpret_cast<uint4 *>(dst);
-        const size_t n16 = bytes / 16;
+        const int tail = val ? dv.htail : 0;
+        const size_t n16 = (hbytes - (size_t)dv.D * tail * 8) / 16;
+        // the last block of a V page, 16 bytes of its rows of 64 per thread; in flight beside the rest
+        constexpr int kTail = 128 * 4 / kBlock;
+        uint2 t[kTail][2];
+        if (tail) {
+            const uint2 *s2 = reinterpret_cast<const uint2 *>(s4 + n16);
+#pragma unroll
+            for (int q = 0; q < 2 * kTail; ++q) {
+                const int i = threadIdx.x + q / 2 * kBlock, ch = i / 4, unit = i % 4 * 2 + q % 2;
+                t[q / 2][q % 2] = ch < dv.D && unit < tail ? s2[ch * tail + unit] : make_uint2(0, 0);
+            }
+        }
         for (size_t j = threadIdx.x; j < n16; j += 4 * kBlock) {           // four 16-byte loads in flight per thread
             uint4 x[4];
 #pragma unroll
@@ -1755,6 +1775,12 @@ __global__ __launch_bounds__(kBlock) void k_fetch(const DeviceView *self, int u0
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (j + (size_t)q * kBlock < n16) d4[j + (size_t)q * kBlock] = x[q];
+        }
+        if (tail) {
+#pragma unroll
+            for (int q = 0; q < kTail; ++q)
+                if ((int)threadIdx.x + q * kBlock < dv.D * 4)
+                    d4[n16 + threadIdx.x + q * kBlock] = make_uint4(t[q][0].x, t[q][0].y, t[q][1].x, t[q][1].y);
         }
     }
 }

@@ -88,8 +88,12 @@ struct alignas(64) DeviceView {
     // host tier: staging ring the ingest kernel writes (frame f at slot f % SN), and the
     // device-visible address of the pinned host pools the offload kernel writes
     DevPtr<char> stage_k, stage_v;   // [SN][U][page]
+    // A V page in [Tp/32][D][32] leaves out what pads it there: whole blocks of 32 tokens as they are, then [D][4 * htail] of the last T % 32 tokens
+    // (htail = 0: none, or so many that nothing is saved; the page is then as on the GPU).
+    // The link bounds both directions: 512 frames of 196 tokens offloaded and four questions' clusters fetched back 15.35 -> 14.55 ms.
     DevPtr<char> host_k, host_v;     // pinned pools: [U][HP/SFh] slabs of [SFh K pages][SFh V pages]
-    size_t h_ustride, h_bstride;
+    size_t h_ustride, h_bstride, hvpage;   // hvpage: bytes of a V page there
+    int htail;
     int SFh;                   // frames per host slab
     int HP;                    // host pages per unit
     DevPtr<const int> dest;           // [2][U][SN] host page of each staged frame of a batch, two tables in turn (pinned memory)
@@ -118,11 +122,11 @@ struct alignas(64) DeviceView {
     DevPtr<double> mt_nrm;          // [U][F]
     // retrieval augmentation (paper Sec. V-C)
     int nt_max;
-    DevPtr<double> vsumm;    // [U][F][D]   per-frame value summaries (mean of the frame's T value vectors)
-    DevPtr<double> rvsum;    // [U][C][D]   per-cluster sums of them (value representative = rvsum / n)
     DevPtr<float> rep_k, rep_v;   // [U][C][D] fp32 pseudo-token tables: representative, value representative
     DevPtr<float> aug_o;     // [U][nt_max][16][D]  partial of the representatives' part, same form as part_o
     DevPtr<float> aug_ml;    // [U][nt_max][2][16]
+    DevPtr<double> vsumm;    // [U][F][D]   per-frame value summaries (mean of the frame's T value vectors)
+    DevPtr<double> rvsum;    // [U][C][D]   per-cluster sums of them (value representative = rvsum / n)
     // nested visual-semantic hierarchy (paper Sec. V-B, V-C)
     int Dv;
     DevPtr<double> vemb;     // [F][Dv]     visual embeddings of the frames (the visual level's states)

@@ -952,6 +952,14 @@ def test_host_tier_parity_ragged_pages_two_layers():
     _report(rep)
 
 
+# The last tokens of a value page, kept in the host pool without what pads them on the GPU: no whole block before them and one, one unit of four
+# tokens full and begun, the most units that are kept so, one too many, none
+@pytest.mark.parametrize("tokens,head_dim", [(3, 128), (28, 64), (29, 64), (33, 128), (36, 64), (37, 128), (59, 64), (60, 128), (61, 128), (64, 64)])
+def test_host_tier_parity_ends_of_value_pages(tokens, head_dim):
+    wl = _small(tokens_per_frame=tokens, head_dim=head_dim, n_frames=70, n_clusters=9, top_k=3, question_tokens=3)
+    harness.run_workload(wl, decode_steps=2, slab_frames=3, tier=binding.TIER_HOST)
+
+
 def test_host_tier_matches_hbm_tier_bitwise_and_overlaps_layers():
     wl = _small(n_layers=3, n_frames=144, n_clusters=10, top_k=3)
     st = inputs.SceneStream(wl)
