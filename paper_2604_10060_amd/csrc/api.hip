@@ -279,12 +279,12 @@ Layout make_layout(const mosaic_config &c, size_t arena_bytes) {
     return L;
 }
 
-// The copy of a view that kernels read, where the view says it is.  One workgroup; a launch, so that it stands in the context's stream (and in a capture
-// of it) before every launch that reads it.
-__global__ __launch_bounds__(128) void k_set_view(DeviceView v) {
+// The copy of a view that kernels read, where the view says it is.  One wavefront; a launch, so that it stands in the context's stream before
+// every launch that reads it.
+__global__ __launch_bounds__(64) void k_set_view(DeviceView v) {
     unsigned long long w[sizeof(DeviceView) / 8];
     __builtin_memcpy(w, &v, sizeof v);
-    unsigned long long *dst = (unsigned long long *)v.self;
+    unsigned long long *dst = (unsigned long long *)const_cast<DeviceView *>(v.self);
     if (threadIdx.x == 0)
 #pragma unroll
         for (size_t i = 0; i < sizeof(DeviceView) / 8; ++i) dst[i] = w[i];
@@ -575,15 +575,9 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
                 (e = hipEventCreateWithFlags(&ht->attend_done[l], hipEventDisableTiming)) != hipSuccess)
                 return bail(MOSAIC_EHIP, std::string("host tier event creation: ") + hipGetErrorString(e));
     }
-    // the kernels' views: [0] with the arena's attention partials, [1] with the static ones (mosaic_attend_static)
-    DeviceView *views = (DeviceView *)(base + L.views);
-    for (int i = 0; i < 2; ++i) {
-        DeviceView v = i ? static_view(ctx) : dv;
-        v.self = views + i;
-        k_set_view<<<1, 128, 0, ctx->stream>>>(v);
-    }
-    dv.self = views;
-    if (hipGetLastError() != hipSuccess || clear_maintainer(ctx) != hipSuccess) {     // (no context to keep a message in: the code says it)
+    dv.self = (DeviceView *)(base + L.views);       // (written by the first call that launches: write_views())
+    ctx->views_written = false;
+    if (clear_maintainer(ctx) != hipSuccess) {     // (no context to keep a message in: the code says it)
         (void)mosaic_destroy(ctx);
         *out = nullptr;
         return MOSAIC_EHIP;
@@ -618,9 +612,28 @@ int32_t mosaic_destroy(mosaic_ctx *ctx) {
     return MOSAIC_OK;
 }
 
+// The kernels' views: [0] with the arena's attention partials, [1] with the static ones (mosaic_attend_static).  Written on the context's stream before
+// the first kernel that reads them, by everything that ingests or comes through join_ingest(); a call in a capture records the writes with its own
+// kernels, and leaves them to be done again by the next call outside, which may come before the graph's first replay.
+static int write_views(mosaic_ctx *ctx) {
+    if (ctx->views_written) return MOSAIC_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess) capture = hipStreamCaptureStatusNone;
+    for (int i = 0; i < 2; ++i) {
+        DeviceView v = i ? static_view(ctx) : ctx->dv;
+        v.self = ctx->dv.self + i;
+        void *args[] = {&v};
+        const hipError_t e = hipLaunchKernel((const void *)k_set_view, dim3(1), dim3(64), args, 0, ctx->stream);
+        if (e != hipSuccess) return fail_hip(ctx, e, "view launch");
+    }
+    ctx->views_written = capture == hipStreamCaptureStatusNone;
+    return MOSAIC_OK;
+}
+
 // Overlapped ingest: the caller's stream waits for the order-dependent part that earlier ingest calls
 // left on the context's own stream.  Called by everything that reads or changes the index.
 static int join_ingest(mosaic_ctx *ctx) {
+    { const int rc = write_views(ctx); if (rc != MOSAIC_OK) return rc; }
     if (!ctx->assign_pending) return MOSAIC_OK;
     const hipError_t e = hipStreamWaitEvent(ctx->stream, ctx->assigned, 0);
     if (e != hipSuccess) return fail_hip(ctx, e, "hipStreamWaitEvent(overlapped ingest)");
@@ -875,6 +888,7 @@ static int ingest_frames(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, 
     if (n_frames < 1) return fail(ctx, MOSAIC_EINVAL, "n_frames must be >= 1");
     const DeviceView &dv = ctx->dv;
     if (ctx->n_frames + n_frames > dv.F) return fail(ctx, MOSAIC_ECAPACITY, "max_frames exceeded");
+    { const int rc = write_views(ctx); if (rc != MOSAIC_OK) return rc; }
     if (ctx->host) {
         const long long before = ctx->n_frames;
         const int rc = ingest_host(ctx, k_dev, v_dev, n_frames);
