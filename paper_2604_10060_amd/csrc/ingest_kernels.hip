@@ -1246,21 +1246,6 @@ constexpr int kChordOne = 1 << 14, kChordNever = 65534, kChordNone = 65535;    /
 __device__ __forceinline__ int chord_up(double d) { return d < 2.0 ? (int)(d * kChordOne) + 1 : 2 * kChordOne; }          // (also where d is no number)
 __device__ __forceinline__ int chord_down(double d) { return d > 0.0 ? (int)fmin(d * kChordOne, 2.0 * kChordOne) : 0; }
 
-// The groups: a frame's candidates span `span` tiles of 16 ids at most, counted from the tile of its first candidate; group g has
-// tiles lo(g) .. lo(g + 1) - 1 of them.
-struct LloydGroups {
-    int span;
-    __device__ __forceinline__ explicit LloydGroups(const DeviceView &dv)
-        : span(dv.P > 0 ? (dv.Cs % 16 == 0 ? dv.Cs / 16 : (dv.Cs + 14) / 16 + 1) : (dv.C + 15) / 16) {}
-    __device__ __forceinline__ int lo(int g) const { return span <= kLloydGroups ? min(g, span) : (g * span + kLloydGroups - 1) / kLloydGroups; }
-    __device__ __forceinline__ int of(int t) const { return span <= kLloydGroups ? t : t * kLloydGroups / span; }
-    // tiles of group g of a frame whose candidates lie in tiles t0 .. t1 - 1, as a mask
-    __device__ __forceinline__ unsigned long long tiles(int g, int t0, int t1) const {
-        const int a = t0 + lo(g), b = min(t0 + lo(g + 1), t1);
-        return a < b ? (~0ull >> (64 - (b - a))) << a : 0ull;
-    }
-};
-
 // (written out: the compiler's own fmaxf first makes a quiet number of every operand that comes from another lane)
 __device__ __forceinline__ float max_f32(float a, float b) { float r; asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
 __device__ __forceinline__ float min_f32(float a, float b) { float r; asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
@@ -1298,6 +1283,7 @@ template <int D, bool LATER, bool NESTED>
 __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const DeviceView *self, int n_frames, int it) {
     const DeviceView dv = device_view(self);
     constexpr int KS = D / 8;
+    static_assert(kLloydTiles <= kBlock, "a thread per tile writes its group");
     static_assert(kLloydTest <= kBlock && kLloydTest % 64 == 0, "a thread per frame, whole wavefronts");
     const int u = blockIdx.x, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, C = dv.C;
     const int row = lane % 16, kq = lane / 16;
@@ -1305,7 +1291,7 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
     if (blockIdx.y == 0 && tid == 0) moved[(it + 1) % 3] = 0;
     const double *r = dv.r + (size_t)u * C * D;
     const int n_tiles = (C + 15) / 16;
-    const LloydGroups groups(dv);
+    const LloydGroups groups(dv.P, dv.Cs, C);
     ChordBounds *bounds = dv.lloyd_bounds + (size_t)u * dv.F;
     // A tile of 16 representatives is shared by the four wavefronts through LDS (each row is read
     // from L2 once per workgroup); rows are padded by 16 bytes so that the 16 lanes of a k group hit
@@ -1338,10 +1324,10 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
     __shared__ __attribute__((aligned(16))) f64x2 scale_sh[1024 + 16];    // the cluster-count limit of a context, rounded up to tiles
     __shared__ double sn_sh[4][16];
     __shared__ unsigned long long tiles_sh[4];
-    __shared__ unsigned char group_sh[64];                                // group of a tile, counted from the frame's first
+    __shared__ unsigned char group_sh[kLloydTiles];                       // group of a tile, counted from the frame's first
     // LATER: a tile's largest movement of a representative * 16 + 15 - whose, and its second largest; the live frames, and the tiles they ask for
     __shared__ unsigned short delta_sh[LATER ? 1024 + 16 : 1];            // what the last update moved a representative by, at most
-    __shared__ int top_sh[LATER ? 64 : 1], second_sh[LATER ? 64 : 1], live_sh[LATER ? 4 : 1];
+    __shared__ int top_sh[LATER ? kLloydTiles : 1], second_sh[LATER ? kLloydTiles : 1], live_sh[LATER ? 4 : 1];
     __shared__ unsigned char list_sh[LATER ? kLloydTest : 1];
     __shared__ unsigned long long need_sh[LATER ? kLloydTest : 1];
     const int f0 = blockIdx.y * (LATER ? kLloydTest : 64);

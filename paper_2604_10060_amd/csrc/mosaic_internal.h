@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/mosaic.h"
+#include "lloyd_groups.h"
 
 namespace mosaic {
 
@@ -21,7 +22,6 @@ constexpr int kFp32Tiles = 2;     // row tiles per wavefront in the fp32 attenti
 constexpr int kPrefillWaves = 4;  // wavefronts per workgroup of that kernel (64 * kPrefillTiles * 4 = 128 query rows)
 constexpr int kMlRows = 3;        // rows of 16 floats per attention partial besides O: max, normaliser, exact-weight sum
 
-constexpr int kLloydGroups = 7;   // groups of representatives that a frame keeps a K-means bound for
 // A frame's K-means bounds, in units of 2^-14: its chord to its own representative from above, to the others of each group from below
 struct __attribute__((aligned(16))) ChordBounds { unsigned short ub, lb[kLloydGroups]; };
 

@@ -130,7 +130,8 @@ def test_recluster_rounds_with_skipped_frames_parity(kw):
 
 
 # Bounds are kept by groups of tiles of representatives: as many tiles as groups, one more, groups of two to nine tiles; frames on both
-# sides of a workgroup's 128; partitions whose ids begin and end inside a tile, and of more tiles than groups; and summaries that are zero,
+# sides of a workgroup's 128; partitions whose ids begin and end inside a tile, of more tiles than groups, and a single one of almost all
+# the ids a table holds, with a last workgroup of one busy wavefront; and summaries that are zero,
 # equal, or far too small for the bounds' fp32 similarities
 @pytest.mark.parametrize("kw", [
     dict(n_clusters=112, warmup_frames=128, n_frames=400, recluster_every=129),
@@ -144,7 +145,7 @@ def test_recluster_bounds_by_groups_parity(kw):
     _report(rep)
 
 
-@pytest.mark.parametrize("P,C,W,D", [(5, 60, 200, 64), (3, 120, 300, 128), (1, 200, 260, 64), (2, 500, 600, 64)])
+@pytest.mark.parametrize("P,C,W,D", [(5, 60, 200, 64), (3, 120, 300, 128), (1, 200, 260, 64), (2, 500, 600, 64), (1, 1015, 1029, 128), (1, 1023, 1040, 64)])
 def test_nested_bounds_by_groups_parity(P, C, W, D):
     wl = inputs.CONFIGS[1].scaled(name="nested_groups", n_frames=W + 20, scene_model="rapid", noise=0.8, n_clusters=C, top_k=5, head_dim=D,
                                   tokens_per_frame=3, question_tokens=2, visual_dim=20, n_visual=P, warmup_frames=W, lloyd_iters=10)
