@@ -576,8 +576,9 @@ hipError_t launch_visual_assign(const DeviceView &dv, const float *e_in, int f0,
     return after_launch();
 }
 
+// (a launch holds fewer than 2^32 threads in a dimension: 37449 frames of 112 units; what is larger goes to launches of its own)
 bool store_visual_assign_takes(const DeviceView &dv, int n_frames) {
-    return n_frames > kVisFew && (long long)n_frames * dv.U < (1 << 24);
+    return n_frames > kVisFew && (1 + 2 * (long long)n_frames * dv.U) * kVisAssign < (1ll << 32);
 }
 
 hipError_t launch_store_visual_assign(const DeviceView &dv, const void *k_in, const void *v_in, const float *e_in, int f0, int f1, bool beyond,
