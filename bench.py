@@ -883,9 +883,7 @@ def run_host_leg(layers=0, steps=128, check=True):
     lat = np.array(lat)
     cold = lat[::per_topic]
     warm = np.delete(lat, np.arange(0, steps, per_topic))
-    # (value pages cross the link without most of their padding to 32 tokens)
-    on_link = 1.0 if wl.kv_dtype == "fp32" else (T + (T + 3) // 4 * 4) / (T + (T + 31) // 32 * 32)
-    h2d_gbps = s.h2d_bytes * on_link / (s.h2d_busy_ms * 1e-3) / 1e9 if s.h2d_busy_ms > 0 else 0.0
+    h2d_gbps = s.h2d_bytes / (s.h2d_busy_ms * 1e-3) / 1e9 if s.h2d_busy_ms > 0 else 0.0
     checked = None
     if check and refused_steps == 0:
         from oracle import mosaic_oracle as orc

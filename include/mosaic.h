@@ -186,9 +186,8 @@ typedef struct {
                                   launch with size-proportional splits */
     /* host tier */
     int64_t cache_hits, cache_misses;   /* selected clusters found in / missing from the GPU cache */
-    int64_t h2d_bytes, h2d_copies;      /* cluster fetches: bytes of the fetched pages as they lie on the GPU (over the link: less the
-                                           padding of a bf16 value page, whose T tokens take a multiple of 4 there and of 32
-                                           on the GPU) and fetch-kernel launches */
+    int64_t h2d_bytes, h2d_copies;      /* cluster fetches: bytes moved host-to-device (of a bf16 value page, as they lie in the host
+                                           pool: T rounded up to a multiple of 4 tokens) and fetch-kernel launches */
     double h2d_busy_ms;                 /* time of those fetch kernels (event pairs around each launch while
                                            mosaic_profile_enable is on; filled by mosaic_get_stats, which
                                            synchronises) */

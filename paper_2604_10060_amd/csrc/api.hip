@@ -558,7 +558,7 @@ int32_t mosaic_create(const mosaic_config *cfg, mosaic_ctx **out) {
         HostTier *ht = new (std::nothrow) HostTier();
         if (!ht) return bail(MOSAIC_ENOMEM, "host allocation failed");
         ctx->host = ht;
-        ht->init(dv.U, dv.C, dv.C + L.buf_max, dv.F, L.SF, L.slabs_per_unit, L.PU, L.max_clusters, dv.k, L.kpage, L.vpage);
+        ht->init(dv.U, dv.C, dv.C + L.buf_max, dv.F, L.SF, L.slabs_per_unit, L.PU, L.max_clusters, dv.k, L.kpage + L.hvpage);
         // default-priority streams for selection and for the fetches
         // two internal streams only: selection (+ value fetches) and key fetches
         if ((e = hipStreamCreateWithFlags(&ht->sel_stream, hipStreamNonBlocking)) != hipSuccess ||

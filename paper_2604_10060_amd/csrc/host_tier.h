@@ -38,7 +38,7 @@ struct HostTier {
         bool resident_dirty = false;             // the device's copy of the residency flags is out of date
     };
     int U = 0, C = 0, E = 0, F = 0, SF = 8, slabs_per_unit = 0, cache_pages = 0, max_clusters = 0, top_k = 0;
-    size_t kpage = 0, vpage = 0;                // bytes of one K / V page
+    size_t link_page = 0;                       // bytes of a frame's K and V page as they lie in the host pool and cross the link
     std::vector<Unit> units;
     std::vector<char> pinned;                   // [E] scratch of fetch(): the current selection
     long long clock = 0;
@@ -72,7 +72,7 @@ struct HostTier {
     std::vector<int> seen_nbuf;                  // [U]
 
     void init(int U, int C, int n_entries, int F, int SF, int slabs_per_unit, int cache_pages, int max_clusters,
-              int top_k, size_t kpage, size_t vpage);
+              int top_k, size_t link_page);
     void reset();
     int place(int u, int f, int c);
     void join(int u, int f, int e);

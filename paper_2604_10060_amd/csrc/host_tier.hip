@@ -28,9 +28,9 @@
 namespace mosaic {
 
 void HostTier::init(int U_, int C_, int n_entries, int F_, int SF_, int slabs_per_unit_, int cache_pages_,
-                    int max_clusters_, int top_k_, size_t kpage_, size_t vpage_) {
+                    int max_clusters_, int top_k_, size_t link_page_) {
     U = U_; C = C_; E = n_entries; F = F_; SF = SF_; slabs_per_unit = slabs_per_unit_; cache_pages = cache_pages_;
-    max_clusters = max_clusters_; top_k = top_k_; kpage = kpage_; vpage = vpage_;
+    max_clusters = max_clusters_; top_k = top_k_; link_page = link_page_;
     units.assign(U, Unit());
     pinned.assign(E, 0);
     seen_splits.assign((size_t)U * 2, 0);
@@ -202,7 +202,7 @@ int HostTier::fetch(int u, const int *ids, int n_ids, int *moves, int *n_moves, 
             pages[np++] = un.slot[f];
             if (!prefetch) un.last_frames[un.n_last_frames++] = f;
         }
-        h2d_bytes += (long long)(want - have) * (long long)(kpage + vpage);
+        h2d_bytes += (long long)(want - have) * (long long)link_page;
         un.cached[c] = want;
         un.stamp[c] = now;
         un.by_prefetch[c] = prefetch ? (char)(un.by_prefetch[c] | !complete) : (char)0;

@@ -473,8 +473,8 @@ def run_maintained(wl, mt: dict, units=None, device="cuda:0", batch_pattern=(1, 
                         for name in ("hits", "misses", "evictions", "pages_moved")}
         assert (s.cache_hits, s.cache_misses) == (tot["cache"]["hits"], tot["cache"]["misses"])
         page_bytes = 2 * wl.tokens_per_frame * wl.head_dim * (4 if wl.kv_dtype == "fp32" else 2)
-        if wl.kv_dtype == "bf16":          # (value pages are padded to whole 32-token chunks)
-            page_bytes = (wl.tokens_per_frame + (wl.tokens_per_frame + 31) // 32 * 32) * wl.head_dim * 2
+        if wl.kv_dtype == "bf16":          # (over the link a value page's last tokens go in units of four)
+            page_bytes = (wl.tokens_per_frame + (wl.tokens_per_frame + 3) // 4 * 4) * wl.head_dim * 2
         assert s.h2d_bytes == tot["cache"]["pages_moved"] * page_bytes
     rep.notes.append(tot)
     m.close()
