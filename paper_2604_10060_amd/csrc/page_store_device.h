@@ -27,21 +27,35 @@ template <bool BEYOND, typename W> __device__ __forceinline__ void keep_words(W 
     else *p = w;
 }
 
-// N elements of a row.  The caller's rows are read once: their loads carry the non-temporal hint, so that they displace less of what the kernels
-// beside and after a page store work with (one frame of 28 layers 4.16 -> 4.02 us, with the assignment 5.90 -> 5.83 us).
-template <typename E, int N> struct RowPiece {
-    static constexpr int W = N * (int)sizeof(E) / 4;
-    typedef unsigned int Words __attribute__((ext_vector_type(W), aligned(W >= 4 ? 16 : 4 * W)));
-    Words w;
-    __device__ __forceinline__ void load(const E *p) { w = __builtin_nontemporal_load(reinterpret_cast<const Words *>(p)); }
-    template <bool BEYOND> __device__ __forceinline__ void store(E *p) const { keep_words<BEYOND>(reinterpret_cast<Words *>(p), w); }
+// N elements of a row of D.  The caller's rows are read once: their loads carry the non-temporal hint, so that they displace less of what the kernels
+// beside and after a page store work with.  What a lane takes of more than 16 bytes are pieces of 16, as far apart as the row has pieces: a wavefront's load is
+// then whole lines.  (With 32 bytes side by side each of the two loads takes half of every line, and a hinted line is fetched for both.)
+// One frame of 112 units in one call, assignment included, us; without the hint / hinted, 32 bytes side by side / hinted, 16-byte pieces.
+// Frames that lie in no cache: bf16, 196 tokens of 128 channels 9.4 / - / 8.8, fp32 14.2 / 14.0 / 12.4, fp32, 64 channels 9.2 / 8.6 / 7.6; frames that a kernel
+// has just written: 6.6 / - / 5.7, 11.6 / 12.4 / 10.7, 5.8 / 5.8 / 5.0.  (A frame that an earlier call took, and nothing has
+// written since, is faster without it: 7.9 / 8.8 in bf16, 11.5 / 14.0 / 12.4 in fp32.)
+template <typename E, int D, int N> struct RowPiece {
+    static constexpr int W = N * (int)sizeof(E) / 4, PIECES = W > 4 ? W / 4 : 1, PW = W / PIECES, PN = N / PIECES;
+    typedef unsigned int Words __attribute__((ext_vector_type(PW)));
+    Words w[PIECES];
+    static __device__ __forceinline__ int first(int lane) { return lane * PN; }                       // a lane's first channel,
+    static __device__ __forceinline__ constexpr int next(int i) { return i / PN * (D / PIECES) + i % PN; }    // and its i-th from there
+    __device__ __forceinline__ unsigned int word(int i) const { return w[i / PW][i % PW]; }
+    __device__ __forceinline__ void load(const E *p) {
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) w[i] = __builtin_nontemporal_load(reinterpret_cast<const Words *>(p + i * (D / PIECES)));
+    }
+    template <bool BEYOND> __device__ __forceinline__ void store(E *p) const {
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) keep_words<BEYOND>(reinterpret_cast<Words *>(p + i * (D / PIECES)), w[i]);
+    }
     __device__ __forceinline__ void unpack(float (&v)[N]) const {
 #pragma unroll
         for (int i = 0; i < W; ++i) {
-            if constexpr (sizeof(E) == 4) v[i] = __uint_as_float(w[i]);
+            if constexpr (sizeof(E) == 4) v[i] = __uint_as_float(word(i));
             else {
-                v[2 * i] = __uint_as_float(w[i] << 16);
-                v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+                v[2 * i] = __uint_as_float(word(i) << 16);
+                v[2 * i + 1] = __uint_as_float(word(i) & 0xffff0000u);
             }
         }
     }
@@ -51,14 +65,14 @@ template <typename E, int D, int NT, bool BEYOND>
 __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_in, char *kdst_base, int u, int fl,
                                                int f, StoreShared<D> &sh, double *s_out) {
     constexpr int RP = kStoreRows<D>, LPR = NT / RP, N = D / LPR;      // rows per pass, lanes per row, elements each
-    const int tid = threadIdx.x, c0 = tid % LPR * N, r0 = tid / LPR;
+    const int tid = threadIdx.x, c0 = RowPiece<E, D, N>::first(tid % LPR), r0 = tid / LPR;
     const int T = dv.T;
     const size_t in_page = ((size_t)fl * dv.U + u) * (size_t)T * D;
     const size_t page = (size_t)u * dv.F + f;          // summary slot
     const bool host = dv.tier == MOSAIC_TIER_HOST;
     const size_t spage = host ? (size_t)(f % dv.SN) * dv.U + u : (size_t)u * dv.PU + f;
     const E *src = k_in + in_page + c0;
-    // (a thread's channels lie in one piece of a row)
+    // (a thread's channels lie in one of the pieces that bf16 keys are stored in; fp32 pages are row by row)
     E *dst = reinterpret_cast<E *>(kdst_base) + spage * (size_t)T * D + c0 / 32 * dv.k_ps() + c0 % 32;
     double acc[N];
 #pragma unroll
@@ -67,7 +81,7 @@ __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_
     // it, which may alias it for all the compiler knows, and a 64-token page is four trips to memory instead of one (28
     // layers, one frame a call: 12.2 -> 9.0 us a frame; 64 a call, C = 20: 6.5 -> 4.9)
     for (int t0 = r0; t0 < T; t0 += 4 * RP) {
-        RowPiece<E, N> x[4];
+        RowPiece<E, D, N> x[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) x[k].load(src + (size_t)min(t0 + k * RP, T - 1) * D);
 #pragma unroll
@@ -81,7 +95,7 @@ __device__ __forceinline__ void store_key_page(const DeviceView &dv, const E *k_
             }
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) sh.red[r0][c0 + i] = acc[i];
+    for (int i = 0; i < N; ++i) sh.red[r0][c0 + RowPiece<E, D, N>::next(i)] = acc[i];
     __syncthreads();
     if (tid < D) {
         double sm = 0.0;
@@ -96,7 +110,7 @@ template <typename E, int D, int NT, bool BEYOND>
 __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *v_in, char *vdst_base, int u, int fl,
                                                  int f, StoreShared<D> &sh) {
     constexpr int RP = kStoreRows<D>, LPR = NT / RP, N = D / LPR;
-    const int tid = threadIdx.x, c0 = tid % LPR * N, r0 = tid / LPR;
+    const int tid = threadIdx.x, c0 = RowPiece<E, D, N>::first(tid % LPR), r0 = tid / LPR;
     const int T = dv.T;
     const size_t in_page = ((size_t)fl * dv.U + u) * (size_t)T * D;
     const size_t page = (size_t)u * dv.F + f;
@@ -111,7 +125,7 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
 #pragma unroll
         for (int i = 0; i < N; ++i) acc[i] = 0.0;
         for (int t0 = r0; t0 < T; t0 += 4 * RP) {      // (as in store_key_page)
-            RowPiece<E, N> x[4];
+            RowPiece<E, D, N> x[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) x[k].load(src + (size_t)min(t0 + k * RP, T - 1) * D);
 #pragma unroll
@@ -128,7 +142,7 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
         }
         if (dv.vsumm) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) sh.red[r0][c0 + i] = acc[i];
+            for (int i = 0; i < N; ++i) sh.red[r0][c0 + RowPiece<E, D, N>::next(i)] = acc[i];
             __syncthreads();
             if (tid < D) {
                 double sv = 0.0;
@@ -149,7 +163,7 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
         unsigned short *dst = reinterpret_cast<unsigned short *>(vdst_base) + spage * (size_t)D * Tp;
         // a tile's rows are loaded together (row clamped, loads unconditional), the next tile's while this one is written out
         constexpr int RPT = TC / RP;                 // rows per thread and tile
-        RowPiece<E, N> w[RPT];
+        RowPiece<E, D, N> w[RPT];
         auto load_tile = [&](int tc0) {
 #pragma unroll
             for (int k = 0; k < RPT; ++k) w[k].load(src + (size_t)min(tc0 + r0 + k * RP, T - 1) * D);
@@ -161,7 +175,7 @@ __device__ __forceinline__ void store_value_page(const DeviceView &dv, const E *
                 const bool in = tc0 + r0 + k * RP < T;
                 unsigned int *row = reinterpret_cast<unsigned int *>(&sh.tile[r0 + k * RP][c0]);
 #pragma unroll
-                for (int i = 0; i < RowPiece<E, N>::W; ++i) row[i] = in ? w[k].w[i] : 0u;
+                for (int i = 0; i < RowPiece<E, D, N>::W; ++i) row[i] = in ? w[k].word(i) : 0u;
             }
             if (tc0 + TC < Tp) load_tile(tc0 + TC);
             __syncthreads();
