@@ -53,12 +53,12 @@ template <> __device__ __forceinline__ void load8_f64<unsigned short>(const unsi
     }
 }
 
-template <typename E, int D, int BLK>
-__device__ __forceinline__ void mean_query_partials(const E *q, int lc, int h, int Tq, int G, int Hq, int row0, int R,
-                                                    double (*wpart)[D]) {      // rows row0 .. R - 1
-    constexpr int LPR = D / 8, NPART = BLK / LPR, UN = 8;
+template <typename E, int D>
+__device__ __forceinline__ void mean_query_partials(const E *q, int lc, int h, int Tq, int G, int Hq,
+                                                    double (*wpart)[D]) {
+    constexpr int BLK = kRetrBlock, LPR = D / 8, NPART = BLK / LPR, UN = 8;
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-    const int c8 = tid % LPR, part = row0 + tid / LPR;
+    const int c8 = tid % LPR, part = tid / LPR, R = Tq * G;
     const E *qb = q + (size_t)lc * Tq * Hq * D + (size_t)h * G * D + 8 * c8;
     double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     // (token and head of a row by increments: a division per row cost 3 of a 256-token question's 25 us in this kernel)
@@ -93,34 +93,66 @@ __device__ __forceinline__ void mean_query_partials(const E *q, int lc, int h, i
     }
 }
 
-// A long question's rows, kMeanRows of each unit per workgroup: sums to dv.part_o, [unit of the call][workgroup][D] doubles.  grid (n_units,
-// mean_query_parts()), 256 threads.  One workgroup per unit is bound by what its CU takes in and converts: 1792 rows of 128 channels cost k_retrieve 10 us of
-// its 22.9 (256 tokens, 7 heads a unit, 4 units, bf16); here they take 4.8, and k_retrieve 13.1.
-constexpr int kMeanBlock = 256, kMeanRows = 128;
+// The same partials of a long question, a workgroup for each wavefront of k_retrieve's: to dv.part_o, [unit of the call][wavefront][D] doubles.  grid
+// (n_units, kMeanParts), 128 threads, each with half of the eight channels that a lane has there.  Rows and partials are added in the same order, so that a
+// question's scores are the same bit for bit whichever kernel sums its rows: those of a layer's call and of all layers' at once, of either tier.
+// One workgroup per unit is bound by what its CU takes in and converts.
+constexpr int kMeanBlock = 128, kMeanParts = kRetrBlock / 64;
 template <typename E, int D>
 __global__ __launch_bounds__(kMeanBlock) void k_mean_query(const DeviceView *self, int u0, const E *q, int Tq) {
     const DeviceView dv = device_view(self);
-    const int uc = blockIdx.x, u = u0 + uc, tid = threadIdx.x, row0 = blockIdx.y * kMeanRows;
-    __shared__ double wpart[kMeanBlock / 64][D];
-    mean_query_partials<E, D, kMeanBlock>(q, uc / dv.Hkv, u % dv.Hkv, Tq, dv.G, dv.Hq, row0, min(Tq * dv.G, row0 + kMeanRows), wpart);
+    constexpr int NC = 4, LPR = D / 8, NPART = kRetrBlock / LPR, PW = 64 / LPR;        // channels of a thread; parts in k_retrieve, in a wavefront of it
+    constexpr int UN = 8;                                                              // rows in flight (16: up to 4 % longer)
+    static_assert(PW * (D / NC) == kMeanBlock, "a thread per part and four channels");
+    struct __attribute__((aligned(NC * sizeof(E)))) Quad { E x[NC]; };
+    const int uc = blockIdx.x, u = u0 + uc, tid = threadIdx.x, c = tid % (D / NC) * NC, p = tid / (D / NC);
+    const int G = dv.G, Hq = dv.Hq, R = Tq * G, part = (int)blockIdx.y * PW + p;
+    const E *qb = q + (size_t)(uc / dv.Hkv) * Tq * Hq * D + (size_t)(u % dv.Hkv) * G * D + c;
+    __shared__ double sum_sh[PW][D];
+    double a[NC] = {};
+    const int dt = NPART / G, dg = NPART - dt * G;          // (as in mean_query_partials)
+    int t = part / G, g = part - t * G;
+    for (int r0 = part; r0 < R; r0 += UN * NPART) {
+        Quad v[UN];
+#pragma unroll
+        for (int x = 0; x < UN; ++x) {
+            const bool in = r0 + x * NPART < R;
+            v[x] = *reinterpret_cast<const Quad *>(qb + (size_t)(in ? t * Hq + g : (Tq - 1) * Hq + G - 1) * D);
+            t += dt;
+            g += dg;
+            if (g >= G) { g -= G; ++t; }
+        }
+#pragma unroll
+        for (int x = 0; x < UN; ++x)
+            if (r0 + x * NPART < R) {
+#pragma unroll
+                for (int e = 0; e < NC; ++e) a[e] += to_f64<E>(v[x].x[e]);
+            }
+    }
+#pragma unroll
+    for (int e = 0; e < NC; ++e) sum_sh[p][c + e] = a[e];
     __syncthreads();
     if (tid < D) {
-        double a = 0.0;
+        double x[PW];
 #pragma unroll
-        for (int w = 0; w < kMeanBlock / 64; ++w) a += wpart[w][tid];
-        reinterpret_cast<double *>((float *)dv.part_o)[((size_t)uc * gridDim.y + blockIdx.y) * D + tid] = a;
+        for (int i = 0; i < PW; ++i) x[i] = sum_sh[i][tid];
+#pragma unroll
+        for (int o = 1; o < PW; o <<= 1)
+#pragma unroll
+            for (int i = 0; i < PW; i += 2 * o) x[i] += x[i + o];
+        reinterpret_cast<double *>((float *)dv.part_o)[((size_t)uc * kMeanParts + blockIdx.y) * D + tid] = x[0];
     }
 }
 
-// Sums of how many workgroups k_retrieve finds (0: it sums the rows itself).  The launch costs less than it saves from about 900 rows a unit (fp32: 500) on,
-// unless the units fill the chip by themselves.  Calls of mosaic_retrieve in us, rows summed in k_retrieve / before it: bf16, 4 units 560 rows 10.8 / 11.6,
-// 896 12.1 / 12.3, 1344 14.2 / 11.9, 1792 16.3 / 11.7; 16 units 1792 rows 16.5 / 12.4; 112 units 1792 rows 18.5 / 19.0; fp32, 4 units 448 rows
-// 12.1 / 12.1, 560 13.2 / 12.3, 1792 18.1 / 12.2; 112 units 1792 rows 25.4 / 26.3.  The sums lie in the attention partials, which the context's one
-// stream uses after them (the host tier selects on another stream).
-int mean_query_parts(const DeviceView &dv, int n_units, int Tq) {
-    const long long rows = (long long)Tq * dv.G, parts = (rows + kMeanRows - 1) / kMeanRows;
-    const long long room = dv.part_entries * kRowTile / 2 / n_units;           // rows of D doubles in the attention partials
-    return rows >= (dv.esize == 4 ? 640 : 1024) && n_units <= 64 && dv.tier == MOSAIC_TIER_HBM && parts <= std::min<long long>(room, 4096) ? (int)parts : 0;
+// Whether k_mean_query sums the rows before k_retrieve.  Calls of mosaic_retrieve in us, rows summed in k_retrieve / before it.  D = 128: bf16, 4 units 560
+// rows 8.8 / 8.4, 896 10.0 / 8.6, 1029 10.4 / 9.0, 1792 14.1 / 9.8; 64 units 560 rows 9.0 / 9.2, 896 10.3 / 9.6, 1792 15.5 / 11.6; 112 units 896 rows
+// 11.2 / 11.2, 1792 16.1 / 15.9; fp32, 4 units 560 rows 11.0 / 8.3, 1792 15.8 / 9.6; 112 units 1792 rows 23.1 / 22.3.  D = 64: bf16, 4 units 1029 rows
+// 8.1 / 7.4, 112 units 8.4 / 8.5; fp32, 4 units 672 rows 7.9 / 7.0, 112 units 1792 rows 13.3 / 14.0.  Up to 64 units it is never slower from the lines below
+// on (they are those of an earlier form of the sums, which cost more on 64 units); more units fill the chip by themselves.
+// The sums lie in the attention partials, which the context's one stream uses after them (the host tier selects on another stream).
+bool mean_query_before(const DeviceView &dv, int n_units, int Tq) {
+    const long long rows = (long long)Tq * dv.G;
+    return rows >= (dv.esize == 4 ? 640 : 1024) && n_units <= 64 && dv.tier == MOSAIC_TIER_HBM && dv.part_entries * kRowTile / 2 >= (long long)n_units * kMeanParts;
 }
 
 // NESTED (paper Sec. V-C "Two-Stage Retrieval"): the mean query is first scored against the
@@ -232,17 +264,12 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve(const DeviceView *self,
         if (wa >= 0) atomicAdd(&wcnt_sh[wa], 1);         // (read after the scores' barrier at the earliest)
     } else if (SUMMED) {
         if (tid < D) {
-            const int mean_parts = (R + kMeanRows - 1) / kMeanRows;
-            const double *qb = reinterpret_cast<const double *>((const float *)dv.part_o) + (size_t)uc * mean_parts * D + tid;
-            double acc = 0.0;
-            for (int p0 = 0; p0 < mean_parts; p0 += 16) {
-                double v[16];
+            const double *qb = reinterpret_cast<const double *>((const float *)dv.part_o) + (size_t)uc * kMeanParts * D + tid;
+            double acc = 0.0, v[kMeanParts];
 #pragma unroll
-                for (int x = 0; x < 16; ++x) v[x] = qb[(size_t)min(p0 + x, mean_parts - 1) * D];
+            for (int p = 0; p < kMeanParts; ++p) v[p] = qb[p * D];
 #pragma unroll
-                for (int x = 0; x < 16; ++x)
-                    if (p0 + x < mean_parts) acc += v[x];
-            }
+            for (int p = 0; p < kMeanParts; ++p) acc += v[p];
             qbar[tid] = acc / (double)R;
         }
         if (tid < C) { n_sh[tid] = n_reg; rn_sh[tid] = rn_reg; cnt_sh[tid] = 0; wcnt_sh[tid] = 0; }
@@ -250,7 +277,7 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve(const DeviceView *self,
         if (wa >= 0) atomicAdd(&wcnt_sh[wa], 1);
     } else {
         if (tid < C) { n_sh[tid] = n_reg; rn_sh[tid] = rn_reg; cnt_sh[tid] = 0; wcnt_sh[tid] = 0; }
-        mean_query_partials<E, D, BLK>(q, lc, h, Tq, G, Hq, 0, R, qpart);
+        mean_query_partials<E, D>(q, lc, h, Tq, G, Hq, qpart);
         __syncthreads();
         if (wa >= 0) atomicAdd(&wcnt_sh[wa], 1);
         if (tid < D) {
@@ -444,7 +471,7 @@ __global__ __launch_bounds__(kRetrBlock) void k_retrieve_deferred(const DeviceVi
 
     for (int j = tid; j < 1024; j += BLK) { n_sh[j] = j < C ? n[j] : (j < R ? 1 : 0); cnt_sh[j] = 0; }
     if (tid == 0) tk_sh.n_live = 0;
-    mean_query_partials<E, D, BLK>(q, lc, h, Tq, G, Hq, 0, Tq * G, qpart);
+    mean_query_partials<E, D>(q, lc, h, Tq, G, Hq, qpart);
     __syncthreads();
     if (tid < D) {
         double acc = 0.0;
@@ -547,10 +574,10 @@ __global__ __launch_bounds__(kBlock) void k_expand_tok_idx(const DeviceView *sel
 template <bool NESTED>
 static void launch_retrieve_t(const DeviceView &dv, int u0, int n_units, const void *q, int Tq,
                               int n_frames, int score_mode, bool write_pages, hipStream_t s) {
-    const int parts = mean_query_parts(dv, n_units, Tq);
+    const bool before = mean_query_before(dv, n_units, Tq);
     auto run = [&](auto sums, auto summed, auto kern, auto *qq) {
-        if (parts > 0) sums<<<dim3(n_units, parts), kMeanBlock, 0, s>>>(dv.self, u0, qq, Tq);
-        (parts > 0 ? summed : kern)<<<n_units, kRetrBlock, 0, s>>>(dv.self, u0, qq, Tq, n_frames, score_mode, write_pages);
+        if (before) sums<<<dim3(n_units, kMeanParts), kMeanBlock, 0, s>>>(dv.self, u0, qq, Tq);
+        (before ? summed : kern)<<<n_units, kRetrBlock, 0, s>>>(dv.self, u0, qq, Tq, n_frames, score_mode, write_pages);
     };
     if (dv.esize == 4) {
         const float *qq = (const float *)q;

@@ -349,12 +349,39 @@ def test_question_whose_weights_outgrow_their_reference(T, D, tq, frames, rise):
         assert (got_lse - torch.logsumexp(logit, 1)).abs().max().item() <= 1e-6 * logit.abs().max().item() + harness.LSE_TOL["bf16"]
 
 
-# Rows of a long question are summed by workgroups of 128 rows each in a launch of its own: the least it takes, a row more than a workgroup's
-# share, sixteen of them and one, and one row less than it takes
+# Rows of a long question are summed by sixteen workgroups a unit in a launch of its own: the least it takes, rows that are no multiple of the workgroups'
+# parts, more than one trip of them, and one row less than it takes
 @pytest.mark.parametrize("tq,kw", [(147, dict()), (183, dict()), (147, dict(head_dim=64, n_layers=3)), (80, dict(n_q_heads=32, kv_dtype="fp32")),
                                    (129, dict(n_q_heads=64)), (146, dict()), (79, dict(n_q_heads=32, kv_dtype="fp32"))])
 def test_mean_query_of_a_long_question(tq, kw):
     harness.run_workload(_small(**{**dict(question_tokens=tq, n_frames=40, n_clusters=9, top_k=2, tokens_per_frame=6), **kw}), layer_mode="all")
+
+
+@pytest.mark.parametrize("D,G,tq,dtype", [(128, 8, 80, "fp32"), (64, 7, 150, "fp32"), (128, 7, 256, "bf16"), (64, 32, 33, "bf16")])
+def test_scores_of_a_long_question_do_not_depend_on_the_call(D, G, tq, dtype):
+    """Rows are summed by k_retrieve itself for many units at once and in the host tier, and by workgroups of their own for a few units: the same sums, also of
+    values so different in size that every order of additions rounds differently."""
+    H, L = 4, 17                                     # 68 units at once, four in a layer's call
+    wl = _small(n_layers=L, n_kv_heads=H, n_q_heads=H * G, head_dim=D, tokens_per_frame=1, n_frames=24, n_clusters=8, top_k=2, question_tokens=tq,
+                warmup_frames=24, kv_dtype=dtype)
+    g = torch.Generator().manual_seed(tq)
+    t = torch.float32 if dtype == "fp32" else torch.bfloat16
+    k = torch.randn(24, L, H, 1, D, generator=g).to(t).to(DEV)
+    q = (torch.randn(L, tq, H * G, D, generator=g) * 2.0 ** torch.randint(-45, 1, (L, tq, 1, 1), generator=g)).to(t).to(DEV)
+    scores = []
+    for tier in (binding.TIER_HBM, binding.TIER_HOST):
+        m = binding.Mosaic(binding.config_for(wl, max_q_tokens=tq, tier=tier), device=DEV)
+        m.ingest_frame(k, k)
+        if tier == binding.TIER_HBM:
+            m.retrieve(-1, q)
+            scores.append(np.concatenate([m.selection(l)[2] for l in range(L)]))
+        for l in range(L):
+            m.retrieve(l, q[l].contiguous())
+        scores.append(np.concatenate([m.selection(l)[2] for l in range(L)]))
+        m.close()
+    assert np.isfinite(scores[0]).any()
+    np.testing.assert_array_equal(scores[0], scores[1])
+    np.testing.assert_array_equal(scores[0], scores[2])
 
 
 def test_question_with_room_for_few_partials(monkeypatch):
