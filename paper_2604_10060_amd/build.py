@@ -14,7 +14,7 @@ SOURCES = ("api.hip", "host_tier.hip", "ingest_kernels.hip", "visual_kernels.hip
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-kernarg-preload-count=16",
-         "-Wall", "-Wno-unused-function"]
+         "-Wall", "-Wno-unused-function", "-Werror=align-mismatch", "-Werror=unused-variable", "-Werror=unused-const-variable"]
 
 
 def build(verbose: bool = False) -> str:

@@ -117,7 +117,7 @@ int check_config(const mosaic_config *c, std::string &why) {
         if (c->tier != MOSAIC_TIER_HBM) { why = "retrieval augmentation is available in the HBM tier only"; return MOSAIC_EINVAL; }
         if (c->maint_mode == MOSAIC_MAINT_DEFERRED) { why = "retrieval augmentation is not available with MOSAIC_MAINT_DEFERRED"; return MOSAIC_EINVAL; }
     }
-    if (c->n_partitions < 0 || c->n_partitions > 64) { why = "n_partitions must be in 0..64"; return MOSAIC_EINVAL; }
+    if (c->n_partitions < 0 || c->n_partitions > kMaxPartitions) { why = "n_partitions must be in 0..64"; return MOSAIC_EINVAL; }
     if (c->n_partitions > 0) {
         if (c->tier != MOSAIC_TIER_HBM) { why = "the nested hierarchy is available in the HBM tier only"; return MOSAIC_EINVAL; }
         if (c->maint_mode != MOSAIC_MAINT_OFF || c->recluster_every != 0) { why = "the nested hierarchy excludes the maintainer and periodic re-clustering"; return MOSAIC_EINVAL; }

@@ -61,19 +61,22 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     return r;
 }
 
-template <int D, bool AUG, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfma(const DeviceView *self, int u0, int n_units,
+constexpr int kPrefillSlots = 4;   // LDS slots of one chunk per operand
+
+template <int D, bool AUG>
+__global__ __launch_bounds__(64 * kPrefillWaves, 2) void k_attend_prefill_mfma(const DeviceView *self, int u0, int n_units,
                                                                                     const unsigned short *q, int Tq,
                                                                                     int NT, int G, int n_groups, int n_row_blocks,
                                                                                     int group_blocks) {
     const DeviceView dv = device_view(self);
+    constexpr int NW = kPrefillWaves;
     static_assert(!AUG || 64 * NW == kBlock, "the representatives' workgroups are written for kBlock threads");
     constexpr int KK = D / 32, DB = D / 16, RTW = kPrefillTiles;
     constexpr int KSEG = D / 8;                  // 16-byte pieces per key row
     constexpr int KRP = 16 / KSEG;               // key rows per 256 bytes (1 at D = 128, 2 at D = 64)
     constexpr int KBYTES = kChunk * D * 2, VBYTES = D * kChunk * 2;
     static_assert(NW == 4, "a wavefront for the even and one for the odd chunks of each operand");
-    constexpr int NS = 4;                        // LDS slots per operand
+    constexpr int NS = kPrefillSlots;
     constexpr int NL = KBYTES / 1024;            // wavefront-sized loads per chunk and operand
     static_assert(KBYTES == VBYTES, "the same loads for either operand");
     // LDS (dynamic): NS key slots, then NS value slots, one chunk each
@@ -130,7 +133,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void k_attend_prefill_mfm
     // registers across the loop over the chunks)
     int n_ = n, g_ = g;
     asm volatile("" : "+v"(n_), "+v"(g_));
-    const int uc = w.uc, c0 = w.c0, c1 = w.c1, n_pages = w.n;
+    const int uc = w.uc, c0 = w.c0, c1 = w.c1;
     const int u = u0 + uc, lc = uc / dv.Hkv, h = u % dv.Hkv;
     bf16x8 qf[RTW][KK];
 #pragma unroll
@@ -398,22 +401,22 @@ hipError_t launch_attend_prefill(const DeviceView &dv, int u0, int n_units, cons
                                  Shares shares, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     constexpr int NW = kPrefillWaves;
     const int NT = (Tq * dv.G + kRowTile - 1) / kRowTile;
-    // dynamic LDS: NW key slots and NW value slots of one chunk (32 x D bf16) each
-    const size_t lds = (size_t)2 * NW * (kChunk * dv.D * 2);
+    // dynamic LDS: key slots and value slots of one chunk (32 x D bf16) each
+    const size_t lds = (size_t)2 * kPrefillSlots * (kChunk * dv.D * 2);
     static std::once_flag attr_once;          // process-wide, but set exactly once whichever handle comes first
     std::call_once(attr_once, [] {
-        const int big = 2 * NW * kChunk * 128 * 2;
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<64, true, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<64, false, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<128, true, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<128, false, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
+        const int big = 2 * kPrefillSlots * kChunk * 128 * 2;
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<64, true>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<64, false>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<128, true>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attend_prefill_mfma<128, false>), hipFuncAttributeMaxDynamicSharedMemorySize, big);
     });
     const int n_groups = shares.walk ? shares.groups : shares.groups + n_units - 1, rb = (NT + NW * kPrefillTiles - 1) / (NW * kPrefillTiles);
     const int gb = (n_groups * rb + 7) / 8 * 8;
     const dim3 grid(gb + (dv.aug_reps ? n_units * NT : 0)), block(64 * NW);
     auto go = [&](auto kern) { launch_timed(kern, grid, block, lds, s, ev0, ev1, dv.self, u0, n_units, q, Tq, NT, shares.groups, n_groups, rb, gb); };
-    if (dv.aug_reps) { if (dv.D == 64) go(k_attend_prefill_mfma<64, true, NW>); else go(k_attend_prefill_mfma<128, true, NW>); }
-    else { if (dv.D == 64) go(k_attend_prefill_mfma<64, false, NW>); else go(k_attend_prefill_mfma<128, false, NW>); }
+    if (dv.aug_reps) { if (dv.D == 64) go(k_attend_prefill_mfma<64, true>); else go(k_attend_prefill_mfma<128, true>); }
+    else { if (dv.D == 64) go(k_attend_prefill_mfma<64, false>); else go(k_attend_prefill_mfma<128, false>); }
     return hipGetLastError();
 }
 

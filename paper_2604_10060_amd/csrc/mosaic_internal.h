@@ -20,6 +20,7 @@ constexpr int kMaxUnitSplits = 256; // ... and the most one unit can be given wh
 constexpr int kPrefillTiles = 2;  // row tiles per wavefront in the multi-tile MFMA kernel
 constexpr int kFp32Tiles = 2;     // row tiles per wavefront in the fp32 attention kernel when there is more than one
 constexpr int kPrefillWaves = 4;  // wavefronts per workgroup of that kernel (64 * kPrefillTiles * 4 = 128 query rows)
+constexpr int kMaxPartitions = 64;   // of the visual level
 constexpr int kMlRows = 3;        // rows of 16 floats per attention partial besides O: max, normaliser, exact-weight sum
 
 // A frame's K-means bounds, in units of 2^-14: its chord to its own representative from above, to the others of each group from below

@@ -45,7 +45,8 @@ __device__ __forceinline__ double block_sum(double x, double *red) {
 // result register v = (row 4v + lane/16, column lane%16); step x of 16 channels from c takes channels c + 4 (lane/16) + x.
 // VEC: Dv is a multiple of 4 (16-byte loads).
 // TILES: columns (16 TILES >= P).  What bounds it is the trip to memory of its operands: up to eight steps' loads are in flight.
-constexpr int kVisTiles = 4;                // P <= 64
+constexpr int kVisTiles = 4;                // at most
+static_assert(16 * kVisTiles >= kMaxPartitions, "a column for every centroid");
 template <typename E, bool VEC, bool GRAM, int TILES>
 __device__ __forceinline__ void visual_products(const DeviceView &dv, const E *base, int n_rows, int ks, int ke,
                                                 f64x4 (&acc)[TILES + 1]) {
@@ -335,7 +336,7 @@ __device__ __forceinline__ void visual_assign(const DeviceView &dv, const float 
             auto by_tiles = [&](auto vec) {
                 if (P <= 16) products(vec, std::integral_constant<int, 1>{});
                 else if (P <= 32) products(vec, std::integral_constant<int, 2>{});
-                else products(vec, std::integral_constant<int, 4>{});
+                else products(vec, std::integral_constant<int, kVisTiles>{});
             };
             if (Dv % 4 == 0) by_tiles(std::true_type{});                 // (16-byte loads)
             else by_tiles(std::false_type{});
@@ -555,7 +556,7 @@ hipError_t launch_visual_lloyd(const DeviceView &dv, int W, int iters, hipStream
             constexpr bool VEC = decltype(vec)::value;
             if (dv.P <= 16) go(k_visual_lloyd_assign<VEC, 1>);
             else if (dv.P <= 32) go(k_visual_lloyd_assign<VEC, 2>);
-            else go(k_visual_lloyd_assign<VEC, 4>);
+            else go(k_visual_lloyd_assign<VEC, kVisTiles>);
         };
         if (dv.Dv % 4 == 0) by_tiles(std::true_type{});
         else by_tiles(std::false_type{});
