@@ -888,8 +888,8 @@ static int ingest_frames(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, 
     if (n_frames < 1) return fail(ctx, MOSAIC_EINVAL, "n_frames must be >= 1");
     const DeviceView &dv = ctx->dv;
     if (ctx->n_frames + n_frames > dv.F) return fail(ctx, MOSAIC_ECAPACITY, "max_frames exceeded");
-    { const int rc = write_views(ctx); if (rc != MOSAIC_OK) return rc; }
     if (ctx->host) {
+        { const int rc = write_views(ctx); if (rc != MOSAIC_OK) return rc; }
         const long long before = ctx->n_frames;
         const int rc = ingest_host(ctx, k_dev, v_dev, n_frames);
         ctx->epoch += 1;
@@ -905,7 +905,7 @@ static int ingest_frames(mosaic_ctx *ctx, const void *k_dev, const void *v_dev, 
     // Overlapped ingest: the order-dependent part of a batched call goes to the context's own stream
     // (it reads nothing of the caller's buffers), so that the next call's page stores run beside it.
     const bool overlap = ctx->assign_stream != nullptr && n_frames > 1;
-    if (!overlap) { const int rc = join_ingest(ctx); if (rc != MOSAIC_OK) return rc; }
+    { const int rc = overlap ? write_views(ctx) : join_ingest(ctx); if (rc != MOSAIC_OK) return rc; }
     const hipStream_t dep = overlap ? ctx->assign_stream : ctx->stream;
     // Nested hierarchy, frames of the online phase: the visual level decides them beside their page stores.
     const bool with_visual = e_dev && ctx->n_frames >= ctx->W && !one_launch && store_visual_assign_takes(dv, n_frames);

@@ -56,7 +56,29 @@ print("OK")
 """
 
 
-@pytest.mark.parametrize("script", [pytest.param(NESTED, id="nested_call_of_many_frames")])
+# The views that kernels read are written before the first launch.  A call in a capture records the writes and leaves them to be done again: the next call
+# outside may come before the graph's first launch
+CAPTURE = r"""
+h, mem = context(max_frames=20, warmup_frames=10)
+assert rt.launches() == 0
+rt.set_capturing(1)
+for _ in range(2):
+    ok(lib.mosaic_ingest_frame(h, p, p, 3), h)
+    assert [l[0] for l in launched()][:3] == ["k_set_view", "k_set_view", "k_store_summary"]
+rt.set_capturing(0)
+ok(lib.mosaic_ingest_frame(h, p, p, 5), h)
+assert [l[0] for l in launched()][:3] == ["k_set_view", "k_set_view", "k_store_summary"]
+ok(lib.mosaic_ingest_frame(h, p, p, 1), h)
+assert "k_set_view" not in [l[0] for l in launched()]
+ok(lib.mosaic_retrieve(h, 0, p, 1), h)
+got = [l[0] for l in launched()]
+assert got == ["k_retrieve"], got
+ok(lib.mosaic_destroy(h), h)
+print("OK")
+"""
+
+
+@pytest.mark.parametrize("script", [pytest.param(NESTED, id="nested_call_of_many_frames"), pytest.param(CAPTURE, id="first_call_in_a_capture")])
 def test_launches(tmp_path, script):
     so = str(tmp_path / "launches.so")
     subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "launches.c")])
