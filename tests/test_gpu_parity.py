@@ -2081,3 +2081,67 @@ def test_nested_question_that_overflowed_keeps_the_first_partitions():
         frames = np.concatenate([np.flatnonzero(A[h] == c) for c in chosen])
         np.testing.assert_array_equal(toks[h], (frames[:, None] * T + np.arange(T)).ravel())
     m.close()
+
+
+def test_first_call_in_a_capture():
+    """A context whose first launching call is recorded in a graph: launched once, and again between later calls, it leaves what direct calls leave.  (Its
+    frames end before the warm-up does: no clear of memory is recorded.)"""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    P, V = ctypes.POINTER, ctypes.c_void_p
+    hip.hipStreamBeginCapture.argtypes = [V, ctypes.c_int]
+    hip.hipStreamEndCapture.argtypes = [V, P(V)]
+    hip.hipGraphInstantiate.argtypes = [P(V), V, V, V, ctypes.c_size_t]
+    hip.hipGraphLaunch.argtypes = [V, V]
+    hip.hipGraphExecDestroy.argtypes = hip.hipGraphDestroy.argtypes = [V]
+    wl = _small(n_frames=48, n_clusters=6, top_k=2, warmup_frames=16, question_tokens=3)
+    st = inputs.SceneStream(wl)
+    K, Vv = (x.to(DEV) for x in st.frames(0, wl.n_frames))
+    q = st.question(st.draw_scene(), wl.question_tokens, 0).to(DEV)[0].contiguous()
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    found = []
+    for recorded in (False, True):
+        m = binding.Mosaic(binding.config_for(wl), device=DEV, stream=side)
+        torch.cuda.synchronize()
+        graph, run = V(), V()
+        if recorded:
+            assert hip.hipStreamBeginCapture(side.cuda_stream, 0) == 0
+        m.ingest_frame(K[:5], Vv[:5])
+        if recorded:
+            assert hip.hipStreamEndCapture(side.cuda_stream, ctypes.byref(graph)) == 0
+            assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, 0) == 0
+            assert hip.hipGraphLaunch(run, side.cuda_stream) == 0
+        outs = []
+        for lo, hi in ((5, 30), (30, 31), (31, 48)):
+            m.ingest_frame(K[lo:hi], Vv[lo:hi])
+            if recorded:                             # (the same pages, summaries and views again)
+                assert hip.hipGraphLaunch(run, side.cuda_stream) == 0
+            m.retrieve(0, q)
+            torch.cuda.synchronize()
+            out = m.attend(0, q)
+            side.synchronize()
+            outs += [t.float().cpu().numpy() for t in out]
+        found.append((m.summaries(), m.assignments(), *m.centroids(), *m.selection(0)[:3], *outs))
+        if recorded:
+            side.synchronize()
+            assert hip.hipGraphExecDestroy(run) == 0 and hip.hipGraphDestroy(graph) == 0
+        m.close()
+    for a, b in zip(*found):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("frames,room,units", [(2049, 2049, 3), (8800, 9000, 2), (19001, 19001, 1)])
+def test_large_read_backs_on_the_device(frames, room, units):
+    """Summaries of pages of one token are the tokens themselves, read back unit by unit: in two pieces of pinned memory, the second short, in one more than
+    there are, in ten."""
+    wl = _small(n_frames=room, n_clusters=4, top_k=1, n_layers=units, n_kv_heads=1, n_q_heads=7, tokens_per_frame=1, warmup_frames=8, kv_dtype="fp32")
+    g = torch.Generator().manual_seed(3)
+    k = torch.randn(frames, units, 1, 1, wl.head_dim, generator=g)
+    want = k[:, :, 0, 0].permute(1, 0, 2).double().numpy()
+    m = binding.Mosaic(binding.config_for(wl), device=DEV)
+    m.ingest_frame(k.to(DEV), k.to(DEV))
+    for _ in range(3):
+        got = m.summaries()
+        np.testing.assert_array_equal(got.reshape(want.shape), want)
+    m.close()
