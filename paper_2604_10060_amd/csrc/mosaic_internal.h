@@ -151,8 +151,11 @@ static_assert(offsetof(DeviceView, tier) == 64 && offsetof(DeviceView, scores) =
               offsetof(DeviceView, stage_k) == 256 && offsetof(DeviceView, nt_max) / 64 == 8 && offsetof(DeviceView, aug_ml) / 64 == 8, "lines of what decode reads");
 
 // A kernel's view: the fields that it uses, by scalar loads.  A launch carries the address, which lies in registers when a wavefront starts (the build asks
-// for that).  With the struct itself as an argument a launch of a few us is longer by 0.2 us and more, and so is the way to it: a token through 28 layers
-// (84 launches) 846 -> 828 us, four fp32 layers 95.7 -> 92.5, 768 frames one by one (784 launches) 5.20 -> 4.95 ms.
+// for that).  With the struct itself as an argument a launch of a few us is longer by 0.2 us and more, and so is the way to it.  What that is of a call is
+// little, and the same for a question asked over and over / never before / with 1 GB read between the steps (us, with the struct -> so, runs
+// within 0.5 %): a token through 28 layers (84 launches) 981 -> 961 / 990 -> 970 / 1030 -> 1009, four fp32 layers 129 -> 126 / 123 -> 121 / 130 -> 125, four with
+// window and representatives 81.7 -> 81.3 / 84.0 -> 82.1 / 91.4 -> 89.4, one layer 19.3 -> 19.0 / 20.8 -> 20.8 / 25.7 -> 25.0.  768 frames one by one
+// (784 launches) 5.20 -> 4.95 ms.
 // LINES of it are fetched at once: the compiler loads a field where it is first used, which is one more trip to the L2 on a kernel's chain.
 template <int... LINES>
 __device__ __forceinline__ DeviceView device_view(const DeviceView *self) {
