@@ -1243,6 +1243,7 @@ __global__ __launch_bounds__(kBlock) void k_exact_var(const DeviceView *self, in
 // again, 45 % of the frame-candidate pairs of the second round of 112 units x 1536 frames and 10 to 60 % of those after it; by groups and single
 // frames 3 and 0.1 to 3 %.)
 constexpr int kChordOne = 1 << 14, kChordNever = 65534, kChordNone = 65535;    // 1.0; an ub no lb exceeds; the lb of a group without candidates
+constexpr int kChordLost = 65535;                                              // the movement of a representative whose chords are, or were, no number
 __device__ __forceinline__ int chord_up(double d) { return d < 2.0 ? (int)(d * kChordOne) + 1 : 2 * kChordOne; }          // (also where d is no number)
 __device__ __forceinline__ int chord_down(double d) { return d > 0.0 ? (int)fmin(d * kChordOne, 2.0 * kChordOne) : 0; }
 
@@ -1326,7 +1327,8 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
     __shared__ unsigned long long tiles_sh[4];
     __shared__ unsigned char group_sh[kLloydTiles];                       // group of a tile, counted from the frame's first
     // LATER: a tile's largest movement of a representative * 16 + 15 - whose, and its second largest; the live frames, and the tiles they ask for
-    __shared__ unsigned short delta_sh[LATER ? 1024 + 16 : 1];            // what the last update moved a representative by, at most
+    __shared__ unsigned short delta_sh[LATER ? 1024 + 16 : 1];            // what the last update moved a representative by, at most, or kChordLost
+    __shared__ unsigned char odd_sh[kLloydTiles];                         // a tile with a live representative that is not finite
     __shared__ int top_sh[LATER ? kLloydTiles : 1], second_sh[LATER ? kLloydTiles : 1], live_sh[LATER ? 4 : 1];
     __shared__ unsigned char list_sh[LATER ? kLloydTest : 1];
     __shared__ unsigned long long need_sh[LATER ? kLloydTest : 1];
@@ -1358,10 +1360,13 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
             e.y = 0.0;
         }
         scale_sh[j] = e;
+        const bool odd = j < C && nj > 0 && !(rnj < INFINITY);
+        const unsigned long long odd_lanes = __ballot(odd);
+        if (row == 0) odd_sh[j / 16] = (odd_lanes >> lane & 0xffff) != 0;
         if constexpr (LATER) {
             if (j >= C) dj = 0.0;
             const int d = dj == 0.0 ? 0 : chord_up(dj);
-            delta_sh[j] = (unsigned short)d;
+            delta_sh[j] = (unsigned short)(odd || dj != dj ? kChordLost : d);
             int top = 16 * d + 15 - row;
             top = max(top, dpp_i32<kDppXor8>(top));
             top = max(top, dpp_i32<kDppXor7>(top));
@@ -1382,6 +1387,7 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
         const int t0 = plo_t / 16, t1 = (NESTED ? plo_t + dv.Cs - 1 : C - 1) / 16 + 1;
         const bool in = tid < kLloydTest && f0 + tid < n_frames;
         const int ub = min((int)cb.ub + (int)delta_sh[own], kChordNever);
+        const bool lost = delta_sh[own] == kChordLost;                      // every other candidate may win, a later one than any bound knows of too
         unsigned long long need = 0;
 #pragma unroll
         for (int g = 0; g < kLloydGroups; ++g) {
@@ -1393,7 +1399,7 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
             }
             const int lb = cb.lb[g] == kChordNone ? kChordNone : max(0, (int)cb.lb[g] - d);
             cb.lb[g] = (unsigned short)lb;
-            if (ub >= lb) need |= groups.tiles(g, t0, t1);
+            if (ub >= lb || lost) need |= groups.tiles(g, t0, t1);
         }
         cb.ub = (unsigned short)ub;
         if (in) bounds[f0 + tid] = cb;
@@ -1508,6 +1514,7 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
             ct = next;
             buf ^= 1;
         }
+        const unsigned long long odd_tiles = __ballot(lane < n_tiles && odd_sh[lane]);
         if (busy) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -1528,7 +1535,8 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
                     if (a_was[v] >= 0 && a_was[v] < C) dv.lloyd_changed[(size_t)u * C + a_was[v]] = 1;
                 }
                 // Chords to the winner (lane 7) and to the best other candidate of group `row` (a frame without a winner, or whose
-                // summary is all zeros or nearly, is never skipped).  Roots in fp32, pushed outwards (relative error below 2e-7 with the
+                // summary is all zeros or nearly, is never skipped).  A representative that is not finite is no candidate as long as it is not, and may
+                // be finite after the next update: its group has no bound.  Roots in fp32, pushed outwards (relative error below 2e-7 with the
                 // conversion); a similarity that has been rounded to fp32 is pushed upwards first.
                 const double sn = sn_sh[wave][4 * v + kq], inv = 1.0 / sn;
                 const bool sound = !none && sn > 1e-30 && sn < 1e30;         // (what fp32 similarities hold)
@@ -1540,7 +1548,7 @@ __global__ __launch_bounds__(kBlock, LATER ? 2 : 3) void k_lloyd_assign(const De
                 unsigned short *o = reinterpret_cast<unsigned short *>(bounds + f);
                 if (row == 7) o[0] = (unsigned short)(sound ? chord_up(chord * (1.0 + 1e-6) + 1e-9) : kChordNever);
                 else if (row < kLloydGroups && (mine & gt) == gt)
-                    o[1 + row] = (unsigned short)(!sound ? 0 : sim == -INFINITY ? kChordNone : chord_down(chord * (1.0 - 1e-6) - 1e-9));
+                    o[1 + row] = (unsigned short)(!sound || (gt & odd_tiles) ? 0 : sim == -INFINITY ? kChordNone : chord_down(chord * (1.0 - 1e-6) - 1e-9));
             }
         }
         if constexpr (!LATER) break;

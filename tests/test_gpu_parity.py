@@ -153,12 +153,16 @@ def test_nested_bounds_by_groups_parity(P, C, W, D):
     _report(rep)
 
 
-@pytest.mark.parametrize("kind", ["zeros", "equal", "tiny"])
+@pytest.mark.parametrize("kind", ["zeros", "equal", "tiny"] + [f"infinite{i}" for i in range(6)])
 def test_recluster_of_summaries_without_usable_bounds(kind):
     """K-means rounds whose frames may not be skipped end where rounds that skip nothing end: 64-bit rounds on the CPU."""
-    F, C, D, iters = 300, 24, 64, 6
-    g = torch.Generator().manual_seed(7)
+    # (infinite: representatives come and go that are no candidate of any frame, alone in their group of tiles or not)
+    F, C, D, iters = (300, 24, 64, 6) if not kind.startswith("infinite") else (150, [3, 20, 40, 130][int(kind[8:]) % 4], 64, 12)
+    g = torch.Generator().manual_seed(7 if not kind.startswith("infinite") else int(kind[8:]))
     s = torch.randn(F, D, generator=g)
+    if kind.startswith("infinite"):
+        s[torch.randperm(F, generator=g)[:F // 10], 0] = float("inf")
+        s[torch.randperm(F, generator=g)[:F // 10], 1] = -float("inf")
     if kind == "zeros": s[::3] = 0.0
     if kind == "equal": s[1::4] = s[:1]
     if kind == "tiny": s *= 1e-36
@@ -176,9 +180,13 @@ def test_recluster_of_summaries_without_usable_bounds(kind):
         rn = r.norm(dim=1)
         cos = torch.where(rn > 0, (x @ r.t()) / torch.where(rn > 0, rn, 1.0), 0.0)
         cos[:, ~live] = -float("inf")
+        cos[cos.isnan()] = -float("inf")
         a = cos.argmax(1)
         for f in range(F):                       # equal representatives: the lowest id (their products have the same bits on the device)
             j = int(a[f])
+            if cos[f, j].isinf():                # (no candidate at all: the first id; several that are infinite: the lowest of them)
+                a[f] = int((cos[f] == cos[f, j]).nonzero()[0])
+                continue
             a[f] = next(i for i in range(j + 1) if live[i] and (i == j or torch.equal(r[i], r[j]) or cos[f].abs().max() == 0.0))
         n = torch.bincount(a, minlength=C)
         for j in range(C):
