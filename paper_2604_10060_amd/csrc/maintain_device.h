@@ -120,7 +120,7 @@ __device__ int mt_split_cluster(const DeviceView &dv, int u, int a, int n_frames
             if (lr == 0) nrm[i] = sqrt(p);
         }
         __syncthreads();
-        // ---- seeds: the pair with the lowest mutual cosine, first in (i, k) order ----
+        // ---- seeds: the pair with the lowest mutual cosine, first in (i, k) order; the first two members if no pair's is finite ----
         double bv = INFINITY;
         int bi = 0x7fffffff, bk = 0x7fffffff;
         for (int i = grp; i + 1 < m; i += NG) {
@@ -154,7 +154,7 @@ __device__ int mt_split_cluster(const DeviceView &dv, int u, int a, int n_frames
                     for (int e = 0; e < EPL; ++e) p += si[e] * t[x][e];
                     p = mt_g16sum(p);
                     const double cs = (ni == 0.0 || nk[x] == 0.0) ? 0.0 : p / (ni * nk[x]);
-                    if (k < m && (cs < bv || (cs == bv && (i < bi || (i == bi && k < bk))))) { bv = cs; bi = i; bk = k; }
+                    if (k < m && cs < INFINITY && (cs < bv || (cs == bv && (i < bi || (i == bi && k < bk))))) { bv = cs; bi = i; bk = k; }
                 }
             }
         }
@@ -172,7 +172,8 @@ __device__ int mt_split_cluster(const DeviceView &dv, int u, int a, int n_frames
                 const int oi = sh.red_i[x], ok = sh.red_k[x];
                 if (ov < bv || (ov == bv && (oi < bi || (oi == bi && ok < bk)))) { bv = ov; bi = oi; bk = ok; }
             }
-            sh.red_i[0] = bi; sh.red_k[0] = bk;
+            const bool none = bi == 0x7fffffff;
+            sh.red_i[0] = none ? 0 : bi; sh.red_k[0] = none ? 1 : bk;
         }
         __syncthreads();
         bi = sh.red_i[0]; bk = sh.red_k[0];

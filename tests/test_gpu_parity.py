@@ -1216,6 +1216,33 @@ def test_maintainer_deferred_on_the_host_tier_bf16_small_buffer():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("mode,value,dtype,D", [(1, float("nan"), "fp32", 64), (1, float("inf"), "bf16", 128), (2, float("nan"), "bf16", 64),
+                                                (2, -float("inf"), "fp32", 128)])
+def test_split_of_members_without_a_finite_cosine(mode, value, dtype, D):
+    """A frame whose key is no number joins the first cluster, whose variance then is none either: the split finds no pair with a cosine, begins from the
+    first two members and leaves them together, on insertion and when a query asks for it."""
+    wl = _small(n_frames=12, n_clusters=8, top_k=8, head_dim=D, tokens_per_frame=1, n_kv_heads=1, n_q_heads=2, kv_dtype=dtype, warmup_frames=4)
+    m = binding.Mosaic(binding.config_for(wl, **harness.maintainer_overrides(_mt(mode, 4, 0.1, 0.2, buf_max=3 if mode == 2 else 0))), device=DEV)
+    k = torch.zeros(6, 1, 1, 1, D)
+    for f in range(4):
+        k[f, ..., f] = 1.0                           # a cluster each
+    k[4, ..., 1] = value
+    k[5, ..., 3] = 1.0                               # (its cluster is as it was)
+    k = k.to(torch.float32 if dtype == "fp32" else torch.bfloat16).to(DEV)
+    m.ingest_frame(k[:4], k[:4])
+    for f in (4, 5):
+        m.ingest_frame(k[f:f + 1], k[f:f + 1])
+    q = torch.ones(1, 2, D, dtype=k.dtype, device=DEV)
+    m.retrieve(0, q)
+    np.testing.assert_array_equal(m.assignments()[0], [0, 1, 2, 3, 0, 3])
+    r, n = m.centroids()
+    np.testing.assert_array_equal(n[0], [2, 1, 1, 2, 0, 0, 0, 0])
+    mt = m.maintainer()
+    assert mt["n_slots"][0] == 4 and (mode == 1 or mt["n_buf"][0] == 0)
+    m.close()
+
+
+@pytest.mark.gpu
 def test_maintainer_config_errors():
     wl = inputs.CONFIGS[0]
     base = dict(maint_mode=binding.MAINT_EAGER, init_clusters=4, tau_min=1.0, tau_max=2.0, tau_n0=8.0)
